@@ -13,7 +13,7 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Work is only
  *    enqueued; no call synchronises with the host, and no call allocates device memory.
  *  - h is passed as double so that the derived constants are formed in double and rounded
- *    once; the pairwise arithmetic itself is fp32 (fp32 MFMA inputs, fp32 accumulation) unless
+ *    once; the pairwise arithmetic itself is fp32 (every operand held to its 24 bits, fp32 accumulation) unless
  *    `flags` selects another input mode.
  *  - Accuracy domain of the matrix path (d >= 7, and the eval calls at d >= 4): squared distances are formed as
  *    |p|^2 + |x|^2 - 2 p.x on coordinates taken relative to a centre of the samples (the mean of an evenly
@@ -71,7 +71,9 @@ enum {
 enum {
     SDKDE_MAX_D = 128,
     /* flags: precision mode of the distance cross term (the Gram-matrix tile of the Method section) */
-    SDKDE_PREC_FP32 = 0,    /* fp32 MFMA inputs, fp32 accumulate: the reference path */
+    SDKDE_PREC_FP32 = 0,    /* fp32 inputs, fp32 accumulate: the reference path.  On the matrix path every fp32 operand
+                               (coordinates and weights) is held exactly, as the sum of three bf16 parts, and a product is
+                               summed over its six part products that reach 2^-24 of it (the symmetric mode: fp32 MFMA) */
     SDKDE_PREC_FP16X2 = 1,  /* each input split into two fp16 halves (hi + lo, ~22 mantissa bits) and
                                multiplied on the fp16 matrix units with fp32 accumulate; Phi X, exp and all
                                sums stay fp32.  A lower-precision-input mode: its error is reported
@@ -202,9 +204,9 @@ int sdkde_fit_eval(const float *samples, int64_t n, const float *queries, int64_
  * library's device image, one copy per GPU, held until the process ends.  No allocation of any kind happens
  * in the call; inputs and outputs are still the caller's device arrays, with the meaning they have in
  * sdkde_fit_eval, and the results are bit-identical to those of sdkde_fit_eval with a workspace of
- * sdkde_workspace_bytes(n, m, d, flags).  Sizes for which that figure exceeds SDKDE_STATIC_SCRATCH_BYTES are
- * refused with SDKDE_ETOOLARGE and nothing is launched (the buffer serves e.g. n = m = 32768 at d = 16,
- * n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
+ * sdkde_workspace_bytes(n, m, d, flags) where that figure is at most SDKDE_STATIC_SCRATCH_BYTES.  A larger pass is
+ * served (fp32 matrix path) while both of its steps fit with fewer splits, and refused with SDKDE_ETOOLARGE, nothing launched,
+ * otherwise (the buffer serves e.g. n = m = 32768 at d = 16, n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
  * in it has to start at zero, every call rewrites what it reads.  All calls on one GPU share the one buffer:
  * two calls that overlap in time on the same GPU (different streams or host threads) race; order them on
  * one stream.  The first call on a device looks up the buffer's device address (no stream work); make it
@@ -231,7 +233,7 @@ int sdkde_eval_laplace(const float *samples, int64_t n, const float *queries, in
  * Introspection of the host-side plan (grid decomposition and workspace layout) that a call with these
  * sizes would use; touches no device.  call: 0 = sdkde_score at the samples, 1 = sdkde_score at m
  * separate points, 2 = sdkde_eval / sdkde_eval_laplace at m queries.  out (host, at least 20 entries):
- *   [0] thin path (0/1)      [1] padded dimension   [2] row tiles per wave (thin: rows per thread)
+ *   [0] thin path (0/1)      [1] padded dimension   [2] row tiles per quarter of a workgroup (thin: rows per thread)
  *   [3] rows per workgroup   [4] row blocks         [5] splits of the sample axis
  *   [6] sample tiles per split   [7] sample tiles (of 16)   [8] padded sample rows   [9] padded point rows
  *   [10] workspace bytes     [11..17] byte offsets in the workspace of: prepared samples, their
@@ -256,7 +258,7 @@ int sdkde_describe_plan(int64_t n, int64_t m, int32_t d, int32_t call, uint32_t 
  * is meant for have been issued.  Normal use never calls this; the library reads no environment variables.
  */
 enum {
-    SDKDE_TUNE_SCORE_ROW_TILES = 0, /* row tiles per wave (thin path: rows per thread) of the score calls */
+    SDKDE_TUNE_SCORE_ROW_TILES = 0, /* row tiles per quarter of a workgroup (thin path: rows per thread) of the score calls */
     SDKDE_TUNE_SCORE_SPLITS = 1,    /* splits of the sample axis of the score calls */
     SDKDE_TUNE_EVAL_ROW_TILES = 2,  /* the same two for sdkde_eval / sdkde_eval_laplace */
     SDKDE_TUNE_EVAL_SPLITS = 3,

@@ -1,6 +1,7 @@
 // Reductions of the partial sums and the elementwise kernels: score / eval epilogues, debias, max-shift.
 #pragma once
 #include "common.h"
+#include "split3.h"
 
 namespace {
 
@@ -44,7 +45,27 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     return r;
 }
 
-// ps_split_half: p~ is stored as fp16 hi/lo pairs (fp16x2 input mode) and is rebuilt as hi + lo.
+// p~_i[c] of the prepared rows, from whichever format holds them.
+__device__ __forceinline__ float prepared_value(const float* ps, int64_t i, int c, int dp, int format)
+{
+    if (format == kFormatSplit3) return split3_value(ps, i, c, dp);
+    if (format != SDKDE_PREC_FP32) {       // fp16 hi + lo
+        const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);
+        return (float)ph[0] + (float)ph[16];
+    }
+    return ps[i * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))];      // fp32 layout of the prepared rows
+}
+
+// Columns c0 .. c0+3 of it (c0 a multiple of four, below dp).
+__device__ __forceinline__ f32x4 prepared_quad(const float* ps, int64_t i, int c0, int dp, int format)
+{
+    if (format == kFormatSplit3) return split3_quad(ps, i, c0, dp);
+    f32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = prepared_value(ps, i, c0 + k, dp, format);
+    return v;
+}
+
 // mode 0 (MFMA path, separate points): score = (T/D - p~) * inv_ah2            (T = Phi X regrouping)
 // mode 1 (thin path):                   score = (N/D) * inv_ah2                (direct-form numerator)
 // mode 2 (MFMA path, at the samples):   score = (T' - p~ D') / (D' + 1) * inv_ah2
@@ -55,7 +76,7 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
-    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int ps_split_half, float inv_ah2,
+    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
     float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, float min_sum)
 {
     constexpr int kEpiOutputs = kBlock / PARTS;
@@ -67,15 +88,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const float tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
     const float dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
-    float pc = 0.0f;                       // p~_i[c]
-    if (mode != 1) {
-        if (ps_split_half) {
-            const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);
-            pc = (float)ph[0] + (float)ph[16];
-        } else {
-            pc = ps[i * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))];      // fp32 layout of the prepared rows
-        }
-    }
+    const float pc = mode != 1 ? prepared_value(ps, i, c, dp, format) : 0.0f;
     float out = 0.0f;
     if (mode == 2) {
         out = fmaf(-pc, dsum, tsum) / (dsum + 1.0f) * inv_ah2;
@@ -94,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
 // Grid: one workgroup per kBlock / kEpiPartsFew (row, four columns) pairs of the [m, dp] partials.
 __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
-    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int ps_split_half, float inv_ah2,
+    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
     float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, int quad_io,
     float min_sum)
 {
@@ -126,20 +139,13 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
         tsum += red_t[k][lane];
         dsum += red_d[k][lane];
     }
+    const f32x4 pc = prepared_quad(ps, i, c0, dp, format);     // may run past d in the last quad: padding, not stored
     f32x4 out;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const int c = c0 + v;       // may run past d in the last quad: computed from padding, not stored
-        float pc;
-        if (ps_split_half) {
-            const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);
-            pc = (float)ph[0] + (float)ph[16];
-        } else {
-            pc = ps[i * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))];      // fp32 layout of the prepared rows
-        }
         float o = 0.0f;
-        if (mode == 2) o = fmaf(-pc, dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;
-        else if (dsum >= min_sum) o = (tsum[v] / dsum - pc) * inv_ah2;
+        if (mode == 2) o = fmaf(-pc[v], dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;
+        else if (dsum >= min_sum) o = (tsum[v] / dsum - pc[v]) * inv_ah2;
         out[v] = o;
     }
     const int64_t at = i * d + c0;

@@ -16,9 +16,9 @@ namespace {
 // Workgroups [blocks_sd, ...): the queries, as prep_mfma_kernel prepares them (centre read from the workspace).
 __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* ps, int nsplit, int64_t m,
-    int64_t m_pad, int d, int dp, int ps_split_half, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
+    int64_t m_pad, int d, int dp, int format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
     float half_h2, float* __restrict__ x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
-    PrepCommon common, float a, int prec, Stamp stamp)
+    PrepCommon common, float a, Stamp stamp)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
     __shared__ double red[kBlock];
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const bool poisoned = stamp_poisons(stamp, &stamp_flag);
     prep_common(common, d, red, smean);
     if ((int)blockIdx.x >= blocks_sd) {
-        prep_rows<false>(q_job, (int64_t)(blockIdx.x - blocks_sd) * kPrepRows, d, dp, a, prec, poisoned, smean, raw, used);
+        prep_rows<false>(q_job, (int64_t)(blockIdx.x - blocks_sd) * kPrepRows, d, dp, a, format, poisoned, smean, raw, used);
         return;
     }
 
@@ -62,20 +62,12 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
                 tsum += red_t[k][lane];
                 dsum += red_d[k][lane];
             }
+            const f32x4 pc = prepared_quad(ps, i, c0, dp, format);     // may run past d in the last quad: padding, not stored
             f32x4 out, shifted;
             const int64_t at = i * d + c0;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int c = c0 + v;       // may run past d in the last quad: computed from padding, not stored
-                float pc;
-                if (ps_split_half) {
-                    const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);
-                    pc = (float)ph[0] + (float)ph[16];
-                } else {
-                    pc = ps[i * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))];
-                }
-                out[v] = fmaf(-pc, dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;      // the samples' own pair is not in the sums
-            }
+            for (int v = 0; v < 4; ++v)
+                out[v] = fmaf(-pc[v], dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;   // the samples' own pair is not in the sums
             if (quad_io) {                  // d is a multiple of four and the caller's arrays are 16-byte aligned
                 const f32x4 xv = *reinterpret_cast<const f32x4*>(x + at);
 #pragma unroll
@@ -97,7 +89,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
         }
         __syncthreads();            // red_t / red_d are reused by the next pass; raw is read below
     }
-    prep_rows<true>(sd_job, r0, d, dp, a, prec, poisoned, smean, raw, used);
+    prep_rows<true>(sd_job, r0, d, dp, a, format, poisoned, smean, raw, used);
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-// Pair kernel of the matrix path (d >= 4): pair_mfma_kernel and its operand helpers.
+// Pair kernel of the fp16 input modes and of the in-block pass of the symmetric mode: pair_mfma_kernel and its helpers.
 #pragma once
 #include "common.h"
 
@@ -157,7 +157,7 @@ __device__ __forceinline__ void store_partials(float* __restrict__ part_t, float
     }
 }
 
-template <int KB, int NI, int KIND, int PREC, int KLAST = 4>
+template <int KB, int NI, int KIND, int PREC>
 __global__ __launch_bounds__(kBlock) void pair_mfma_kernel(
     const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs,
     const float* __restrict__ xt, const float* __restrict__ xn, float* __restrict__ part_t,
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void pair_mfma_kernel(
     const int64_t row_block = blockIdx.x / nsplit;
     const int64_t row0 = (row_block * kWavesPerBlock + wave) * (NI * kTile);
 
-    RowTiles<KB, NI, PREC, KLAST> rows;
+    RowTiles<KB, NI, PREC> rows;
     rows.load(ps, pn, row0, r, g);
     constexpr bool SCALED = SCORE && (PREC == SDKDE_PREC_FP16X2_ALL || PREC == SDKDE_PREC_FP16X2_PHI16);
     if (SCALED) {

@@ -1,6 +1,7 @@
 // Prep kernels: centre + scale + pad (+ fp16 hi/lo split) into the layouts the pair kernels read.
 #pragma once
 #include "common.h"
+#include "split3.h"
 
 namespace {
 
@@ -78,7 +79,7 @@ constexpr int kStampWords = 6;
 struct Stamp {
     uint64_t* where;                // in the workspace; null: no record kept or checked
     int check;                      // 0: write `value` (workgroup 0), 1: compare with `value`
-    uint64_t value[kStampWords];    // kind of call, samples pointer, n, d, precision mode, bits of the scale a
+    uint64_t value[kStampWords];    // kind of call, samples pointer, n, d, operand format, bits of the scale a
 };
 
 // Thread 0 of every workgroup reads or (workgroup 0) writes the record; returns whether this launch is poisoned.
@@ -105,18 +106,20 @@ constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (tw
 //                    16-column block coordinate c sits at position 4 (c % 4) + c / 4,
 //   dst_t[row/16][col][row%16] = the same values with each 16-sample tile transposed (if dst_t),
 //   dst_n[row]     = -|dst[row]|^2 in double, rounded once; kPadNorm for padding rows.
-// prec >= SDKDE_PREC_FP16X2 (fp16x2 input modes): dst holds, per 16-column block, 16 fp16 "hi" values
+// format kFormatSplit3: dst and dst_t hold three bf16 parts of each value in the layouts of split3.h (kPrepRows rows are
+// one chunk of either, so a workgroup writes two contiguous blocks, 16 bytes a thread), and the norm is halved.
+// fp16x2 input modes: dst holds, per 16-column block, 16 fp16 "hi" values
 // followed by 16 fp16 "lo" values with hi + lo = the fp32 coordinate to ~22 mantissa bits (same bytes
 // per row as fp32); the norm is then taken of hi + lo so that it matches what the MFMA multiplies.
-// prec == SDKDE_PREC_FP16X2_ALL: dst_t holds fp16 pairs too, laid out as the A operand of the K = 32
+// FP16X2_ALL: dst_t holds fp16 pairs too, laid out as the A operand of the K = 32
 // second contraction: for tile, column c and lane group g, eight halves [hi(4g..4g+3) | the same again]
 // followed by eight halves [lo(4g..4g+3) | the same again] (twice the bytes of the fp32 layout).
-// prec == SDKDE_PREC_FP16X2_PHI16: dst_t holds, for tile, column c and lane group g, eight halves
+// FP16X2_PHI16: dst_t holds, for tile, column c and lane group g, eight halves
 // [hi(4g..4g+3) | lo(4g..4g+3)].
 // The body for one workgroup: rows r0 .. r0 + kPrepRows of `job`.  STAGED: the input values of those rows are
 // already in raw[][] (a caller that has just computed them); otherwise they are read from job.src.
 template <bool STAGED>
-__device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, float a, int prec, bool poisoned,
+__device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, float a, int format, bool poisoned,
                                           const float* smean, float (*raw)[SDKDE_MAX_D + 1], float (*used)[SDKDE_MAX_D + 1])
 {
     _Float16* dst_h = reinterpret_cast<_Float16*>(job.dst);
@@ -126,7 +129,8 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         float v = 0.0f;
         if (row < job.rows && c < d) v = a * ((STAGED ? raw[rr][c] : job.src[row * d + c]) - smean[c]);
         raw[rr][c] = v;
-        if (prec != SDKDE_PREC_FP32) {
+        if (format == kFormatSplit3) continue;              // the parts are written below
+        if (format != SDKDE_PREC_FP32) {
             const _Float16 hi = (_Float16)v;
             const _Float16 lo = (_Float16)(v - (float)hi);
             _Float16* out = dst_h + row * 2 * dp + (c / 16) * 32 + (c % 16);
@@ -140,7 +144,39 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         used[rr][c] = v;
     }
     __syncthreads();
-    if (job.dst_t && prec == SDKDE_PREC_FP16X2_PHI16) {
+    if (format == kFormatSplit3) {
+        static_assert(kPrepRows == kChunkRows, "a workgroup writes whole chunks");
+        const int kb = dp / 16;
+        char* rows_out = reinterpret_cast<char*>(job.dst) + r0 * 6 * dp;
+        char* t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
+        // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other
+        // (at dp = 16 one wave each), the norms below are left to the last wave.
+        const int row_items = kPrepRows * dp / 8, t_items = t_out ? kb * kWave : 0;
+        for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += kBlock) {
+            char* at;
+            int stride;
+            float v[8];
+            if (at_item < row_items) {
+                const int rr = at_item % kPrepRows, c0 = at_item / kPrepRows * 8;
+                at = rows_out + split3_offset(rr, c0, dp, &stride);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = raw[rr][c0 + k];
+            } else {
+                const int lane = at_item % kWave, mb = (at_item - row_items) / kWave;
+                const int c = mb * 16 + (lane & 15), s0 = (lane >> 4) * 4;
+                at = t_out + mb * 3 * kPartBytes + lane * 16;
+                stride = kPartBytes;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = raw[s0 + (k & 3) + (k >> 2) * kTile][c];
+            }
+            uint32_t part[4][3];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) split3_rne(v[2 * k], v[2 * k + 1], part[k]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<u32x4*>(at + q * stride) = u32x4{part[0][q], part[1][q], part[2][q], part[3][q]};
+        }
+    } else if (job.dst_t && format == SDKDE_PREC_FP16X2_PHI16) {
         // A operand of the K = 32 second contraction with single-fp16 weights: for tile, column c and lane group g,
         // eight halves [hi(4g..4g+3) | lo(4g..4g+3)] (the bytes of the fp32 layout)
         _Float16* base = reinterpret_cast<_Float16*>(job.dst_t) + (r0 / kTile) * (int64_t)dp * 32;
@@ -151,7 +187,7 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
             const _Float16 hi = (_Float16)v;
             base[idx] = e < 4 ? hi : (_Float16)(v - (float)hi);
         }
-    } else if (job.dst_t && prec != SDKDE_PREC_FP16X2_ALL) {
+    } else if (job.dst_t && format != SDKDE_PREC_FP16X2_ALL) {
         float* base = job.dst_t + (r0 / kTile) * (int64_t)dp * kTile;
         for (int idx = threadIdx.x; idx < kPrepRows * dp; idx += kBlock) {
             const int tile = idx / (dp * kTile), c = (idx / kTile) % dp, rr = idx % kTile;
@@ -167,17 +203,20 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
             base[idx] = e < 8 ? hi : (_Float16)(v - (float)hi);
         }
     }
-    if (threadIdx.x < kPrepRows) {
+    if (threadIdx.x >= kBlock - kPrepRows) {
+        const int rr = threadIdx.x - (kBlock - kPrepRows);
         double acc = 0.0;
-        for (int c = 0; c < dp; ++c) acc += (double)used[threadIdx.x][c] * (double)used[threadIdx.x][c];
-        const int64_t row = r0 + threadIdx.x;
+        const float* v = format == kFormatSplit3 ? raw[rr] : used[rr];
+        for (int c = 0; c < dp; ++c) acc += (double)v[c] * (double)v[c];
+        if (format == kFormatSplit3) acc *= 0.5;
+        const int64_t row = r0 + rr;
         job.dst_n[row] = poisoned ? __builtin_nanf("") : row < job.rows ? -(float)acc : kPadNorm;
     }
 }
 
 // Grid: job0's blocks first (blocks0 of them), then job1's.
 __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob job1, int blocks0, int d, int dp,
-                                                           PrepCommon common, float a, int prec, Stamp stamp)
+                                                           PrepCommon common, float a, int format, Stamp stamp)
 {
     __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
@@ -190,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob& job = second ? job1 : job0;
     const int64_t r0 = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kPrepRows;
-    prep_rows<false>(job, r0, d, dp, a, prec, poisoned, smean, raw, used);
+    prep_rows<false>(job, r0, d, dp, a, format, poisoned, smean, raw, used);
 }
 
 // Thin-d variant: dst[row][d] = a (x - mean), padding rows get pad_value in every coordinate.

@@ -1,5 +1,5 @@
-// SD-KDE hot path for MI355X (gfx950 / CDNA4): prep, pair-interaction kernels (fp32 MFMA for
-// d >= 4, direct differences for thin d), split reduction + epilogues, and the C ABI.
+// SD-KDE hot path for MI355X (gfx950 / CDNA4): prep, pair-interaction kernels (MFMA for d >= 4, direct
+// differences for thin d), split reduction + epilogues, and the C ABI.
 //
 // Notation follows the paper: c = 1/(2h^2), phi_ij = exp(-c |p_i - x_j|^2),
 // D_i = sum_j phi_ij, T_i = sum_j phi_ij x_j  (Method section: T = Phi X).
@@ -7,16 +7,16 @@
 // All coordinates are taken relative to a centre of the samples and scaled by a = sqrt(c log2 e), so that
 // the squared distance in scaled units is directly the (negated) argument of exp2:
 //     phi_ij = exp2( 2 p~_i . x~_j - |p~_i|^2 - |x~_j|^2 ).
-// The cross term is the Gram-matrix tile of the Method section, computed with fp32 MFMA;
-// the score numerator uses Phi X with the Phi tile still in the registers the first MFMA
-// left it in.
+// The cross term is the Gram-matrix tile of the Method section, computed with MFMAs (fp32 operands as
+// three bf16 parts each, split3.h); the score numerator uses Phi X with the Phi tile still in the
+// registers the first MFMA left it in.
 #include <string.h>
 #include <atomic>
 #include <mutex>
 #include "common.h"
 #include "prep.h"
 #include "pair_mfma.h"
-#include "pair_lds.h"
+#include "pair_split.h"
 #include "pair_sym.h"
 #include "pair_thin.h"
 #include "epilogue.h"
@@ -28,28 +28,44 @@ namespace {
 // Host side: plan, workspace layout, dispatch.
 // ------------------------------------------------------------------------------------------
 
-// Whether the kinds without a second contraction run pair_lds_kernel (sample tile staged in LDS) instead of
-// pair_mfma_kernel: fp32 inputs from dp = 64 on.  Measured (eval, n = 262144, m = 65536, best plan of each):
-// d = 32 9.42 against 9.10 ms (slower), d = 48 13.03 / 13.16, d = 64 16.37 / 17.57, d = 128 32.0 / 43.5 ms.
-constexpr bool lds_staged(int kb, int prec) { return prec == SDKDE_PREC_FP32 && kb >= 4; }
-
-// Most row tiles per wave for which the pair kernels are instantiated (larger ones would spill registers).
-constexpr int max_row_tiles(int kb, int kind, int prec = SDKDE_PREC_FP32)
+// Most row tiles per wave for which pair_mfma_kernel is instantiated (larger ones would spill registers): the fp16 input
+// modes, and the in-block pass of the symmetric mode.
+constexpr int max_row_tiles(int kb, int kind, int prec)
 {
     const bool second = kind == kScoreSelf || kind == kScorePoints || kind == kScoreBand;   // has the Phi X contraction
     if ((prec == SDKDE_PREC_FP16X2_ALL || prec == SDKDE_PREC_FP16X2_PHI16) && kb > 1) return 0;      // see effective_prec()
-    if (kind == kScoreBand && (kb > 2 || prec != SDKDE_PREC_FP32)) return 0;          // see sym_row_tiles()
-    if (!second && lds_staged(kb, prec)) return 4;
-    return second ? (kb == 1 ? 8 : (kb <= 4 || (kb == 5 && prec == SDKDE_PREC_FP32)) ? 4 : 2)
+    if ((kind == kScoreBand) != (prec == SDKDE_PREC_FP32)) return 0;
+    if (kind == kScoreBand && kb > 2) return 0;                                       // see sym_row_tiles()
+    return second ? (kb == 1 ? 8 : kb <= 4 ? 4 : 2)
                   : (kb == 1 ? 16 : kb == 2 ? 8 : kb <= 4 ? 4 : 2);
 }
 
-// Whether pair_mfma_kernel is also built with fewer MFMAs for a partly filled last 16-column block (KLAST < 4):
-// fp32 inputs and d <= 32, where the saving is largest (d = 5..8 needs 6 instead of 8 MFMAs per tile in the score,
-// 2 instead of 4 in eval); every kind but the symmetric mode's in-block pass, which is a sliver of its work.
-constexpr bool partial_last_block_built(int kb, int kind, int prec)
+// Shapes of pair_split_kernel: a workgroup of `waves` waves of `ni` row tiles each holds 16 ni waves rows; the plan counts
+// them as rt = ni waves / 4 (so that a workgroup has 64 rt rows, as in the other kernels).  nb, ahead, minw: see there.
+// ni = 0: not built.  Which shapes are built was measured at n = m = 65536 (clocks per 256 pairs and SIMD at 2.4 GHz;
+// the sum of the MFMAs at 16 clocks and the vector work alone is 210 / 306 / 402 / 498 for the score at dp = 16 .. 64):
+//   score  dp = 16   rt 8 / 4 / 2: 232 / 227 / 231        dp = 32  rt 4 / 2: 342 / 356    dp = 48  554 / 521
+//          dp = 64   623 / 651     dp = 80  812 / 840     dp = 96  960 / 1245 (one wave per SIMD)
+//   eval   dp = 16   rt 8 / 4 / 2: 105 / 103 / 112        dp = 32  rt 4 / 2: 156 / 166    dp = 48  224 / 235
+//          dp = 64   273 / 288     dp = 96  420 / 424     dp = 128 580 / 557
+// At dp >= 112 the score's operands leave room for one wave per SIMD only (two would spill).
+struct SplitShape { int ni, waves, nb; bool ahead; int minw; };
+constexpr SplitShape split_shape(int kb, bool score, int rt)
 {
-    return prec == SDKDE_PREC_FP32 && kb <= 2 && kind != kScoreBand;
+    if (score) {
+        if (rt == 2) return {2, 4, 2, kb != 5, kb == 1 ? 4 : kb <= 5 ? 2 : 1};
+        if (rt == 4) return kb <= 2 ? SplitShape{4, 4, 4, true, 2} : kb <= 6 ? SplitShape{2, 8, 2, kb < 6, 2} : SplitShape{};
+        if (rt == 8 && kb == 1) return {8, 4, 1, false, 2};
+    } else {
+        if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : 2};
+        if (rt == 4) return kb <= 5 ? SplitShape{4, 4, kb == 5 ? 2 : 4, false, kb <= 2 ? 3 : 2} : SplitShape{2, 8, 2, false, 2};
+        if (rt == 8 && kb == 1) return {8, 4, 4, false, 2};
+    }
+    return {};
+}
+constexpr int max_split_rt(int kb, bool score)
+{
+    return split_shape(kb, score, 8).ni ? 8 : split_shape(kb, score, 4).ni ? 4 : 2;
 }
 
 // Precision mode a call actually runs in: the thin path is fp32 VALU code; the fp16 second contraction is
@@ -78,6 +94,7 @@ inline uint32_t anchored_flags(uint32_t flags, bool self)
 
 struct Plan {
     bool thin;
+    bool split3;          // three-part operands (pair_split_kernel), unless sym_on
     int d, dp;            // true and padded dimension (thin: dp == d)
     int ni;               // MFMA: row tiles per wave; thin: rows per thread
     int rows_per_block;
@@ -90,6 +107,17 @@ struct Plan {
     bool sym_on;
     int sym_ni, sym_rb, sym_per_group, sym_nblocks, sym_ngroups;
 };
+
+// How a call's prepared rows are held (common.h), and the scale of its coordinates: sqrt(c log2 e),
+// times sqrt 2 in the three-part format, which carries the factor 2 of the cross term in both of its operands.
+inline int operand_format(const Plan& p, uint32_t flags)
+{
+    return p.split3 && !p.sym_on ? kFormatSplit3 : (int)effective_prec(flags, p.thin, p.dp);
+}
+inline double operand_scale(int format, double h)
+{
+    return sqrt(1.4426950408889634074 / (format == kFormatSplit3 ? h * h : 2.0 * h * h));
+}
 
 // Overrides of the plan's own choices, set through sdkde_set_tuning (tests and sweeps); 0: none.
 std::atomic<int> g_tuning[SDKDE_TUNE_COUNT];
@@ -105,17 +133,13 @@ constexpr int64_t kTargetBlocks = 2048;
 constexpr int kComputeUnits = 256;
 
 // Relative cost per unit of work of running the matrix-path kernels with `ni` row tiles per wave instead of the
-// best count (operand reuse against register pressure), measured on MI355X at n = 65536 .. 262144 with fp32
-// inputs: score d = 16: 2 / 4 / 8 row tiles 2.67 / 2.37 / 2.37 ms (n = 65536); d = 64: 2 / 4: 9.67 / 8.11 ms;
-// eval d = 16 (n = 262144, m = 65536): 2 / 4 / 8 / 16: 5.70 / 5.55 / 5.51 / 5.57 ms; d = 32: 2 / 4 / 8:
-// 9.57 / 9.21 / 9.10 ms; d = 48: 2 / 4: 14.3 / 13.1 ms; d = 64 and 128 (pair_lds_kernel): 2 / 4: 16.9 / 16.8 and
-// 32.5 / 32.0 ms.
+// best count (operand reuse against register pressure), measured on MI355X: the fp32 mode from the figures at split_shape,
+// the fp16 input modes at n = 131072 resp. n = 262144, m = 65536.
 double row_tiles_penalty(bool score, int kb, int ni, uint32_t prec)
 {
     if (prec != SDKDE_PREC_FP32) {
-        // fp16 input modes (n = 131072 resp. n = 262144, m = 65536): the cheap MFMAs leave the operand loads and
-        // the VALU work exposed, so few row tiles cost much more than with fp32 inputs.  Score, fp16x2: d = 16
-        // 2 / 4 / 8 row tiles 6.51 / 6.02 / 6.13 ms, d = 32 2 / 4: 12.1 / 10.7, d = 64: 24.0 / 21.7; fp16x2-all
+        // The cheap MFMAs leave the operand loads and the VALU work exposed, so few row tiles cost much.  Score, fp16x2:
+        // d = 16 2 / 4 / 8 row tiles 6.51 / 6.02 / 6.13 ms, d = 32 2 / 4: 12.1 / 10.7, d = 64: 24.0 / 21.7; fp16x2-all
         // (d = 16 only): 9.88 / 5.25 / 4.36 ms.  Eval: d = 16 2 / 4 / 8 / 16: 3.01 / 2.41 / 2.27 / 2.95 ms,
         // d = 32 2 / 4 / 8: 8.15 / 4.30 / 3.39, d = 64 2 / 4: 15.3 / 7.9 ms.
         if (score && (prec == SDKDE_PREC_FP16X2_ALL || prec == SDKDE_PREC_FP16X2_PHI16)) return ni >= 8 ? 1.0 : ni == 4 ? 1.2 : 2.25;
@@ -125,16 +149,12 @@ double row_tiles_penalty(bool score, int kb, int ni, uint32_t prec)
         return kb >= 5 ? 1.0 : ni == 4 ? 1.0 : 1.94;
     }
     if (score) {
-        if (kb >= 6) return 1.0;                              // only ni = 2 is built
-        // dp = 80: two row tiles leave room for two waves per SIMD, whose tile streams evict each other from the
-        // vector cache (n = 262144: 201 ms against 162 ms with four row tiles and one wave per SIMD)
-        if (kb == 5) return ni >= 4 ? 1.0 : 1.25;
-        return ni >= 8 ? 1.0 : ni == 4 ? (kb == 1 ? 1.004 : 1.0) : (kb == 1 ? 1.12 : 1.15);
+        if (kb == 1) return ni == 8 ? 1.0 : ni == 4 ? 1.01 : 1.05;
+        if (kb == 3) return ni == 2 ? 1.0 : 1.06;
+        return ni == 4 ? 1.0 : kb == 6 ? 1.3 : 1.04;
     }
-    if (kb == 1) return ni == 16 ? 1.013 : ni == 8 ? 1.0 : ni == 4 ? 1.005 : 1.035;
-    if (kb == 2) return ni == 8 ? 1.0 : ni == 4 ? 1.008 : 1.05;
-    if (lds_staged(kb, (int)prec)) return ni == 4 ? 1.0 : 1.01;
-    return ni == 4 ? 1.0 : 1.09;                              // kb = 3
+    if (kb == 1) return ni == 4 ? 1.0 : ni == 8 ? 1.02 : 1.085;
+    return kb >= 6 ? 1.0 : ni == 4 ? 1.0 : 1.05;
 }
 
 // Estimated time of the pair kernel plus its share of the epilogue for `ni` row tiles per wave and `nsplit`
@@ -152,15 +172,27 @@ double plan_cost(bool score, int kb, uint32_t prec, int64_t m, int64_t m_pad, in
     const int64_t rounds = (groups + kComputeUnits - 1) / kComputeUnits;
     int tps = (ntiles + nsplit - 1) / nsplit;
     tps += tps & 1;
+    const double slot_bytes = (double)m_pad * (score ? 16 * kb + 1 : 1) * 8.0;
+    if (prec == SDKDE_PREC_FP32) {
+        // pair_split_kernel, fitted to sweeps at n = 600 .. 100000: four (eval: one) tiles' time to start a workgroup; waves of
+        // several workgroups are needed on a SIMD to overlap its matrix and vector work (score at n = 4096, d = 16: one
+        // workgroup per compute unit 23.6 us, two 21.3; eval at 32768 x 4096: two 43.3 us, four 38.9); long workgroups
+        // leave eval a longer tail (65536 x 8192: four per unit 118 us, eight 114); a slot moves at 6 TB/s.
+        double work = (double)rounds * ni * (tps + (score ? 4.0 : 1.0)) * row_tiles_penalty(score, kb, ni, prec);
+        const int64_t waves = rounds * split_shape(kb, score, ni).waves / 4;
+        if (waves == 1) work *= 1.3;
+        else if (score && kb == 1 && waves == 2) work *= 1.02;
+        else if (!score && kb <= 2 && waves <= 3) work *= waves == 2 ? 1.1 : 1.04;
+        const double tile_clk = score ? 115.0 + 130.0 * kb : 45.0 + 62.0 * kb;      // measured, see split_shape
+        return work + (score ? 0.11 : 0.25) * ni * tps + nsplit * slot_bytes / 2500.0 / tile_clk;
+    }
     const double work = (double)rounds * ni * (tps + 1.0) * row_tiles_penalty(score, kb, ni, prec);
     const double tail = 0.1 * ni * tps;
-    // clocks per tile: the MFMAs at their measured issue time (33 clocks in fp32; the fp16 modes in proportion to
-    // their measured kernel times), plus exp and sums
+    // clocks per tile, in proportion to the measured kernel times, from those of an fp32 MFMA kernel
     double tile_clk = 33.0 * (score ? 8 : 4) * kb + 50.0;
     if (prec == SDKDE_PREC_FP16X2) tile_clk *= 0.62;
     if (prec == SDKDE_PREC_FP16X2_ALL) tile_clk *= score ? 0.41 : 0.62;
     if (prec == SDKDE_PREC_FP16X2_PHI16) tile_clk *= score ? 0.36 : 0.62;
-    const double slot_bytes = (double)m_pad * (score ? 16 * kb + 1 : 1) * 8.0;
     const double slot = slot_bytes / 1250.0 / tile_clk;          // 1250 bytes per clock = 3 TB/s at 2.4 GHz
     return work + tail + nsplit * slot;
 }
@@ -186,6 +218,11 @@ double plan_cost_thin(bool score, int d, int64_t m, int64_t m_pad, int ntiles, i
     return work + tail + nsplit * slot;
 }
 
+int most_row_tiles(int kb, bool score, uint32_t prec)
+{
+    return prec == SDKDE_PREC_FP32 ? max_split_rt(kb, score) : max_row_tiles(kb, score ? kScoreSelf : kEval, (int)prec);
+}
+
 Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
 {
     Plan p{};
@@ -200,7 +237,12 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
     p.n_pad = round_up(n, kRowPad);
     p.m_pad = round_up(m > 0 ? m : 1, kRowPad);
     p.ntiles = (int)((n + 2 * kTile - 1) / (2 * kTile)) * 2;   // even: the pair kernel alternates two operand sets
-    const int max_split = p.ntiles >= 32 ? p.ntiles / 16 : 1;   // at least 16 tiles per split
+    // at least 16 tiles per split; the three-part kernels take 4 (score at n = 600, d = 8: 8 splits 14.2 us, 2 splits 17.8;
+    // eval at 4096 x 512, d = 64: 64 splits 15.9 us, 16 splits 20.7)
+    const uint32_t prec = effective_prec(flags, false, p.dp);
+    p.split3 = !p.thin && prec == SDKDE_PREC_FP32;
+    const int least_tiles = p.split3 ? 4 : 16;
+    const int max_split = p.ntiles >= 2 * least_tiles ? p.ntiles / least_tiles : 1;
 
     // Candidate row-tile counts, largest (most operand reuse) first.
     int cand[5];
@@ -211,8 +253,7 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
         cand[nc++] = 4; cand[nc++] = 2; cand[nc++] = 1;
     } else {
         const int kb = p.dp / 16;
-        const int top = max_row_tiles(kb, score ? kScoreSelf : kEval, (int)effective_prec(flags, false, p.dp));
-        for (int v = top; v >= 2; v /= 2) cand[nc++] = v;
+        for (int v = most_row_tiles(kb, score, effective_prec(flags, false, p.dp)); v >= 2; v /= 2) cand[nc++] = v;
     }
     const int forced_ni = tuning(score ? SDKDE_TUNE_SCORE_ROW_TILES : SDKDE_TUNE_EVAL_ROW_TILES, 0);
     int forced_split = tuning(score ? SDKDE_TUNE_SCORE_SPLITS : SDKDE_TUNE_EVAL_SPLITS, 0);
@@ -221,7 +262,7 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
         // a forced value must be one the dispatch tables below instantiate
         const int kb = p.thin ? 0 : p.dp / 16;
         const int widest = p.thin ? (d > kThinMaxDEval ? 1 : 4)
-                                  : max_row_tiles(kb, score ? kScoreSelf : kEval, (int)effective_prec(flags, false, p.dp));
+                                  : most_row_tiles(kb, score, effective_prec(flags, false, p.dp));
         const int narrowest = p.thin ? 1 : 2;
         if (forced_ni >= narrowest && forced_ni <= widest && (forced_ni & (forced_ni - 1)) == 0) {
             cand[0] = forced_ni;
@@ -235,15 +276,17 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
         if (p.row_blocks < 1) p.row_blocks = 1;
     };
 
-    if (max_split >= 8) {
+    if (max_split >= 8 || p.split3) {
         // Enough samples for one group of splits per XCD: the (row tiles or rows per thread, splits) pair of least
-        // estimated time; ties go to more rows per workgroup, then fewer splits.
-        const uint32_t prec = effective_prec(flags, false, p.dp);
-        const int most = max_split / 8 * 8 < 1024 ? max_split / 8 * 8 : 1024;
+        // estimated time; ties go to more rows per workgroup, then fewer splits.  Up to n = 16384 the three-part
+        // kernels may take fewer splits too: the prepared samples then fit one XCD's L2 whole.
+        const int most = max_split >= 8 ? (max_split / 8 * 8 < 1024 ? max_split / 8 * 8 : 1024) : max_split;
+        const int first = forced_split > 0 ? forced_split : p.split3 && p.ntiles <= 1024 ? 1 : 8;
+        const int last = forced_split > 0 ? forced_split : most;
         double best = 0.0;
         int best_ni = 0, best_split = 0;
         for (int k = 0; k < nc; ++k) {
-            for (int sp = forced_split > 0 ? forced_split : 8; sp <= (forced_split > 0 ? forced_split : most); sp += 8) {
+            for (int sp = first; sp <= last; sp += sp < 8 ? 1 : 8) {
                 const double c = p.thin ? plan_cost_thin(score, d, m > 0 ? m : 1, p.m_pad, p.ntiles, cand[k], sp)
                                         : plan_cost(score, p.dp / 16, prec, m > 0 ? m : 1, p.m_pad, p.ntiles, cand[k], sp);
                 if (best_ni == 0 || c < best) {
@@ -358,13 +401,15 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
     };
     w.centre = (float*)take(sizeof(float) * SDKDE_MAX_D);
     w.stamp = (uint64_t*)take(sizeof(uint64_t) * kStampWords);
-    w.xs = (float*)take(sizeof(float) * p.n_pad * p.dp);
-    // blocked transpose for the second contraction: fp32, or hi/lo fp16 pairs stored twice (2x the bytes)
-    const size_t xt_scale = effective_prec(flags, p.thin, p.dp) == SDKDE_PREC_FP16X2_ALL ? 2 : 1;
-    w.xt = (score && !p.thin) ? (float*)take(sizeof(float) * xt_scale * p.n_pad * p.dp) : nullptr;
+    const int format = operand_format(p, flags);
+    auto rows_floats = [&](int64_t rows) { return (size_t)(format == kFormatSplit3 ? split3_floats(rows, p.dp) : rows * p.dp); };
+    w.xs = (float*)take(sizeof(float) * rows_floats(p.n_pad));
+    // blocked transpose for the second contraction: as the rows, or hi/lo fp16 pairs stored twice (2x the bytes)
+    const size_t xt_scale = format == SDKDE_PREC_FP16X2_ALL ? 2 : 1;
+    w.xt = (score && !p.thin) ? (float*)take(sizeof(float) * xt_scale * rows_floats(p.n_pad)) : nullptr;
     w.xn = (float*)take(sizeof(float) * p.n_pad);
     if (separate_points) {
-        w.ps = (float*)take(sizeof(float) * p.m_pad * p.dp);
+        w.ps = (float*)take(sizeof(float) * rows_floats(p.m_pad));
         w.pn = (float*)take(sizeof(float) * p.m_pad);
         w.shift = (float*)take(sizeof(float) * p.m_pad);
     } else {
@@ -382,19 +427,30 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
 
 bool bad_bandwidth(double h) { return !(h > 0.0) || !isfinite(h); }
 
+// One group of splits per XCD, or a single split for tiny sample sets and for the three-part operands (their prepared
+// copies are half as large again, so the calls that used to fit a given buffer may have to give up more slots).
+inline int least_splits(const Plan& p) { return p.ntiles >= 128 && !p.split3 ? 8 : 1; }
+
 // For a workspace smaller than the plan's own decomposition needs (a buffer sized for another m, say): halves the
-// splits, down to one group per XCD (a single split for tiny sample sets).  False when already there.  Fewer
+// splits, down to least_splits.  False when already there.  Fewer
 // splits mean fewer partial-sum slots; the call is then slower for few points but needs less memory.
 bool fewer_splits(Plan& p)
 {
-    const int least = p.ntiles >= 128 ? 8 : 1;
-    if (p.sym_on || p.nsplit <= least) return false;
+    if (p.sym_on || p.nsplit <= least_splits(p)) return false;
     int s = p.nsplit / 2;
-    if (least == 8) s = s / 8 * 8;
-    p.nsplit = s < least ? least : s;
+    if (s >= 8) s = s / 8 * 8;
+    p.nsplit = s < least_splits(p) ? least_splits(p) : s;
     p.tiles_per_split = (p.ntiles + p.nsplit - 1) / p.nsplit;
     p.tiles_per_split += p.tiles_per_split & 1;
     return true;
+}
+
+// Lays the call's plan out in `bytes` bytes at base, with fewer splits if it has to; false: does not fit.
+bool fit_workspace(Plan& p, bool score, bool separate_points, void* base, size_t bytes, uint32_t flags, Workspace* w)
+{
+    *w = layout(p, score, separate_points, base, flags);
+    while (w->bytes > bytes && fewer_splits(p)) *w = layout(p, score, separate_points, base, flags);
+    return w->bytes <= bytes;
 }
 
 // Optional instrumentation: event pairs around the main pair kernel of each call.
@@ -410,140 +466,159 @@ struct Profile {
         if ((call) != hipSuccess) return SDKDE_EDEVICE;   \
     } while (0)
 
-template <int KIND, int PREC>
-int launch_pair(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+// Host-side shape check of every pair kernel: the grid's size, and that every row it touches exists in the padded arrays.
+int check_grid(const Plan& p)
+{
+    if ((int64_t)p.row_blocks * p.nsplit > 0x7fffffffLL) return SDKDE_EUNSUPPORTED;
+    if (p.row_blocks * p.rows_per_block > p.m_pad || (int64_t)p.ntiles * kTile > p.n_pad) return SDKDE_EINVAL;
+    return SDKDE_OK;
+}
+
+inline int launched() { return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE; }
+
+template <int KIND>
+int launch_thin(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
     const dim3 grid((unsigned)(p.row_blocks * p.nsplit)), block(kBlock);
-    if ((int64_t)p.row_blocks * p.nsplit > 0x7fffffffLL) return SDKDE_EUNSUPPORTED;
     const float laplace_c0 = 1.0f + 0.5f * (float)p.d;
-    // Host-side shape check: every row the grid touches exists in the padded arrays.
-    if (p.row_blocks * p.rows_per_block > p.m_pad || (int64_t)p.ntiles * kTile > p.n_pad) return SDKDE_EINVAL;
-
-#define SDKDE_LAUNCH_MFMA_K(KB_, NI_, KLAST_)                                                                     \
-    hipLaunchKernelGGL((pair_mfma_kernel<KB_, NI_, KIND, PREC, KLAST_>), grid, block, 0, st, w.ps, w.pn, w.xs,    \
-                       w.xt, w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,            \
-                       laplace_c0, shift)
-#define SDKDE_LAUNCH_MFMA(KB_, NI_)                                                                               \
-    do {                                                                                                          \
-        if constexpr (partial_last_block_built(KB_, KIND, PREC)) {                                                \
-            switch (p.klast) {                                                                                    \
-                case 1: SDKDE_LAUNCH_MFMA_K(KB_, NI_, 1); break;                                                  \
-                case 2: SDKDE_LAUNCH_MFMA_K(KB_, NI_, 2); break;                                                  \
-                case 3: SDKDE_LAUNCH_MFMA_K(KB_, NI_, 3); break;                                                  \
-                default: SDKDE_LAUNCH_MFMA_K(KB_, NI_, 4); break;                                                 \
-            }                                                                                                     \
-        } else {                                                                                                  \
-            SDKDE_LAUNCH_MFMA_K(KB_, NI_, 4);                                                                     \
-        }                                                                                                         \
-    } while (0)
-#define SDKDE_LAUNCH_THIN(D_, R_)                                                                      \
-    do {                                                                                               \
-        if constexpr (KIND != kScoreBand)                                                              \
-            hipLaunchKernelGGL((pair_thin_kernel<D_, R_, KIND>), grid, block, 0, st, w.ps, w.xs,       \
-                               w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,     \
-                               laplace_c0, shift);                                               \
-    } while (0)
-// d = 4 .. 6: the kinds a score call runs (one row per thread)
-#define SDKDE_LAUNCH_THIN_SCORE(D_)                                                                    \
-    do {                                                                                               \
-        if constexpr (KIND == kScoreSelf || KIND == kScorePoints || KIND == kRowMax) SDKDE_LAUNCH_THIN(D_, 1); \
-        else return SDKDE_EUNSUPPORTED;                                                                \
-    } while (0)
-#define SDKDE_CASE_NI(KB_, NI_)                                            \
-    case NI_:                                                              \
-        if constexpr (NI_ <= max_row_tiles(KB_, KIND, PREC)) SDKDE_LAUNCH_MFMA(KB_, NI_); \
-        else return SDKDE_EUNSUPPORTED;                                    \
-        break;
-
-    if (p.thin) {
-        if constexpr (KIND == kScoreBand) return SDKDE_EUNSUPPORTED;     // the symmetric mode is matrix-path only
-        const int key = p.d * 10 + p.ni;
-        switch (key) {
-            case 14: SDKDE_LAUNCH_THIN(1, 4); break;
-            case 12: SDKDE_LAUNCH_THIN(1, 2); break;
-            case 11: SDKDE_LAUNCH_THIN(1, 1); break;
-            case 24: SDKDE_LAUNCH_THIN(2, 4); break;
-            case 22: SDKDE_LAUNCH_THIN(2, 2); break;
-            case 21: SDKDE_LAUNCH_THIN(2, 1); break;
-            case 34: SDKDE_LAUNCH_THIN(3, 4); break;
-            case 32: SDKDE_LAUNCH_THIN(3, 2); break;
-            case 31: SDKDE_LAUNCH_THIN(3, 1); break;
-            case 41: SDKDE_LAUNCH_THIN_SCORE(4); break;
-            case 51: SDKDE_LAUNCH_THIN_SCORE(5); break;
-            case 61: SDKDE_LAUNCH_THIN_SCORE(6); break;
-            default: return SDKDE_EUNSUPPORTED;
-        }
-    } else if (lds_staged(p.dp / 16, PREC) && (KIND == kEval || KIND == kEvalLaplace || KIND == kRowMax)) {
-        if constexpr (PREC == SDKDE_PREC_FP32 && (KIND == kEval || KIND == kEvalLaplace || KIND == kRowMax)) {
-#define SDKDE_LAUNCH_LDS(KB_, NI_)                                                                                \
-    hipLaunchKernelGGL((pair_lds_kernel<KB_, NI_, KIND>), grid, block, 0, st, w.ps, w.pn, w.xs, w.xn, w.part_d,   \
+#define SDKDE_LAUNCH_THIN(D_, R_)                                                                          \
+    hipLaunchKernelGGL((pair_thin_kernel<D_, R_, KIND>), grid, block, 0, st, w.ps, w.xs, w.part_t, w.part_d, \
                        p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad, laplace_c0, shift)
-#define SDKDE_CASE_LDS(KB_)                                                                   \
-    case KB_:                                                                                 \
-        switch (p.ni) {                                                                       \
-            case 2: SDKDE_LAUNCH_LDS(KB_, 2); break;                                          \
-            case 4: SDKDE_LAUNCH_LDS(KB_, 4); break;                                          \
-            default: return SDKDE_EUNSUPPORTED;                                               \
-        }                                                                                     \
-        break;
-            switch (p.dp / 16) {
-                SDKDE_CASE_LDS(4) SDKDE_CASE_LDS(5) SDKDE_CASE_LDS(6) SDKDE_CASE_LDS(7) SDKDE_CASE_LDS(8)
-                default: return SDKDE_EUNSUPPORTED;
-            }
-#undef SDKDE_CASE_LDS
-#undef SDKDE_LAUNCH_LDS
-        }
-    } else {
-        const int kb = p.dp / 16;
-        switch (kb) {
-            case 1:
-                switch (p.ni) { SDKDE_CASE_NI(1, 16) SDKDE_CASE_NI(1, 8) SDKDE_CASE_NI(1, 4) SDKDE_CASE_NI(1, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 2:
-                switch (p.ni) { SDKDE_CASE_NI(2, 8) SDKDE_CASE_NI(2, 4) SDKDE_CASE_NI(2, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 3:
-                switch (p.ni) { SDKDE_CASE_NI(3, 4) SDKDE_CASE_NI(3, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 4:
-                switch (p.ni) { SDKDE_CASE_NI(4, 4) SDKDE_CASE_NI(4, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 5:
-                switch (p.ni) { SDKDE_CASE_NI(5, 4) SDKDE_CASE_NI(5, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 6:
-                switch (p.ni) { SDKDE_CASE_NI(6, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 7:
-                switch (p.ni) { SDKDE_CASE_NI(7, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            case 8:
-                switch (p.ni) { SDKDE_CASE_NI(8, 2) default: return SDKDE_EUNSUPPORTED; }
-                break;
-            default: return SDKDE_EUNSUPPORTED;
-        }
+// d = 4 .. 6: the kinds a score call runs (one row per thread)
+#define SDKDE_LAUNCH_THIN_SCORE(D_)                                                                        \
+    do {                                                                                                   \
+        if constexpr (KIND == kScoreSelf || KIND == kScorePoints || KIND == kRowMax) SDKDE_LAUNCH_THIN(D_, 1); \
+        else return SDKDE_EUNSUPPORTED;                                                                    \
+    } while (0)
+    switch (p.d * 10 + p.ni) {
+        case 14: SDKDE_LAUNCH_THIN(1, 4); break;
+        case 12: SDKDE_LAUNCH_THIN(1, 2); break;
+        case 11: SDKDE_LAUNCH_THIN(1, 1); break;
+        case 24: SDKDE_LAUNCH_THIN(2, 4); break;
+        case 22: SDKDE_LAUNCH_THIN(2, 2); break;
+        case 21: SDKDE_LAUNCH_THIN(2, 1); break;
+        case 34: SDKDE_LAUNCH_THIN(3, 4); break;
+        case 32: SDKDE_LAUNCH_THIN(3, 2); break;
+        case 31: SDKDE_LAUNCH_THIN(3, 1); break;
+        case 41: SDKDE_LAUNCH_THIN_SCORE(4); break;
+        case 51: SDKDE_LAUNCH_THIN_SCORE(5); break;
+        case 61: SDKDE_LAUNCH_THIN_SCORE(6); break;
+        default: return SDKDE_EUNSUPPORTED;
     }
-#undef SDKDE_CASE_NI
 #undef SDKDE_LAUNCH_THIN_SCORE
 #undef SDKDE_LAUNCH_THIN
-#undef SDKDE_LAUNCH_MFMA
-#undef SDKDE_LAUNCH_MFMA_K
-    return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
+    return launched();
+}
+
+// The fp32 mode at d >= 4 (score kinds d >= 7).
+template <int KIND, int KB, int RT>
+int launch_split_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+{
+    constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints;
+    constexpr SplitShape sh = split_shape(KB, score, RT);
+    if constexpr (sh.ni == 0) {
+        return SDKDE_EUNSUPPORTED;
+    } else {
+        static_assert(sh.ni * sh.waves == 4 * RT, "64 rt rows per workgroup");
+        hipLaunchKernelGGL((pair_split_kernel<KB, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND>),
+                           dim3((unsigned)(p.row_blocks * p.nsplit)), dim3(sh.waves * kWave), 0, st, w.ps, w.pn, w.xs, w.xt,
+                           w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,
+                           1.0f + 0.5f * (float)p.d, shift);
+        return launched();
+    }
+}
+
+template <int KIND, int KB>
+int launch_split_kb(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+{
+    switch (p.ni) {
+        case 8: return launch_split_shape<KIND, KB, 8>(p, w, shift, st);
+        case 4: return launch_split_shape<KIND, KB, 4>(p, w, shift, st);
+        case 2: return launch_split_shape<KIND, KB, 2>(p, w, shift, st);
+        default: return SDKDE_EUNSUPPORTED;
+    }
+}
+
+template <int KIND>
+int launch_split(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+{
+    switch (p.dp / 16) {
+        case 1: return launch_split_kb<KIND, 1>(p, w, shift, st);
+        case 2: return launch_split_kb<KIND, 2>(p, w, shift, st);
+        case 3: return launch_split_kb<KIND, 3>(p, w, shift, st);
+        case 4: return launch_split_kb<KIND, 4>(p, w, shift, st);
+        case 5: return launch_split_kb<KIND, 5>(p, w, shift, st);
+        case 6: return launch_split_kb<KIND, 6>(p, w, shift, st);
+        case 7: return launch_split_kb<KIND, 7>(p, w, shift, st);
+        case 8: return launch_split_kb<KIND, 8>(p, w, shift, st);
+        default: return SDKDE_EUNSUPPORTED;
+    }
+}
+
+// The fp16 input modes, and the in-block pass of the symmetric mode.
+template <int KIND, int PREC>
+int launch_mfma(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+{
+    const dim3 grid((unsigned)(p.row_blocks * p.nsplit)), block(kBlock);
+    const float laplace_c0 = 1.0f + 0.5f * (float)p.d;
+#define SDKDE_CASE_NI(KB_, NI_)                                                                                      \
+    case NI_:                                                                                                        \
+        if constexpr (NI_ <= max_row_tiles(KB_, KIND, PREC))                                                         \
+            hipLaunchKernelGGL((pair_mfma_kernel<KB_, NI_, KIND, PREC>), grid, block, 0, st, w.ps, w.pn, w.xs, w.xt, \
+                               w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad, laplace_c0, \
+                               shift);                                                                               \
+        else return SDKDE_EUNSUPPORTED;                                                                              \
+        break;
+    switch (p.dp / 16) {
+        case 1:
+            switch (p.ni) { SDKDE_CASE_NI(1, 16) SDKDE_CASE_NI(1, 8) SDKDE_CASE_NI(1, 4) SDKDE_CASE_NI(1, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 2:
+            switch (p.ni) { SDKDE_CASE_NI(2, 8) SDKDE_CASE_NI(2, 4) SDKDE_CASE_NI(2, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 3:
+            switch (p.ni) { SDKDE_CASE_NI(3, 4) SDKDE_CASE_NI(3, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 4:
+            switch (p.ni) { SDKDE_CASE_NI(4, 4) SDKDE_CASE_NI(4, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 5:
+            switch (p.ni) { SDKDE_CASE_NI(5, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 6:
+            switch (p.ni) { SDKDE_CASE_NI(6, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 7:
+            switch (p.ni) { SDKDE_CASE_NI(7, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        case 8:
+            switch (p.ni) { SDKDE_CASE_NI(8, 2) default: return SDKDE_EUNSUPPORTED; }
+            break;
+        default: return SDKDE_EUNSUPPORTED;
+    }
+#undef SDKDE_CASE_NI
+    return launched();
 }
 
 template <int KIND>
 int launch_pair_prec(const Plan& p, const Workspace& w, uint32_t flags, const float* shift, hipStream_t st)
 {
-    // the thin-d path has no matrix inputs: it runs the same fp32 VALU code for every mode
-    const uint32_t prec = effective_prec(flags, p.thin, p.dp);
-    constexpr bool has_second = KIND == kScoreSelf || KIND == kScorePoints || KIND == kScoreBand;
-    if constexpr (has_second) {
-        if (prec == SDKDE_PREC_FP16X2_ALL) return launch_pair<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
-        if (prec == SDKDE_PREC_FP16X2_PHI16) return launch_pair<KIND, SDKDE_PREC_FP16X2_PHI16>(p, w, shift, st);
+    const int rc = check_grid(p);
+    if (rc != SDKDE_OK) return rc;
+    if constexpr (KIND == kScoreBand) {
+        return launch_mfma<KIND, SDKDE_PREC_FP32>(p, w, shift, st);
+    } else {
+        // the thin-d path has no matrix inputs: it runs the same fp32 VALU code for every mode
+        if (p.thin) return launch_thin<KIND>(p, w, shift, st);
+        const uint32_t prec = effective_prec(flags, p.thin, p.dp);
+        if (prec == SDKDE_PREC_FP32) return launch_split<KIND>(p, w, shift, st);
+        if constexpr (KIND == kScoreSelf || KIND == kScorePoints) {
+            if (prec == SDKDE_PREC_FP16X2_ALL) return launch_mfma<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
+            if (prec == SDKDE_PREC_FP16X2_PHI16) return launch_mfma<KIND, SDKDE_PREC_FP16X2_PHI16>(p, w, shift, st);
+        }
+        // kinds without a second contraction: the fp16 modes are the same kernel
+        return launch_mfma<KIND, SDKDE_PREC_FP16X2>(p, w, shift, st);
     }
-    // kinds without a second contraction: the two fp16 modes are the same kernel
-    if (prec != SDKDE_PREC_FP32) return launch_pair<KIND, SDKDE_PREC_FP16X2>(p, w, shift, st);
-    return launch_pair<KIND, SDKDE_PREC_FP32>(p, w, shift, st);
 }
 
 // Symmetric mode: pairs across blocks (pair_sym_kernel), then the pairs inside each block with the ordinary
@@ -613,6 +688,9 @@ int launch_symmetric(const Plan& p, const Workspace& w, uint32_t flags, hipStrea
     Plan band = p;
     band.nsplit = 1;
     band.tiles_per_split = p.sym_rb / kTile;        // kScoreBand: the length of a block in tiles
+    band.ni = max_row_tiles(p.dp / 16, kScoreBand, SDKDE_PREC_FP32);
+    band.rows_per_block = kWavesPerBlock * kTile * band.ni;
+    band.row_blocks = ((int64_t)p.ntiles * kTile + band.rows_per_block - 1) / band.rows_per_block;
     Workspace wb = w;                               // its slots follow pair_sym_kernel's
     wb.part_t = w.part_t + (size_t)(p.sym_ngroups + 1) * p.m_pad * p.dp;
     wb.part_d = w.part_d + (size_t)(p.sym_ngroups + 1) * p.m_pad;
@@ -647,15 +725,15 @@ int launch_max_shift(const Plan& p, const Workspace& w, uint32_t flags, hipStrea
 // centre_src: the samples whose strided subsample gives the centre (also left in w.centre); null: w.centre as an
 // earlier launch on this workspace left it.
 // What identifies prepared samples: the kind of call that prepared them (the score and eval layouts differ), the
-// caller's array, its shape, the precision mode and the scale a = sqrt(log2 e / 2) / h as it reached the kernels.
-Stamp make_stamp(const Workspace& w, bool check, bool score, const float* samples, int64_t n, int d, uint32_t prec, float a)
+// caller's array, its shape, the operand format and the coordinate scale as it reached the kernels.
+Stamp make_stamp(const Workspace& w, bool check, bool score, const float* samples, int64_t n, int d, int format, float a)
 {
     Stamp s{};
     s.where = w.stamp;
     s.check = check ? 1 : 0;
     uint32_t abits;
     memcpy(&abits, &a, sizeof abits);
-    const uint64_t v[kStampWords] = {score ? 1u : 2u, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, prec, abits};
+    const uint64_t v[kStampWords] = {score ? 1u : 2u, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, (uint64_t)format, abits};
     for (int k = 0; k < kStampWords; ++k) s.value[k] = v[k];
     return s;
 }
@@ -674,7 +752,7 @@ int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, cons
         hipLaunchKernelGGL(prep_thin_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, common, a, stamp);
     else
         hipLaunchKernelGGL(prep_mfma_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, p.dp, common, a,
-                           (int)effective_prec(flags, p.thin, p.dp), stamp);
+                           operand_format(p, flags), stamp);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
@@ -725,7 +803,8 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     // 28.4 / 29.9 us, 4096 33.7 / 35.7, 8192 66.2 / 67.5, 32768 x 4096 662.3 / 665.0; d = 32: 4096 50.0 / 49.1;
     // d = 64: 4096 81.8 / 77.0; d = 128: 145.0 / 131.2.  It pays at dp = 16 only.
     if (ps.dp != 16) return false;
-    if (effective_prec(sflags, false, ps.dp) != effective_prec(flags, false, pe.dp)) return false;
+    const int format = operand_format(pe, flags);
+    if (operand_format(ps, sflags) != format) return false;
     const Workspace ws = layout(ps, true, false, workspace, sflags);
     const Workspace we = layout(pe, false, true, workspace, flags);
     if (ws.bytes > workspace_bytes || we.bytes > workspace_bytes) return false;
@@ -737,10 +816,10 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     const char* wr_end = (const char*)(we.pn + pe.m_pad);
     if (we.xs != ws.xs || wr_begin < dead_begin || wr_end > dead_end) return false;
     if ((const char*)we.ps < (const char*)(we.xn + pe.n_pad)) return false;
-    const double a = sqrt(1.4426950408889634074 / (2.0 * h * h));
+    const double a = operand_scale(format, h);
     out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord};
     out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f};
-    out->stamp = make_stamp(we, false, false, samples_sd, n, d, effective_prec(flags, false, pe.dp), (float)a);
+    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a);
     return true;
 }
 
@@ -763,19 +842,19 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
 
     Plan p = make_plan(n, m, d, true, flags);
     apply_symmetric(p, n, flags, self);
-    Workspace w = layout(p, true, !self, workspace, flags);
-    while (w.bytes > workspace_bytes && fewer_splits(p)) w = layout(p, true, !self, workspace, flags);
-    if (w.bytes > workspace_bytes) return SDKDE_EWORKSPACE;
+    Workspace w;
+    if (!fit_workspace(p, true, !self, workspace, workspace_bytes, flags, &w)) return SDKDE_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
 
-    const double a = sqrt(1.4426950408889634074 / (2.0 * h * h));   // sqrt(c log2 e)
+    const int format = operand_format(p, flags);
+    const double a = operand_scale(format, h);
     // at the samples themselves the largest weight is the self pair (exponent 0): nothing to shift
     const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
     const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord};
     const PrepJob point_job{self ? nullptr : points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f};
-    const Stamp stamp = make_stamp(w, false, true, samples, n, d, effective_prec(flags, p.thin, p.dp), (float)a);
+    const Stamp stamp = make_stamp(w, false, true, samples, n, d, format, (float)a);
     if ((rc = launch_prep(p, sample_job, point_job, samples, n, (float)a, w, flags, stamp, st)) != SDKDE_OK) return rc;
 
     if ((rc = profile_mark(0, 0, st)) != SDKDE_OK) return rc;
@@ -790,7 +869,6 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     const int64_t total = m * (int64_t)d;
     const int nslots = p.sym_on ? p.sym_ngroups + 2 : p.nsplit;
     const int mode = p.thin ? 1 : (self ? 2 : 0);        // see score_epilogue_kernel
-    const int ps_halves = effective_prec(flags, p.thin, p.dp) != SDKDE_PREC_FP32 ? 1 : 0;
     const float inv_ah2 = (float)(1.0 / (a * h * h)), half_h2 = (float)(0.5 * h * h);
     if (!p.thin && epilogue_parts(nslots, total) == kEpiPartsFew) {
         const int64_t quads = m * (p.dp / 4);
@@ -803,17 +881,17 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
             const int blocks_sd = (int)(fused->sd_job.rows_pad / kPrepRows);
             const int blocks_q = (int)(fused->q_job.rows_pad / kPrepRows);
             hipLaunchKernelGGL(score_epilogue_prep_kernel, dim3((unsigned)(blocks_sd + blocks_q)), dim3(kBlock), 0, st, w.part_t,
-                               w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, ps_halves, inv_ah2, score_out, samples, half_h2,
+                               w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, format, inv_ah2, score_out, samples, half_h2,
                                samples_sd_out, quad_io, fused->sd_job, fused->q_job, blocks_sd,
-                               PrepCommon{nullptr, 0, w.centre}, (float)a, (int)effective_prec(flags, p.thin, p.dp), fused->stamp);
+                               PrepCommon{nullptr, 0, w.centre}, (float)a, fused->stamp);
             return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
         }
         hipLaunchKernelGGL(score_epilogue_quad_kernel, dim3((unsigned)((quads + per_wg - 1) / per_wg)), dim3(kBlock), 0, st,
-                           w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, ps_halves, inv_ah2, score_out,
+                           w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
                            samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n));
     } else {
         SDKDE_LAUNCH_EPILOGUE(score_epilogue_kernel, nslots, total, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d,
-                              p.dp, mode, ps_halves, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n));
+                              p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n));
     }
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
@@ -830,12 +908,12 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
 
     Plan p = make_plan(n, m, d, false, flags);
-    Workspace w = layout(p, false, true, workspace, flags);
-    while (w.bytes > workspace_bytes && fewer_splits(p)) w = layout(p, false, true, workspace, flags);
-    if (w.bytes > workspace_bytes) return SDKDE_EWORKSPACE;
+    Workspace w;
+    if (!fit_workspace(p, false, true, workspace, workspace_bytes, flags, &w)) return SDKDE_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
 
-    const double a = sqrt(1.4426950408889634074 / (2.0 * h * h));
+    const int format = operand_format(p, flags);
+    const double a = operand_scale(format, h);
     const bool shifted = (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord};
     const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f};
@@ -845,11 +923,11 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
         // the workspace still holds the centre and the prepared samples (their place in the workspace depends
         // on n, d and the precision mode only, not on m): only the queries are prepared
         // (a call whose record of the prepared samples does not match gets NaN for every output)
-        const Stamp expect = make_stamp(w, true, false, samples, n, d, effective_prec(flags, p.thin, p.dp), (float)a);
+        const Stamp expect = make_stamp(w, true, false, samples, n, d, format, (float)a);
         if ((rc = launch_prep(p, query_job, PrepJob{}, nullptr, 0, (float)a, w, flags, expect, st)) != SDKDE_OK) return rc;
     } else {
         // reuse_centre: w.centre still holds the centre of an earlier pass over (nearly) the same points
-        const Stamp stamp = make_stamp(w, false, false, samples, n, d, effective_prec(flags, p.thin, p.dp), (float)a);
+        const Stamp stamp = make_stamp(w, false, false, samples, n, d, format, (float)a);
         if ((rc = launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, (float)a, w, flags, stamp, st)) != SDKDE_OK)
             return rc;
     }
@@ -951,11 +1029,18 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     if (!samples_sd_out) return SDKDE_EINVAL;
     int rc = check_common(samples, n, m, d, h, flags);
     if (rc != SDKDE_OK) return rc;
-    // The whole pass must fit the built-in buffer with the decomposition the ordinary call would take, so that
-    // both give the same bits; larger problems are refused, not run with fewer splits.
+    // The pass takes the decomposition the ordinary call would take, so that both give the same bits, where the built-in
+    // buffer holds a workspace of sdkde_workspace_bytes.  A pass that needs more is served on the three-part operands
+    // while both of its steps fit with fewer splits, and refused before anything is launched otherwise.
+    Plan score_plan = make_plan(n, n, d, true, flags), eval_plan = make_plan(n, m, d, false, flags);
+    apply_symmetric(score_plan, n, flags, true);
+    Workspace unused;
     size_t need = 0;
     if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
-    if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES) return SDKDE_ETOOLARGE;
+    if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES && !score_plan.split3 && !eval_plan.split3) return SDKDE_ETOOLARGE;
+    if (!fit_workspace(score_plan, true, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused) ||
+        (m > 0 && !fit_workspace(eval_plan, false, true, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused)))
+        return SDKDE_ETOOLARGE;
     void* ws = static_scratch_address();
     if (!ws) return SDKDE_EDEVICE;
     return sdkde_fit_eval(samples, n, queries, m, d, h, score_out, samples_sd_out, density_out, log_density_out, ws,
@@ -1016,8 +1101,7 @@ int sdkde_describe_plan(int64_t n, int64_t m, int32_t d, int32_t call, uint32_t 
         out[23] = p.sym_on ? p.sym_ngroups : 0;
     }
     if (out_len >= 25)
-        out[24] = (!p.thin && partial_last_block_built(p.dp / 16, score ? kScoreSelf : kEval, (int)effective_prec(flags, p.thin, p.dp)))
-                      ? p.klast : 4;
+        out[24] = !p.thin && p.dp <= 32 && effective_prec(flags, p.thin, p.dp) == SDKDE_PREC_FP32 ? p.klast : 4;
     if (out_len >= 26) {
         out[25] = 0;
         size_t need = 0;

@@ -1,0 +1,64 @@
+"""The fp32 mode's pair kernel (three bf16 parts per operand) in every workgroup shape it is built in, at its edges: one
+and several 16-column blocks, even and odd block counts, a nearly empty and a full last block, a ragged last chunk of
+samples, fewer chunks than splits, and own chunks split over workgroups.  Held to what fp32 arithmetic costs, not only to
+the general tolerance."""
+import numpy as np
+import pytest
+
+import oracle
+import sdkde_inputs
+from parity import assert_laplace_close, gram_exponent_error, score_resolution
+
+pytestmark = pytest.mark.gpu
+
+
+def _score_bound(x, p, h):
+    """Per point: an error e in every exponent moves a weight by e of itself, so the numerator by at most
+    e sum_j phi_j |x_j - p| and, through the denominator, the score by e |s| <= the same over h^2 D; on top of it what the
+    two cancelling sums resolve (score_resolution)."""
+    x, p = x.astype(np.float64), p.astype(np.float64)
+    c = x.mean(axis=0)
+    x, p = x - c, p - c
+    r2 = np.maximum((p * p).sum(1)[:, None] + (x * x).sum(1)[None] - 2.0 * p @ x.T, 0.0)
+    u = r2 / (2.0 * h * h)
+    w = np.exp(-(u - u.min(axis=1, keepdims=True)))
+    pull = (w * np.sqrt(r2)).sum(1) / w.sum(1) / (h * h)
+    return 2.0 * gram_exponent_error(x, p, h) * pull + score_resolution(x, p, h)
+
+
+@pytest.mark.parametrize("d", [7, 16, 17, 32, 37, 64, 80, 96, 97, 128])
+@pytest.mark.parametrize("row_tiles", [2, 4, 8])
+@pytest.mark.parametrize("n", [40, 1111, 4500])
+def test_every_workgroup_shape(tuning, n, d, row_tiles):
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    m = 70
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=n + d)
+    h = float(h)
+    tuning(P.SDKDE_TUNE_SCORE_ROW_TILES, row_tiles)
+    tuning(P.SDKDE_TUNE_EVAL_ROW_TILES, row_tiles)
+    ran = 0
+    xd, qd = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    print(f"split kernel n={n} m={m} d={d} row tiles {row_tiles}", flush=True)
+    if P.sdkde_describe_plan(n, n, d, 0)["row_tiles"] == row_tiles:
+        ran += 1
+        s = P.sdkde_score(xd, h).cpu().numpy()
+        err = np.linalg.norm(s - oracle.score(x, h), axis=1)
+        assert np.all(err <= _score_bound(x, x, h)), (err / _score_bound(x, x, h)).max()
+        s = P.sdkde_score(xd, h, points=qd).cpu().numpy()
+        err = np.linalg.norm(s - oracle.score(x, h, points=q), axis=1)
+        assert np.all(err <= _score_bound(x, q, h)), (err / _score_bound(x, q, h)).max()
+    if P.sdkde_describe_plan(n, m, d, 2)["row_tiles"] == row_tiles:
+        ran += 1
+        ref = oracle.eval_log_density(x, q, h)
+        e = gram_exponent_error(x, q, h)
+        for flags in (0, P.SDKDE_FLAG_MAX_SHIFT):
+            logd = P.sdkde_eval(xd, qd, h, want="log", flags=flags)[1].cpu().numpy()
+            # + the sum's own rounding (chains of 64 tiles and the splits) and the output's
+            assert np.all(np.abs(logd - ref) <= e + 2.0**-18 + 2.0**-23 * np.abs(ref))
+        lap = P.sdkde_eval_laplace(xd, qd, h).cpu().numpy()
+        assert_laplace_close(lap, oracle.eval_laplace_density(x, q, h), oracle.eval_laplace_abs_density(x, q, h), "laplace", e,
+                             np.exp(ref))
+    if ran == 0:
+        pytest.skip("not built")
