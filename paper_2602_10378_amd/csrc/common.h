@@ -34,8 +34,8 @@ enum PairKind {
     kRowMax = 4,        // max_j of the exponent (first pass of the max-shifted mode); kept in the D slot
     kScoreBand = 5      // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
 };
-// How the prepared rows of the matrix path are held: SDKDE_PREC_FP32 .. SDKDE_PREC_FP16X2_PHI16 as the layouts of those
-// modes' kernels (fp32 itself only for the symmetric score), or three bf16 parts (split3.h), the fp32 mode everywhere else.
+// How the prepared rows of the matrix path are held: SDKDE_PREC_FP16X2 .. SDKDE_PREC_FP16X2_PHI16 as the layouts of those
+// modes' kernels, or three bf16 parts (split3.h), the fp32 mode.
 constexpr int kFormatSplit3 = 4;
 constexpr float kNegHuge = -3.0e38f;
 // v_exp_f32 flushes results below the smallest normal fp32 number (2^-126) to zero, so a weight sum over n samples

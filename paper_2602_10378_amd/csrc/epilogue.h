@@ -49,11 +49,8 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
 __device__ __forceinline__ float prepared_value(const float* ps, int64_t i, int c, int dp, int format)
 {
     if (format == kFormatSplit3) return split3_value(ps, i, c, dp);
-    if (format != SDKDE_PREC_FP32) {       // fp16 hi + lo
-        const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);
-        return (float)ph[0] + (float)ph[16];
-    }
-    return ps[i * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))];      // fp32 layout of the prepared rows
+    const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);      // fp16 hi + lo
+    return (float)ph[0] + (float)ph[16];
 }
 
 // Columns c0 .. c0+3 of it (c0 a multiple of four, below dp).

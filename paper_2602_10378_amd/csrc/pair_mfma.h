@@ -1,4 +1,4 @@
-// Pair kernel of the fp16 input modes and of the in-block pass of the symmetric mode: pair_mfma_kernel and its helpers.
+// Pair kernel of the fp16 input modes (d >= 4, score kinds d >= 7): pair_mfma_kernel and its operand helpers.
 #pragma once
 #include "common.h"
 
@@ -10,18 +10,15 @@ namespace {
 // One wave owns NI tiles of 16 evaluation rows (kept in registers as the B operand) and
 // streams 16-sample tiles of the other set.  For every (row tile, sample tile) pair:
 //   C[j][i]  = -|p_i|^2 - |x_j|^2                        (VALU, accumulator initialisation)
-//   C       += X_J (16 x dp) * (2 P_I)^T (dp x 16)       (dp/4 MFMA 16x16x4, fp32)
+//   C       += X_J (16 x dp) * (2 P_I)^T (dp x 16)       (2 MFMA 16x16x32 fp16 per 16 columns, operands as hi + lo)
 //   Phi^T    = exp2(C)                                   (v_exp_f32)
 //   D_i     += sum_j Phi^T[j][i]                         (VALU, per-lane partial)
-//   T^T     += X_J^T (dp x 16) * Phi^T (16 x 16)         (dp/4 MFMA; SCORE only)
+//   T^T     += X_J^T (dp x 16) * Phi^T (16 x 16)         (SCORE only: 4 MFMA 16x16x4 fp32, or fp16 MFMAs, per 16 columns)
 // The 16x16x4 accumulator layout (lane l, register v) = (row 4*(l/16)+v, column l%16) is exactly
 // the B-operand layout (k = l/16, n = l%16) of the second MFMA for the four samples
 // j = 4*(l/16)+v, so Phi never leaves its registers: register v is the B operand of the MFMA
 // whose A operand holds samples {v, 4+v, 8+v, 12+v}; the blocked-transposed copy xt supplies
-// that A operand with one float4 load per lane.  In the first contraction MFMA kk takes component kk of
-// every lane's float4, i.e. positions {kk, 4+kk, 8+kk, 12+kk} of each 16-column block, so that both
-// operands are plain float4 row loads; the fp32 prepared arrays place coordinate 4kk + g at position
-// 4g + kk, which makes those the coordinates 4kk .. 4kk+3 (see KLAST below).
+// that A operand with one float4 load per lane.
 //
 // SELF (score at the samples themselves): the pair (i, i) must stay out of D and T, because
 // T_i/D_i - x_i would otherwise cancel against the large self term whenever a point has few
@@ -72,21 +69,13 @@ __device__ __forceinline__ f16x8 round_phi(const f32x4& phi, float* rowsum)
     return __builtin_bit_cast(f16x8, (u32x4){u01, u23, u01, u23});
 }
 
-// Row-tile operands of one wave for NI row tiles starting at row0: -|p~|^2 and the B operand 2 * p~.
-// fp32 inputs: lane (r, g) holds coordinates 16kb + 4g .. +3 of row r (b[t][kb]).
-// fp16x2 inputs: two K = 32 operands per 16-column block, bh[t][kb][0] = [hi | hi] and
-// bh[t][kb][1] = [lo | lo]; lane (r, g) holds elements 8g .. 8g+7 of that K axis, i.e. halves
-// 8(g&1) .. +7 of the hi (resp. lo) part.  Against the streamed A operand [hi | lo] the two MFMAs
+// Row-tile operands of one wave for NI row tiles starting at row0: -|p~|^2 and the B operand 2 * p~, two K = 32 operands
+// per 16-column block, bh[t][kb][0] = [hi | hi] and bh[t][kb][1] = [lo | lo]; lane (r, g) holds elements 8g .. 8g+7 of that
+// K axis, i.e. halves 8(g&1) .. +7 of the hi (resp. lo) part.  Against the streamed A operand [hi | lo] the two MFMAs
 // sum hi*hi + lo*hi + hi*lo + lo*lo = the full product.
-// KLAST (fp32 inputs only): MFMAs of the last 16-column block that contract real coordinates.  The prepared
-// fp32 arrays store coordinate c of a block at position 4 (c % 4) + c / 4, so that MFMA kk contracts
-// coordinates 4kk .. 4kk+3 and a block with d - 16 (KB - 1) <= 4 KLAST real coordinates needs only KLAST of
-// its four MFMAs (the skipped ones would multiply the zero padding).
-template <int KB, int NI, int PREC, int KLAST = 4>
+template <int KB, int NI>
 struct RowTiles {
-    static_assert(KLAST >= 1 && KLAST <= 4 && (KLAST == 4 || PREC == SDKDE_PREC_FP32), "partial last block: fp32 inputs only");
-    f32x4 b[PREC == SDKDE_PREC_FP32 ? NI : 1][KB];
-    f16x8 bh[PREC != SDKDE_PREC_FP32 ? NI : 1][KB][2];
+    f16x8 bh[NI][KB][2];
     float ni[NI];
 
     __device__ __forceinline__ void load(const float* __restrict__ ps, const float* __restrict__ pn, int64_t row0,
@@ -98,14 +87,9 @@ struct RowTiles {
             const int64_t row = row0 + t * kTile + r;
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                if (PREC == SDKDE_PREC_FP32) {
-                    f32x4 v = *reinterpret_cast<const f32x4*>(ps + row * DP + kb * 16 + g * 4);
-                    b[t][kb] = v * 2.0f;
-                } else {
-                    const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + row * 2 * DP + kb * 32 + (g & 1) * 8;
-                    bh[t][kb][0] = *reinterpret_cast<const f16x8*>(ph) * (_Float16)2;
-                    bh[t][kb][1] = *reinterpret_cast<const f16x8*>(ph + 16) * (_Float16)2;
-                }
+                const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + row * 2 * DP + kb * 32 + (g & 1) * 8;
+                bh[t][kb][0] = *reinterpret_cast<const f16x8*>(ph) * (_Float16)2;
+                bh[t][kb][1] = *reinterpret_cast<const f16x8*>(ph + 16) * (_Float16)2;
             }
             ni[t] = pn[row];
         }
@@ -114,18 +98,9 @@ struct RowTiles {
     // c += (16 samples x 16-column block kb) * (row tile t)^T; a = the lane's 16 bytes of the streamed operand.
     __device__ __forceinline__ f32x4 cross(int t, int kb, const f32x4& a, f32x4 c) const
     {
-        if (PREC == SDKDE_PREC_FP32) {
-            const int steps = kb == KB - 1 ? KLAST : 4;      // compile-time after unrolling
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b[t][kb].x, c, 0, 0, 0);
-            if (steps > 1) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b[t][kb].y, c, 0, 0, 0);
-            if (steps > 2) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b[t][kb].z, c, 0, 0, 0);
-            if (steps > 3) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b[t][kb].w, c, 0, 0, 0);
-        } else {
-            const f16x8 ah = __builtin_bit_cast(f16x8, a);
-            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[t][kb][0], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[t][kb][1], c, 0, 0, 0);
-        }
-        return c;
+        const f16x8 ah = __builtin_bit_cast(f16x8, a);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[t][kb][0], c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[t][kb][1], c, 0, 0, 0);
     }
 };
 
@@ -165,9 +140,8 @@ __global__ __launch_bounds__(kBlock) void pair_mfma_kernel(
     const float* __restrict__ shift)
 {
     static_assert(NI >= 2 && NI % 2 == 0, "the software pipeline alternates two accumulator sets");
-    constexpr bool BAND = KIND == kScoreBand;
-    constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints || BAND;
-    constexpr bool SELF = KIND == kScoreSelf || BAND;
+    constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints;
+    constexpr bool SELF = KIND == kScoreSelf;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
     constexpr bool ROWMAX = KIND == kRowMax;
     constexpr int DP = KB * 16;
@@ -180,7 +154,7 @@ __global__ __launch_bounds__(kBlock) void pair_mfma_kernel(
     const int64_t row_block = blockIdx.x / nsplit;
     const int64_t row0 = (row_block * kWavesPerBlock + wave) * (NI * kTile);
 
-    RowTiles<KB, NI, PREC> rows;
+    RowTiles<KB, NI> rows;
     rows.load(ps, pn, row0, r, g);
     constexpr bool SCALED = SCORE && (PREC == SDKDE_PREC_FP16X2_ALL || PREC == SDKDE_PREC_FP16X2_PHI16);
     if (SCALED) {
@@ -207,21 +181,15 @@ __global__ __launch_bounds__(kBlock) void pair_mfma_kernel(
     // ntiles, tiles_per_split and NI are even (host side), so every span of sample tiles below
     // has even length and the loop can alternate two operand register sets without copies.
     const int dt0 = (int)(row0 / kTile);          // the wave's own row tiles are sample tiles dt0 .. dt0+NI-1
-    int t_begin = split * tiles_per_split;
-    int t_end = min(ntiles, t_begin + tiles_per_split);
-    if (BAND) {
-        // symmetric mode: only the samples of the rows' own block, tiles_per_split tiles long (the pairs
-        // across blocks belong to pair_sym_kernel); nsplit is 1
-        t_begin = dt0 / tiles_per_split * tiles_per_split;
-        t_end = min(ntiles, t_begin + tiles_per_split);
-    }
+    const int t_begin = split * tiles_per_split;
+    const int t_end = min(ntiles, t_begin + tiles_per_split);
 
     // Operands of one sample tile, as each lane holds them.
     constexpr bool HALF2 = PREC == SDKDE_PREC_FP16X2_ALL;      // second contraction on the fp16 units too
     constexpr bool PHI16 = PREC == SDKDE_PREC_FP16X2_PHI16;    // the same with single-fp16 weights
     struct Operands {
-        f32x4 a1[KB];     // first contraction, A: the lane's 16 bytes of sample r's row, block kb (fp32: coordinates
-                          // 16kb + 4g .. +3; fp16x2: elements 8g .. 8g+7 of [hi | lo])
+        f32x4 a1[KB];     // first contraction, A: the lane's 16 bytes of sample r's row, block kb: elements 8g .. 8g+7 of
+                          // [hi | lo]
         f32x4 a2[KT];     // second contraction, A: lane (r, g) = coordinate 16mb + r of samples 4g .. 4g+3
                           // (fp32), the eight halves [hi(4g..4g+3) | again] when HALF2, [hi(4g..4g+3) | lo(4g..4g+3)]
                           // when PHI16

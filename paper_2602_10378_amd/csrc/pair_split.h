@@ -77,8 +77,9 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const float* __restrict__ shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
-    constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints;
-    constexpr bool SELF = KIND == kScoreSelf;
+    constexpr bool BAND = KIND == kScoreBand;
+    constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints || BAND;
+    constexpr bool SELF = KIND == kScoreSelf || BAND;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
     constexpr bool ROWMAX = KIND == kRowMax;
     constexpr int DP = KB * 16;
@@ -212,6 +213,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
                         dt += (phi[u].x + phi[u].y) + (phi[u].z + phi[u].w);
                     }
                 }
+                // keeps the sum here: the compiler would otherwise sink it behind the MFMAs and hold the Phi tiles live
+                if (SCORE) asm volatile("" : "+v"(dt));
                 if (SCORE) split3_weights(phi[0], phi[1], w[t][0], w[t][1], w[t][2]);
             }
             if constexpr (SCORE) {
@@ -245,8 +248,11 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     };
 
     const int own0 = (int)(row0 / kChunkRows);              // SELF: the wave's own rows are chunks own0 .. own0 + NI/2 - 1
-    const int c_begin = split * tiles_per_split / 2;
-    const int c_end = min(ntiles, (split + 1) * tiles_per_split) / 2;
+    // BAND (the symmetric mode's in-block pass): only the samples of the rows' own block, tiles_per_split tiles long and a
+    // multiple of the workgroup's rows; nsplit is 1.
+    const int first_tile = BAND ? (int)(row_block * (WAVES * NI) / tiles_per_split) * tiles_per_split : split * tiles_per_split;
+    const int c_begin = first_tile / 2;
+    const int c_end = min(ntiles, first_tile + tiles_per_split) / 2;
     const char* const xs_b = reinterpret_cast<const char*>(xs);
     const char* const xt_b = reinterpret_cast<const char*>(xt);
     bool flushed = false;                                   // !SUMLDS: the partial slot holds second-level sums

@@ -1,86 +1,94 @@
-// Symmetric score kernel (SDKDE_FLAG_SYMMETRIC): every unordered pair of samples across sample blocks once.
+// Symmetric score kernel: every unordered pair of samples across sample blocks once, on three-part operands.
 #pragma once
 #include "common.h"
-#include "pair_mfma.h"
+#include "pair_split.h"
+#include "split3.h"
 
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// Symmetric score at the samples themselves (separate mode, SDKDE_FLAG_SYMMETRIC).
+// Symmetric score at the samples themselves.
 //
-// phi_ij = phi_ji, so each unordered pair of samples needs one Gram-matrix entry and one exp.  A
-// wave that holds row tile I and streams sample tile J computes the tile Phi once and uses it twice:
-//   T_I^T += X_J^T (dp x 16) * Phi^T (16 x 16)      as in pair_mfma_kernel, Phi^T from its registers,
-//   T_J^T += X_I^T (dp x 16) * Phi   (16 x 16)      with the tile transposed through 1.25 KiB of LDS
-// (three groups of MFMAs for two ordered pairs instead of four, and half the exps).
+// phi_ij = phi_ji, so each unordered pair of samples needs one Gram-matrix entry, one exp and one split of the weight.
+// A wave that holds row tiles I and streams sample tiles J computes the tile Phi once and uses it twice:
+//   T_I^T += X_J^T (dp x 32) * Phi^T (32 x 16)     as in pair_split_kernel, Phi^T from its registers,
+//   T_J^T += X_I^T (dp x 32) * Phi   (32 x 16)     with the tile's parts transposed through LDS
+// (three groups of MFMAs for two ordered pairs instead of four, and half the vector work, which is more than half of
+// pair_split_kernel's time at dp = 16).
 //
-// The samples are cut into blocks of `rb` rows; only pairs (i in an earlier block, j in a later block)
-// are handled here, pairs inside one block go through pair_mfma_kernel restricted to that block.
-// A workgroup (8 waves) takes one item = (chunk c of `per_group` blocks, group gam >= c of `per_group`
-// blocks) and, for every block b of the group:
+// The samples are cut into blocks of `rb` rows; only pairs (i in an earlier block, j in a later block) are handled here,
+// pairs inside one block go through pair_split_kernel restricted to that block (kScoreBand).
+// A workgroup (8 waves) takes one item = (chunk of rows c: `per_group` blocks, group gam >= c: `per_group` blocks) and,
+// for every block b of the group:
 //   - keeps the accumulators [T_J | D_J] of the block's rb rows in LDS ([KB][rb][16] + [rb] floats),
-//   - walks over the rows of the chunk that lie before block b, 8 * NI * 16 at a time; each wave holds
-//     NI row tiles (operands and T_I, D_I in registers) and streams one eighth of the block per phase,
-//     wave w taking eighth (w + phase) mod 8, so that within a phase every LDS accumulator row has one
-//     owner and the order of all additions is fixed (no atomics; barriers between phases),
-//   - adds the wave's T_I, D_I into partial slot gam + 1 of its rows (the same lanes add the blocks of a
-//     group one after the other: first a store, then read-add-write),
+//   - walks over the rows of c that lie before block b, 8 * NI * 16 at a time; each wave holds NI row tiles (operands and
+//     T_I, D_I in registers) and streams one eighth of the block per phase, wave w taking eighth (w + phase) mod 8, so that
+//     within a phase every LDS accumulator row has one owner and the order of all additions is fixed (no atomics;
+//     barriers between phases),
+//   - adds the wave's T_I, D_I into partial slot gam + 1 of its rows (the same lanes add the blocks of a group one after
+//     the other: first a store, then read-add-write),
 //   - writes the block's LDS accumulators into partial slot c.
-// A row of chunk/group rho thus receives slots 0..rho (as streamed sample, one per chunk) and
-// rho+1..ngroups (as row, one per group): ngroups + 1 slots, every one written exactly once (rows that meet
-// no later block in their own group get zeros).
+// A row of chunk/group rho thus receives slots 0..rho (as streamed sample, one per chunk) and rho+1..ngroups (as row, one
+// per group): ngroups + 1 slots, every one written exactly once (rows that meet no later block in their own group get
+// zeros).
 //
-// Pipeline per (sample tile, row tile) pair u, on top of the schedule of pair_mfma_kernel:
-//   [T_I MFMAs of u] [T_J MFMAs of u-1] [Gram MFMAs of u+2] | VALU clump of u+1: exp2, row sum, column sum of
-//   the transposed tile of u, accumulator init; LDS: write Phi(u+1), read it back transposed | ...
-// The T_J MFMAs run one pair behind so that the transposed tile has a whole stage to come back from LDS.
-// The T_J accumulator of a sample tile is added into LDS during the next tile (rows read in the clump of
-// its row tile 0, add and write in that of row tile 1), when its MFMAs have long finished.
+// The transposed tile: every MFMA operand has its contraction index on the (lane group, register) axis and its free index
+// on lane % 16.  Phi^T leaves the Gram MFMA with the sample on the former and the row on the latter, which suits T_I;
+// T_J contracts over the rows.  A lane writes the four bf16 values of one part (samples 4g .. 4g+3 of row r) as 8 bytes of
+// a 16 x 16 tile, ds_read_b64_tr_b16 returns rows 4g .. 4g+3 of sample r: with a second row tile's the K = 32 operand in
+// the row order of the prepared transpose, which therefore serves as X_I^T as it is.
+//
+// Measured (clocks per 256 ordered pairs and SIMD; fp32 MFMA form before): d = 16 n = 32768 268 (317), n = 131072 221 (277),
+// n = 1048576 212 (266); d = 32 n = 100000 416 (583).  Its instructions alone take about 155 at d = 16: the rest is the
+// dependent chain of a pair of row tiles (Gram, weights, transposes, sums) with two waves per SIMD that meet at every phase.
 // ------------------------------------------------------------------------------------------
 constexpr int kSymWaves = 8;
 constexpr int kSymBlock = kSymWaves * kWave;
-
-// x summed over the four lanes that share lane % 16 (the four 16-lane rows of the wave), in every lane, as
-// (row 0 + row 1) + (row 2 + row 3).  The row-swap instructions of gfx950 keep this on the VALU; a shuffle
-// would go through the LDS crossbar and make the wave wait for its round trip.
-__device__ __forceinline__ float sum_over_lane_rows(float x)
-{
-    float a = x, b = x;
-    // lanes 16-31 of a <-> lanes 0-15 of b, lanes 48-63 of a <-> lanes 32-47 of b
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    a += b;
-    b = a;
-    // lanes 32-63 of a <-> lanes 0-31 of b
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    return a + b;
-}
-constexpr int kTrStride = 20;      // floats per row of the 16 x 16 transpose tile: 16-byte aligned rows, no bank conflicts
+constexpr int kSymTrBytes = 2 * 3 * 512;       // a wave's transpose buffer: two row tiles, three parts of a 16 x 16 tile
 
 inline size_t sym_lds_bytes(int kb, int rb)
 {
-    return sizeof(float) * ((size_t)kb * rb * 16 + rb + kSymWaves * 16 * kTrStride);
+    return sizeof(float) * ((size_t)kb * rb * 16 + rb) + kSymWaves * kSymTrBytes;
 }
 
-template <int KB, int NI, int PREC, int KLAST = 4>
-__global__ __launch_bounds__(kSymBlock) void pair_sym_kernel(
+// x summed over the 16 lanes that share lane / 16, in every one of them (row rotations by 8, 4, 2, 1).
+__device__ __forceinline__ float sum_over_row(float x)
+{
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, true));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x124, 0xf, 0xf, true));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x122, 0xf, 0xf, true));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x121, 0xf, 0xf, true));
+    return x;
+}
+
+template <int KB, int NI>
+__global__ __launch_bounds__(kSymBlock, 2) void pair_sym_kernel(
     const float* __restrict__ xs, const float* __restrict__ xt, const float* __restrict__ xn,
     float* __restrict__ part_t, float* __restrict__ part_d, int64_t n_pad, int rb, int nblocks, int per_group,
     int ngroups)
 {
-    static_assert(NI >= 2 && NI % 2 == 0, "the software pipeline alternates two accumulator sets");
-    static_assert(PREC != SDKDE_PREC_FP16X2_ALL, "the transposed tile is consumed in fp32");
+    static_assert(NI % 2 == 0, "row tiles are taken two at a time: one chunk of the prepared transpose");
     extern __shared__ __align__(16) float sym_lds[];
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int DP = KB * 16;
     constexpr int SB = kSymWaves * NI * kTile;          // rows a workgroup holds at a time
+    constexpr int PAIRS = KB / 2;
+    constexpr bool ODD = KB % 2 != 0;
+    constexpr int GROUPS = PAIRS + (ODD ? 1 : 0);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int r = lane & 15, g = lane >> 4;
+    const char* const xs_b = reinterpret_cast<const char*>(xs);
+    const char* const xt_b = reinterpret_cast<const char*>(xt);
+    // byte offsets of the lane, unsigned: added to a scalar base inside the load
+    const uint32_t lane16 = lane * 16u, half = (16u * (g & 1) + r) * 16u, half_hl = half + (g < 2 ? 0u : 1024u), group16 = g * 16u;
 
     float* const lds_t = sym_lds;                            // [KB][rb][16]
     float* const lds_d = lds_t + (size_t)KB * rb * 16;       // [rb]
-    float* const tr = lds_d + rb + wave * (16 * kTrStride);  // this wave's transpose tile
-    f32x4* const tr_wr = reinterpret_cast<f32x4*>(tr + r * kTrStride + g * 4);    // row r, columns 4g .. 4g+3
-    const float* const tr_rd = tr + g * 4 * kTrStride + r;                         // rows 4g .. 4g+3, column r
+    char* const tr = reinterpret_cast<char*>(lds_d + rb) + wave * kSymTrBytes;      // this wave's transpose buffer
+    char* const tr_wr = tr + r * 32 + g * 8;                                        // row r, samples 4g .. 4g+3
+    char* const tr_rd = tr + (4 * g + (r >> 2)) * 32 + (r & 3) * 8;
 
     // item -> (c, gam): the ngroups (ngroups - 1) / 2 full rectangles first, the triangular items c == gam last
     const int id = blockIdx.x;
@@ -98,33 +106,33 @@ __global__ __launch_bounds__(kSymBlock) void pair_sym_kernel(
     const int64_t a_lo = (int64_t)c * per_group * rb;
     const int64_t a_hi = min(n_pad, a_lo + (int64_t)per_group * rb);
     const int64_t slot_a = gam + 1, slot_b = c;
-    const int tiles_per_phase = rb / (kSymWaves * kTile);    // an even power of two (host side)
-    const int tp_shift = __ffs(tiles_per_phase) - 1;
+    const int per_phase = rb / (kSymWaves * kChunkRows);     // chunks, a power of two (host side)
+    const int phase_shift = __ffs(per_phase) - 1;
 
-    struct Operands {
-        f32x4 a1[KB];     // Gram contraction, A: the lane's 16 bytes of sample r's row, block kb
-        f32x4 a2[KB];     // T_I contraction, A: coordinate 16mb + r of samples 4g .. 4g+3
-        f32x4 nj;         // -|x|^2 of samples 4g .. 4g+3
+    // A lane number the compiler cannot see through: address arithmetic of the code around the hot loop stays where it
+    // is used instead of being hoisted into registers that the hot loop needs.
+    auto opaque = [](int v) {
+        asm volatile("" : "+v"(v));
+        return v;
     };
-
     for (int b = b_lo; b < b_hi; ++b) {
-        for (int idx = threadIdx.x; idx < KB * rb * 16 + rb; idx += kSymBlock) sym_lds[idx] = 0.0f;
+        for (int idx = opaque(threadIdx.x); idx < KB * rb * 16 + rb; idx += kSymBlock) sym_lds[idx] = 0.0f;
         __syncthreads();
-        const int bt0 = b * (rb / kTile);                     // first sample tile of the block
+        const int bc0 = b * (rb / kChunkRows);                // first chunk of the block
         const int64_t a_end = min(a_hi, (int64_t)b * rb);     // rows strictly before the block
 
         for (int64_t a0 = a_lo; a0 < a_end; a0 += SB) {
             const int64_t row0 = a0 + (int64_t)wave * (NI * kTile);
-            RowTiles<KB, NI, PREC, KLAST> rows;      // KLAST: Gram MFMAs of a partly filled last block (pair_mfma.h)
-            rows.load(xs, xn, row0, r, g);
-            const float (&ni)[NI] = rows.ni;
-            f32x4 xti[NI][KB];      // T_J contraction, A: coordinate 16mb + r of rows 4g .. 4g+3 of row tile t
+            SplitRows<KB, NI> rows;
+            rows.load(xs, xn, row0, opaque(r), opaque(g));
+            bf16x8 xti[NI / 2][KB][3];      // T_J contraction, A: parts of column 16mb + r of the rows of two row tiles
 #pragma unroll
-            for (int t = 0; t < NI; ++t) {
-                const float* trow = xt + ((row0 / kTile + t) * DP + r) * kTile + g * 4;
+            for (int p = 0; p < NI / 2; ++p)
 #pragma unroll
-                for (int mb = 0; mb < KB; ++mb) xti[t][mb] = *reinterpret_cast<const f32x4*>(trow + mb * 16 * kTile);
-            }
+                for (int mb = 0; mb < KB; ++mb)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        xti[p][mb][q] = load_at<bf16x8>(xt_b + (row0 / kChunkRows + p) * chunk_bytes(KB), (mb * 3 + q) * kPartBytes + opaque(lane) * 16u);
             f32x4 tacc[NI][KB];
             float dacc[NI];
 #pragma unroll
@@ -134,184 +142,184 @@ __global__ __launch_bounds__(kSymBlock) void pair_sym_kernel(
                 for (int mb = 0; mb < KB; ++mb) tacc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
 
-            {
-                // The wave's stream of sample tiles through the block: position q is tile q % TP of eighth
-                // (wave + q / TP) mod 8 (TP = tiles_per_phase, a power of two).  The software pipeline runs through
-                // the whole stream; at every multiple of TP the wave finishes its T_J sums and all waves meet.
-                const int q_last = kSymWaves * tiles_per_phase - 1;     // prefetches past the stream re-read its last tile
-                auto tile_of = [&](int q) {
-                    q = min(q, q_last);
-                    return bt0 + (((wave + (q >> tp_shift)) & (kSymWaves - 1)) << tp_shift) + (q & (tiles_per_phase - 1));
-                };
-                Operands set_a, set_b;
-                f32x4 creg[2], ph[2], pht[2];
-                f32x4 acc3[KB];          // T_J^T of the current sample tile: (lane (r, g), v) = coordinate 16mb + 4g + v
-                                         // of sample r
-                float cacc, cprev;       // sum over rows 4g .. 4g+3 of all row tiles of Phi[.][sample r]; the part of it
-                                         // that arrives one clump late (last pair of the tile)
-                f32x4 fold[KB];          // the LDS accumulator rows the next fold adds to, read one stage ahead
-                float dfold;
+            // The wave's stream of chunks through the block: position q is chunk q % per_phase of eighth
+            // (wave + q / per_phase) mod 8; at every multiple of per_phase all waves meet.
+            const int q_end = kSymWaves * per_phase;
+            auto chunk_of = [&](int q) {
+                q = min(q, q_end - 1);                        // prefetches past the stream re-read its last chunk
+                return bc0 + (((wave + (q >> phase_shift)) & (kSymWaves - 1)) << phase_shift) + (q & (per_phase - 1));
+            };
+            // Operands of the current chunk; each part is reloaded for the next one as soon as its last reader has issued.
+            bf16x8 ga[GROUPS][2][3], ta[KB][3];
+            f32x4 nj[2];
+            auto load_gram = [&](int q) {
+                const char* base = xs_b + (int64_t)chunk_of(q) * chunk_bytes(KB);
+#pragma unroll
+                for (int p = 0; p < GROUPS; ++p)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const char* at = base + u * (KB * 1536) + p * 3072;
+                        if (p < PAIRS) {
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) ga[p][u][k] = load_at<bf16x8>(at, k * kPartBytes + lane16);
+                        } else {                              // [h | h], [m | m], [h | l]
+                            ga[p][u][0] = load_at<bf16x8>(at, half);
+                            ga[p][u][1] = load_at<bf16x8>(at, 512 + half);
+                            ga[p][u][2] = load_at<bf16x8>(at, half_hl);
+                        }
+                    }
+            };
+            auto load_t = [&](int q) {
+                const char* base = xt_b + (int64_t)chunk_of(q) * chunk_bytes(KB);
+#pragma unroll
+                for (int mb = 0; mb < KB; ++mb)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) ta[mb][k] = load_at<bf16x8>(base, (mb * 3 + k) * kPartBytes + lane16);
+            };
+            auto load_nj = [&](int q) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    nj[u] = load_at<f32x4>(reinterpret_cast<const char*>(xn + (int64_t)chunk_of(q) * kChunkRows), u * kTile * 4 + group16);
+            };
+            load_gram(0);
+            load_nj(0);
+            load_t(0);
+            constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};           // Gram: largest product first
+            constexpr int SA[6] = {2, 1, 0, 1, 0, 0}, SW[6] = {0, 1, 2, 0, 1, 0};           // sums: smallest first
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
-                auto load_a1 = [&](int q, Operands& o) {
-                    const float* xrow = xs + ((int64_t)tile_of(q) * kTile + r) * DP + g * 4;
+#pragma unroll 1
+            for (int q = 0; q < q_end; ++q) {
+                f32x4 sum_j[2][KB], dj[2];          // this chunk's T_J^T (lane: columns 16mb + 4g .. +3 of sample r) and, per
+                                                    // lane, the part of D_J that its row r adds to samples 4g .. 4g+3
 #pragma unroll
-                    for (int kb = 0; kb < KB; ++kb) o.a1[kb] = *reinterpret_cast<const f32x4*>(xrow + kb * 16);
-                };
-                auto load_a2 = [&](int q, Operands& o) {
-                    const float* trow = xt + ((int64_t)tile_of(q) * DP + r) * kTile + g * 4;
+                for (int p = 0; p < NI / 2; ++p) {
+                    f32x4 cc[2][2];
 #pragma unroll
-                    for (int mb = 0; mb < KB; ++mb) o.a2[mb] = *reinterpret_cast<const f32x4*>(trow + mb * 16 * kTile);
-                };
-                auto load_nj = [&](int q, Operands& o) {
-                    o.nj = *reinterpret_cast<const f32x4*>(xn + (int64_t)tile_of(q) * kTile + g * 4);
-                };
-                // LDS accumulator rows of sample tile jt (block-local), this lane's 16 bytes of block mb
-                auto lds_row = [&](int jt, int mb) {
-                    return lds_t + ((size_t)mb * rb + (size_t)(jt - bt0) * kTile + r) * 16 + g * 4;
-                };
-                auto load_fold = [&](int jt) {
+                    for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int mb = 0; mb < KB; ++mb) fold[mb] = *reinterpret_cast<const f32x4*>(lds_row(jt, mb));
-                    dfold = lds_d[(jt - bt0) * kTile + r];
-                };
-                // adds the finished tile's T_J^T and column sums to the rows read by load_fold(jt)
-                auto store_fold = [&](int jt) {
+                        for (int u = 0; u < 2; ++u) cc[t][u] = nj[u] + rows.ni[2 * p + t];
 #pragma unroll
-                    for (int mb = 0; mb < KB; ++mb) *reinterpret_cast<f32x4*>(lds_row(jt, mb)) = fold[mb] + acc3[mb];
-                    // all four lanes of a column hold the same sum and write the same value
-                    lds_d[(jt - bt0) * kTile + r] = dfold + sum_over_lane_rows(cacc + cprev);
-                    cacc = 0.0f;
-                };
-
-                load_a1(0, set_a);
-                load_a2(0, set_a);
-                load_nj(0, set_a);
-                creg[0] = set_a.nj + ni[0];
+                    for (int gr = 0; gr < GROUPS; ++gr)
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb) creg[0] = rows.cross(0, kb, set_a.a1[kb], creg[0]);
-                creg[1] = set_a.nj + ni[1];
-                load_a1(1, set_b);
-                load_nj(1, set_b);
-                pht[0] = pht[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-                cacc = cprev = 0.0f;
+                        for (int k = 0; k < (gr < PAIRS ? 6 : 3); ++k)
 #pragma unroll
-                for (int mb = 0; mb < KB; ++mb) acc3[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-                // Stream position q (operands in cur) against all NI row tiles.  The T_J MFMAs run one pair behind
-                // (their transposed tile was read from LDS a whole stage earlier), so the previous tile's T_J^T
-                // is complete after the MFMAs of row tile 0 and is folded into LDS in the clump of row tile 1
-                // (first tile of a phase: nothing is pending, zeros are added to the tile's own rows).
-                auto iteration = [&](int q, Operands& cur, Operands& nxt) {
-                    const int jt = tile_of(q);
-                    const int jprev = (q & (tiles_per_phase - 1)) ? jt - 1 : jt;
-                    load_a2(q + 1, nxt);
+                            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                                for (int u = 0; u < 2; ++u) {
+                                    if (gr < PAIRS)
+                                        cc[t][u] = mfma_bf16(ga[gr][u][PA[k]], rows.b[2 * p + t][gr < PAIRS ? gr : 0][PB[k]], cc[t][u]);
+                                    else
+                                        cc[t][u] = mfma_bf16(ga[gr][u][k < 3 ? k : 0], rows.o[ODD ? 2 * p + t : 0][k == 2 ? 1 : 0], cc[t][u]);
+                                }
                     __builtin_amdgcn_sched_barrier(0);
+                    if (p == NI / 2 - 1) {
+                        load_gram(q + 1);
+                        load_nj(q + 1);
+                    }
+                    bf16x8 w[2][3];
 #pragma unroll
-                    for (int t = 0; t < NI; ++t) {
-                        const int slot = t & 1;
-                        const bool wrap1 = t + 1 >= NI, wrap2 = t + 2 >= NI;
-                        f32x4& cc = creg[slot];
-                        f32x4& phi = ph[slot];
-                        const float nin = ni[(t + 2) % NI];
-
-                        if (t == NI - 2) {
-                            load_nj(q + 2, cur);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                    for (int t = 0; t < 2; ++t) {
+                        f32x4 phi[2];
 #pragma unroll
-                        for (int kb = 0; kb < KB; ++kb)
-                            creg[slot ^ 1] = rows.cross((t + 1) % NI, kb, wrap1 ? nxt.a1[kb] : cur.a1[kb], creg[slot ^ 1]);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (t == NI - 2) load_a1(q + 2, cur);
-
-                        // VALU clump
-                        phi.x = __builtin_amdgcn_exp2f(cc.x);
-                        phi.y = __builtin_amdgcn_exp2f(cc.y);
-                        phi.z = __builtin_amdgcn_exp2f(cc.z);
-                        phi.w = __builtin_amdgcn_exp2f(cc.w);
-                        dacc[t] += (phi.x + phi.y) + (phi.z + phi.w);
-                        asm volatile("" : "+v"(dacc[t]));      // keeps the sum here (the compiler would otherwise sink it
-                                                               // to the end of the loop body and hold every Phi tile live)
-                        cc = (wrap2 ? nxt.nj : cur.nj) + nin;
-                        if (t == 0) load_fold(jprev);
-                        if (t == 1) store_fold(jprev);
-                        {   // column sums of the pair before this one (its transposed tile is in pht[slot ^ 1])
-                            const f32x4& q = pht[slot ^ 1];
-                            const float cs = (q.x + q.y) + (q.z + q.w);
-                            if (t == 0) cprev = cs;      // belongs to the previous tile, folded in the next clump
-                            else cacc += cs;
+                        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) phi[u][v] = __builtin_amdgcn_exp2f(cc[t][u][v]);
+                            dacc[2 * p + t] += (phi[u].x + phi[u].y) + (phi[u].z + phi[u].w);
+                            if (p == 0 && t == 0) dj[u] = phi[u];
+                            else dj[u] += phi[u];
                         }
-                        // transpose Phi through LDS: lane (r, g) holds Phi[i = r][j = 4g + v]; it needs Phi[4g + v][r]
-                        *tr_wr = phi;
+                        // keeps the sums here: the compiler would otherwise sink them out of the loop body's end and hold
+                        // every Phi tile live
+                        asm volatile("" : "+v"(dacc[2 * p + t]), "+v"(dj[0]), "+v"(dj[1]));
+                        split3_weights(phi[0], phi[1], w[t][0], w[t][1], w[t][2]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    // transposed tiles of sample tile 0, then (below) of sample tile 1, through the wave's buffer
+                    bf16x8 wt[2][3];
+                    auto put = [&](int u) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) {
+                                const u32x4 bits = __builtin_bit_cast(u32x4, w[t][k]);
+                                *reinterpret_cast<u32x2*>(tr_wr + (t * 3 + k) * 512) = u ? u32x2{bits.z, bits.w} : u32x2{bits.x, bits.y};
+                            }
+                        // a wave's LDS operations execute in order: the compiler only has to keep them so
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                         __builtin_amdgcn_wave_barrier();
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        pht[slot].x = tr_rd[0];
-                        pht[slot].y = tr_rd[kTrStride];
-                        pht[slot].z = tr_rd[2 * kTrStride];
-                        pht[slot].w = tr_rd[3 * kTrStride];
-                        __builtin_amdgcn_sched_barrier(0);
-
+                    };
+                    auto get = [&](int u) {
+                        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 #pragma unroll
-                        for (int i = 0; i < 4 * KB; ++i) {
-                            const int v = i / KB, mb = i % KB;
-                            tacc[t][mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.a2[mb][v], phi[v], tacc[t][mb], 0, 0, 0);
+                        for (int k = 0; k < 3; ++k) {
+                            const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr_rd + k * 512)));
+                            const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr_rd + (3 + k) * 512)));
+                            wt[u][k] = __builtin_bit_cast(bf16x8, (u32x4){lo.x, lo.y, hi.x, hi.y});
                         }
-                        __builtin_amdgcn_sched_barrier(0);
-                        // T_J of the previous pair: row tile t - 1 of this sample tile, or the last row tile of the
-                        // previous one (first pair of a phase: pht is zero)
+                    };
+                    put(0);
+                    get(0);
+                    put(1);
+                    get(1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int i = 0; i < 4 * KB; ++i) {
-                            const int v = i / KB, mb = i % KB;
-                            // row tile 1 runs the first T_J MFMAs of this sample tile (pair (jt, 0)): start from zero,
-                            // the previous tile's sums have just been folded
-                            const f32x4 c0 = (t == 1 && v == 0) ? f32x4{0.f, 0.f, 0.f, 0.f} : acc3[mb];
-                            acc3[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xti[(t + NI - 1) % NI][mb][v], pht[slot ^ 1][v],
-                                                                           c0, 0, 0, 0);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int mb = 0; mb < KB; ++mb) {       // T_I, while the transposed tiles come back
+                        f32x4 sum_i[2];
+#pragma unroll
+                        for (int k = 0; k < 6; ++k)
+#pragma unroll
+                            for (int t = 0; t < 2; ++t) sum_i[t] = mfma_bf16(ta[mb][SA[k]], w[t][SW[k]], k == 0 ? zero : sum_i[t]);
+                        tacc[2 * p][mb] += sum_i[0];
+                        tacc[2 * p + 1][mb] += sum_i[1];
                     }
-                };
-
-                for (int q = 0; q <= q_last; q += 2) {
-                    iteration(q, set_a, set_b);
-                    iteration(q + 1, set_b, set_a);
-                    if (((q + 2) & (tiles_per_phase - 1)) == 0) {
-                        // end of a phase: T_J and column sums of the last pair, the last sample tile, and the
-                        // meeting point (operand loads and the Gram MFMAs of the next phase's first pair are in flight)
-                        f32x4& last = pht[(NI - 1) & 1];
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (p == NI / 2 - 1) load_t(q + 1);
 #pragma unroll
-                        for (int i = 0; i < 4 * KB; ++i) {
-                            const int v = i / KB, mb = i % KB;
-                            acc3[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xti[NI - 1][mb][v], last[v], acc3[mb], 0, 0, 0);
-                        }
-                        cprev = 0.0f;
-                        cacc += (last.x + last.y) + (last.z + last.w);
-                        const int jt = tile_of(q + 1);
-                        load_fold(jt);
-                        store_fold(jt);
+                    for (int k = 0; k < 6; ++k)
 #pragma unroll
-                        for (int mb = 0; mb < KB; ++mb) acc3[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        last = f32x4{0.f, 0.f, 0.f, 0.f};     // the next stage's trailing T_J MFMAs add nothing
-                        __syncthreads();
-                    }
+                        for (int u = 0; u < 2; ++u)
+#pragma unroll
+                            for (int mb = 0; mb < KB; ++mb)
+                                sum_j[u][mb] = mfma_bf16(xti[p][mb][SA[k]], wt[u][SW[k]], k == 0 && p == 0 ? zero : sum_j[u][mb]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                // fold the chunk's T_J and D_J into the block's accumulators
+                const int row = (chunk_of(q) - bc0) * kChunkRows;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                    for (int mb = 0; mb < KB; ++mb) {
+                        f32x4* at = reinterpret_cast<f32x4*>(lds_t + ((size_t)mb * rb + row + u * kTile + r) * 16 + g * 4);
+                        *at += sum_j[u][mb];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) dj[u][v] = sum_over_row(dj[u][v]);
+                }
+                if (r < 2) {
+                    f32x4* at = reinterpret_cast<f32x4*>(lds_d + row + r * kTile + g * 4);
+                    *at += r ? dj[1] : dj[0];
+                }
+                if (((q + 1) & (per_phase - 1)) == 0) __syncthreads();      // the same q for all waves
             }
 
             // this wave's rows: add into partial slot gam + 1 (the first block that meets these rows stores)
             const bool first = b == max(b_lo, (int)(a0 / rb) + 1);
+            const int ro = opaque(r), go = opaque(g);
 #pragma unroll
             for (int t = 0; t < NI; ++t) {
-                const int64_t row = row0 + t * kTile + r;
-                float* dst = part_t + (slot_a * n_pad + row) * DP + g * 4;
+                const int64_t row = row0 + t * kTile + ro;
+                float* dst = part_t + (slot_a * n_pad + row) * DP + go * 4;
 #pragma unroll
                 for (int mb = 0; mb < KB; ++mb) {
                     f32x4 v = tacc[t][mb];
                     if (!first) v += *reinterpret_cast<const f32x4*>(dst + mb * 16);
                     *reinterpret_cast<f32x4*>(dst + mb * 16) = v;
                 }
-                const float dt = sum_over_lane_rows(dacc[t]);
-                if (g == 0) {
+                float dt = dacc[t] + __shfl_xor(dacc[t], 16);
+                dt += __shfl_xor(dt, 32);
+                if (go == 0) {
                     float* dd = part_d + slot_a * n_pad + row;
                     *dd = first ? dt : *dd + dt;
                 }
@@ -320,11 +328,11 @@ __global__ __launch_bounds__(kSymBlock) void pair_sym_kernel(
 
         // the block's accumulators -> partial slot c (every phase ended with a barrier; an empty walk leaves zeros)
         const int64_t brow = (int64_t)b * rb;
-        for (int idx = threadIdx.x; idx < rb * DP; idx += kSymBlock) {
+        for (int idx = opaque(threadIdx.x); idx < rb * DP; idx += kSymBlock) {
             const int j = idx / DP, col = idx % DP;
             part_t[(slot_b * n_pad + brow + j) * DP + col] = lds_t[((size_t)(col / 16) * rb + j) * 16 + (col % 16)];
         }
-        for (int j = threadIdx.x; j < rb; j += kSymBlock) part_d[slot_b * n_pad + brow + j] = lds_d[j];
+        for (int j = opaque(threadIdx.x); j < rb; j += kSymBlock) part_d[slot_b * n_pad + brow + j] = lds_d[j];
         __syncthreads();
     }
 

@@ -101,16 +101,14 @@ __device__ __forceinline__ bool stamp_poisons(const Stamp& stamp, int* flag)
 
 constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (two 16-sample tiles; 2 x 16.5 KiB of LDS)
 
-// Centre, scale and pad for the MFMA path.  A workgroup stages kPrepRows rows in LDS and writes
-//   dst[row][dp]   = a (x - mean), 0 in padding columns and rows (coalesced row writes); fp32: within each
-//                    16-column block coordinate c sits at position 4 (c % 4) + c / 4,
-//   dst_t[row/16][col][row%16] = the same values with each 16-sample tile transposed (if dst_t),
+// Centre, scale and pad for the matrix path.  A workgroup stages kPrepRows rows in LDS and writes a (x - mean), 0 in
+// padding columns and rows, to dst, the same values for the second contraction to dst_t (if it is there) and
 //   dst_n[row]     = -|dst[row]|^2 in double, rounded once; kPadNorm for padding rows.
 // format kFormatSplit3: dst and dst_t hold three bf16 parts of each value in the layouts of split3.h (kPrepRows rows are
 // one chunk of either, so a workgroup writes two contiguous blocks, 16 bytes a thread), and the norm is halved.
-// fp16x2 input modes: dst holds, per 16-column block, 16 fp16 "hi" values
-// followed by 16 fp16 "lo" values with hi + lo = the fp32 coordinate to ~22 mantissa bits (same bytes
-// per row as fp32); the norm is then taken of hi + lo so that it matches what the MFMA multiplies.
+// fp16x2 input modes: dst[row] holds, per 16-column block, 16 fp16 "hi" values followed by 16 fp16 "lo" values with
+// hi + lo = the fp32 coordinate to ~22 mantissa bits; the norm is taken of hi + lo so that it matches what the MFMA
+// multiplies; dst_t[row/16][col][row%16] = the fp32 values with each 16-sample tile transposed, except
 // FP16X2_ALL: dst_t holds fp16 pairs too, laid out as the A operand of the K = 32
 // second contraction: for tile, column c and lane group g, eight halves [hi(4g..4g+3) | the same again]
 // followed by eight halves [lo(4g..4g+3) | the same again] (twice the bytes of the fp32 layout).
@@ -130,18 +128,12 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         if (row < job.rows && c < d) v = a * ((STAGED ? raw[rr][c] : job.src[row * d + c]) - smean[c]);
         raw[rr][c] = v;
         if (format == kFormatSplit3) continue;              // the parts are written below
-        if (format != SDKDE_PREC_FP32) {
-            const _Float16 hi = (_Float16)v;
-            const _Float16 lo = (_Float16)(v - (float)hi);
-            _Float16* out = dst_h + row * 2 * dp + (c / 16) * 32 + (c % 16);
-            out[0] = hi;
-            out[16] = lo;
-            v = (float)hi + (float)lo;
-        } else {
-            // fp32 layout: coordinate c of a 16-column block at position 4 (c % 4) + c / 4 (RowTiles, KLAST)
-            job.dst[row * dp + ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3))] = v;
-        }
-        used[rr][c] = v;
+        const _Float16 hi = (_Float16)v;
+        const _Float16 lo = (_Float16)(v - (float)hi);
+        _Float16* out = dst_h + row * 2 * dp + (c / 16) * 32 + (c % 16);
+        out[0] = hi;
+        out[16] = lo;
+        used[rr][c] = (float)hi + (float)lo;
     }
     __syncthreads();
     if (format == kFormatSplit3) {

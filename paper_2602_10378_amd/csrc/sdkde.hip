@@ -28,14 +28,11 @@ namespace {
 // Host side: plan, workspace layout, dispatch.
 // ------------------------------------------------------------------------------------------
 
-// Most row tiles per wave for which pair_mfma_kernel is instantiated (larger ones would spill registers): the fp16 input
-// modes, and the in-block pass of the symmetric mode.
+// Most row tiles per wave for which pair_mfma_kernel (fp16 input modes) is instantiated (larger ones would spill registers).
 constexpr int max_row_tiles(int kb, int kind, int prec)
 {
-    const bool second = kind == kScoreSelf || kind == kScorePoints || kind == kScoreBand;   // has the Phi X contraction
     if ((prec == SDKDE_PREC_FP16X2_ALL || prec == SDKDE_PREC_FP16X2_PHI16) && kb > 1) return 0;      // see effective_prec()
-    if ((kind == kScoreBand) != (prec == SDKDE_PREC_FP32)) return 0;
-    if (kind == kScoreBand && kb > 2) return 0;                                       // see sym_row_tiles()
+    const bool second = kind == kScoreSelf || kind == kScorePoints;       // has the Phi X contraction
     return second ? (kb == 1 ? 8 : kb <= 4 ? 4 : 2)
                   : (kb == 1 ? 16 : kb == 2 ? 8 : kb <= 4 ? 4 : 2);
 }
@@ -44,8 +41,8 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 // them as rt = ni waves / 4 (so that a workgroup has 64 rt rows, as in the other kernels).  nb, ahead, minw: see there.
 // ni = 0: not built.  Which shapes are built was measured at n = m = 65536 (clocks per 256 pairs and SIMD at 2.4 GHz;
 // the sum of the MFMAs at 16 clocks and the vector work alone is 210 / 306 / 402 / 498 for the score at dp = 16 .. 64):
-//   score  dp = 16   rt 8 / 4 / 2: 232 / 227 / 231        dp = 32  rt 4 / 2: 342 / 356    dp = 48  554 / 521
-//          dp = 64   623 / 651     dp = 80  812 / 840     dp = 96  960 / 1245 (one wave per SIMD)
+//   score  dp = 16   rt 8 / 4 / 2: 226 / 229 / 235        dp = 32  rt 4 / 2: 346 / 359    dp = 48  554 / 533
+//          dp = 64   640 / 660     dp = 80  811 / 840     dp = 96  1014 / 1245 (one wave per SIMD)   dp = 128  - / 1615
 //   eval   dp = 16   rt 8 / 4 / 2: 105 / 103 / 112        dp = 32  rt 4 / 2: 156 / 166    dp = 48  224 / 235
 //          dp = 64   273 / 288     dp = 96  420 / 424     dp = 128 580 / 557
 // At dp >= 112 the score's operands leave room for one wave per SIMD only (two would spill).
@@ -55,7 +52,7 @@ constexpr SplitShape split_shape(int kb, bool score, int rt)
     if (score) {
         if (rt == 2) return {2, 4, 2, kb != 5, kb == 1 ? 4 : kb <= 5 ? 2 : 1};
         if (rt == 4) return kb <= 2 ? SplitShape{4, 4, 4, true, 2} : kb <= 6 ? SplitShape{2, 8, 2, kb < 6, 2} : SplitShape{};
-        if (rt == 8 && kb == 1) return {8, 4, 1, false, 2};
+        if (rt == 8 && kb == 1) return {8, 4, 2, true, 2};
     } else {
         if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : 2};
         if (rt == 4) return kb <= 5 ? SplitShape{4, 4, kb == 5 ? 2 : 4, false, kb <= 2 ? 3 : 2} : SplitShape{2, 8, 2, false, 2};
@@ -94,7 +91,7 @@ inline uint32_t anchored_flags(uint32_t flags, bool self)
 
 struct Plan {
     bool thin;
-    bool split3;          // three-part operands (pair_split_kernel), unless sym_on
+    bool split3;          // three-part operands (pair_split_kernel, pair_sym_kernel)
     int d, dp;            // true and padded dimension (thin: dp == d)
     int ni;               // MFMA: row tiles per wave; thin: rows per thread
     int rows_per_block;
@@ -112,7 +109,7 @@ struct Plan {
 // times sqrt 2 in the three-part format, which carries the factor 2 of the cross term in both of its operands.
 inline int operand_format(const Plan& p, uint32_t flags)
 {
-    return p.split3 && !p.sym_on ? kFormatSplit3 : (int)effective_prec(flags, p.thin, p.dp);
+    return p.split3 ? kFormatSplit3 : (int)effective_prec(flags, p.thin, p.dp);
 }
 inline double operand_scale(int format, double h)
 {
@@ -320,16 +317,14 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
     return p;
 }
 
-// Row tiles per wave of the pair_sym_kernel instantiation for kb 16-column blocks; 0: not built, the flag is
-// ignored.  Built where it pays (measured at n = 262144 against the ordinary kernels): fp32 inputs with
-// dp = 16 (1.25x) and dp = 32 (1.17x).  With dp >= 48 only two row tiles per wave fit the 256 registers a wave
-// has at two waves per SIMD and the gain was nil; with fp16x2 inputs the Gram MFMAs it saves are already cheap
-// and the mode was slower than the ordinary kernel.
+// Row tiles per wave of the pair_sym_kernel instantiation for kb 16-column blocks; 0: not built, the flag is ignored.
+// (With dp >= 48 its operands leave no room for two waves per SIMD.)
 constexpr int sym_row_tiles(int kb, int prec)
 {
-    if (prec == SDKDE_PREC_FP32) return kb == 1 ? 8 : kb == 2 ? 4 : 0;
-    return 0;
+    return prec != SDKDE_PREC_FP32 ? 0 : kb == 1 ? 4 : kb == 2 ? 2 : 0;
 }
+// Least rows of a sample block, which are also what the smallest block size is a multiple of.
+constexpr int sym_least_rows(int kb) { return kb == 1 ? 1024 : 512; }
 
 // Most groups of sample blocks in the symmetric mode (a row gets one partial slot per group, plus three).
 constexpr int kSymMaxGroups = 64;
@@ -345,7 +340,7 @@ void apply_symmetric(Plan& p, int64_t n, uint32_t flags, bool self)
     const int ni = sym_row_tiles(kb, (int)(flags & 15u));
     if (ni == 0) return;
     p.sym_ni = ni;
-    const int sb = kSymWaves * p.sym_ni * kTile;           // rows a workgroup holds at a time: 512 or 256
+    const int sb = sym_least_rows(kb);
     int rb = kb == 1 ? 2048 : kb == 2 ? 1024 : 512;
     auto items = [&](int rb_) {
         int64_t nb = (n + rb_ - 1) / rb_;
@@ -364,9 +359,11 @@ void apply_symmetric(Plan& p, int64_t n, uint32_t flags, bool self)
     if (nblocks > (1 << 20)) return;
     const int per_group = (int)((nblocks + max_groups - 1) / max_groups);
     const int ngroups = (int)((nblocks + per_group - 1) / per_group);
-    // Below ~512 work items (two rounds of one per CU) the ordinary kernels win: measured at d = 16 the mode pays
-    // from n = 32768 (528 items) and loses 1.5x at n = 24576 (300 items), 4x at n = 8192; at d = 32 it pays from
-    // n = 16384.  The flag is then ignored.  (SDKDE_TUNE_SYM_MIN_ITEMS: for tests of the mode at small sizes.)
+    // Below 512 work items (two rounds of one per CU) the ordinary kernels are well ahead and the flag is ignored
+    // (SDKDE_TUNE_SYM_MIN_ITEMS: for tests of the mode at small sizes).  Measured, symmetric / ordinary: d = 16
+    // n = 32768 457 / 423 us, 131072 6.04 / 6.13 ms, 1048576 371 / 377 ms; d = 32 n = 100000 6.6 / 5.5 ms.  (With fp32
+    // MFMAs on both sides the mode was 1.25 times as fast; three-part operands have made the vector work it halves and
+    // the matrix work it cuts by a quarter cheaper than its transposes, folds and phase barriers.)
     int min_items = tuning(SDKDE_TUNE_SYM_MIN_ITEMS, 512);
     if (min_items < 1) min_items = 1;
     if ((int64_t)ngroups * (ngroups + 1) / 2 < min_items) return;
@@ -514,7 +511,7 @@ int launch_thin(const Plan& p, const Workspace& w, const float* shift, hipStream
 template <int KIND, int KB, int RT>
 int launch_split_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
-    constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints;
+    constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints || KIND == kScoreBand;
     constexpr SplitShape sh = split_shape(KB, score, RT);
     if constexpr (sh.ni == 0) {
         return SDKDE_EUNSUPPORTED;
@@ -555,7 +552,7 @@ int launch_split(const Plan& p, const Workspace& w, const float* shift, hipStrea
     }
 }
 
-// The fp16 input modes, and the in-block pass of the symmetric mode.
+// The fp16 input modes.
 template <int KIND, int PREC>
 int launch_mfma(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
@@ -605,28 +602,29 @@ int launch_pair_prec(const Plan& p, const Workspace& w, uint32_t flags, const fl
 {
     const int rc = check_grid(p);
     if (rc != SDKDE_OK) return rc;
-    if constexpr (KIND == kScoreBand) {
-        return launch_mfma<KIND, SDKDE_PREC_FP32>(p, w, shift, st);
-    } else {
-        // the thin-d path has no matrix inputs: it runs the same fp32 VALU code for every mode
-        if (p.thin) return launch_thin<KIND>(p, w, shift, st);
-        const uint32_t prec = effective_prec(flags, p.thin, p.dp);
-        if (prec == SDKDE_PREC_FP32) return launch_split<KIND>(p, w, shift, st);
-        if constexpr (KIND == kScoreSelf || KIND == kScorePoints) {
-            if (prec == SDKDE_PREC_FP16X2_ALL) return launch_mfma<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
-            if (prec == SDKDE_PREC_FP16X2_PHI16) return launch_mfma<KIND, SDKDE_PREC_FP16X2_PHI16>(p, w, shift, st);
-        }
-        // kinds without a second contraction: the fp16 modes are the same kernel
-        return launch_mfma<KIND, SDKDE_PREC_FP16X2>(p, w, shift, st);
+    // the thin-d path has no matrix inputs: it runs the same fp32 VALU code for every mode
+    if (p.thin) return launch_thin<KIND>(p, w, shift, st);
+    const uint32_t prec = effective_prec(flags, p.thin, p.dp);
+    if (prec == SDKDE_PREC_FP32) return launch_split<KIND>(p, w, shift, st);
+    if constexpr (KIND == kScoreSelf || KIND == kScorePoints) {
+        if (prec == SDKDE_PREC_FP16X2_ALL) return launch_mfma<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
+        if (prec == SDKDE_PREC_FP16X2_PHI16) return launch_mfma<KIND, SDKDE_PREC_FP16X2_PHI16>(p, w, shift, st);
     }
+    // kinds without a second contraction: the fp16 modes are the same kernel
+    return launch_mfma<KIND, SDKDE_PREC_FP16X2>(p, w, shift, st);
 }
 
 // Symmetric mode: pairs across blocks (pair_sym_kernel), then the pairs inside each block with the ordinary
 // kernel restricted to the block (slot ngroups + 1).
-template <int KB, int NI, int PREC, int KLAST>
+template <int KB>
 int launch_sym_kernel(const Plan& p, const Workspace& w, hipStream_t st)
 {
+    constexpr int NI = sym_row_tiles(KB, SDKDE_PREC_FP32);
     const size_t lds = sym_lds_bytes(KB, p.sym_rb);
+    // Host-side shape check: whole blocks of whole workgroup row sets, a power of two of chunks per phase.
+    if (p.sym_rb % (kSymWaves * NI * kTile) || p.sym_rb % (kSymWaves * kChunkRows) || (p.sym_rb & (p.sym_rb - 1)) ||
+        (int64_t)p.sym_nblocks * p.sym_rb != p.n_pad || lds > 160 * 1024)
+        return SDKDE_EINVAL;
     // more than 64 KiB of dynamic LDS has to be enabled per kernel and device; remembered, so that later calls
     // (also ones under stream capture) only launch
     constexpr int kMaxDevices = 64;
@@ -637,64 +635,37 @@ int launch_sym_kernel(const Plan& p, const Workspace& w, hipStream_t st)
     {
         std::lock_guard<std::mutex> lock(guard);
         if (dev < 0 || dev >= kMaxDevices || lds > lds_allowed[dev]) {
-            SDKDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&pair_sym_kernel<KB, NI, PREC, KLAST>),
+            SDKDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&pair_sym_kernel<KB, NI>),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             if (dev >= 0 && dev < kMaxDevices) lds_allowed[dev] = lds;
         }
     }
     const int64_t items = (int64_t)p.sym_ngroups * (p.sym_ngroups + 1) / 2;
-    hipLaunchKernelGGL((pair_sym_kernel<KB, NI, PREC, KLAST>), dim3((unsigned)items), dim3(kSymBlock), lds, st, w.xs, w.xt,
+    hipLaunchKernelGGL((pair_sym_kernel<KB, NI>), dim3((unsigned)items), dim3(kSymBlock), lds, st, w.xs, w.xt,
                        w.xn, w.part_t, w.part_d, p.n_pad, p.sym_rb, p.sym_nblocks, p.sym_per_group, p.sym_ngroups);
-    return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
-}
-
-template <int KB, int PREC>
-int launch_sym_kb(const Plan& p, const Workspace& w, hipStream_t st)
-{
-    constexpr int NI = sym_row_tiles(KB, PREC);
-    if constexpr (NI > 0) {
-        if (p.sym_ni != NI) return SDKDE_EINVAL;
-        switch (p.klast) {
-            case 1: return launch_sym_kernel<KB, NI, PREC, 1>(p, w, st);
-            case 2: return launch_sym_kernel<KB, NI, PREC, 2>(p, w, st);
-            case 3: return launch_sym_kernel<KB, NI, PREC, 3>(p, w, st);
-            default: return launch_sym_kernel<KB, NI, PREC, 4>(p, w, st);
-        }
-    } else {
-        return SDKDE_EUNSUPPORTED;
-    }
-}
-
-template <int PREC>
-int launch_sym_prec(const Plan& p, const Workspace& w, hipStream_t st)
-{
-    // Host-side shape check: whole blocks, whole workgroup row sets, an even power of two of tiles per phase.
-    const int sb = kSymWaves * p.sym_ni * kTile;
-    if (p.sym_ni < 2 || p.sym_rb % sb || p.sym_rb % (2 * kSymWaves * kTile) || (p.sym_rb & (p.sym_rb - 1)) ||
-        (int64_t)p.sym_nblocks * p.sym_rb != p.n_pad || sym_lds_bytes(p.dp / 16, p.sym_rb) > 160 * 1024)
-        return SDKDE_EINVAL;
-    switch (p.dp / 16) {
-        case 1: return launch_sym_kb<1, PREC>(p, w, st);
-        case 2: return launch_sym_kb<2, PREC>(p, w, st);
-        default: return SDKDE_EUNSUPPORTED;
-    }
-}
-
-int launch_symmetric(const Plan& p, const Workspace& w, uint32_t flags, hipStream_t st)
-{
-    if (effective_prec(flags, p.thin, p.dp) != SDKDE_PREC_FP32) return SDKDE_EUNSUPPORTED;   // see sym_row_tiles()
-    int rc = launch_sym_prec<SDKDE_PREC_FP32>(p, w, st);
+    int rc = launched();
     if (rc != SDKDE_OK) return rc;
+
     Plan band = p;
     band.nsplit = 1;
     band.tiles_per_split = p.sym_rb / kTile;        // kScoreBand: the length of a block in tiles
-    band.ni = max_row_tiles(p.dp / 16, kScoreBand, SDKDE_PREC_FP32);
+    band.ni = 4;
     band.rows_per_block = kWavesPerBlock * kTile * band.ni;
     band.row_blocks = ((int64_t)p.ntiles * kTile + band.rows_per_block - 1) / band.rows_per_block;
+    if (p.sym_rb % band.rows_per_block || (rc = check_grid(band)) != SDKDE_OK) return SDKDE_EINVAL;
     Workspace wb = w;                               // its slots follow pair_sym_kernel's
     wb.part_t = w.part_t + (size_t)(p.sym_ngroups + 1) * p.m_pad * p.dp;
     wb.part_d = w.part_d + (size_t)(p.sym_ngroups + 1) * p.m_pad;
-    return launch_pair_prec<kScoreBand>(band, wb, flags, nullptr, st);
+    return launch_split_shape<kScoreBand, KB, 4>(band, wb, nullptr, st);
+}
+
+int launch_symmetric(const Plan& p, const Workspace& w, hipStream_t st)
+{
+    switch (p.dp / 16) {
+        case 1: return launch_sym_kernel<1>(p, w, st);
+        case 2: return launch_sym_kernel<2>(p, w, st);
+        default: return SDKDE_EUNSUPPORTED;
+    }
 }
 
 // Launches an epilogue kernel (template parameter: threads per output) over `outputs` outputs of `nslots` slots.
@@ -860,7 +831,7 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if ((rc = profile_mark(0, 0, st)) != SDKDE_OK) return rc;
     if (shifted && (rc = launch_max_shift(p, w, flags, st)) != SDKDE_OK) return rc;
     const float* shift = shifted ? w.shift : nullptr;
-    rc = p.sym_on ? launch_symmetric(p, w, flags, st)
+    rc = p.sym_on ? launch_symmetric(p, w, st)
          : self   ? launch_pair_prec<kScoreSelf>(p, w, flags, nullptr, st)
                   : launch_pair_prec<kScorePoints>(p, w, flags, shift, st);
     if (rc != SDKDE_OK) return rc;

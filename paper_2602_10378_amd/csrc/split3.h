@@ -111,6 +111,17 @@ __device__ __forceinline__ void split3_weights(const f32x4& p, const f32x4& q, b
     l = __builtin_bit_cast(bf16x8, (u32x4){part[2][0], part[2][1], part[2][2], part[2][3]});
 }
 
+// 16 bytes at a wave-uniform base plus an unsigned lane offset.  The empty asm keeps the base in scalar registers: left
+// to itself the compiler adds the lane offset to a loop-invariant pointer first and carries 64-bit vector addresses.
+template <typename T>
+__device__ __forceinline__ T load_at(const char* base, uint32_t offset)
+{
+    uint64_t bits = reinterpret_cast<uint64_t>(base);
+    asm("" : "+s"(bits));
+    typedef const __attribute__((address_space(1))) char* global_bytes;
+    return *reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<global_bytes>(bits) + offset);
+}
+
 __device__ __forceinline__ f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, const f32x4& c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
