@@ -23,8 +23,9 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
     __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
-    __shared__ float raw[kPrepRows][SDKDE_MAX_D + 1];
-    __shared__ float used[kPrepRows][SDKDE_MAX_D + 1];
+    extern __shared__ float prep_lds[];                     // prep_lds_bytes
+    float* const raw = prep_lds;
+    float* const used = prep_lds + kPrepRows * (dp + 1);
     __shared__ f32x4 red_t[PARTS][LANES];
     __shared__ float red_d[PARTS][LANES];
     __shared__ int stamp_flag;
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                if (c0 + v < d) raw[item / quads][c0 + v] = shifted[v];
+                if (c0 + v < d) raw[(item / quads) * (dp + 1) + c0 + v] = shifted[v];
         }
         __syncthreads();            // red_t / red_d are reused by the next pass; raw is read below
     }

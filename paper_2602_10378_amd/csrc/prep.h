@@ -99,7 +99,7 @@ __device__ __forceinline__ bool stamp_poisons(const Stamp& stamp, int* flag)
     return *flag != 0;
 }
 
-constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (two 16-sample tiles; 2 x 16.5 KiB of LDS)
+constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (two 16-sample tiles, one chunk of split3.h)
 
 // Centre, scale and pad for the matrix path.  A workgroup stages kPrepRows rows in LDS and writes a (x - mean), 0 in
 // padding columns and rows, to dst, the same values for the second contraction to dst_t (if it is there) and
@@ -118,22 +118,26 @@ constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (tw
 // already in raw[][] (a caller that has just computed them); otherwise they are read from job.src.
 template <bool STAGED>
 __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, float a, int format, bool poisoned,
-                                          const float* smean, float (*raw)[SDKDE_MAX_D + 1], float (*used)[SDKDE_MAX_D + 1])
+                                          const float* smean, float* raw_rows, float* used_rows)
 {
+    // kPrepRows rows of dp + 1 floats each (odd stride: columns are read without bank conflicts)
+    const int stride_f = dp + 1;
+    auto raw = [&](int rr) { return raw_rows + rr * stride_f; };
+    auto used = [&](int rr) { return used_rows + rr * stride_f; };
     _Float16* dst_h = reinterpret_cast<_Float16*>(job.dst);
     for (int idx = threadIdx.x; idx < kPrepRows * dp; idx += kBlock) {
         const int rr = idx / dp, c = idx % dp;
         const int64_t row = r0 + rr;
         float v = 0.0f;
-        if (row < job.rows && c < d) v = a * ((STAGED ? raw[rr][c] : job.src[row * d + c]) - smean[c]);
-        raw[rr][c] = v;
+        if (row < job.rows && c < d) v = a * ((STAGED ? raw(rr)[c] : job.src[row * d + c]) - smean[c]);
+        raw(rr)[c] = v;
         if (format == kFormatSplit3) continue;              // the parts are written below
         const _Float16 hi = (_Float16)v;
         const _Float16 lo = (_Float16)(v - (float)hi);
         _Float16* out = dst_h + row * 2 * dp + (c / 16) * 32 + (c % 16);
         out[0] = hi;
         out[16] = lo;
-        used[rr][c] = (float)hi + (float)lo;
+        used(rr)[c] = (float)hi + (float)lo;
     }
     __syncthreads();
     if (format == kFormatSplit3) {
@@ -152,14 +156,14 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
                 const int rr = at_item % kPrepRows, c0 = at_item / kPrepRows * 8;
                 at = rows_out + split3_offset(rr, c0, dp, &stride);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = raw[rr][c0 + k];
+                for (int k = 0; k < 8; ++k) v[k] = raw(rr)[c0 + k];
             } else {
                 const int lane = at_item % kWave, mb = (at_item - row_items) / kWave;
                 const int c = mb * 16 + (lane & 15), s0 = (lane >> 4) * 4;
                 at = t_out + mb * 3 * kPartBytes + lane * 16;
                 stride = kPartBytes;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = raw[s0 + (k & 3) + (k >> 2) * kTile][c];
+                for (int k = 0; k < 8; ++k) v[k] = raw(s0 + (k & 3) + (k >> 2) * kTile)[c];
             }
             uint32_t part[4][3];
 #pragma unroll
@@ -175,7 +179,7 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         for (int idx = threadIdx.x; idx < kPrepRows * dp * 2; idx += kBlock) {
             // idx = ((tile*dp + c)*4 + g)*8 + e
             const int e = idx % 8, g = (idx / 8) % 4, c = (idx / 32) % dp, tile = idx / (32 * dp);
-            const float v = raw[tile * kTile + 4 * g + (e & 3)][c];
+            const float v = raw(tile * kTile + 4 * g + (e & 3))[c];
             const _Float16 hi = (_Float16)v;
             base[idx] = e < 4 ? hi : (_Float16)(v - (float)hi);
         }
@@ -183,14 +187,14 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         float* base = job.dst_t + (r0 / kTile) * (int64_t)dp * kTile;
         for (int idx = threadIdx.x; idx < kPrepRows * dp; idx += kBlock) {
             const int tile = idx / (dp * kTile), c = (idx / kTile) % dp, rr = idx % kTile;
-            base[idx] = raw[tile * kTile + rr][c];        // idx = (tile*dp + c)*16 + rr
+            base[idx] = raw(tile * kTile + rr)[c];        // idx = (tile*dp + c)*16 + rr
         }
     } else if (job.dst_t) {
         _Float16* base = reinterpret_cast<_Float16*>(job.dst_t) + (r0 / kTile) * (int64_t)dp * 64;
         for (int idx = threadIdx.x; idx < kPrepRows * dp * 4; idx += kBlock) {
             // idx = ((tile*dp + c)*4 + g)*16 + e
             const int e = idx % 16, g = (idx / 16) % 4, c = (idx / 64) % dp, tile = idx / (64 * dp);
-            const float v = raw[tile * kTile + 4 * g + (e & 3)][c];
+            const float v = raw(tile * kTile + 4 * g + (e & 3))[c];
             const _Float16 hi = (_Float16)v;
             base[idx] = e < 8 ? hi : (_Float16)(v - (float)hi);
         }
@@ -198,12 +202,19 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
     if (threadIdx.x >= kBlock - kPrepRows) {
         const int rr = threadIdx.x - (kBlock - kPrepRows);
         double acc = 0.0;
-        const float* v = format == kFormatSplit3 ? raw[rr] : used[rr];
+        const float* v = format == kFormatSplit3 ? raw(rr) : used(rr);
         for (int c = 0; c < dp; ++c) acc += (double)v[c] * (double)v[c];
         if (format == kFormatSplit3) acc *= 0.5;
         const int64_t row = r0 + rr;
         job.dst_n[row] = poisoned ? __builtin_nanf("") : row < job.rows ? -(float)acc : kPadNorm;
     }
+}
+
+// As much LDS as the padded dimension needs: with 33 KiB for any of them four workgroups fitted a compute unit and
+// a call with more than 32768 rows took a second round of them (60028 rows at d = 24: 19 us).
+inline size_t prep_lds_bytes(int dp, int format)
+{
+    return sizeof(float) * kPrepRows * (dp + 1) * (format == kFormatSplit3 ? 1 : 2);
 }
 
 // Grid: job0's blocks first (blocks0 of them), then job1's.
@@ -212,8 +223,7 @@ __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob
 {
     __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
-    __shared__ float raw[kPrepRows][SDKDE_MAX_D + 1];     // a (x - mean)
-    __shared__ float used[kPrepRows][SDKDE_MAX_D + 1];    // the value the first contraction multiplies (hi + lo, or raw)
+    extern __shared__ float prep_lds[];     // prep_lds_bytes: a (x - mean), then (fp16 formats) the hi + lo multiplied instead
     __shared__ int stamp_flag;
     const bool poisoned = stamp_poisons(stamp, &stamp_flag);
     prep_common(common, d, red, smean);
@@ -221,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob& job = second ? job1 : job0;
     const int64_t r0 = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kPrepRows;
-    prep_rows<false>(job, r0, d, dp, a, format, poisoned, smean, raw, used);
+    prep_rows<false>(job, r0, d, dp, a, format, poisoned, smean, prep_lds, prep_lds + kPrepRows * (dp + 1));
 }
 
 // Thin-d variant: dst[row][d] = a (x - mean), padding rows get pad_value in every coordinate.

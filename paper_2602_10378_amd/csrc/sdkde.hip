@@ -722,7 +722,7 @@ int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, cons
     if (p.thin)
         hipLaunchKernelGGL(prep_thin_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, common, a, stamp);
     else
-        hipLaunchKernelGGL(prep_mfma_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, p.dp, common, a,
+        hipLaunchKernelGGL(prep_mfma_kernel, grid, block, prep_lds_bytes(p.dp, operand_format(p, flags)), st, first, second, (int)blocks0, p.d, p.dp, common, a,
                            operand_format(p, flags), stamp);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
@@ -851,7 +851,8 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
             if (!self || !samples_sd_out || p.sym_on || mode != 2) return SDKDE_EINVAL;
             const int blocks_sd = (int)(fused->sd_job.rows_pad / kPrepRows);
             const int blocks_q = (int)(fused->q_job.rows_pad / kPrepRows);
-            hipLaunchKernelGGL(score_epilogue_prep_kernel, dim3((unsigned)(blocks_sd + blocks_q)), dim3(kBlock), 0, st, w.part_t,
+            hipLaunchKernelGGL(score_epilogue_prep_kernel, dim3((unsigned)(blocks_sd + blocks_q)), dim3(kBlock),
+                               prep_lds_bytes(p.dp, format), st, w.part_t,
                                w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, format, inv_ah2, score_out, samples, half_h2,
                                samples_sd_out, quad_io, fused->sd_job, fused->q_job, blocks_sd,
                                PrepCommon{nullptr, 0, w.centre}, (float)a, fused->stamp);
