@@ -31,6 +31,8 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     const int lane = threadIdx.x % OUTPUTS, part = threadIdx.x / OUTPUTS;
     float acc = MAX ? kNegHuge : 0.0f;
     if (active) {
+        // several loads in flight, added in slot order (512 slots of 1024 queries, one at a time: 11.6 us)
+#pragma unroll 8
         for (int s = part; s < nslots; s += PARTS) {
             const float v = first[(int64_t)s * stride];
             acc = MAX ? fmaxf(acc, v) : acc + v;
@@ -120,6 +122,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
     float dacc = 0.0f;
     if (active) {
+#pragma unroll 4
         for (int s = part; s < nsplit; s += PARTS) {
             tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
             dacc += part_d[(int64_t)s * m_pad + i];

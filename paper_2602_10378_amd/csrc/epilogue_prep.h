@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
         f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
         float dacc = 0.0f;
         if (active) {
+#pragma unroll 4
             for (int s = part; s < nsplit; s += PARTS) {
                 tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
                 dacc += part_d[(int64_t)s * m_pad + i];
