@@ -31,8 +31,8 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     const int lane = threadIdx.x % OUTPUTS, part = threadIdx.x / OUTPUTS;
     float acc = MAX ? kNegHuge : 0.0f;
     if (active) {
-        // several loads in flight, added in slot order (512 slots of 1024 queries, one at a time: 11.6 us)
-#pragma unroll 8
+        // several loads in flight, added in slot order (512 slots of 1024 queries 4.8 us, one at a time 11.6)
+#pragma unroll 4
         for (int s = part; s < nslots; s += PARTS) {
             const float v = first[(int64_t)s * stride];
             acc = MAX ? fmaxf(acc, v) : acc + v;

@@ -24,8 +24,9 @@ namespace {
 //
 // SELF (score at the samples themselves): the pair (i, i) must stay out of D and T, because T_i/D_i - x_i would
 // otherwise cancel against the large self term whenever a point has few neighbours; the epilogue restores it
-// analytically (phi_ii = 1).  A wave sits out the chunks that are its own rows (no masking code in the loop) and goes over
-// them afterwards, from global memory, with the diagonal masked.
+// analytically (phi_ii = 1).  In the chunks that are a wave's own rows a wave-uniform branch sets the diagonal's exponents to
+// -3e38 between the Gram MFMAs and the exponentials (a masked copy of the whole body in the loop spills; going over those
+// chunks after the loop, from global memory, kept the workgroups they fall to longer).
 //
 // Grid: blockIdx.x = row_block * S + split; each workgroup handles 16 NI WAVES rows and the sample tiles
 // [split*tiles_per_split, min(ntiles, (split+1)*tiles_per_split)).  With S a multiple of 8 the round-robin placement of
@@ -122,9 +123,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
         return reinterpret_cast<f32x4*>(part_t + ((int64_t)split * m_pad + row0 + t * kTile + r) * DP + g * 4 + mb * 16);
     };
 
-    // One chunk against all NI row tiles.  own (MASK only): the row tile that is the chunk's first sample tile.
-    auto chunk = [&](auto mask_tag, const char* xc, const char* tc, const f32x4& nj0, const f32x4& nj1, int own) {
-        constexpr bool MASK = decltype(mask_tag)::value;
+    // One chunk against all NI row tiles.  own (SELF): the row tile that is the chunk's first sample tile, if it is one.
+    auto chunk = [&](const char* xc, const char* tc, const f32x4& nj0, const f32x4& nj1, int own) {
         constexpr int GROUPS = PAIRS + (ODD ? 1 : 0);
         // Operands of one group of MFMAs; scheduling barriers keep an early read early.
         bf16x8 ga[2][2][3], ta[2][3];
@@ -187,6 +187,16 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
                 }
                 pin();
             }
+            if (SELF && (unsigned)own < (unsigned)NI) {         // wave-uniform: the pairs of a point with itself
+#pragma unroll
+                for (int t = 0; t < NB; ++t)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        if (own + u == t0 + t) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) c[t][u][v] = g * 4 + v == r ? kNegHuge : c[t][u][v];
+                        }
+            }
             bf16x8 w[NB][3];
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
@@ -200,10 +210,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float e = __builtin_amdgcn_exp2f(c[t][u][v]);
-                        phi[u][v] = (MASK && t0 + t == own + u && g * 4 + v == r) ? 0.0f : e;
-                    }
+                    for (int v = 0; v < 4; ++v) phi[u][v] = __builtin_amdgcn_exp2f(c[t][u][v]);
                     if (LAPLACE) {
                         // c is the base-2 exponent -r^2/(2h^2) log2(e) (less the row's shift), so the Laplace factor
                         // 1 + d/2 - r^2/(2h^2) is lc0 + c ln 2 (Laplace-corrected KDE section)
@@ -288,8 +295,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
             const char* cur = stage_lds[(c - c_begin) & 1];
             fetch(c + 1);                                   // lands in registers while this chunk is worked on
             const f32x4 nn0 = norms(c + 1, 0), nn1 = norms(c + 1, 1);
-            if (!SELF || (unsigned)(c - own0) >= (unsigned)(NI / 2))     // wave-uniform
-                chunk(std::false_type{}, cur, cur + XCH * kPartBytes, nj0, nj1, 0);
+            chunk(cur, cur + XCH * kPartBytes, nj0, nj1, 2 * (c - own0));
             if (!ROWMAX && ((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
 #pragma unroll
                 for (int t = 0; t < NI; ++t) {
@@ -312,15 +318,6 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
             // ends the reads of the current one.
             deposit(stage_lds[(c + 1 - c_begin) & 1]);
             __syncthreads();
-        }
-    }
-    if constexpr (SELF) {
-        // The wave's own chunks, as far as they lie in this split: every pair but that of a point with itself.
-        const int d_end = min(c_end, own0 + NI / 2);
-        for (int c = max(c_begin, own0); c < d_end; ++c) {
-            const float* nb = xn + (int64_t)c * kChunkRows + g * 4;
-            chunk(std::true_type{}, xs_b + (int64_t)c * XCH * kPartBytes, xt_b + (int64_t)c * XCH * kPartBytes,
-                  *reinterpret_cast<const f32x4*>(nb), *reinterpret_cast<const f32x4*>(nb + kTile), 2 * (c - own0));
         }
     }
 #pragma unroll
