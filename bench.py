@@ -49,7 +49,8 @@ def traffic_from_profile(config, plan, launch_ms=None):
     rec = json.loads(m.group(1))
     n_pad, m_pad, dp, slots = plan["n_pad"], plan["m_pad"], plan["dp"], plan["partial_slots"]
     xt = plan["xt_scale"] * n_pad * dp if plan["off_xt"] >= 0 else 0
-    algorithmic = 4.0 * (n_pad * dp + xt + n_pad) + 4.0 * slots * m_pad * ((dp + 1) if plan["off_part_t"] >= 0 else 1)
+    operand_bytes = 4.0 if plan["thin"] else 6.0              # fp32 coordinates, or three bf16 parts of each
+    algorithmic = operand_bytes * (n_pad * dp + xt) + 4.0 * n_pad + 4.0 * slots * m_pad * ((dp + 1) if plan["off_part_t"] >= 0 else 1)
     detail = {"source": os.path.relpath(files[0], ROOT), "kernel": rec["kernel"], "read_bytes": rec["read_bytes"],
               "written_bytes": rec["written_bytes"], "algorithmic_bytes_of_the_launch": algorithmic,
               "ratio_to_algorithmic": rec["bytes"] / algorithmic,
@@ -164,9 +165,10 @@ class Workload:
         P, n, m, d = self.P, self.n, self.m, self.d
         flags = MODE_FLAGS[mode]
         plan_s, plan_e = P.sdkde_describe_plan(n, n, d, 0, flags), P.sdkde_describe_plan(n, m, d, 2, flags)
-        eff = mode
+        # the fp32 mode's matrix path multiplies three bf16 parts per operand
+        eff = {"fp32": "bf16x3", "symmetric": "symmetric_bf16x3"}.get(mode, mode)
         if mode == "symmetric" and not plan_s["symmetric"]:
-            eff = "fp32"
+            eff = "bf16x3"
         if mode == "fp16x2_all" and plan_s["xt_scale"] != 2:
             eff = "fp16x2"
         if mode == "fp16x2_phi16" and plan_s["dp"] != 16:
@@ -175,18 +177,18 @@ class Workload:
         for key, stage, ms, plan, pairs in (("roofline", "score", score_ms, plan_s, float(n) * n),
                                             ("roofline_eval_kernel", "eval", eval_ms, plan_e, float(m) * n)):
             thin = bool(plan["thin"])
-            r = cm.roofline(stage, d, pairs, ms * 1e-3, "fp32" if (stage == "eval" and eff == "symmetric") else eff, thin)
+            stage_eff = "bf16x3" if (stage == "eval" and eff == "symmetric_bf16x3") else eff
+            r = cm.roofline(stage, d, pairs, ms * 1e-3, stage_eff, thin)
             r["launch_ms"] = ms
-            r["kernel"] = ("pair_thin_kernel" if thin else "pair_sym_kernel + in-block pass" if (eff == "symmetric" and stage == "score")
-                           else "pair_lds_kernel" if (stage == "eval" and plan["dp"] >= 64 and eff == "fp32") else "pair_mfma_kernel") + f" ({stage})"
-            r["ceiling"] = self.mix_ceiling(stage, "fp32" if (stage == "eval" and eff == "symmetric") else eff, thin, ms, pairs,
-                                            max(r["seconds_at_peak"].values()))
+            r["kernel"] = ("pair_thin_kernel" if thin else "pair_sym_kernel + in-block pass" if stage_eff == "symmetric_bf16x3"
+                           else "pair_split_kernel" if stage_eff == "bf16x3" else "pair_mfma_kernel") + f" ({stage})"
+            r["ceiling"] = self.mix_ceiling(stage, stage_eff, thin, ms, pairs, max(r["seconds_at_peak"].values()))
             out[key] = r
         return out, plan_s
 
     def mix_ceiling(self, stage, mode, thin, ms, pairs, at_peak_s):
-        """What this kernel's instruction mix can reach on gfx950, where fp32 MFMA and vector work do not overlap
-        on a SIMD: SIMD clocks per 256 pairs (nominal 2.4 GHz, 1024 SIMDs) of the kernel as timed, of its mix as
+        """What this kernel's instruction mix can reach on gfx950, where matrix and vector work of a SIMD overlap little
+        (fp32 MFMA: not at all): SIMD clocks per 256 pairs (nominal 2.4 GHz, 1024 SIMDs) of the kernel as timed, of its mix as
         sdkde_peaks measures it (profiles/peaks_mfma_valu_coissue.txt), and of the bound resource alone at its
         published peak; frac = the last over the second = the share of the peak the mix allows."""
         d = self.d
@@ -199,13 +201,15 @@ class Workload:
             out["mix_clk_per_256_pairs"] = 4 * (8.1 + 3.05 * plain)
             out["basis"] = ("per pair and lane one v_exp_f32 (8.1 clk per wave instruction, overlaps nothing) and the plain "
                             "instructions at the 3.05 clk measured next to exps (2 at the published rate)")
-        elif mode == "fp32":
-            out["mix_clk_per_256_pairs"] = 32.0 * (8 if stage == "score" else 4) * blocks + 4 * 8 + 8 * 4 + (13 if stage == "score" else 6)
-            out["basis"] = ("per 16x16 tile: the MFMAs at 32 clk each, then 4 v_exp_f32 (8 clk) + 8 v_add_f32 (4 clk) that cannot "
-                            "overlap them, + 6-13 clk of switching (measured: 333 clk for the d = 16 score mix, 206 for eval)")
+        elif mode == "bf16x3":
+            score = stage == "score"
+            out["mix_clk_per_256_pairs"] = (16.0 * (6 if score else 3) * blocks + 4 * 8.1 + 2.4 * (24 + 2 * blocks if score else 8)
+                                            + 4.6 * (6 if score else 0))
+            out["basis"] = ("per 16x16 tile: the bf16 MFMAs at 16 clk each (about 21 under the power limit), 4 v_exp_f32 (8.1 clk), plain "
+                            "instructions at 2.4 and v_perm_b32 at 4.6, added up: they overlap by little")
         elif blocks == 1:
-            measured = {("symmetric", "score"): (265.5, "12 MFMAs + exp, row and column sums, LDS transpose and fold per tile of unordered "
-                                                         "pairs: 531 clk per 512 ordered pairs (kernel breakdown, not a micro-benchmark)"),
+            measured = {("symmetric_bf16x3", "score"): (155.0, "9 bf16 MFMAs at 16 clk, 4 exp, split, row and column sums and fold per tile of "
+                                                               "unordered pairs, added up: 310 clk per 512 ordered pairs"),
                         ("fp16x2", "score"): (226.0, "2 fp16 + 4 fp32 MFMAs + 4 exp + 8 add: 226-250 clk"),
                         ("fp16x2", "eval"): (92.0, "2 fp16 MFMAs + 4 exp + 8 add: 92-108 clk"),
                         ("fp16x2_all", "score"): (139.0, "4 fp16 MFMAs + 4 exp + 16 plain instructions: 139-147 clk")}
@@ -388,7 +392,8 @@ def main():
     s_fp32, logd_fp32 = w.s.clone(), w.logd.clone()
     default_shape = args.n is None and args.m is None
     if main_run["roofline"]["bound"] == "mfma":
-        main_run["roofline"]["flops_per_launch"] = main_run["roofline"]["work_per_pair"]["mfma_f32"] * float(n) * n
+        r = main_run["roofline"]
+        r["flops_per_launch"] = r["work_per_pair"][r["resource"]] * float(n) * n
     traffic, traffic_detail = (traffic_from_profile(args.config, plan, main_run["roofline"]["launch_ms"]) if default_shape
                                else (None, None))
     main_run["roofline"]["traffic"] = traffic

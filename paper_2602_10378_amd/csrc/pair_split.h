@@ -17,9 +17,9 @@ namespace {
 //
 // What bounds it: on this chip the bf16 MFMA (16 clocks; about 21 when every SIMD issues nothing else, the clock then
 // drops under the power limit) and the vector instructions of a SIMD overlap by little, so the time is close to the
-// sum of both: per 256 pairs 3 KB MFMAs for each contraction, 4 v_exp_f32 at 8 clocks, 16 adds / subtracts / ands at
-// about 2.4 and 6 v_perm_b32 at 4.6.  That sum is 210 clocks for the score at dp = 16 (fp32 MFMA kernel before: 333), 80 + 20 KB
-// for eval; measured figures at the dispatch (split_shape in sdkde.hip).  Two waves per SIMD are needed (one wave:
+// sum of both: per 256 pairs 3 KB MFMAs for each contraction, 4 v_exp_f32 at 8 clocks, 24 + 2 KB (eval: 8) adds, subtracts
+// and ands at about 2.4 and (score) 6 v_perm_b32 at 4.6.  That sum is 218 clocks for the score at dp = 16 (fp32 MFMA kernel
+// before: 333) and 52 + 48 KB for eval; measured figures at the dispatch (split_shape in sdkde.hip).  Two waves per SIMD are needed (one wave:
 // 1245 clocks against 933 at dp = 96) and more do not help; NI row tiles share every operand read from LDS.
 //
 // SELF (score at the samples themselves): the pair (i, i) must stay out of D and T, because T_i/D_i - x_i would

@@ -40,7 +40,7 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 // Shapes of pair_split_kernel: a workgroup of `waves` waves of `ni` row tiles each holds 16 ni waves rows; the plan counts
 // them as rt = ni waves / 4 (so that a workgroup has 64 rt rows, as in the other kernels).  nb, ahead, minw: see there.
 // ni = 0: not built.  Which shapes are built was measured at n = m = 65536 (clocks per 256 pairs and SIMD at 2.4 GHz;
-// the sum of the MFMAs at 16 clocks and the vector work alone is 210 / 306 / 402 / 498 for the score at dp = 16 .. 64):
+// the sum of the MFMAs at 16 clocks and the vector work alone is 218 / 318 / 419 / 520 for the score at dp = 16 .. 64):
 //   score  dp = 16   rt 8 / 4 / 2: 226 / 229 / 235        dp = 32  rt 4 / 2: 346 / 359    dp = 48  554 / 533
 //          dp = 64   640 / 660     dp = 80  811 / 840     dp = 96  1014 / 1245 (one wave per SIMD)   dp = 128  - / 1615
 //   eval   dp = 16   rt 8 / 4 / 2: 105 / 103 / 112        dp = 32  rt 4 / 2: 156 / 166    dp = 48  224 / 235

@@ -11,14 +11,14 @@ namespace {
 //     ah bh + ah bm + am bh + am bm + ah bl + al bh,
 // each exact in the fp32 accumulator's own format.  The three left out (am bl, al bm, al bl) are at most 2^-23 of
 // |a b| together and of either sign, the size of one fp32 rounding.  Six bf16 MFMAs per fp32 product still leave 2.6
-// times the fp32 MFMA rate, and unlike the fp32 MFMA they run beside the vector unit.
+// times the fp32 MFMA rate.
 //
 // Prepared rows ("xs" / "ps"), in chunks of kChunkRows = 32 rows of KB * 3072 bytes (KB = dp / 16), two 16-row tiles of
 // KB * 1536 bytes each:
 //   32-column block b (columns 32b .. 32b+31): part q at b * 3072 + q * 1024; lane l = 16 g + r of the operand holds
 //     columns 8g .. 8g+7 of row r at l * 16.
 //   the odd 16-column block left over when KB is odd: part q at (KB / 2) * 3072 + q * 512; columns 8g .. 8g+7 (g < 2) of
-//     row r at (16 g + r) * 16.  An MFMA's K = 32 then holds two parts: see Gram::cross in pair_split.h.
+//     row r at (16 g + r) * 16.  An MFMA's K = 32 then holds two parts: see read_gram in pair_split.h.
 // Prepared transpose ("xt"), same chunks: 16-column block mb, part q at mb * 3072 + q * 1024; lane l = 16 g + r holds
 //   column 16 mb + r of rows 4g .. 4g+3 of the first tile and 4g .. 4g+3 of the second, which is the order the Gram
 //   accumulators of the two tiles leave Phi in.
