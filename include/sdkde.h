@@ -28,7 +28,8 @@
  *    size of the result, about 1e-6 (1 + R/h) / h of the score is lost, which shows only where the true score is
  *    that small against 1/h (a sample whose only neighbours are its exact duplicates, a bandwidth so narrow that
  *    every neighbour's weight vanishes).  (Far outside that domain, R/h above ~1e18, the scaled
- *    coordinates overflow fp32 on either path and the outputs are NaN.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
+ *    coordinates overflow fp32 on either path and the outputs are NaN.  A sample with an infinite
+ *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
  *    is kept, and weights below the smallest normal fp32 number (2^-126) are flushed to zero: a point whose
  *    weights phi_j sum to less than 1000 n 2^-126 (so that the flushed ones could be more than one part in a
  *    thousand of the sum; the point is then farther than about 11.5 - 13 h from every sample, depending on n)

@@ -69,6 +69,7 @@ struct PrepJob {
     float* dst_t;
     float* dst_n;
     float pad_value;      // thin path only: coordinate value of padding rows
+    bool samples;         // the rows are summed over (not only evaluated at)
 };
 
 // Record of what a prep launch left in the workspace (sample arrays and column sums), kept in the workspace itself:
@@ -147,6 +148,10 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         char* t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
         // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other
         // (at dp = 16 one wave each), the norms below are left to the last wave.
+        // A sample's coordinate too large for bf16 goes in as zero: its norm is -inf, so every weight of the sample is
+        // exactly 0 (or NaN, if another coordinate is NaN).  Its parts (inf, NaN, NaN) would make the exponents NaN
+        // instead.  A point keeps them: nothing can be said of its own row.
+        auto usable = [&](float v) { return job.samples && fabsf(v) > kBf16Max ? 0.0f : v; };
         const int row_items = kPrepRows * dp / 8, t_items = t_out ? kb * kWave : 0;
         for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += kBlock) {
             char* at;
@@ -156,14 +161,14 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
                 const int rr = at_item % kPrepRows, c0 = at_item / kPrepRows * 8;
                 at = rows_out + split3_offset(rr, c0, dp, &stride);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = raw(rr)[c0 + k];
+                for (int k = 0; k < 8; ++k) v[k] = usable(raw(rr)[c0 + k]);
             } else {
                 const int lane = at_item % kWave, mb = (at_item - row_items) / kWave;
                 const int c = mb * 16 + (lane & 15), s0 = (lane >> 4) * 4;
                 at = t_out + mb * 3 * kPartBytes + lane * 16;
                 stride = kPartBytes;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = raw(s0 + (k & 3) + (k >> 2) * kTile)[c];
+                for (int k = 0; k < 8; ++k) v[k] = usable(raw(s0 + (k & 3) + (k >> 2) * kTile)[c]);
             }
             uint32_t part[4][3];
 #pragma unroll

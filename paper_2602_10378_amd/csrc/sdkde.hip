@@ -788,8 +788,8 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     if (we.xs != ws.xs || wr_begin < dead_begin || wr_end > dead_end) return false;
     if ((const char*)we.ps < (const char*)(we.xn + pe.n_pad)) return false;
     const double a = operand_scale(format, h);
-    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord};
-    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f};
+    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true};
+    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false};
     out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a);
     return true;
 }
@@ -823,8 +823,8 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord};
-    const PrepJob point_job{self ? nullptr : points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true};
+    const PrepJob point_job{self ? nullptr : points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
     const Stamp stamp = make_stamp(w, false, true, samples, n, d, format, (float)a);
     if ((rc = launch_prep(p, sample_job, point_job, samples, n, (float)a, w, flags, stamp, st)) != SDKDE_OK) return rc;
 
@@ -887,8 +887,8 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     const int format = operand_format(p, flags);
     const double a = operand_scale(format, h);
     const bool shifted = (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord};
-    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true};
+    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
     if (all_prepared) {
         // sdkde_fit_eval: the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
     } else if (flags & SDKDE_FLAG_SAMPLES_PREPARED) {

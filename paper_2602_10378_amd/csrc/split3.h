@@ -29,6 +29,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunkRows = 32;
+constexpr float kBf16Max = 3.38953139e38f;       // largest finite bf16 value
 constexpr int kPartBytes = 1024;                 // one part of a 16-row x 32-column operand
 constexpr int chunk_bytes(int kb) { return kb * 3 * kPartBytes; }
 // fp32 values needed to hold `rows` prepared rows of kb blocks (6 bytes a value)

@@ -62,3 +62,33 @@ def test_every_workgroup_shape(tuning, n, d, row_tiles):
                              np.exp(ref))
     if ran == 0:
         pytest.skip("not built")
+
+
+@pytest.mark.parametrize("d", [7, 16, 24, 37])
+def test_a_sample_at_infinity_has_no_weight(d):
+    """One infinite coordinate of one sample (not one of the rows the centre is formed of: every 17th at d = 16, every
+    40th at d = 37): its weight is zero wherever it is looked at from, whatever the signs of the other coordinates, so
+    every other output is that of the samples without it."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 4500, 70
+    print(f"sample at infinity n={n} m={m} d={d}", flush=True)
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=d)
+    h = float(h)
+    rest = x[:-1]
+    logd_ref = oracle.eval_log_density(rest, q, h) + np.log((n - 1) / n)
+    e = gram_exponent_error(rest, q, h)
+    for value in (np.inf, -np.inf):
+        y = x.copy()
+        y[-1, d // 2] = value
+        yd, qd = torch.from_numpy(y).cuda(), torch.from_numpy(q).cuda()
+        for flags in (0, P.SDKDE_FLAG_MAX_SHIFT):
+            logd = P.sdkde_eval(yd, qd, h, want="log", flags=flags)[1].cpu().numpy()
+            assert np.all(np.abs(logd - logd_ref) <= e + 2.0**-18 + 2.0**-23 * np.abs(logd_ref))
+            s = P.sdkde_score(yd, h, points=qd, flags=flags).cpu().numpy()
+            err = np.linalg.norm(s - oracle.score(rest, h, points=q), axis=1)
+            assert np.all(err <= _score_bound(rest, q, h))
+        s = P.sdkde_score(yd, h).cpu().numpy()[:-1]
+        err = np.linalg.norm(s - oracle.score(rest, h), axis=1)
+        assert np.all(err <= _score_bound(rest, rest, h))
