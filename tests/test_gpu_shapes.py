@@ -328,6 +328,26 @@ def test_a_workspace_made_for_more_points_serves_fewer():
     assert P.sdkde_describe_plan(72994, 54645, 16, 1)["workspace_bytes"] > P.sdkde_workspace_bytes(72994, 73086, 16)
 
 
+@pytest.mark.parametrize("n,m,d,flags", [(13000, 500, 16, 3), (13000, 500, 16, 2), (8241, 419, 17, 1), (12304, 560, 128, 1)])
+def test_a_workspace_of_the_fp32_mode_serves_the_fp16_modes(n, m, d, flags):
+    """The fp32 plan takes fewer than eight splits at these sizes, and its workspace holds no more slots than that: a
+    call in another mode on the same buffer then takes fewer splits too instead of being refused."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    print(f"fp32 workspace n={n} m={m} d={d}, call with flags {flags}", flush=True)
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=d)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h) * (2.0 if d > 64 else 1.0)
+    ws = torch.empty(P.sdkde_workspace_bytes(n, m, d, 0), dtype=torch.uint8, device="cuda")
+    assert P.sdkde_describe_plan(n, n, d, 0, flags)["workspace_bytes"] > ws.numel()
+    got = P.sdkde_score(xd, h, workspace=ws, flags=flags)
+    assert torch.equal(got, P.sdkde_score(xd, h, workspace=ws, flags=flags))
+    want = P.sdkde_score(xd, h, flags=flags)
+    assert float((got - want).norm() / want.norm()) < 1e-5
+    got, want = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=flags)[1], P.sdkde_eval(xd, qd, h, want="log", flags=flags)[1]
+    assert float((got - want).abs().max()) < 1e-4
+
+
 def test_sweep_module_times_the_papers_shapes():
     """paper_2602_10378_amd.sweep (runtime and utilisation in the shapes of the paper's sweeps, n_test = n_train / 8):
     one small shape per dimension; times are positive, the whole SD-KDE pass costs more than the KDE alone, and no
