@@ -137,7 +137,9 @@ enum {
  * decomposition, and with it the number of partial-sum slots, is chosen per shape and
  * precision mode).  A call given less than its own size (a buffer made for another m, say)
  * falls back to fewer splits of the samples - the same results to rounding, in a different but
- * equally fixed summation order, slower when there are few points - and returns
+ * equally fixed summation order, slower when there are few points - and, in the fp32 mode's eval
+ * calls and scores at separate points, to taking the points in batches, if the buffer would hold
+ * all of them with 4 bytes a prepared value instead of the 6 it takes; it returns
  * SDKDE_EWORKSPACE, doing nothing, only if its smallest decomposition does not fit either (a
  * buffer made for m points always serves fewer points with the same n, d and flags).  The
  * symmetric mode has one decomposition only and is refused without its full size.
@@ -207,8 +209,8 @@ int sdkde_fit_eval(const float *samples, int64_t n, const float *queries, int64_
  * in the call; inputs and outputs are still the caller's device arrays, with the meaning they have in
  * sdkde_fit_eval, and the results are bit-identical to those of sdkde_fit_eval with a workspace of
  * sdkde_workspace_bytes(n, m, d, flags) where that figure is at most SDKDE_STATIC_SCRATCH_BYTES.  A larger pass is
- * served (fp32 matrix path) while both of its steps fit with fewer splits, and refused with SDKDE_ETOOLARGE, nothing launched,
- * otherwise (the buffer serves e.g. n = m = 32768 at d = 16, n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
+ * served (fp32 matrix path) while both of its steps fit with fewer splits, or the queries in batches (see
+ * sdkde_workspace_bytes), and refused with SDKDE_ETOOLARGE, nothing launched, otherwise (the buffer serves e.g. n = m = 32768 at d = 16, n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
  * in it has to start at zero, every call rewrites what it reads.  All calls on one GPU share the one buffer:
  * two calls that overlap in time on the same GPU (different streams or host threads) race; order them on
  * one stream.  The first call on a device looks up the buffer's device address (no stream work); make it

@@ -451,6 +451,35 @@ bool fit_workspace(Plan& p, bool score, bool separate_points, void* base, size_t
     return w->bytes <= bytes;
 }
 
+// As above for separate points on the three-part operands, which take 6 bytes a value of a prepared point.  A buffer that
+// would hold the call with 4 bytes a value (640000 queries at dp = 16, one split: 49 MB, with 6 bytes 69 MB) serves it all
+// the same, the points in equal batches of whole workgroups' rows, one pass after the other; the plan is then one batch's.
+// Smaller buffers are refused.  Returns the points of a batch (m: all of them); 0: does not fit.
+int64_t fit_points(Plan& p, bool score, void* base, size_t bytes, uint32_t flags, int64_t m, Workspace* w)
+{
+    if (fit_workspace(p, score, true, base, bytes, flags, w)) return m;
+    if (!p.split3) return 0;
+    Plan four_bytes = p;
+    four_bytes.split3 = false;
+    if (layout(four_bytes, score, true, base, flags).bytes > bytes) return 0;
+    const int64_t all = p.row_blocks;
+    auto fits = [&](int64_t blocks) {
+        p.row_blocks = blocks;
+        p.m_pad = blocks * p.rows_per_block;
+        *w = layout(p, score, true, base, flags);
+        return w->bytes <= bytes;
+    };
+    int64_t most = 0, over = all + 1;               // row blocks known to fit, and known (or taken) not to
+    while (over - most > 1) {
+        const int64_t mid = most + (over - most) / 2;
+        (fits(mid) ? most : over) = mid;
+    }
+    if (most == 0) return 0;
+    const int64_t batches = (all + most - 1) / most;
+    fits((all + batches - 1) / batches);
+    return p.m_pad;
+}
+
 // Optional instrumentation: event pairs around the main pair kernel of each call.
 constexpr int kProfileSlots = 256;
 struct Profile {
@@ -795,29 +824,14 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     return true;
 }
 
-// Shared body of sdkde_score and of the first half of sdkde_fit_eval.  samples_sd_out (optional, only at
-// the samples themselves): also writes samples + (h^2/2) score from the same epilogue.
-int score_impl(const float* samples, int64_t n, const float* points, int64_t m, int32_t d, double h,
-               float* score_out, float* samples_sd_out, void* workspace, size_t workspace_bytes, uint32_t flags,
-               void* stream, const FusedPrep* fused = nullptr)
+// One pass of a score call over the samples at m points (null: at the samples themselves, m = n).  samples_ready: they
+// stand prepared in the workspace, by an earlier pass of the same call.
+int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n, const float* points, int64_t m, bool samples_ready,
+               double h, float* score_out, float* samples_sd_out, uint32_t flags, hipStream_t st, const FusedPrep* fused)
 {
-    int rc = check_common(samples, n, m, d, h, flags);
-    if (rc != SDKDE_OK) return rc;
-    const bool self = points == nullptr || (points == samples && m == n);
-    if (points == nullptr && m != n) return SDKDE_EINVAL;
-    if (m == 0) return SDKDE_OK;
-    if (!score_out && !samples_sd_out) return SDKDE_EINVAL;
-    if (samples_sd_out && !self) return SDKDE_EINVAL;
-    if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
-    if (flags & SDKDE_FLAG_SAMPLES_PREPARED) return SDKDE_EUNSUPPORTED;      // sdkde_eval / sdkde_eval_laplace only
-    flags = anchored_flags(flags, self);
-
-    Plan p = make_plan(n, m, d, true, flags);
-    apply_symmetric(p, n, flags, self);
-    Workspace w;
-    if (!fit_workspace(p, true, !self, workspace, workspace_bytes, flags, &w)) return SDKDE_EWORKSPACE;
-    hipStream_t st = (hipStream_t)stream;
-
+    int rc;
+    const int d = p.d;
+    const bool self = points == nullptr;
     const int format = operand_format(p, flags);
     const double a = operand_scale(format, h);
     // at the samples themselves the largest weight is the self pair (exponent 0): nothing to shift
@@ -825,9 +839,11 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
     const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true};
-    const PrepJob point_job{self ? nullptr : points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
-    const Stamp stamp = make_stamp(w, false, true, samples, n, d, format, (float)a);
-    if ((rc = launch_prep(p, sample_job, point_job, samples, n, (float)a, w, flags, stamp, st)) != SDKDE_OK) return rc;
+    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
+    const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
+    rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, (float)a, w, flags, stamp, st)
+                       : launch_prep(p, sample_job, point_job, samples, n, (float)a, w, flags, stamp, st);
+    if (rc != SDKDE_OK) return rc;
 
     if ((rc = profile_mark(0, 0, st)) != SDKDE_OK) return rc;
     if (shifted && (rc = launch_max_shift(p, w, flags, st)) != SDKDE_OK) return rc;
@@ -869,40 +885,61 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
-// Shared body of sdkde_eval and sdkde_eval_laplace.
-int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, int32_t d, double h,
-              float* density_out, float* log_density_out, void* workspace, size_t workspace_bytes, uint32_t flags,
-              void* stream, bool laplace, bool reuse_centre = false, bool all_prepared = false)
+// Shared body of sdkde_score and of the first half of sdkde_fit_eval.  samples_sd_out (optional, only at
+// the samples themselves): also writes samples + (h^2/2) score from the same epilogue.
+int score_impl(const float* samples, int64_t n, const float* points, int64_t m, int32_t d, double h,
+               float* score_out, float* samples_sd_out, void* workspace, size_t workspace_bytes, uint32_t flags,
+               void* stream, const FusedPrep* fused = nullptr)
 {
     int rc = check_common(samples, n, m, d, h, flags);
     if (rc != SDKDE_OK) return rc;
+    const bool self = points == nullptr || (points == samples && m == n);
+    if (points == nullptr && m != n) return SDKDE_EINVAL;
     if (m == 0) return SDKDE_OK;
-    if (!queries || (!density_out && !log_density_out)) return SDKDE_EINVAL;
+    if (!score_out && !samples_sd_out) return SDKDE_EINVAL;
+    if (samples_sd_out && !self) return SDKDE_EINVAL;
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
+    if (flags & SDKDE_FLAG_SAMPLES_PREPARED) return SDKDE_EUNSUPPORTED;      // sdkde_eval / sdkde_eval_laplace only
+    flags = anchored_flags(flags, self);
 
-    Plan p = make_plan(n, m, d, false, flags);
+    Plan p = make_plan(n, m, d, true, flags);
+    apply_symmetric(p, n, flags, self);
     Workspace w;
-    if (!fit_workspace(p, false, true, workspace, workspace_bytes, flags, &w)) return SDKDE_EWORKSPACE;
-    hipStream_t st = (hipStream_t)stream;
+    int64_t batch = m;
+    if (self ? !fit_workspace(p, true, false, workspace, workspace_bytes, flags, &w)
+             : (batch = fit_points(p, true, workspace, workspace_bytes, flags, m, &w)) == 0)
+        return SDKDE_EWORKSPACE;
+    for (int64_t first = 0; first < m; first += batch) {
+        const int64_t rows = m - first < batch ? m - first : batch;
+        if (first > 0) p.row_blocks = (rows + p.rows_per_block - 1) / p.rows_per_block;      // the last batch is shorter
+        rc = score_pass(p, w, samples, n, self ? nullptr : points + first * d, rows, first > 0, h,
+                        score_out ? score_out + first * d : nullptr, samples_sd_out, flags, (hipStream_t)stream, fused);
+        if (rc != SDKDE_OK) return rc;
+    }
+    return SDKDE_OK;
+}
 
+// One pass of an eval call over m queries.  samples_ready: the centre and the prepared samples stand in the workspace, by an
+// earlier call (SDKDE_FLAG_SAMPLES_PREPARED) or an earlier pass of this one.  Their place depends on n, d and the precision
+// mode only, not on m, and a pass whose record of them does not match gets NaN for every output.
+int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n, const float* queries, int64_t m, bool samples_ready,
+              double h, float* density_out, float* log_density_out, uint32_t flags, hipStream_t st, bool laplace,
+              bool reuse_centre, bool all_prepared)
+{
+    int rc;
+    const int d = p.d;
     const int format = operand_format(p, flags);
     const double a = operand_scale(format, h);
     const bool shifted = (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true};
     const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
-    if (all_prepared) {
-        // sdkde_fit_eval: the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
-    } else if (flags & SDKDE_FLAG_SAMPLES_PREPARED) {
-        // the workspace still holds the centre and the prepared samples (their place in the workspace depends
-        // on n, d and the precision mode only, not on m): only the queries are prepared
-        // (a call whose record of the prepared samples does not match gets NaN for every output)
-        const Stamp expect = make_stamp(w, true, false, samples, n, d, format, (float)a);
-        if ((rc = launch_prep(p, query_job, PrepJob{}, nullptr, 0, (float)a, w, flags, expect, st)) != SDKDE_OK) return rc;
-    } else {
+    // all_prepared (sdkde_fit_eval): the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
+    if (!all_prepared) {
+        const Stamp stamp = make_stamp(w, samples_ready, false, samples, n, d, format, (float)a);
         // reuse_centre: w.centre still holds the centre of an earlier pass over (nearly) the same points
-        const Stamp stamp = make_stamp(w, false, false, samples, n, d, format, (float)a);
-        if ((rc = launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, (float)a, w, flags, stamp, st)) != SDKDE_OK)
-            return rc;
+        rc = samples_ready ? launch_prep(p, query_job, PrepJob{}, nullptr, 0, (float)a, w, flags, stamp, st)
+                           : launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, (float)a, w, flags, stamp, st);
+        if (rc != SDKDE_OK) return rc;
     }
 
     const double lognorm = -log((double)n) - (double)d * log(h) - 0.5 * (double)d * log(6.283185307179586476925286766559);
@@ -916,6 +953,32 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     SDKDE_LAUNCH_EPILOGUE(eval_epilogue_kernel, p.nsplit, m, st, w.part_d, p.nsplit, m, p.m_pad, lognorm, laplace ? 1 : 0,
                           shift, least_trusted_sum(n), density_out, log_density_out);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
+}
+
+// Shared body of sdkde_eval and sdkde_eval_laplace.
+int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, int32_t d, double h,
+              float* density_out, float* log_density_out, void* workspace, size_t workspace_bytes, uint32_t flags,
+              void* stream, bool laplace, bool reuse_centre = false, bool all_prepared = false)
+{
+    int rc = check_common(samples, n, m, d, h, flags);
+    if (rc != SDKDE_OK) return rc;
+    if (m == 0) return SDKDE_OK;
+    if (!queries || (!density_out && !log_density_out)) return SDKDE_EINVAL;
+    if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
+
+    Plan p = make_plan(n, m, d, false, flags);
+    Workspace w;
+    const int64_t batch = fit_points(p, false, workspace, workspace_bytes, flags, m, &w);
+    if (batch == 0) return SDKDE_EWORKSPACE;
+    for (int64_t first = 0; first < m; first += batch) {
+        const int64_t rows = m - first < batch ? m - first : batch;
+        if (first > 0) p.row_blocks = (rows + p.rows_per_block - 1) / p.rows_per_block;      // the last batch is shorter
+        rc = eval_pass(p, w, samples, n, queries + first * d, rows, first > 0 || (flags & SDKDE_FLAG_SAMPLES_PREPARED) != 0, h,
+                       density_out ? density_out + first : nullptr, log_density_out ? log_density_out + first : nullptr,
+                       flags, (hipStream_t)stream, laplace, reuse_centre, all_prepared);
+        if (rc != SDKDE_OK) return rc;
+    }
+    return SDKDE_OK;
 }
 
 }  // namespace
@@ -1004,7 +1067,8 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     if (rc != SDKDE_OK) return rc;
     // The pass takes the decomposition the ordinary call would take, so that both give the same bits, where the built-in
     // buffer holds a workspace of sdkde_workspace_bytes.  A pass that needs more is served on the three-part operands
-    // while both of its steps fit with fewer splits, and refused before anything is launched otherwise.
+    // while both of its steps fit with fewer splits or the queries in batches, and refused before anything is launched
+    // otherwise.
     Plan score_plan = make_plan(n, n, d, true, flags), eval_plan = make_plan(n, m, d, false, flags);
     apply_symmetric(score_plan, n, flags, true);
     Workspace unused;
@@ -1012,7 +1076,7 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
     if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES && !score_plan.split3 && !eval_plan.split3) return SDKDE_ETOOLARGE;
     if (!fit_workspace(score_plan, true, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused) ||
-        (m > 0 && !fit_workspace(eval_plan, false, true, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused)))
+        (m > 0 && !fit_points(eval_plan, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, m, &unused)))
         return SDKDE_ETOOLARGE;
     void* ws = static_scratch_address();
     if (!ws) return SDKDE_EDEVICE;

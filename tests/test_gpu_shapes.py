@@ -348,6 +348,62 @@ def test_a_workspace_of_the_fp32_mode_serves_the_fp16_modes(n, m, d, flags):
     assert float((got - want).abs().max()) < 1e-4
 
 
+@pytest.mark.parametrize("n,m,d", [(4000, 3000, 16), (1000, 5003, 16), (600, 2500, 37), (300, 1700, 80)])
+def test_points_in_batches_where_four_bytes_a_value_would_fit(n, m, d, tuning):
+    """A workspace that would hold a call with 4 bytes a prepared value, but not with the 6 of the three-part operands,
+    serves it with the points in batches: the same bits (one split on both sides), also when the samples stand prepared,
+    and NaN everywhere when they do not.  A byte less is refused."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, 1)
+    tuning(P.SDKDE_TUNE_EVAL_SPLITS, 1)
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=n)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h) * (1.5 if d > 16 else 1.0)
+    print(f"points in batches n={n} m={m} d={d}", flush=True)
+
+    def tight(call, flags=0):
+        p = P.sdkde_describe_plan(n, m, d, call, flags)
+        assert p["splits"] == 1
+        copies = 2 if call == 1 else 1                  # of the samples
+        return p["workspace_bytes"] - 2 * p["dp"] * (copies * p["n_pad"] + p["m_pad"])
+
+    def buffer(bytes_):
+        return torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+
+    ws = buffer(tight(2))
+    for flags in (0, P.SDKDE_FLAG_MAX_SHIFT):
+        for got, want in zip(P.sdkde_eval(xd, qd, h, want="both", workspace=ws, flags=flags), P.sdkde_eval(xd, qd, h, want="both", flags=flags)):
+            assert torch.equal(got, want)
+        want = P.sdkde_eval_laplace(xd, qd, h, flags=flags)
+        assert torch.equal(P.sdkde_eval_laplace(xd, qd, h, workspace=ws, flags=flags), want)
+        prepared = flags | P.SDKDE_FLAG_SAMPLES_PREPARED
+        assert torch.equal(P.sdkde_eval_laplace(xd, qd, h, workspace=ws, flags=prepared), want)
+        assert torch.isnan(P.sdkde_eval_laplace(xd, qd, 1.25 * h, workspace=ws, flags=prepared)).all()
+        score_ws = buffer(tight(1))
+        want = P.sdkde_score(xd, h, points=qd, flags=flags)
+        assert torch.equal(P.sdkde_score(xd, h, points=qd, workspace=score_ws, flags=flags), want)
+    with pytest.raises(P.SdkdeError) as e:
+        P.sdkde_eval(xd, qd, h, want="log", workspace=buffer(tight(2) - 256))
+    assert e.value.status == 3
+
+
+def test_static_scratch_serves_many_queries_in_batches(tuning):
+    """The static entry's buffer holds 700000 queries of d = 4 with 4 bytes a prepared value, not with 6."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    tuning(P.SDKDE_TUNE_EVAL_SPLITS, 1)
+    n, m, d = 500, 700000, 4
+    print(f"static scratch in batches n={n} m={m} d={d}", flush=True)
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=n)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h)
+    x_sd, logd = torch.empty_like(xd), torch.empty(m, device="cuda")
+    P.sdkde_fit_eval_static(xd, qd, h, x_sd, log_density_out=logd)
+    want_sd, _, want = P.sdkde_fit_eval(xd, qd, h, want="log")
+    assert torch.equal(x_sd, want_sd) and torch.equal(logd, want)
+
+
 def test_sweep_module_times_the_papers_shapes():
     """paper_2602_10378_amd.sweep (runtime and utilisation in the shapes of the paper's sweeps, n_test = n_train / 8):
     one small shape per dimension; times are positive, the whole SD-KDE pass costs more than the KDE alone, and no
