@@ -245,8 +245,8 @@ int sdkde_eval_laplace(const float *samples, int64_t n, const float *queries, in
  *   [18] partial slots       [19] size factor of the transposed copy (2 in the FP16X2_ALL mode)
  * and, when out_len >= 24: [20] symmetric mode in effect   [21] rows per sample block   [22] blocks per group
  *   [23] groups (work items = groups (groups + 1) / 2)
- * and, when out_len >= 25: [24] matrix instructions of the first contraction spent on the last 16-column block
- *   (4 = all; fewer when the block holds at most 12 real coordinates: fp32 inputs, d <= 32)
+ * and, when out_len >= 25: [24] quarters of the last 16-column block that the first contraction works on: 4, the whole
+ *   block however few real coordinates it holds
  * and, when out_len >= 26: [25] call 2 only: 1 if sdkde_fit_eval at these sizes and flags, with a workspace of
  *   sdkde_workspace_bytes, prepares the eval pass's operands inside its score epilogue (five launches instead
  *   of six), else 0

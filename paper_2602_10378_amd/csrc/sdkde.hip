@@ -99,7 +99,6 @@ struct Plan {
     int ntiles;           // 16-sample tiles
     int nsplit, tiles_per_split;
     int64_t row_blocks;
-    int klast;            // MFMAs of the last 16-column block that contract real coordinates: ceil((d - (dp - 16)) / 4)
     // symmetric mode of the score at the samples themselves (pair_sym_kernel), off unless sym_on
     bool sym_on;
     int sym_ni, sym_rb, sym_per_group, sym_nblocks, sym_ngroups;
@@ -230,7 +229,6 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
     // 3.7 / 2.8 ms, d = 5 4.2 / 3.7, d = 6 4.7 / 3.7.
     p.thin = d <= (score ? kThinMaxDScore : kThinMaxDEval);
     p.dp = p.thin ? d : (int)round_up(d, 16);
-    p.klast = p.thin ? 4 : (d - (p.dp - 16) + 3) / 4;
     p.n_pad = round_up(n, kRowPad);
     p.m_pad = round_up(m > 0 ? m : 1, kRowPad);
     p.ntiles = (int)((n + 2 * kTile - 1) / (2 * kTile)) * 2;   // even: the pair kernel alternates two operand sets
@@ -1137,8 +1135,7 @@ int sdkde_describe_plan(int64_t n, int64_t m, int32_t d, int32_t call, uint32_t 
         out[22] = p.sym_on ? p.sym_per_group : 0;
         out[23] = p.sym_on ? p.sym_ngroups : 0;
     }
-    if (out_len >= 25)
-        out[24] = !p.thin && p.dp <= 32 && effective_prec(flags, p.thin, p.dp) == SDKDE_PREC_FP32 ? p.klast : 4;
+    if (out_len >= 25) out[24] = 4;
     if (out_len >= 26) {
         out[25] = 0;
         size_t need = 0;
