@@ -1,7 +1,7 @@
 """The fp32 mode's pair kernel (three bf16 parts per operand) in every workgroup shape it is built in, at its edges: one
 and several 16-column blocks, even and odd block counts, a nearly empty and a full last block, a ragged last chunk of
-samples, fewer chunks than splits, and own chunks split over workgroups.  Held to what fp32 arithmetic costs, not only to
-the general tolerance."""
+samples, fewer chunks than splits, own chunks split over workgroups, splits long enough to fold their running sums, and
+weights whose lower parts leave the bf16 range.  Held to what fp32 arithmetic costs, not only to the general tolerance."""
 import numpy as np
 import pytest
 
@@ -62,6 +62,60 @@ def test_every_workgroup_shape(tuning, n, d, row_tiles):
                              np.exp(ref))
     if ran == 0:
         pytest.skip("not built")
+
+
+@pytest.mark.parametrize("d,row_tiles", [(16, 8), (32, 4), (64, 4), (64, 2), (80, 4), (80, 2), (90, 4), (96, 4), (96, 2), (112, 2),
+                                         (128, 2)])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_splits_that_fold_their_running_sums(tuning, d, row_tiles, splits):
+    """A split of more than 64 sample tiles folds its running sums, at dp <= 64 into LDS, above into its own rows of the
+    partial slot (stored first, then read and added to, and read once more at the end): several folds and a ragged
+    remainder, at the samples and at separate points, one and two slots."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 4517, 130
+    x, q, _ = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=d)
+    h = 0.5 * d**0.5        # every sample of a component weighs about exp(-4): no fold is small beside the others
+    tuning(P.SDKDE_TUNE_SCORE_ROW_TILES, row_tiles)
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, splits)
+    print(f"folds n={n} m={m} d={d} row tiles {row_tiles} splits {splits}", flush=True)
+    for call in (0, 1):
+        p = P.sdkde_describe_plan(n, m, d, call)
+        assert p["row_tiles"] == row_tiles and p["splits"] == splits and p["tiles_per_split"] >= 128
+        assert p["tiles_per_split"] % 64 != 0
+    xd, qd = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    s = P.sdkde_score(xd, h).cpu().numpy()
+    err = np.linalg.norm(s - oracle.score(x, h), axis=1)
+    assert np.all(err <= _score_bound(x, x, h)), (err / _score_bound(x, x, h)).max()
+    s = P.sdkde_score(xd, h, points=qd, flags=P.SDKDE_FLAG_MAX_SHIFT).cpu().numpy()
+    err = np.linalg.norm(s - oracle.score(x, h, points=q), axis=1)
+    assert np.all(err <= _score_bound(x, q, h)), (err / _score_bound(x, q, h)).max()
+
+
+@pytest.mark.parametrize("d", [7, 16, 40])
+@pytest.mark.parametrize("binades", [109, 112, 115])
+def test_weights_whose_lower_parts_leave_the_bf16_range(d, binades):
+    """Points about sqrt(2 binades ln 2) bandwidths from a tight cloud: weights about 2^-binades, whose second and third
+    parts lie near or below 2^-126, in T but not in D.  A part cut there is less than 2^-126 of each sample's weight, so
+    beside the bound that the exponents give, T / D may be off by n 2^-126 (max_j |x_j - c| + |p - c|) / D per part."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, h = 1000, 64, 1.0
+    rng = np.random.default_rng(binades + d)
+    x = (0.05 * rng.standard_normal((n, d))).astype(np.float32)
+    q = rng.standard_normal((m, d))
+    q = (q / np.linalg.norm(q, axis=1, keepdims=True) * np.sqrt(2.0 * binades * np.log(2.0)) * h).astype(np.float32)
+    print(f"weights about 2^-{binades}, d={d}", flush=True)
+    s = P.sdkde_score(torch.from_numpy(x).cuda(), h, points=torch.from_numpy(q).cuda()).cpu().numpy().astype(np.float64)
+    x64, q64 = x.astype(np.float64), q.astype(np.float64)
+    weight_sum = np.exp(-((q64[:, None, :] - x64[None]) ** 2).sum(-1) / (2.0 * h * h)).sum(1)
+    live = weight_sum > 1.01 * 1000.0 * n * 2.0**-126          # below: reported as underflow
+    assert live.all() and weight_sum.max() < n * 2.0 ** (-binades + 12)
+    cut = 2.0 * n * 2.0**-126 * (np.linalg.norm(x64, axis=1).max() + np.linalg.norm(q64, axis=1)) / weight_sum / (h * h)
+    err = np.linalg.norm(s - oracle.score(x, h, points=q), axis=1)
+    assert np.all(err <= _score_bound(x, q, h) + cut), (err / (_score_bound(x, q, h) + cut)).max()
 
 
 @pytest.mark.parametrize("d", [7, 16, 24, 37])

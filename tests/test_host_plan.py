@@ -34,12 +34,15 @@ def _check(n, m, d, call, flags):
         assert p["rows_per_block"] % (16 * p["row_tiles"]) == 0      # own-tile spans are aligned to row tiles
     # workspace: blocks are 256-byte aligned, disjoint, and inside workspace_bytes
     score = call != 2
-    blocks = [("xs", p["off_xs"], 4 * p["n_pad"] * p["dp"]), ("xn", p["off_xn"], 4 * p["n_pad"]),
+    # a prepared value: three bf16 parts in the fp32 mode's matrix path, four bytes otherwise (the transpose of the
+    # FP16X2_ALL mode twice that)
+    value = 6 if not thin and (flags & 15) == 0 else 4
+    blocks = [("xs", p["off_xs"], value * p["n_pad"] * p["dp"]), ("xn", p["off_xn"], 4 * p["n_pad"]),
               ("part_d", p["off_part_d"], 4 * p["partial_slots"] * p["m_pad"])]
     if p["off_xt"] >= 0:
-        blocks.append(("xt", p["off_xt"], 4 * p["xt_scale"] * p["n_pad"] * p["dp"]))
+        blocks.append(("xt", p["off_xt"], value * p["xt_scale"] * p["n_pad"] * p["dp"]))
     if call != 0:
-        blocks += [("ps", p["off_ps"], 4 * p["m_pad"] * p["dp"]), ("pn", p["off_pn"], 4 * p["m_pad"])]
+        blocks += [("ps", p["off_ps"], value * p["m_pad"] * p["dp"]), ("pn", p["off_pn"], 4 * p["m_pad"])]
     if score:
         blocks.append(("part_t", p["off_part_t"], 4 * p["partial_slots"] * p["m_pad"] * p["dp"]))
         assert (p["off_xt"] >= 0) == (not thin)
@@ -68,7 +71,7 @@ def _check_symmetric(p, n, d, call, flags):
         assert p["sym_block_rows"] == p["sym_blocks_per_group"] == p["sym_groups"] == 0
         return
     rb, per_group, groups = p["sym_block_rows"], p["sym_blocks_per_group"], p["sym_groups"]
-    rows_held = 8 * 16 * (8 if p["dp"] == 16 else 4)        # rows a workgroup of the symmetric kernel holds
+    rows_held = 8 * 16 * (4 if p["dp"] == 16 else 2)        # rows a workgroup of the symmetric kernel holds
     assert rb & (rb - 1) == 0 and rb % rows_held == 0 and rb % 256 == 0
     assert p["n_pad"] % rb == 0 and p["n_pad"] - n < max(rb, 1024)
     blocks = p["n_pad"] // rb
@@ -76,7 +79,8 @@ def _check_symmetric(p, n, d, call, flags):
     assert groups * per_group >= blocks > (groups - 1) * per_group
     assert p["partial_slots"] == groups + 2      # one per group, one more, and the in-block pass
     assert groups * (groups + 1) // 2 >= 512
-    assert 4 * ((p["dp"] // 16) * rb * 16 + rb + 8 * 16 * 20) <= 160 * 1024
+    # the block's accumulators and the eight waves' transpose buffers (two row tiles of three 512-byte parts each)
+    assert 4 * ((p["dp"] // 16) * rb * 16 + rb) + 8 * 2 * 3 * 512 <= 160 * 1024
 
 
 @settings(max_examples=300, deadline=None)
