@@ -35,7 +35,9 @@ namespace {
 // ------------------------------------------------------------------------------------------
 
 // Row-tile operands of one wave: -|p~|^2/2 and the parts of p~ as the lane's 16 bytes of each B operand.
-template <int KB, int NI>
+// FOUR (KB = 1, d <= 4): the six part products of four columns fill 24 of the 32 of one operand, four columns each:
+// [h h | m m | h l | -] against [h m | h m | l h | 0].
+template <int KB, int NI, bool FOUR = false>
 struct SplitRows {
     static constexpr int PAIRS = KB / 2;        // 32-column blocks
     static constexpr bool ODD = KB % 2 != 0;    // and a 16-column one
@@ -53,7 +55,14 @@ struct SplitRows {
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     b[t][p][q] = *reinterpret_cast<const bf16x8*>(tile + p * 3072 + q * kPartBytes + (16 * g + r) * 16);
-            if (ODD) {
+            if (FOUR) {
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                const char* base = tile + r * 16;
+                const u32x2 lo = *reinterpret_cast<const u32x2*>(base + (g == 2 ? 1024 : 0));
+                const u32x2 hi = *reinterpret_cast<const u32x2*>(base + (g < 2 ? 512 : 0));
+                const u32x4 both = g == 3 ? u32x4{0, 0, 0, 0} : u32x4{lo.x, lo.y, hi.x, hi.y};
+                o[t][0] = __builtin_bit_cast(bf16x8, both);
+            } else if (ODD) {
                 const char* base = tile + PAIRS * 3072 + (16 * (g & 1) + r) * 16;
                 o[t][0] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 0 : 512));
                 o[t][1] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 1024 : 0));
@@ -69,8 +78,8 @@ struct SplitRows {
 constexpr bool split_sums_in_lds(int kb) { return kb <= 4; }
 
 // NB: row tiles whose Gram accumulators and split weights are live at a time.  AHEAD: operands are read from LDS a whole
-// group of MFMAs before their use.
-template <int KB, int NI, int WAVES, int NB, bool AHEAD, int MINW, int KIND>
+// group of MFMAs before their use.  FOUR: see SplitRows.
+template <int KB, int NI, int WAVES, int NB, bool AHEAD, int MINW, int KIND, bool FOUR = false>
 __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs,
     const float* __restrict__ xt, const float* __restrict__ xn, float* __restrict__ part_t,
@@ -78,6 +87,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const float* __restrict__ shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
+    static_assert(!FOUR || (KB == 1 && !AHEAD), "four columns: one operand, read where it is used");
     constexpr bool BAND = KIND == kScoreBand;
     constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints || BAND;
     constexpr bool SELF = KIND == kScoreSelf || BAND;
@@ -101,7 +111,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const int64_t row_block = blockIdx.x / nsplit;
     const int64_t row0 = (row_block * WAVES + wave) * (NI * kTile);
 
-    SplitRows<KB, NI> rows;
+    SplitRows<KB, NI, FOUR> rows;
     rows.load(ps, pn, row0, r, g);
 
     // Two-level accumulation: the running sums (tacc, dacc) are folded into a second level every kFlushTiles sample
@@ -140,6 +150,12 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
                 if (p < PAIRS) {
 #pragma unroll
                     for (int q = 0; q < parts; ++q) a[u][q] = *reinterpret_cast<const bf16x8*>(base + q * kPartBytes + lane * 16);
+                } else if (FOUR) {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    const char* row = base + r * 16;
+                    const u32x2 lo = *reinterpret_cast<const u32x2*>(row + (g == 1 ? 512 : 0));
+                    const u32x2 hi = *reinterpret_cast<const u32x2*>(row + (g == 1 ? 512 : g == 2 ? 1024 : 0));
+                    a[u][0] = __builtin_bit_cast(bf16x8, (u32x4){lo.x, lo.y, hi.x, hi.y});
                 } else {                            // [h | h], [m | m], [h | l]
                     const char* half = base + (16 * (g & 1) + r) * 16;
                     a[u][0] = *reinterpret_cast<const bf16x8*>(half);
@@ -185,7 +201,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
                 } else {
                     // [h | h] [h | m], [m | m] [h | m], [h | l] [l | h]
 #pragma unroll
-                    for (int k = 0; k < 3; ++k)
+                    for (int k = 0; k < (FOUR ? 1 : 3); ++k)
 #pragma unroll
                         for (int t = 0; t < NB; ++t)
 #pragma unroll

@@ -64,6 +64,32 @@ def test_every_workgroup_shape(tuning, n, d, row_tiles):
         pytest.skip("not built")
 
 
+@pytest.mark.parametrize("d", [4, 5])
+@pytest.mark.parametrize("row_tiles", [2, 4, 8])
+@pytest.mark.parametrize("n", [40, 1111, 4500])
+def test_row_maxima_of_four_columns(tuning, n, d, row_tiles):
+    """The shifted sums' first pass holds all part products of up to four columns in one matrix instruction (d = 5: the
+    general form), in every workgroup shape, for queries among the samples and up to 300 bandwidths away."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    m = 70
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=n + d)
+    h = float(h)
+    q[m // 2:] *= np.geomspace(1.0, 100.0, m - m // 2, dtype=np.float32)[:, None]
+    tuning(P.SDKDE_TUNE_EVAL_ROW_TILES, row_tiles)
+    assert P.sdkde_describe_plan(n, m, d, 2)["row_tiles"] == row_tiles
+    print(f"row maxima n={n} m={m} d={d} row tiles {row_tiles}", flush=True)
+    xd, qd = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    ref = oracle.eval_log_density(x, q, h)
+    e = gram_exponent_error(x, q, h)
+    logd = P.sdkde_eval(xd, qd, h, want="log", flags=P.SDKDE_FLAG_MAX_SHIFT)[1].cpu().numpy()
+    assert np.all(np.abs(logd - ref) <= e + 2.0**-18 + 2.0**-23 * np.abs(ref)), np.abs(logd - ref).max()
+    lap = P.sdkde_eval_laplace(xd, qd, h, flags=P.SDKDE_FLAG_MAX_SHIFT).cpu().numpy()
+    assert_laplace_close(lap, oracle.eval_laplace_density(x, q, h), oracle.eval_laplace_abs_density(x, q, h), "laplace", e,
+                         np.exp(ref))
+
+
 @pytest.mark.parametrize("d,row_tiles", [(16, 8), (32, 4), (64, 4), (64, 2), (80, 4), (80, 2), (90, 4), (96, 4), (96, 2), (112, 2),
                                          (128, 2)])
 @pytest.mark.parametrize("splits", [1, 2])
