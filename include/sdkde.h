@@ -29,7 +29,8 @@
  *    that small against 1/h (a sample whose only neighbours are its exact duplicates, a bandwidth so narrow that
  *    every neighbour's weight vanishes).  (Far outside that domain, R/h above ~1e18, the scaled
  *    coordinates overflow fp32 on either path and the outputs are NaN.  A sample with an infinite
- *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
+ *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path; its term
+ *    of the Laplace estimate is NaN.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
  *    is kept, and weights below the smallest normal fp32 number (2^-126) are flushed to zero: a point whose
  *    weights phi_j sum to less than 1000 n 2^-126 (so that the flushed ones could be more than one part in a
  *    thousand of the sum; the point is then farther than about 11.5 - 13 h from every sample, depending on n)
@@ -73,8 +74,10 @@ enum {
     SDKDE_MAX_D = 128,
     /* flags: precision mode of the distance cross term (the Gram-matrix tile of the Method section) */
     SDKDE_PREC_FP32 = 0,    /* fp32 inputs, fp32 accumulate: the reference path.  On the matrix path every fp32 operand
-                               (coordinates and weights) is held exactly, as the sum of three bf16 parts, and a product is
-                               summed over its six part products that reach 2^-24 of it (the symmetric mode: fp32 MFMA) */
+                               (coordinates and weights) is held exactly, as the sum of three bf16 parts (weights down to
+                               about 2^-110 of a weight of one), and a product is summed over the six largest of its nine
+                               part products: the rest is at most 2^-24 of it in the cross term, 1.5 2^-23 in Phi X.  So
+                               in the symmetric mode. */
     SDKDE_PREC_FP16X2 = 1,  /* each input split into two fp16 halves (hi + lo, ~22 mantissa bits) and
                                multiplied on the fp16 matrix units with fp32 accumulate; Phi X, exp and all
                                sums stay fp32.  A lower-precision-input mode: its error is reported
@@ -115,7 +118,8 @@ enum {
        up to 64 groups of sample blocks: about 4.6 GiB at n = 2^20, d = 16).  Takes effect for sdkde_score at the
        samples themselves and sdkde_fit_eval with 7 <= d <= 32, SDKDE_PREC_FP32 and enough samples to fill the chip with
        its work items (n >= 32768 at d <= 16, n >= 16384 at d <= 32); ignored otherwise (sdkde_describe_plan tells).
-       It is ahead of the ordinary kernels only at d <= 16 and n >= ~100000, by 2 %. */
+       It is ahead of the ordinary kernels only at d <= 16 and n >= ~131072, by 2 - 6 %; below that it takes 2 - 11 %
+       longer, at d > 16 7 - 36 %. */
     SDKDE_FLAG_SYMMETRIC = 32,
     /* flags bit 6, sdkde_eval and sdkde_eval_laplace only (evaluating one fitted estimate at many batches of
        queries): the workspace still holds what the previous sdkde_eval / sdkde_eval_laplace call on it prepared

@@ -14,10 +14,12 @@ namespace {
 // thousands of slots and few outputs), and are combined through LDS in the fixed order part 0, 1, ..., PARTS - 1.
 // The host picks PARTS from the slot and output counts alone (epilogue_parts), so a plan always sums in the same
 // order: the many-thread form only where the outputs are too few to fill the chip otherwise, since its loads are
-// narrow (kBlock / PARTS consecutive floats per slot).
+// narrow (kBlock / PARTS consecutive floats per slot).  32 / 4 threads: 1024 outputs of 1024 slots 5.3 / 22.6 us, 4000 of
+// 512 7.1 / 10.8, 8000 of 128 4.8 / 4.6, 16000 of 256 11.9 / 6.8, 18000 of 512 36.7 / 22.9, 40000 of 256 26.0 / 8.0,
+// 60033 of 64 18.2 / 5.8.  (Between 8000 and the line below, the four-thread form would be 0.2 to 5 us ahead.)
 constexpr int kEpiPartsFew = 4, kEpiPartsMany = 32;
 constexpr int kEpiManySlots = 64;                   // least slot count and
-constexpr int64_t kEpiFewOutputs = 16384;           // most outputs for kEpiPartsMany (64 slots of 60033 outputs: 18.2 us in that form, 5.8 with four)
+constexpr int64_t kEpiFewOutputs = 16384;           // most outputs for kEpiPartsMany
 inline int epilogue_parts(int nslots, int64_t outputs)
 {
     return nslots >= kEpiManySlots && outputs <= kEpiFewOutputs ? kEpiPartsMany : kEpiPartsFew;

@@ -20,7 +20,7 @@ namespace {
 // sum of both: per 256 pairs 3 KB MFMAs for each contraction, 4 v_exp_f32 at 8 clocks, 24 + 2 KB (eval: 8) adds, subtracts
 // and ands at about 2.4 and (score) 6 v_perm_b32 at 4.6.  That sum is 218 clocks for the score at dp = 16 (fp32 MFMA kernel
 // before: 333) and 52 + 48 KB for eval; measured figures at the dispatch (split_shape in sdkde.hip).  Two waves per SIMD are needed (one wave:
-// 1245 clocks against 933 at dp = 96) and more do not help; NI row tiles share every operand read from LDS.
+// 1238 clocks against 983 at dp = 96) and more do not help; NI row tiles share every operand read from LDS.
 //
 // SELF (score at the samples themselves): the pair (i, i) must stay out of D and T, because T_i/D_i - x_i would
 // otherwise cancel against the large self term whenever a point has few neighbours; the epilogue restores it

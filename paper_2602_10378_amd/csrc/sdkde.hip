@@ -39,12 +39,15 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 
 // Shapes of pair_split_kernel: a workgroup of `waves` waves of `ni` row tiles each holds 16 ni waves rows; the plan counts
 // them as rt = ni waves / 4 (so that a workgroup has 64 rt rows, as in the other kernels).  nb, ahead, minw: see there.
-// ni = 0: not built.  Which shapes are built was measured at n = m = 65536 (clocks per 256 pairs and SIMD at 2.4 GHz;
-// the sum of the MFMAs at 16 clocks and the vector work alone is 218 / 318 / 419 / 520 for the score at dp = 16 .. 64):
-//   score  dp = 16   rt 8 / 4 / 2: 226 / 229 / 235        dp = 32  rt 4 / 2: 346 / 359    dp = 48  554 / 533
-//          dp = 64   640 / 660     dp = 80  811 / 840     dp = 96  1014 / 1245 (one wave per SIMD)   dp = 128  - / 1615
-//   eval   dp = 16   rt 8 / 4 / 2: 105 / 103 / 112        dp = 32  rt 4 / 2: 156 / 166    dp = 48  224 / 235
-//          dp = 64   273 / 288     dp = 96  420 / 424     dp = 128 580 / 557
+// ni = 0: not built.  Clocks per 256 pairs and SIMD at 2.4 GHz of the kernels in the library, n = m = 65536, eight splits,
+// Gaussian mixture at the rule-of-thumb bandwidth (the clock sits under the power limit, so other data gives other figures:
+// eval is up to 8 % faster on operands of random bits); the sum of the MFMAs at 16 clocks and the vector work alone is
+// 218 / 318 / 419 / 520 for the score at dp = 16 .. 64:
+//   score  dp = 16   rt 8 / 4 / 2: 242 / 236 / 247        dp = 32  rt 4 / 2: 356 / 377    dp = 48  533 / 544
+//          dp = 64   643 / 669     dp = 80  820 / 885     dp = 96  983 / 1238 (one wave per SIMD)
+//          dp = 112  - / 1388      dp = 128 - / 1550
+//   eval   dp = 16   rt 8 / 4 / 2: 111 / 114 / 128        dp = 32  rt 4 / 2: 173 / 191    dp = 48  244 / 268
+//          dp = 64   302 / 329     dp = 80  373 / 409     dp = 96  502 / 484    dp = 112  645 / 577    dp = 128  626 / 646
 // At dp >= 112 the score's operands leave room for one wave per SIMD only (two would spill).
 struct SplitShape { int ni, waves, nb; bool ahead; int minw; };
 constexpr SplitShape split_shape(int kb, bool score, int rt)
@@ -129,8 +132,9 @@ constexpr int64_t kTargetBlocks = 2048;
 constexpr int kComputeUnits = 256;
 
 // Relative cost per unit of work of running the matrix-path kernels with `ni` row tiles per wave instead of the
-// best count (operand reuse against register pressure), measured on MI355X: the fp32 mode from the figures at split_shape,
-// the fp16 input modes at n = 131072 resp. n = 262144, m = 65536.
+// best count (operand reuse against register pressure), measured on MI355X: the fp32 mode at n = m = 65536 with an earlier
+// order of the Gram products (by the present figures at split_shape the better count is another one for the score at
+// dp = 48 and eval at dp = 96 and 112, by 2, 4 and 12 %), the fp16 input modes at n = 131072 resp. n = 262144, m = 65536.
 double row_tiles_penalty(bool score, int kb, int ni, uint32_t prec)
 {
     if (prec != SDKDE_PREC_FP32) {
@@ -223,10 +227,10 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
 {
     Plan p{};
     p.d = d;
-    // Direct differences on the VALU: up to d = 6 for the score kinds, up to d = 3 for eval.  Measured at
-    // n = 262144, m = 65536, fp32, VALU form against matrix form (with the shortened last block): score d = 4
-    // 19.8 / 26.2 ms, d = 5 22.9 / 29.9, d = 6 26.9 / 30.0, d = 7 30.6 / 30.0, d = 8 33.6 / 30.0; eval d = 4
-    // 3.7 / 2.8 ms, d = 5 4.2 / 3.7, d = 6 4.7 / 3.7.
+    // Direct differences on the VALU: up to d = 6 for the score kinds, up to d = 3 for eval, because they have no
+    // Gram-expansion error.  It is not the faster form everywhere: at n = 262144, m = 65536, fp32, VALU / matrix form, score
+    // d = 4 19.7 / 23.4 ms, d = 5 22.9 / 23.5, d = 6 26.9 / 23.6; eval d = 1 2.04 / 2.80, d = 2 2.59 / 2.64, d = 3
+    // 3.22 / 2.63; at 4000 x 3000 the matrix form is ahead from d = 1 (eval 23.5 / 16.9 us, score d = 4 35.1 / 21.3).
     p.thin = d <= (score ? kThinMaxDScore : kThinMaxDEval);
     p.dp = p.thin ? d : (int)round_up(d, 16);
     p.n_pad = round_up(n, kRowPad);
@@ -274,7 +278,9 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
     if (max_split >= 8 || p.split3) {
         // Enough samples for one group of splits per XCD: the (row tiles or rows per thread, splits) pair of least
         // estimated time; ties go to more rows per workgroup, then fewer splits.  Up to n = 16384 the three-part
-        // kernels may take fewer splits too: the prepared samples then fit one XCD's L2 whole.
+        // kernels may take fewer splits too: whole rounds of workgroups then count for more than each XCD streaming an
+        // eighth of the samples.  Score with 7 / 8 / 16 splits at n = 9000: d = 16 50 / 56 / 52 us, d = 64 116 / 148 / 126,
+        // d = 128 254 / 325 / 281; with 4 / 8 / 16 at n = 16000: d = 64 310 / 297 / 311, d = 128 682 / 704 / 758.
         const int most = max_split >= 8 ? (max_split / 8 * 8 < 1024 ? max_split / 8 * 8 : 1024) : max_split;
         const int first = forced_split > 0 ? forced_split : p.split3 && p.ntiles <= 1024 ? 1 : 8;
         const int last = forced_split > 0 ? forced_split : most;
@@ -358,10 +364,13 @@ void apply_symmetric(Plan& p, int64_t n, uint32_t flags, bool self)
     const int per_group = (int)((nblocks + max_groups - 1) / max_groups);
     const int ngroups = (int)((nblocks + per_group - 1) / per_group);
     // Below 512 work items (two rounds of one per CU) the ordinary kernels are well ahead and the flag is ignored
-    // (SDKDE_TUNE_SYM_MIN_ITEMS: for tests of the mode at small sizes).  Measured, symmetric / ordinary: d = 16
-    // n = 32768 457 / 423 us, 131072 6.04 / 6.13 ms, 1048576 371 / 377 ms; d = 32 n = 100000 6.6 / 5.5 ms.  (With fp32
-    // MFMAs on both sides the mode was 1.25 times as fast; three-part operands have made the vector work it halves and
-    // the matrix work it cuts by a quarter cheaper than its transposes, folds and phase barriers.)
+    // (SDKDE_TUNE_SYM_MIN_ITEMS: for tests of the mode at small sizes).  The line is where the mode began to pay with fp32
+    // MFMAs, and callers that set the flag get the mode, its workspace and its summation order from there on; with
+    // three-part operands it pays at dp = 16 from about 131072 samples only.  Score, symmetric / ordinary: d = 16 n = 32768
+    // 455 / 425 us, 65536 1.67 / 1.61 ms, 100000 3.79 / 3.74, 131072 6.02 / 6.38, 262144 23.6 / 25.0, 1048576 373 / 398;
+    // d = 8 n = 32768 455 / 414 us, 131072 6.01 / 6.17 ms; d = 32 n = 16384 225 / 176 us, 100000 6.58 / 5.83 ms, 524288
+    // 162 / 153.  (The vector work the mode halves and the matrix work it cuts by a quarter have become cheaper than its
+    // transposes, folds and phase barriers.)
     int min_items = tuning(SDKDE_TUNE_SYM_MIN_ITEMS, 512);
     if (min_items < 1) min_items = 1;
     if ((int64_t)ngroups * (ngroups + 1) / 2 < min_items) return;

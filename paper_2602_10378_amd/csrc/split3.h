@@ -7,11 +7,14 @@ namespace {
 // ------------------------------------------------------------------------------------------
 // The fp32 path multiplies on the bf16 matrix units without giving up fp32 operands: every fp32 value v is held as
 // three bf16 parts h + m + l = v (8 significant bits each; the 24 bits of v exactly, at any magnitude whose last bit
-// is a normal bf16 number), and a product a b is summed over the six part products that reach 2^-24 of it,
+// is a normal bf16 number), and a product a b is summed over six of its nine part products,
 //     ah bh + ah bm + am bh + am bm + ah bl + al bh,
-// each exact in the fp32 accumulator's own format.  The three left out (am bl, al bm, al bl) are at most 2^-23 of
-// |a b| together and of either sign, the size of one fp32 rounding.  Six bf16 MFMAs per fp32 product still leave 2.6
-// times the fp32 MFMA rate.
+// each exact in the fp32 accumulator's own format.  The three left out (am bl, al bm, al bl) are of either sign and
+// together at most 2^-24 of |a b| where both operands are split to nearest (the Gram tile: |m| <= 2^-8, |l| <= 2^-17 of
+// the value's power of two), the size of one fp32 rounding, and at most 1.5 2^-23 where one is truncated (the weights in
+// Phi X: m < 2^-7, l < 2^-15).  Weights below about 2^-110 lose their last bits, since a bf16 part has none below 2^-133:
+// less than 2^-126 of each, what the exp already flushes.  Six bf16 MFMAs per fp32 product still leave 2.6 times the
+// fp32 MFMA rate.
 //
 // Prepared rows ("xs" / "ps"), in chunks of kChunkRows = 32 rows of KB * 3072 bytes (KB = dp / 16), two 16-row tiles of
 // KB * 1536 bytes each:
