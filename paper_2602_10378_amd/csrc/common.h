@@ -32,7 +32,8 @@ enum PairKind {
     kEval = 2,          // D only (Gaussian KDE)
     kEvalLaplace = 3,   // sum of phi * (1 + d/2 - r^2/2h^2) (Laplace-corrected KDE; signed)
     kRowMax = 4,        // max_j of the exponent (first pass of the max-shifted mode); kept in the D slot
-    kScoreBand = 5      // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
+    kScoreBand = 5,     // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
+    kRowMaxFour = 6     // kRowMax of pair_split_kernel at d <= 4
 };
 // How the prepared rows of the matrix path are held: SDKDE_PREC_FP16X2 .. SDKDE_PREC_FP16X2_PHI16 as the layouts of those
 // modes' kernels, or three bf16 parts (split3.h), the fp32 mode.

@@ -78,8 +78,8 @@ struct SplitRows {
 constexpr bool split_sums_in_lds(int kb) { return kb <= 4; }
 
 // NB: row tiles whose Gram accumulators and split weights are live at a time.  AHEAD: operands are read from LDS a whole
-// group of MFMAs before their use.  FOUR: see SplitRows.
-template <int KB, int NI, int WAVES, int NB, bool AHEAD, int MINW, int KIND, bool FOUR = false>
+// group of MFMAs before their use.
+template <int KB, int NI, int WAVES, int NB, bool AHEAD, int MINW, int KIND>
 __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs,
     const float* __restrict__ xt, const float* __restrict__ xn, float* __restrict__ part_t,
@@ -87,12 +87,13 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     const float* __restrict__ shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
-    static_assert(!FOUR || (KB == 1 && !AHEAD), "four columns: one operand, read where it is used");
     constexpr bool BAND = KIND == kScoreBand;
     constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints || BAND;
     constexpr bool SELF = KIND == kScoreSelf || BAND;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
-    constexpr bool ROWMAX = KIND == kRowMax;
+    constexpr bool FOUR = KIND == kRowMaxFour;                   // see SplitRows
+    constexpr bool ROWMAX = KIND == kRowMax || FOUR;
+    static_assert(!FOUR || (KB == 1 && !AHEAD), "four columns: one operand, read where it is used");
     constexpr int DP = KB * 16;
     constexpr int KT = SCORE ? KB : 1;
     constexpr int PAIRS = KB / 2;

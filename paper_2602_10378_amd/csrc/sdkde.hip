@@ -554,16 +554,10 @@ int launch_split_shape(const Plan& p, const Workspace& w, const float* shift, hi
         return SDKDE_EUNSUPPORTED;
     } else {
         static_assert(sh.ni * sh.waves == 4 * RT, "64 rt rows per workgroup");
-        if constexpr (KIND == kRowMax && KB == 1) {
-            // One MFMA a sample tile where the general form takes three and one fp32 MFMA took 32 clocks: shifted eval of
-            // 262144 x 65536 at d = 4 3.94 ms, with three 4.74, with the fp32 one 4.44; 65536 x 8192 161, 187 and 180 us.
-            if (p.d <= 4) {
-                hipLaunchKernelGGL((pair_split_kernel<KB, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND, true>),
-                                   dim3((unsigned)(p.row_blocks * p.nsplit)), dim3(sh.waves * kWave), 0, st, w.ps, w.pn, w.xs,
-                                   w.xt, w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad, 0.0f, shift);
-                return launched();
-            }
-        }
+        // One MFMA a sample tile where the general form takes three and one fp32 MFMA took 32 clocks: shifted eval of
+        // 262144 x 65536 at d = 4 3.94 ms, with three 4.74, with the fp32 one 4.44; 65536 x 8192 161, 187 and 180 us.
+        if constexpr (KIND == kRowMax && KB == 1)
+            if (p.d <= 4) return launch_split_shape<kRowMaxFour, KB, RT>(p, w, shift, st);
         hipLaunchKernelGGL((pair_split_kernel<KB, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND>),
                            dim3((unsigned)(p.row_blocks * p.nsplit)), dim3(sh.waves * kWave), 0, st, w.ps, w.pn, w.xs, w.xt,
                            w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,
