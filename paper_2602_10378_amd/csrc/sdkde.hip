@@ -432,7 +432,7 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
 bool bad_bandwidth(double h) { return !(h > 0.0) || !isfinite(h); }
 
 // One group of splits per XCD, or a single split for tiny sample sets and on the matrix path: there a buffer may have been
-// made for a plan with fewer splits (the fp32 mode takes four at 13000 samples of d = 16) and is used in another mode, and
+// made for a plan with fewer splits (the fp32 mode takes five at 13000 samples of d = 16) and is used in another mode, and
 // the three-part copies are half as large again, so that calls may have to give up more slots for them.
 inline int least_splits(const Plan& p) { return p.ntiles >= 128 && p.thin ? 8 : 1; }
 
