@@ -49,7 +49,7 @@ def traffic_from_profile(config, plan, launch_ms=None):
     rec = json.loads(m.group(1))
     n_pad, m_pad, dp, slots = plan["n_pad"], plan["m_pad"], plan["dp"], plan["partial_slots"]
     xt = plan["xt_scale"] * n_pad * dp if plan["off_xt"] >= 0 else 0
-    operand_bytes = 4.0 if plan["thin"] else 6.0              # fp32 coordinates, or three bf16 parts of each
+    operand_bytes = 4.0 if plan["thin"] else 6.0              # fp32 coordinates, or their parts
     algorithmic = operand_bytes * (n_pad * dp + xt) + 4.0 * n_pad + 4.0 * slots * m_pad * ((dp + 1) if plan["off_part_t"] >= 0 else 1)
     detail = {"source": os.path.relpath(files[0], ROOT), "kernel": rec["kernel"], "read_bytes": rec["read_bytes"],
               "written_bytes": rec["written_bytes"], "algorithmic_bytes_of_the_launch": algorithmic,
@@ -165,10 +165,10 @@ class Workload:
         P, n, m, d = self.P, self.n, self.m, self.d
         flags = MODE_FLAGS[mode]
         plan_s, plan_e = P.sdkde_describe_plan(n, n, d, 0, flags), P.sdkde_describe_plan(n, m, d, 2, flags)
-        # the fp32 mode's matrix path multiplies three bf16 parts per operand
-        eff = {"fp32": "bf16x3", "symmetric": "symmetric_bf16x3"}.get(mode, mode)
+        # the fp32 mode's matrix path multiplies two fp16 parts per operand, its symmetric mode three bf16 parts
+        eff = {"fp32": "half2", "symmetric": "symmetric_bf16x3"}.get(mode, mode)
         if mode == "symmetric" and not plan_s["symmetric"]:
-            eff = "bf16x3"
+            eff = "half2"
         if mode == "fp16x2_all" and plan_s["xt_scale"] != 2:
             eff = "fp16x2"
         if mode == "fp16x2_phi16" and plan_s["dp"] != 16:
@@ -177,11 +177,11 @@ class Workload:
         for key, stage, ms, plan, pairs in (("roofline", "score", score_ms, plan_s, float(n) * n),
                                             ("roofline_eval_kernel", "eval", eval_ms, plan_e, float(m) * n)):
             thin = bool(plan["thin"])
-            stage_eff = "bf16x3" if (stage == "eval" and eff == "symmetric_bf16x3") else eff
+            stage_eff = "half2" if (stage == "eval" and eff == "symmetric_bf16x3") else eff
             r = cm.roofline(stage, d, pairs, ms * 1e-3, stage_eff, thin)
             r["launch_ms"] = ms
             r["kernel"] = ("pair_thin_kernel" if thin else "pair_sym_kernel + in-block pass" if stage_eff == "symmetric_bf16x3"
-                           else "pair_split_kernel" if stage_eff == "bf16x3" else "pair_mfma_kernel") + f" ({stage})"
+                           else "pair_half_kernel" if stage_eff == "half2" else "pair_mfma_kernel") + f" ({stage})"
             r["ceiling"] = self.mix_ceiling(stage, stage_eff, thin, ms, pairs, max(r["seconds_at_peak"].values()))
             out[key] = r
         return out, plan_s
@@ -201,12 +201,13 @@ class Workload:
             out["mix_clk_per_256_pairs"] = 4 * (8.1 + 3.05 * plain)
             out["basis"] = ("per pair and lane one v_exp_f32 (8.1 clk per wave instruction, overlaps nothing) and the plain "
                             "instructions at the 3.05 clk measured next to exps (2 at the published rate)")
-        elif mode == "bf16x3":
+        elif mode == "half2":
             score = stage == "score"
-            out["mix_clk_per_256_pairs"] = (16.0 * (6 if score else 3) * blocks + 4 * 8.1 + 2.4 * (24 + 2 * blocks if score else 8)
-                                            + 4.6 * (6 if score else 0))
-            out["basis"] = ("per 16x16 tile: the bf16 MFMAs at 16 clk each (about 21 under the power limit), 4 v_exp_f32 (8.1 clk), plain "
-                            "instructions at 2.4 and v_perm_b32 at 4.6, added up: they overlap by little")
+            mfmas = 3 * (blocks // 2) + (blocks % 2 and (1 if (d - 1) % 16 < 8 else 2)) + (1.5 * blocks if score else 0)
+            plain = (4 if blocks % 2 else 8) + (4 + 2 * blocks if score else 0)
+            out["mix_clk_per_256_pairs"] = 16.0 * mfmas + 4 * 8.1 + 2.4 * plain + 4.6 * (8 if score else 0)
+            out["basis"] = ("per 16x16 tile: the fp16 MFMAs at 16 clk each (about 21 under the power limit), 4 v_exp_f32 (8.1 clk), plain "
+                            "instructions at 2.4, conversions and v_fma_mix_f32 at 4.6, added up: they overlap by little")
         elif blocks == 1:
             measured = {("symmetric_bf16x3", "score"): (155.0, "9 bf16 MFMAs at 16 clk, 4 exp, split, row and column sums and fold per tile of "
                                                                "unordered pairs, added up: 310 clk per 512 ordered pairs"),

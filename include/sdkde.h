@@ -73,11 +73,14 @@ enum {
 enum {
     SDKDE_MAX_D = 128,
     /* flags: precision mode of the distance cross term (the Gram-matrix tile of the Method section) */
-    SDKDE_PREC_FP32 = 0,    /* fp32 inputs, fp32 accumulate: the reference path.  On the matrix path every fp32 operand
-                               (coordinates and weights) is held exactly, as the sum of three bf16 parts (weights down to
-                               about 2^-110 of a weight of one), and a product is summed over the six largest of its nine
-                               part products: the rest is at most 2^-24 of it in the cross term, 1.5 2^-23 in Phi X.  So
-                               in the symmetric mode. */
+    SDKDE_PREC_FP32 = 0,    /* fp32 inputs, fp32 accumulate: the reference path.  On the matrix path an operand is the
+                               sum of two fp16 parts (to 2^-23 of it, the size of the fp32 rounding that forming the
+                               coordinates in two floats saves; weights, scaled per point by a power of two, to 2^-22 of
+                               themselves or 2^-42 of the point's largest if that is more) and a product is summed
+                               over the three largest of its four part products: the rest is at most 2^-22 of it.  In the symmetric mode an operand is the sum of three bf16 parts,
+                               exactly (weights down to about 2^-110 of a weight of one), and a product is summed over
+                               the six largest of its nine: the rest is at most 2^-24 of it in the cross term, 1.5 2^-23
+                               in Phi X. */
     SDKDE_PREC_FP16X2 = 1,  /* each input split into two fp16 halves (hi + lo, ~22 mantissa bits) and
                                multiplied on the fp16 matrix units with fp32 accumulate; Phi X, exp and all
                                sums stay fp32.  A lower-precision-input mode: its error is reported
@@ -118,8 +121,8 @@ enum {
        up to 64 groups of sample blocks: about 4.6 GiB at n = 2^20, d = 16).  Takes effect for sdkde_score at the
        samples themselves and sdkde_fit_eval with 7 <= d <= 32, SDKDE_PREC_FP32 and enough samples to fill the chip with
        its work items (n >= 32768 at d <= 16, n >= 16384 at d <= 32); ignored otherwise (sdkde_describe_plan tells).
-       It is ahead of the ordinary kernels only at d <= 16 and n >= ~131072, by 2 - 6 %; below that it takes 2 - 11 %
-       longer, at d > 16 7 - 36 %. */
+       It takes 25 - 37 % longer than the ordinary kernels at d <= 16, 60 - 75 % at d > 16, and is kept for its
+       summation order. */
     SDKDE_FLAG_SYMMETRIC = 32,
     /* flags bit 6, sdkde_eval and sdkde_eval_laplace only (evaluating one fitted estimate at many batches of
        queries): the workspace still holds what the previous sdkde_eval / sdkde_eval_laplace call on it prepared

@@ -56,18 +56,18 @@ PEAK_MFMA_F16 = 2.5e15
 PEAK_VALU_SLOTS = 256 * 4 * 32 * 2.4e9
 EXP_SLOTS = 4
 
-# stage: "score" | "eval"; mode: "bf16x3" (what the fp32 mode's matrix path runs: fp32 operands as three bf16 parts) |
-# "symmetric_bf16x3" | "fp16x2" | "fp16x2_all" | "fp16x2_phi16", and "fp32" | "symmetric": the same two on fp32 MFMAs,
-# the paper's arithmetic priced at the fp32 matrix peak
+# stage: "score" | "eval"; mode: "half2" (what the fp32 mode's matrix path runs: operands as two fp16 parts) |
+# "symmetric_bf16x3" (its symmetric mode: three bf16 parts) | "fp16x2" | "fp16x2_all" | "fp16x2_phi16", and "fp32" |
+# "symmetric": the same two on fp32 MFMAs, the paper's arithmetic priced at the fp32 matrix peak
 
 
 def pair_work(stage: str, d: int, mode: str = "fp32", thin: bool = False) -> dict:
     """Work per ordered pair as the kernels of `mode` issue it: matrix flops by input type, exps, and plain
     vector instructions (one lane-slot each).  The fp32 matrix path spends 2d flops per pair on the cross term
     and 2d on Phi X (score only); the fp16x2 modes multiply (hi + lo)(hi + lo) = four products per term; the
-    symmetric score forms the Gram tile and the exp once per unordered pair.  bf16x3: six part products per term, and
-    in the score 5.5 vector instructions per weight to split it (22 per four) beside the init add, the row sum and half
-    an add of the chunk's sums per 16 columns."""
+    symmetric score forms the Gram tile and the exp once per unordered pair.  half2: three part products per term, the row
+    sum, the init add where no spare columns hold the row's term (an even number of 16-column blocks), and in the score
+    three vector instructions per weight to split it and half an FMA of the chunk's sums per 16 columns."""
     score = stage == "score"
     if thin:
         # direct differences: d subs + d FMAs (r^2), 1 add (D); the score adds d FMAs (numerator)
@@ -76,9 +76,9 @@ def pair_work(stage: str, d: int, mode: str = "fp32", thin: bool = False) -> dic
     if mode == "symmetric_bf16x3" and score:
         # per unordered pair: Gram, T_I and T_J, one exp, one split, init + row sum + column sum adds, half a chunk add each
         return {"mfma_f32": 0.0, "mfma_f16": 18.0 * d, "exp": 0.5, "valu": (8.5 + 0.5 * blocks) / 2.0}
-    if mode in ("bf16x3", "symmetric_bf16x3"):
-        return {"mfma_f32": 0.0, "mfma_f16": (24.0 if score else 12.0) * d, "exp": 1.0,
-                "valu": (7.5 + 0.5 * blocks) if score else 2.0}
+    if mode in ("half2", "symmetric_bf16x3"):
+        return {"mfma_f32": 0.0, "mfma_f16": (12.0 if score else 6.0) * d, "exp": 1.0,
+                "valu": (1.0 if blocks % 2 else 2.0) + ((3.0 + 0.5 * blocks) if score else 0.0)}
     if mode == "symmetric" and score:
         # per unordered pair: Gram 2d, T_I and T_J 2d each, one exp, init + row sum + column sum adds
         return {"mfma_f32": 3.0 * d, "mfma_f16": 0.0, "exp": 0.5, "valu": 1.5}

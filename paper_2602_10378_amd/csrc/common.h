@@ -32,12 +32,11 @@ enum PairKind {
     kEval = 2,          // D only (Gaussian KDE)
     kEvalLaplace = 3,   // sum of phi * (1 + d/2 - r^2/2h^2) (Laplace-corrected KDE; signed)
     kRowMax = 4,        // max_j of the exponent (first pass of the max-shifted mode); kept in the D slot
-    kScoreBand = 5,     // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
-    kRowMaxFour = 6     // kRowMax of pair_split_kernel at d <= 4
+    kScoreBand = 5      // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
 };
 // How the prepared rows of the matrix path are held: SDKDE_PREC_FP16X2 .. SDKDE_PREC_FP16X2_PHI16 as the layouts of those
-// modes' kernels, or three bf16 parts (split3.h), the fp32 mode.
-constexpr int kFormatSplit3 = 4;
+// modes' kernels; in the fp32 mode two fp16 parts (half2.h), or three bf16 parts for the symmetric score (split3.h).
+constexpr int kFormatSplit3 = 4, kFormatHalf2 = 5;
 constexpr float kNegHuge = -3.0e38f;
 // v_exp_f32 flushes results below the smallest normal fp32 number (2^-126) to zero, so a weight sum over n samples
 // may have lost up to n * 2^-126.  A sum that this could change by more than one part in a thousand (the

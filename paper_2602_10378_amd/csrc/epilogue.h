@@ -1,6 +1,7 @@
 // Reductions of the partial sums and the elementwise kernels: score / eval epilogues, debias, max-shift.
 #pragma once
 #include "common.h"
+#include "half2.h"
 #include "split3.h"
 
 namespace {
@@ -49,21 +50,51 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     return r;
 }
 
-// p~_i[c] of the prepared rows, from whichever format holds them.
-__device__ __forceinline__ float prepared_value(const float* ps, int64_t i, int c, int dp, int format)
-{
-    if (format == kFormatSplit3) return split3_value(ps, i, c, dp);
-    const _Float16* ph = reinterpret_cast<const _Float16*>(ps) + i * 2 * dp + (c / 16) * 32 + (c % 16);      // fp16 hi + lo
-    return (float)ph[0] + (float)ph[16];
-}
+// Columns c0 .. c0+3 of prepared row i, in any of the formats.  The loads are asked for apart from their use, without a
+// branch, so that a kernel can have them in flight beside the split slots it sums (read after the sums they are one more
+// memory latency of a kernel that is little else).  scaled_rows (not 0: their padded count): points, whose rows may be held
+// scaled down (half2.h).
+struct PreparedQuad {
+    u32x2 part[3];
+    float scale;
 
-// Columns c0 .. c0+3 of it (c0 a multiple of four, below dp).
-__device__ __forceinline__ f32x4 prepared_quad(const float* ps, int64_t i, int c0, int dp, int format)
+    __device__ __forceinline__ void load(const float* ps, int64_t i, int c0, int dp, int format, int64_t scaled_rows)
+    {
+        int stride = 32;
+        const int64_t offset = format == kFormatSplit3  ? split3_offset(i, c0, dp, &stride)
+                               : format == kFormatHalf2 ? half2_offset(i, c0, dp, &stride)
+                                                        : (i * 2 * dp + (c0 / 16) * 32 + c0 % 16) * 2;      // fp16 hi, lo
+        const char* const at = reinterpret_cast<const char*>(ps) + offset;
+        part[0] = *reinterpret_cast<const u32x2*>(at);
+        part[1] = *reinterpret_cast<const u32x2*>(at + stride);
+        part[2] = *reinterpret_cast<const u32x2*>(at + (format == kFormatSplit3 ? 2 * stride : 0));
+        scale = *(format == kFormatHalf2 && scaled_rows ? half2_scale(const_cast<float*>(ps), scaled_rows, dp) + i
+                                                        : reinterpret_cast<const float*>(at));
+    }
+    // The values, as a sum of two where that is more than a float holds.
+    __device__ __forceinline__ f32x4 value(int format, int64_t scaled_rows, f32x4* rest) const
+    {
+        *rest = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (format == kFormatSplit3) return split3_sum(part);
+        f32x4 v = half_values(part[0]), low = half_values(part[1]);
+        if (format != kFormatHalf2) return v + low;
+        if (scaled_rows) {
+            v *= scale;
+            low *= scale;
+        }
+        *rest = low;
+        return v;
+    }
+};
+
+// Up to four values of a row, `left` of them there; as_quad: a multiple of four are, at a multiple of 16 bytes.
+__device__ __forceinline__ f32x4 load_quad(const float* at, int as_quad, int left)
 {
-    if (format == kFormatSplit3) return split3_quad(ps, i, c0, dp);
-    f32x4 v;
+    if (as_quad) return *reinterpret_cast<const f32x4*>(at);
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = prepared_value(ps, i, c0 + k, dp, format);
+    for (int k = 0; k < 4; ++k)
+        if (k < left) v[k] = at[k];
     return v;
 }
 
@@ -86,16 +117,23 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const bool active = idx < m * d;
     const int64_t i = active ? idx / d : 0;
     const int c = active ? (int)(idx % d) : 0;
+    PreparedQuad own = {};
+    if (mode != 1) own.load(ps, i, c & ~3, dp, format, mode == 0 ? m_pad : 0);
     const float tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
     const float dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
-    const float pc = mode != 1 ? prepared_value(ps, i, c, dp, format) : 0.0f;
+    float pc = 0.0f, rest = 0.0f;
+    if (mode != 1) {
+        f32x4 low;
+        pc = own.value(format, mode == 0 ? m_pad : 0, &low)[c & 3];
+        rest = low[c & 3];
+    }
     float out = 0.0f;
     if (mode == 2) {
-        out = fmaf(-pc, dsum, tsum) / (dsum + 1.0f) * inv_ah2;
+        out = fmaf(-rest, dsum, fmaf(-pc, dsum, tsum)) / (dsum + 1.0f) * inv_ah2;
     } else if (dsum >= min_sum) {
         float ratio = tsum / dsum;
-        out = (mode == 1 ? ratio : ratio - pc) * inv_ah2;
+        out = (mode == 1 ? ratio : (ratio - pc) - rest) * inv_ah2;
     }
     if (score) score[idx] = out;
     if (x_sd) x_sd[idx] = fmaf(half_h2, out, x[idx]);      // fused debiasing shift (sdkde_fit_eval)
@@ -121,6 +159,11 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     const bool active = q < m * quads;
     const int64_t i = active ? q / quads : 0;
     const int c0 = active ? (int)(q % quads) * 4 : 0;
+    const int64_t at = i * d + c0;
+    PreparedQuad own;
+    own.load(ps, i, c0, dp, format, mode == 0 ? m_pad : 0);       // may run past d in the last quad: padding, not stored
+    f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (x_sd && part == 0) xv = load_quad(x + at, quad_io, d - c0);
     f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
     float dacc = 0.0f;
     if (active) {
@@ -141,20 +184,19 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
         tsum += red_t[k][lane];
         dsum += red_d[k][lane];
     }
-    const f32x4 pc = prepared_quad(ps, i, c0, dp, format);     // may run past d in the last quad: padding, not stored
+    f32x4 rest;
+    const f32x4 pc = own.value(format, mode == 0 ? m_pad : 0, &rest);
     f32x4 out;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         float o = 0.0f;
-        if (mode == 2) o = fmaf(-pc[v], dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;
-        else if (dsum >= min_sum) o = (tsum[v] / dsum - pc[v]) * inv_ah2;
+        if (mode == 2) o = fmaf(-rest[v], dsum, fmaf(-pc[v], dsum, tsum[v])) / (dsum + 1.0f) * inv_ah2;
+        else if (dsum >= min_sum) o = ((tsum[v] / dsum - pc[v]) - rest[v]) * inv_ah2;
         out[v] = o;
     }
-    const int64_t at = i * d + c0;
     if (quad_io) {                  // d is a multiple of four and the caller's arrays are 16-byte aligned
         if (score) *reinterpret_cast<f32x4*>(score + at) = out;
         if (x_sd) {
-            const f32x4 xv = *reinterpret_cast<const f32x4*>(x + at);
             f32x4 r;
 #pragma unroll
             for (int v = 0; v < 4; ++v) r[v] = fmaf(half_h2, out[v], xv[v]);
@@ -165,19 +207,20 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
         for (int v = 0; v < 4; ++v) {
             if (c0 + v >= d) break;
             if (score) score[at + v] = out[v];
-            if (x_sd) x_sd[at + v] = fmaf(half_h2, out[v], x[at + v]);
+            if (x_sd) x_sd[at + v] = fmaf(half_h2, out[v], xv[v]);
         }
     }
 }
 
 // log p = log D + lognorm, lognorm = -log n - d log h - (d/2) log 2 pi (formed on the host in double).
 // signed != 0 (Laplace-corrected sum, which may be negative): density = sum * exp(lognorm) only.
-// shift (may be null): per-query base-2 exponent shift of the max-shifted mode.  min_sum: least_trusted_sum(n).
+// shift (may be null): per-query base-2 exponent shift of the max-shifted mode.  residual (may be null): half2.h.  min_sum: least_trusted_sum(n).
 // Grid: one workgroup per kBlock / PARTS queries.
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void eval_epilogue_kernel(const float* __restrict__ part_d, int nsplit,
                                                                int64_t m, int64_t m_pad, double lognorm, int is_signed,
-                                                               const float* __restrict__ shift, float min_sum,
+                                                               const float* __restrict__ shift,
+                                                               const float* __restrict__ residual, float min_sum,
                                                                float* __restrict__ density,
                                                                float* __restrict__ log_density)
 {
@@ -185,20 +228,24 @@ __global__ __launch_bounds__(kBlock) void eval_epilogue_kernel(const float* __re
     __shared__ float red[PARTS][kEpiOutputs];
     const int64_t i = (int64_t)blockIdx.x * kEpiOutputs + threadIdx.x % kEpiOutputs;
     const bool active = i < m;
-    float dsum = reduce_slots<PARTS, false>(part_d + (active ? i : 0), m_pad, nsplit, active, red);
+    // max-shifted mode: the sums were taken of phi / 2^shift; residual: what rounding -|p~|^2 / 2 (less the shift) left
+    // (read from somewhere in any case: behind a branch their latency would come on top of that of the sums)
+    const float* const sums = part_d + (active ? i : 0);
+    const float of_shift = *(shift && active ? shift + i : sums), of_residual = *(residual && active ? residual + i : sums);
+    float dsum = reduce_slots<PARTS, false>(sums, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
+    const double shift_ln = ((shift ? (double)of_shift : 0.0) + (residual ? (double)of_residual : 0.0)) * 0.69314718055994530942;
     // too close to the flush threshold of the weights: the all-underflow case (the signed sum of the Laplace-corrected
     // estimate may be small because its terms cancel, and is left as it is)
     if (!is_signed && dsum < min_sum) dsum = 0.0f;
-    // max-shifted mode: the sums were taken of phi / 2^shift
-    const double shift_ln = shift ? (double)shift[i] * 0.69314718055994530942 : 0.0;
     if (is_signed) {
         if (density) density[i] = (float)((double)dsum * exp(lognorm + shift_ln));
         return;
     }
-    double lp = log((double)dsum) + lognorm + shift_ln;      // -inf when dsum == 0
+    const double lp = log((double)dsum) + lognorm + shift_ln;      // -inf when dsum == 0
     if (log_density) log_density[i] = (float)lp;
-    if (density) density[i] = (float)exp(lp);
+    // beside the logarithm instead of after it where neither end of the double range is near (the float is 0 or inf there)
+    if (density) density[i] = (float)(fabs(lognorm + shift_ln) < 600.0 ? (double)dsum * exp(lognorm + shift_ln) : exp(lp));
 }
 
 // out may alias x or s (each thread reads its one element before it writes it): no __restrict__ here.
@@ -211,20 +258,31 @@ __global__ __launch_bounds__(kBlock) void debias_kernel(const float* x, const fl
 
 
 // shift[i] = max over splits of the row maxima left in part_d by a kRowMax pass; on the MFMA path the
-// shift is also folded into the row constant pn (-|p~|^2 - shift), so the main pass needs no extra work.
+// shift is also folded into the row constant pn (-|p~|^2 - shift), so the main pass needs no extra work; residual (may be
+// null) takes the rounding of that difference.  Rows held scaled down (their
+// scale follows the residuals) keep their norm, see pair_half.h.
 // Grid: one workgroup per kBlock / PARTS rows.
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void shift_kernel(const float* __restrict__ part_d, int nsplit, int64_t m_pad,
-                                                       float* __restrict__ shift, float* __restrict__ pn)
+                                                       float* __restrict__ shift, float* __restrict__ pn,
+                                                       float* __restrict__ residual)
 {
     constexpr int kEpiOutputs = kBlock / PARTS;
     __shared__ float red[PARTS][kEpiOutputs];
     const int64_t i = (int64_t)blockIdx.x * kEpiOutputs + threadIdx.x % kEpiOutputs;
     const bool active = i < m_pad;
-    const float mx = reduce_slots<PARTS, true>(part_d + (active ? i : 0), m_pad, nsplit, active, red);
+    // read from somewhere in any case, see eval_epilogue_kernel
+    const float* const maxima = part_d + (active ? i : 0);
+    const float before = *(pn && active ? pn + i : maxima);
+    const float scale = *(residual && active ? residual + m_pad + i : maxima), left = *(residual && active ? residual + i : maxima);
+    const float mx = reduce_slots<PARTS, true>(maxima, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
     shift[i] = mx;
-    if (pn) pn[i] -= mx;
+    if (pn && !(residual && scale != 1.0f)) {
+        const float after = before - mx;
+        pn[i] = after;
+        if (residual) residual[i] = left + (float)(((double)before - (double)mx) - (double)after);
+    }
 }
 
 }  // namespace

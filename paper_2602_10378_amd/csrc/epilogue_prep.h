@@ -18,10 +18,9 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* ps, int nsplit, int64_t m,
     int64_t m_pad, int d, int dp, int format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
     float half_h2, float* __restrict__ x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
-    PrepCommon common, float a, Stamp stamp)
+    const float* centre, double a, Stamp stamp)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
-    __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
     extern __shared__ float prep_lds[];                     // prep_lds_bytes
     float* const raw = prep_lds;
@@ -29,69 +28,79 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     __shared__ f32x4 red_t[PARTS][LANES];
     __shared__ float red_d[PARTS][LANES];
     __shared__ int stamp_flag;
-    const bool poisoned = stamp_poisons(stamp, &stamp_flag);
-    prep_common(common, d, red, smean);
-    if ((int)blockIdx.x >= blocks_sd) {
-        prep_rows<false>(q_job, (int64_t)(blockIdx.x - blocks_sd) * kPrepRows, d, dp, a, format, poisoned, smean, raw, used);
-        return;
-    }
-
-    const int64_t r0 = (int64_t)blockIdx.x * kPrepRows;
-    const int lane = threadIdx.x % LANES, part = threadIdx.x / LANES;
-    const int quads = dp / 4;
-    for (int first = 0; first < kPrepRows * quads; first += LANES) {        // kPrepRows * quads is a multiple of 64
-        const int item = first + lane;
-        const int64_t i = r0 + item / quads;
-        const int c0 = (item % quads) * 4;
-        const bool active = i < m;
-        f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
-        float dacc = 0.0f;
-        if (active) {
-#pragma unroll 4
-            for (int s = part; s < nsplit; s += PARTS) {
-                tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
-                dacc += part_d[(int64_t)s * m_pad + i];
-            }
-        }
-        red_t[part][lane] = tacc;
-        red_d[part][lane] = dacc;
-        __syncthreads();
-        if (active && part == 0 && c0 < d) {
-            f32x4 tsum = red_t[0][lane];
-            float dsum = red_d[0][lane];
-#pragma unroll
-            for (int k = 1; k < PARTS; ++k) {
-                tsum += red_t[k][lane];
-                dsum += red_d[k][lane];
-            }
-            const f32x4 pc = prepared_quad(ps, i, c0, dp, format);     // may run past d in the last quad: padding, not stored
-            f32x4 out, shifted;
+    __shared__ uint32_t far_rows;
+    if (threadIdx.x == 0) far_rows = 0;
+    const float of_centre = (int)threadIdx.x < d ? centre[threadIdx.x] : 0.0f;      // needed by prep_rows only
+    const bool of_queries = (int)blockIdx.x >= blocks_sd;
+    const PrepJob job = of_queries ? q_job : sd_job;
+    const int64_t r0 = (int64_t)(blockIdx.x - (of_queries ? blocks_sd : 0)) * kPrepRows;
+    StagedRows staged;
+    if (of_queries) staged.load(job, r0, d);
+    stamp_check(stamp, &stamp_flag);
+    if (of_queries) {
+        staged.store(raw, d, dp);
+    } else {
+        const int lane = threadIdx.x % LANES, part = threadIdx.x / LANES;
+        const int quads = dp / 4;
+        for (int first = 0; first < kPrepRows * quads; first += LANES) {        // kPrepRows * quads is a multiple of 64
+            const int item = first + lane;
+            const int64_t i = r0 + item / quads;
+            const int c0 = (item % quads) * 4;
+            const bool active = i < m;
+            f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f}, xv = tacc;
+            float dacc = 0.0f;
+            PreparedQuad prepared = {};
             const int64_t at = i * d + c0;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                out[v] = fmaf(-pc[v], dsum, tsum[v]) / (dsum + 1.0f) * inv_ah2;   // the samples' own pair is not in the sums
-            if (quad_io) {                  // d is a multiple of four and the caller's arrays are 16-byte aligned
-                const f32x4 xv = *reinterpret_cast<const f32x4*>(x + at);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) shifted[v] = fmaf(half_h2, out[v], xv[v]);
-                if (score) *reinterpret_cast<f32x4*>(score + at) = out;
-                *reinterpret_cast<f32x4*>(x_sd + at) = shifted;
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (c0 + v >= d) break;
-                    shifted[v] = fmaf(half_h2, out[v], x[at + v]);
-                    if (score) score[at + v] = out[v];
-                    x_sd[at + v] = shifted[v];
+            if (active) {
+                prepared.load(ps, i, c0, dp, format, 0);        // may run past d in the last quad: padding, not stored
+                if (part == 0) xv = load_quad(x + at, quad_io, d - c0);     // (quad_io: d is a multiple of four and the caller's arrays are 16-byte aligned)
+#pragma unroll 4
+                for (int s = part; s < nsplit; s += PARTS) {
+                    tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
+                    dacc += part_d[(int64_t)s * m_pad + i];
                 }
             }
+            red_t[part][lane] = tacc;
+            red_d[part][lane] = dacc;
+            __syncthreads();
+            if (active && part == 0 && c0 < d) {
+                f32x4 tsum = red_t[0][lane];
+                float dsum = red_d[0][lane];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (c0 + v < d) raw[(item / quads) * (dp + 1) + c0 + v] = shifted[v];
+                for (int k = 1; k < PARTS; ++k) {
+                    tsum += red_t[k][lane];
+                    dsum += red_d[k][lane];
+                }
+                f32x4 rest;
+                const f32x4 pc = prepared.value(format, 0, &rest);
+                f32x4 out, shifted;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    out[v] = fmaf(-rest[v], dsum, fmaf(-pc[v], dsum, tsum[v])) / (dsum + 1.0f) * inv_ah2;   // the samples' own pair is not in the sums
+#pragma unroll
+                for (int v = 0; v < 4; ++v) shifted[v] = fmaf(half_h2, out[v], xv[v]);
+                if (quad_io) {
+                    if (score) *reinterpret_cast<f32x4*>(score + at) = out;
+                    *reinterpret_cast<f32x4*>(x_sd + at) = shifted;
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (c0 + v >= d) break;
+                        if (score) score[at + v] = out[v];
+                        x_sd[at + v] = shifted[v];
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (c0 + v < d) raw[(item / quads) * (dp + 1) + c0 + v] = shifted[v];
+            }
+            __syncthreads();            // red_t / red_d are reused by the next pass; raw is read below
         }
-        __syncthreads();            // red_t / red_d are reused by the next pass; raw is read below
     }
-    prep_rows<true>(sd_job, r0, d, dp, a, format, poisoned, smean, raw, used);
+    if ((int)threadIdx.x < d) smean[threadIdx.x] = of_centre;
+    __syncthreads();
+    const bool poisoned = stamp_flag != 0;
+    prep_rows(job, r0, d, dp, a, format, poisoned, smean, raw, used, &far_rows);
 }
 
 }  // namespace

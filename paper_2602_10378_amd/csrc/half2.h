@@ -1,0 +1,105 @@
+// Two-part fp16 operands of the fp32 path: layout of the prepared arrays and the splits.
+#pragma once
+#include "common.h"
+
+namespace {
+
+// ------------------------------------------------------------------------------------------
+// The fp32 path multiplies on the fp16 matrix units.  A coordinate v = a sqrt 2 (x - mean), formed in two floats, is held as
+// h + l, h = fp16(v), l = fp16(v - h), both to nearest: 11 significant bits each and a sign between them, so |v - h - l| is
+// at most 2^-23 of v's power of two (0.47 of that in the root mean square; the fp32 rounding of x - mean and of its product
+// with a that the second float replaces came to 0.41), or 2^-25 where |v| < 2^-2.  A product a b is summed over three of its four
+// part products, ah bh + al bh + ah bl, each exact in fp32; al bl is at most 2^-22 |a b|, 2^-24.6 in the root mean square,
+// of either sign.  Norms are those of h + l, so what is computed is the exact sum for samples and points moved by their
+// split error, whose effect on an exponent is that error times the distance of the pair and not times the norms.
+//
+// Range: a sample's coordinate beyond kHalfMax goes in as zero and keeps its norm: its exponents lie below
+// -kHalfMax^2 / 2 + ..., so its weight is 0.  A point with one, for the max-shifted sums already one beyond kFarPoint, is held as
+// 2^-k times itself (2^k in the prepared `scale`), see pair_half.h: without the shift its weights are 0.  (fp32 exponents at
+// such distances, R / h > 46000, are off by a hundred and more.)
+//
+// Prepared rows ("xs" / "ps"), in chunks of kChunkRows = 32 rows, two 16-row tiles of half_tile_bytes each (KB = dp / 16):
+//   32-column block b (columns 32b .. 32b+31): part q (h, l) at b * 2048 + q * 1024; lane l = 16 g + r of the operand holds
+//     columns 8g .. 8g+7 of row r at l * 16.
+//   the odd 16-column block left over when KB is odd, at (KB / 2) * 2048: columns 8g .. 8g+7 (g < 2) of row r, part q at
+//     (32 q + 16 g + r) * 16, so that a lane's 16 bytes at (16 g + r) * 16 for g = 0 .. 3 are the K = 32 operand [h | l].
+//     Behind it, at 1024 + 16 r, what fills the columns that the block's second operand (its only one, if it has at most
+//     eight columns) leaves: kTermFactor, 2^7 of what rounding the norm left, and the second parts of four columns (the
+//     products l l of which then are in the sum, too): columns 8 .. 11 of the block, or 0 .. 3 of eight.
+// Prepared transpose ("xt"), chunks of KB * 3072 bytes: 16-column block mb, part q (h, l, 2^-11 h) at mb * 3072 + q * 1024; lane
+//   16 g + r holds column 16 mb + r of rows 4g .. 4g+3 of the first tile and 4g .. 4g+3 of the second, which is the order the
+//   Gram accumulators of the two tiles leave Phi in.
+// Norms are -|h + l|^2 / 2, rounded once from double; for points `residual` holds what that rounding left.
+// ------------------------------------------------------------------------------------------
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr float kHalfMax = 65504.0f;             // largest finite fp16 value
+// From here on the shifted sums round a point's exponents at the size of its norm and only then shift them (the exponents'
+// last place is 2^-3 there): rounded differently for the maximum and for the sums they would miss each other, and the sums
+// were 0 or infinite from about 10^5 bandwidths on.
+constexpr float kFarPoint = 2047.0f;
+constexpr float kWeightScale = 2048.0f;          // see pair_half.h
+constexpr int half_tile_bytes(int kb) { return kb * 1024 + (kb % 2) * 256; }
+// How the columns beyond whole 32-column blocks are held: none, 9 .. 16 in a 16-column block (two MFMAs), 1 .. 8 (one).
+enum HalfTail { kTailNone = 0, kTailSixteen = 1, kTailEight = 2 };
+__host__ __device__ constexpr int half_tail(int d) { return (d + 15) / 16 % 2 == 0 ? kTailNone : (d - 1) % 16 < 8 ? kTailEight : kTailSixteen; }
+
+// A value in two parts, the first in the low half of the word.
+__device__ __forceinline__ uint32_t half2_split(float v, float low)       // v + low
+{
+    const _Float16 h = (_Float16)v;
+    const _Float16 l = (_Float16)((v - (float)h) + low);
+    return (uint32_t)__builtin_bit_cast(uint16_t, h) | (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
+}
+__device__ __forceinline__ float half_low(uint32_t w) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu)); }
+__device__ __forceinline__ float half_high(uint32_t w) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16)); }
+
+// Byte offset of (row, column c), first part, in the prepared rows; *part_stride: bytes to the second.
+__device__ __forceinline__ int64_t half2_offset(int64_t row, int c, int dp, int* part_stride)
+{
+    const int kb = dp / 16, r = (int)(row & 15);
+    const int64_t tile = (row >> 4) * (int64_t)half_tile_bytes(kb);
+    const int b = c >> 5;
+    const bool odd = 2 * b + 1 >= kb;
+    *part_stride = odd ? 512 : 1024;
+    return tile + b * 2048 + (((c >> 3) & (odd ? 1 : 3)) * 16 + r) * 16 + (c & 7) * 2;
+}
+
+// Behind the prepared points (their rows take at most 5 of the 6 bytes a value that are theirs, and dp >= 16): what rounding
+// their norms left, and 2^k of points held as 2^-k times themselves.
+__host__ __device__ inline float* half2_residual(float* ps, int64_t rows_pad, int dp)
+{
+    return ps + rows_pad / kTile * half_tile_bytes(dp / 16) / (int64_t)sizeof(float);
+}
+__host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int dp) { return half2_residual(ps, rows_pad, dp) + rows_pad; }
+
+// Four consecutive halves.
+__device__ __forceinline__ f32x4 half_values(const u32x2& two)
+{
+    return f32x4{half_low(two.x), half_high(two.x), half_low(two.y), half_high(two.y)};
+}
+
+// The constant term of a row's exponents as three elements of a row operand: their sum with kTermFactor is the fp32 value,
+// cut off where every weight is zero (NaN stays NaN).  Each part's factor keeps it inside the fp16 range whatever v's size.
+constexpr float kTermFactor[3] = {32768.0f, 16.0f, 0.0078125f};
+constexpr float kLeastTerm = -kHalfMax * 32768.0f;
+constexpr float kResidualFactor = 0.0078125f;       // of the samples' norms, see above
+__device__ __forceinline__ void split_term(float v, float residual, _Float16 (&part)[3])
+{
+    v = v < kLeastTerm ? kLeastTerm : v;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        if (q == 2) v += residual;
+        part[q] = (_Float16)(v * (1.0f / kTermFactor[q]));
+        v = fmaf(-(float)part[q], kTermFactor[q], v);
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma_f16(const f16x8& a, const f16x8& b, const f32x4& c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+}  // namespace

@@ -70,7 +70,6 @@ __global__ __launch_bounds__(kSymBlock, 2) void pair_sym_kernel(
     static_assert(NI % 2 == 0, "row tiles are taken two at a time: one chunk of the prepared transpose");
     extern __shared__ __align__(16) float sym_lds[];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int DP = KB * 16;
     constexpr int SB = kSymWaves * NI * kTile;          // rows a workgroup holds at a time
     constexpr int PAIRS = KB / 2;

@@ -1,6 +1,7 @@
 // Prep kernels: centre + scale + pad (+ fp16 hi/lo split) into the layouts the pair kernels read.
 #pragma once
 #include "common.h"
+#include "half2.h"
 #include "split3.h"
 
 namespace {
@@ -9,54 +10,89 @@ namespace {
 // Prep: the centre (mean of a strided subsample, formed by every workgroup for itself), then centre + scale + pad.
 // ------------------------------------------------------------------------------------------
 
+// v summed over each group of eight lanes, in all of them (lane ^ 1, lane ^ 2, then the row of eight mirrored).
+__device__ __forceinline__ double sum_of_eight(double v)
+{
+    auto add = [](double x, auto ctrl) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)bits, decltype(ctrl)::value, 0xf, 0xf, true);
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(bits >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return x + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    v = add(v, std::integral_constant<int, 0xB1>());        // quad_perm [1, 0, 3, 2]
+    v = add(v, std::integral_constant<int, 0x4E>());        // quad_perm [2, 3, 0, 1]
+    return add(v, std::integral_constant<int, 0x141>());    // row_half_mirror
+}
+
 // The centre all coordinates are taken relative to: the column means of an evenly strided subsample of the
 // samples (about kCentreElems input values, at least 32 rows), summed in double in a fixed order, so every
 // workgroup that computes it gets the same bits.  Any point near the data serves (the exponent
 // -|p - x|^2 / 2h^2 does not depend on it; it only keeps the norms of the Gram expansion small), so a few hundred
 // rows spread over the whole array are as good as all of them and need no pass of their own.
-// Result in smean[0 .. d); ends with a barrier.
-__device__ __forceinline__ int64_t centre_rows(int64_t n, int d)
+// Result in smean[0 .. d).
+inline int64_t centre_rows(int64_t n, int d)
 {
     const int64_t want = kCentreElems / d > 32 ? kCentreElems / d : 32;
     return n < want ? n : want;
 }
 
-__device__ __forceinline__ void block_centre(const float* __restrict__ src, int64_t n, int d, double* red, float* smean)
+// Where a prep launch gets the centre from.
+struct PrepCommon {
+    const float* centre_src;   // samples to take the centre of; null: read `centre`
+    int64_t rows, stride;      // centre_rows of them, this many rows apart (>= 1)
+    double weight;             // 1 / rows
+    float* centre;             // in the workspace: written by workgroup 0 when computed, read otherwise
+};
+inline PrepCommon centre_of(const float* src, int64_t n, int d, float* centre)
+{
+    const int64_t rows = src ? centre_rows(n, d) : 1;
+    return {src, rows, src ? n / rows : 1, 1.0 / (double)rows, centre};
+}
+
+// Ends with a barrier; meanwhile() is called before one, once the loads above it have been waited for.
+template <typename F>
+__device__ __forceinline__ void block_centre(const PrepCommon& pc, int d, double* red, float* smean, F meanwhile)
 {
     const int rows_per_iter = kBlock / d;                 // d <= 128 < kBlock
     const int rr = threadIdx.x / d, c = threadIdx.x % d;
-    const int64_t rows = centre_rows(n, d);
-    const int64_t stride = n / rows;                      // >= 1
+    const int rows = (int)pc.rows;
     double acc = 0.0;
     if (rr < rows_per_iter) {
 #pragma unroll 16
-        for (int64_t k = rr; k < rows; k += rows_per_iter) acc += (double)src[k * stride * d + c];
+        for (int k = rr; k < rows; k += rows_per_iter) acc += (double)pc.centre_src[k * pc.stride * d + c];
     }
     red[threadIdx.x] = acc;
+    meanwhile();
     __syncthreads();
-    if ((int)threadIdx.x < d) {
+    // eight threads a column (by one the reads of its partial sums were a chain of 256 / d LDS latencies)
+    if (8 * d <= kBlock) {
+        const int col = threadIdx.x / 8;
+        if (col < d) {
+            double t = 0.0;
+#pragma unroll 4
+            for (int q = threadIdx.x % 8; q < rows_per_iter; q += 8) t += red[q * d + col];
+            t = sum_of_eight(t);
+            if (threadIdx.x % 8 == 0) smean[col] = (float)(t * pc.weight);
+        }
+    } else if ((int)threadIdx.x < d) {
         double t = 0.0;
+#pragma unroll 4
         for (int q = 0; q < rows_per_iter; ++q) t += red[q * d + threadIdx.x];
-        smean[threadIdx.x] = (float)(t / (double)rows);
+        smean[threadIdx.x] = (float)(t * pc.weight);
     }
     __syncthreads();
 }
 
-// Where a prep launch gets the centre from.
-struct PrepCommon {
-    const float* centre_src;   // samples to take the centre of (centre_rows of them, strided); null: read `centre`
-    int64_t centre_n;          // rows of centre_src
-    float* centre;             // in the workspace: written by workgroup 0 when computed, read otherwise
-};
-
 // Centre into smean (computed or read back).  Ends with a barrier.
-__device__ __forceinline__ void prep_common(const PrepCommon& pc, int d, double* red, float* smean)
+template <typename F>
+__device__ __forceinline__ void prep_common(const PrepCommon& pc, int d, double* red, float* smean, F meanwhile)
 {
     if (pc.centre_src) {
-        block_centre(pc.centre_src, pc.centre_n, d, red, smean);
+        block_centre(pc, d, red, smean, meanwhile);
         if (blockIdx.x == 0 && (int)threadIdx.x < d) pc.centre[threadIdx.x] = smean[threadIdx.x];
     } else {
         if ((int)threadIdx.x < d) smean[threadIdx.x] = pc.centre[threadIdx.x];
+        meanwhile();
         __syncthreads();
     }
 }
@@ -70,6 +106,7 @@ struct PrepJob {
     float* dst_n;
     float pad_value;      // thin path only: coordinate value of padding rows
     bool samples;         // the rows are summed over (not only evaluated at)
+    bool shifted;         // points of max-shifted sums
 };
 
 // Record of what a prep launch left in the workspace (sample arrays and column sums), kept in the workspace itself:
@@ -83,9 +120,8 @@ struct Stamp {
     uint64_t value[kStampWords];    // kind of call, samples pointer, n, d, operand format, bits of the scale a
 };
 
-// Thread 0 of every workgroup reads or (workgroup 0) writes the record; returns whether this launch is poisoned.
-// Ends with a barrier.
-__device__ __forceinline__ bool stamp_poisons(const Stamp& stamp, int* flag)
+// Thread 0 of every workgroup reads or (workgroup 0) writes the record; *flag, after a barrier: whether this launch is poisoned.
+__device__ __forceinline__ void stamp_check(const Stamp& stamp, int* flag)
 {
     if (threadIdx.x == 0) {
         int bad = 0;
@@ -96,11 +132,195 @@ __device__ __forceinline__ bool stamp_poisons(const Stamp& stamp, int* flag)
         }
         *flag = bad;
     }
-    __syncthreads();
-    return *flag != 0;
 }
 
-constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (two 16-sample tiles, one chunk of split3.h)
+constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (two 16-sample tiles, one chunk of half2.h, split3.h)
+
+// The input values of rows r0 .. r0 + kPrepRows of a job, on their way to words[][] (rows of dp + 1 floats): columns
+// 16 k + 2 (threadIdx.x % 8) and the next of row threadIdx.x / 8 by each thread.  Loaded before the centre is known, so that the
+// two latencies of a small call's first launch are one.
+struct StagedRows {
+    float own[2 * SDKDE_MAX_D / 16];
+
+    __device__ __forceinline__ void load(const PrepJob& job, int64_t r0, int d)
+    {
+        const int64_t row = r0 + (threadIdx.x >> 3);
+        const float* const in = job.src + row * d;
+#pragma unroll
+        for (int k = 0; k < SDKDE_MAX_D / 16; ++k) {
+            if (16 * k >= d) break;
+            const int c = 16 * k + 2 * (threadIdx.x & 7);
+            own[2 * k] = row < job.rows && c < d ? in[c] : 0.0f;
+            own[2 * k + 1] = row < job.rows && c + 1 < d ? in[c + 1] : 0.0f;
+        }
+    }
+    __device__ __forceinline__ void store(float* words, int d, int dp) const
+    {
+        float* const at = words + (threadIdx.x >> 3) * (dp + 1) + 2 * (threadIdx.x & 7);
+#pragma unroll
+        for (int k = 0; k < SDKDE_MAX_D / 16; ++k) {
+            if (16 * k >= d) break;
+            at[16 * k] = own[2 * k];
+            at[16 * k + 1] = own[2 * k + 1];
+        }
+    }
+};
+
+// The body of prep_mfma_kernel for one workgroup and two fp16 parts a value (half2.h): rows r0 .. r0 + kPrepRows of `job`.
+// Their input values stand in words[][] as floats.  far_rows: zero, since before a barrier.  Coordinates are
+// formed as sums of two floats: what the split leaves of them is then all that is lost (one float rounded the difference and the
+// product first; in double, with its conversions, a small launch took 0.8 us longer).  A launch of a few workgroups is a chain
+// of latencies: kernel arguments, centre, coordinates, stores.  Rows loaded beside the centre's, eight lanes summing each
+// column of the centre, one barrier less and the norms in a wave without other work: 4.9 to 4.7 us at 4096 x 1024, d = 16.
+__device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, int d, int dp, double a, bool poisoned,
+                                                const float* smean, uint32_t* words, uint32_t* far_rows)
+{
+    static_assert(kPrepRows == kChunkRows && kBlock == 8 * kPrepRows, "a workgroup writes whole chunks, eight lanes a row");
+    const int stride = dp + 1;                  // odd: columns are read without bank conflicts
+    const float far_from = job.samples || !job.shifted ? kHalfMax : kFarPoint;      // largest coordinate held as it is
+    auto coordinate = [&](int c, float in) { return a * ((double)in - (double)smean[c]); };
+    const float a_high = (float)a, a_low = (float)(a - (double)a_high);
+    __shared__ double squares[kPrepRows];
+    {
+        const int own = threadIdx.x >> 3, lane8 = threadIdx.x & 7;
+        const int64_t row = r0 + own;
+        const bool live = row < job.rows;
+        double square = 0.0;
+        uint32_t* const at = words + own * stride;
+        bool beyond = false;
+#pragma unroll 1
+        for (int c0 = 2 * lane8; c0 < dp; c0 += 16)
+#pragma unroll
+            for (int c = c0; c < c0 + 2; ++c) {
+                const float x = __builtin_bit_cast(float, at[c]), y = c < d ? smean[c] : 0.0f;
+                const float diff = x - y, part = diff - x, left = (x - (diff - part)) + (-y - part);      // x - y = diff + left
+                float v = a_high * diff, low = fmaf(a_high, diff, -v) + fmaf(a_high, left, a_low * diff);
+                const bool out = fabsf(v) > far_from;
+                beyond |= out;
+                if (out || !live || c >= d) v = low = 0.0f;
+                const uint32_t word = half2_split(v, low);
+                at[c] = word;
+                const double held = (double)half_low(word) + (double)half_high(word);
+                square = fma(held, held, square);
+            }
+        if (beyond) atomicOr(far_rows, 1u << own);          // rows with a coordinate beyond that, a bit each
+        square = sum_of_eight(square);
+        if (lane8 == 0) squares[own] = square;
+    }
+    __syncthreads();
+    const uint32_t far = *far_rows;
+    // such rows of points: 2^-k times themselves (the largest coordinate then has the exponent 10, k > 0)
+    auto largest = [&](int rr) __attribute__((always_inline)) {
+        double most = 0.0;
+#pragma unroll 1
+        for (int c = 0; c < d; ++c) {
+            const double v = fabs(coordinate(c, job.src[(r0 + rr) * d + c]));
+            most = v > most || v != v ? v : most;
+        }
+        return most;
+    };
+    auto finite = [](double v) { return v <= 1.7e308; };
+    // 2^k and 2^-k from the exponent bits (beyond 2^1022: 2^-k is 0)
+    auto far_scale = [](double most) __attribute__((always_inline)) {
+        return __builtin_bit_cast(double, ((__builtin_bit_cast(uint64_t, most) >> 52) - 10) << 52);
+    };
+    auto far_down = [](double most) __attribute__((always_inline)) {
+        return __builtin_bit_cast(double, (2046 - ((__builtin_bit_cast(uint64_t, most) >> 52) - 10)) << 52);
+    };
+    if (far != 0 && !job.samples) {             // the same for all threads
+#pragma unroll 1
+        for (int rr = 0; rr < kPrepRows; ++rr) {
+            if (!(far >> rr & 1u)) continue;
+            const double most = largest(rr);
+            const double down = finite(most) ? far_down(most) : 0.0;
+#pragma unroll 1
+            for (int c = threadIdx.x; c < d; c += kBlock) {
+                const double v = coordinate(c, job.src[(r0 + rr) * d + c]) * down;
+                words[rr * stride + c] = finite(most) ? half2_split((float)v, (float)(v - (double)(float)v)) : 0u;
+            }
+        }
+        __syncthreads();
+    }
+    const int kb = dp / 16;
+    char* const rows_out = reinterpret_cast<char*>(job.dst) + r0 / kTile * half_tile_bytes(kb);
+    char* const t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
+    if (threadIdx.x >= kBlock - kPrepRows) {        // the last wave: at dp = 16 it has no other items
+        const int rr = threadIdx.x - (kBlock - kPrepRows);
+        const int64_t row = r0 + rr;
+        const uint32_t* w = words + rr * stride;
+        double acc = squares[rr], scale = 1.0;
+        if (far >> rr & 1u) {
+            if (job.samples) {          // a coordinate that went in as zero counts in the norm
+#pragma unroll 1
+                for (int c = 0; c < d; ++c) {
+                    const double v = coordinate(c, job.src[row * d + c]);
+                    if (fabs(v) > far_from) acc += v * v;
+                }
+            } else {
+                const double most = largest(rr);
+                if (finite(most)) scale = far_scale(most);
+                acc = 0.0;
+#pragma unroll 1
+                for (int c = 0; c < dp; ++c) {
+                    const double v = ((double)half_low(w[c]) + (double)half_high(w[c])) * scale;
+                    acc = fma(v, v, acc);
+                }
+                if (!finite(most)) acc = (double)__builtin_nanf("");            // a point that is not finite: NaN
+            }
+        }
+        const float norm = poisoned ? __builtin_nanf("") : row < job.rows ? -(float)(0.5 * acc) : kPadNorm;
+        const double rest = -0.5 * acc - (double)norm;
+        const float left = row < job.rows && fabs(rest) < 500.0 ? (float)rest : 0.0f;       // (a norm below 2^31)
+        job.dst_n[row] = norm;
+        if (!job.samples) {
+            half2_residual(job.dst, job.rows_pad, dp)[row] = left;
+            half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
+        }
+        if (kb % 2 != 0) {              // what goes into the tail's spare columns
+            const int block = dp - 16, lows = half_tail(d) == kTailSixteen ? block + 8 : block;
+            uint32_t e[4];
+            auto half_bits = [](float v) { return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v); };
+            e[0] = half_bits(kTermFactor[0]) | half_bits(kTermFactor[1]) << 16;
+            e[1] = half_bits(kTermFactor[2]) | half_bits(left * (1.0f / kResidualFactor)) << 16;
+            e[2] = w[lows] >> 16 | (w[lows + 1] & 0xffff0000u);
+            e[3] = w[lows + 2] >> 16 | (w[lows + 3] & 0xffff0000u);
+            *reinterpret_cast<u32x4*>(rows_out + rr / kTile * half_tile_bytes(kb) + kb / 2 * 2048 + 1024 + rr % kTile * 16) = u32x4{e[0], e[1], e[2], e[3]};
+        }
+    }
+    // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other (at dp = 16
+    // one wave each).
+    const int row_items = kPrepRows * dp / 8, t_items = t_out ? kb * kWave : 0;
+    for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += kBlock) {
+        uint32_t word[8];
+        char* at;
+        int part_stride;
+        const bool of_row = at_item < row_items;
+        if (of_row) {
+            const int rr = at_item % kPrepRows, c0 = at_item / kPrepRows * 8;
+            at = rows_out + half2_offset(rr, c0, dp, &part_stride);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) word[k] = words[rr * stride + c0 + k];
+        } else {
+            const int lane = at_item % kWave, mb = (at_item - row_items) / kWave;
+            const int c = mb * 16 + (lane & 15), s0 = (lane >> 4) * 4;
+            at = t_out + mb * 3 * kPartBytes + lane * 16;
+            part_stride = kPartBytes;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) word[k] = words[(s0 + (k & 3) + (k >> 2) * kTile) * stride + c];
+        }
+        u32x4 h, l, scaled;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            h[k] = (word[2 * k] & 0xffffu) | word[2 * k + 1] << 16;
+            l[k] = word[2 * k] >> 16 | (word[2 * k + 1] & 0xffff0000u);
+            const _Float16 s0 = (_Float16)(half_low(word[2 * k]) * (1.0f / kWeightScale)), s1 = (_Float16)(half_low(word[2 * k + 1]) * (1.0f / kWeightScale));
+            scaled[k] = (uint32_t)__builtin_bit_cast(uint16_t, s0) | (uint32_t)__builtin_bit_cast(uint16_t, s1) << 16;
+        }
+        *reinterpret_cast<u32x4*>(at) = h;
+        *reinterpret_cast<u32x4*>(at + part_stride) = l;
+        if (!of_row) *reinterpret_cast<u32x4*>(at + 2 * part_stride) = scaled;
+    }
+}
 
 // Centre, scale and pad for the matrix path.  A workgroup stages kPrepRows rows in LDS and writes a (x - mean), 0 in
 // padding columns and rows, to dst, the same values for the second contraction to dst_t (if it is there) and
@@ -115,12 +335,14 @@ constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (tw
 // followed by eight halves [lo(4g..4g+3) | the same again] (twice the bytes of the fp32 layout).
 // FP16X2_PHI16: dst_t holds, for tile, column c and lane group g, eight halves
 // [hi(4g..4g+3) | lo(4g..4g+3)].
-// The body for one workgroup: rows r0 .. r0 + kPrepRows of `job`.  STAGED: the input values of those rows are
-// already in raw[][] (a caller that has just computed them); otherwise they are read from job.src.
-template <bool STAGED>
-__device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, float a, int format, bool poisoned,
-                                          const float* smean, float* raw_rows, float* used_rows)
+// The body for one workgroup: rows r0 .. r0 + kPrepRows of `job`, whose input values are already in raw[][].
+__device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, double a, int format, bool poisoned,
+                                          const float* smean, float* raw_rows, float* used_rows, uint32_t* far_rows)
 {
+    if (format == kFormatHalf2) {
+        prep_rows_half2(job, r0, d, dp, a, poisoned, smean, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
+        return;
+    }
     // kPrepRows rows of dp + 1 floats each (odd stride: columns are read without bank conflicts)
     const int stride_f = dp + 1;
     auto raw = [&](int rr) { return raw_rows + rr * stride_f; };
@@ -130,7 +352,7 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         const int rr = idx / dp, c = idx % dp;
         const int64_t row = r0 + rr;
         float v = 0.0f;
-        if (row < job.rows && c < d) v = a * ((STAGED ? raw(rr)[c] : job.src[row * d + c]) - smean[c]);
+        if (row < job.rows && c < d) v = (float)a * (raw(rr)[c] - smean[c]);
         raw(rr)[c] = v;
         if (format == kFormatSplit3) continue;              // the parts are written below
         const _Float16 hi = (_Float16)v;
@@ -223,24 +445,28 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
 // a call with more than 32768 rows took a second round of them (60028 rows at d = 24: 19 us).
 inline size_t prep_lds_bytes(int dp, int format)
 {
-    return sizeof(float) * kPrepRows * (dp + 1) * (format == kFormatSplit3 ? 1 : 2);
+    return sizeof(float) * kPrepRows * (dp + 1) * (format == kFormatSplit3 || format == kFormatHalf2 ? 1 : 2);
 }
 
 // Grid: job0's blocks first (blocks0 of them), then job1's.
 __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob job1, int blocks0, int d, int dp,
-                                                           PrepCommon common, float a, int format, Stamp stamp)
+                                                           PrepCommon common, double a, int format, Stamp stamp)
 {
     __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
     extern __shared__ float prep_lds[];     // prep_lds_bytes: a (x - mean), then (fp16 formats) the hi + lo multiplied instead
     __shared__ int stamp_flag;
-    const bool poisoned = stamp_poisons(stamp, &stamp_flag);
-    prep_common(common, d, red, smean);
-
+    __shared__ uint32_t far_rows;
     const bool second = (int)blockIdx.x >= blocks0;
-    const PrepJob& job = second ? job1 : job0;
+    const PrepJob job = second ? job1 : job0;
     const int64_t r0 = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kPrepRows;
-    prep_rows<false>(job, r0, d, dp, a, format, poisoned, smean, prep_lds, prep_lds + kPrepRows * (dp + 1));
+    StagedRows staged;
+    staged.load(job, r0, d);
+    if (threadIdx.x == 0) far_rows = 0;
+    stamp_check(stamp, &stamp_flag);
+    prep_common(common, d, red, smean, [&] { staged.store(prep_lds, d, dp); });
+    const bool poisoned = stamp_flag != 0;
+    prep_rows(job, r0, d, dp, a, format, poisoned, smean, prep_lds, prep_lds + kPrepRows * (dp + 1), &far_rows);
 }
 
 // Thin-d variant: dst[row][d] = a (x - mean), padding rows get pad_value in every coordinate.
@@ -251,8 +477,9 @@ __global__ __launch_bounds__(kBlock) void prep_thin_kernel(PrepJob job0, PrepJob
     __shared__ double red[kBlock];
     __shared__ float smean[SDKDE_MAX_D];
     __shared__ int stamp_flag;
-    const bool poisoned = stamp_poisons(stamp, &stamp_flag);
-    prep_common(common, d, red, smean);
+    stamp_check(stamp, &stamp_flag);
+    prep_common(common, d, red, smean, [] {});
+    const bool poisoned = stamp_flag != 0;
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob& job = second ? job1 : job0;
     const int64_t row = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kBlock + threadIdx.x;

@@ -8,7 +8,7 @@
 // the squared distance in scaled units is directly the (negated) argument of exp2:
 //     phi_ij = exp2( 2 p~_i . x~_j - |p~_i|^2 - |x~_j|^2 ).
 // The cross term is the Gram-matrix tile of the Method section, computed with MFMAs (fp32 operands as
-// three bf16 parts each, split3.h); the score numerator uses Phi X with the Phi tile still in the
+// two fp16 parts each, half2.h); the score numerator uses Phi X with the Phi tile still in the
 // registers the first MFMA left it in.
 #include <string.h>
 #include <atomic>
@@ -16,6 +16,7 @@
 #include "common.h"
 #include "prep.h"
 #include "pair_mfma.h"
+#include "pair_half.h"
 #include "pair_split.h"
 #include "pair_sym.h"
 #include "pair_thin.h"
@@ -37,35 +38,30 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
                   : (kb == 1 ? 16 : kb == 2 ? 8 : kb <= 4 ? 4 : 2);
 }
 
-// Shapes of pair_split_kernel: a workgroup of `waves` waves of `ni` row tiles each holds 16 ni waves rows; the plan counts
+// Shapes of pair_half_kernel: a workgroup of `waves` waves of `ni` row tiles each holds 16 ni waves rows; the plan counts
 // them as rt = ni waves / 4 (so that a workgroup has 64 rt rows, as in the other kernels).  nb, ahead, minw: see there.
-// ni = 0: not built.  Clocks per 256 pairs and SIMD at 2.4 GHz of the kernels in the library, n = m = 65536, eight splits,
-// Gaussian mixture at the rule-of-thumb bandwidth (the clock sits under the power limit, so other data gives other figures:
-// eval is up to 8 % faster on operands of random bits); the sum of the MFMAs at 16 clocks and the vector work alone is
-// 218 / 318 / 419 / 520 for the score at dp = 16 .. 64:
-//   score  dp = 16   rt 8 / 4 / 2: 242 / 236 / 247        dp = 32  rt 4 / 2: 356 / 377    dp = 48  533 / 544
-//          dp = 64   643 / 669     dp = 80  820 / 885     dp = 96  983 / 1238 (one wave per SIMD)
-//          dp = 112  - / 1388      dp = 128 - / 1550
-//   eval   dp = 16   rt 8 / 4 / 2: 111 / 114 / 128        dp = 32  rt 4 / 2: 173 / 191    dp = 48  244 / 268
-//          dp = 64   302 / 329     dp = 80  373 / 409     dp = 96  502 / 484    dp = 112  645 / 577    dp = 128  626 / 646
-// At dp >= 112 the score's operands leave room for one wave per SIMD only (two would spill).
-struct SplitShape { int ni, waves, nb; bool ahead; int minw; };
-constexpr SplitShape split_shape(int kb, bool score, int rt)
+// ni = 0: not built.
+// Clocks of a wave's 16 x 16 pairs (as in pair_half.h) with rt = 2 / 4 / 8: score d = 16 187 / 180 / 178; eval d = 16 83 / 77 / 75.
+// Four row tiles a wave take the fewest operand reads that the registers allow up to dp = 32 (eval 96); above, eight waves of
+// two share a workgroup's reads instead.  The score at dp = 48 has four at the samples themselves only, without reading ahead
+// (both together spill), likewise four instead of eight at dp = 16 where rows may be scaled.
+struct HalfShape { int ni, waves, nb; bool ahead; int minw; };
+constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false)
 {
     if (score) {
-        if (rt == 2) return {2, 4, 2, kb != 5, kb == 1 ? 4 : kb <= 5 ? 2 : 1};
-        if (rt == 4) return kb <= 2 ? SplitShape{4, 4, 4, true, 2} : kb <= 6 ? SplitShape{2, 8, 2, kb < 6, 2} : SplitShape{};
-        if (rt == 8 && kb == 1) return {8, 4, 2, true, 2};
+        if (rt == 2) return {2, 4, 2, true, kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 ? 2 : 1};
+        if (rt == 4) return kb <= 2 ? HalfShape{4, 4, 4, true, 2} : kb == 3 && self ? HalfShape{4, 4, 2, false, 2} : kb <= 6 ? HalfShape{2, 8, 2, true, 2} : HalfShape{};
+        if (rt == 8 && kb == 1) return far ? HalfShape{4, 8, 2, true, 2} : HalfShape{8, 4, 2, true, 2};
     } else {
-        if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : 2};
-        if (rt == 4) return kb <= 5 ? SplitShape{4, 4, kb == 5 ? 2 : 4, false, kb <= 2 ? 3 : 2} : SplitShape{2, 8, 2, false, 2};
+        if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : kb <= 4 ? 3 : 2};
+        if (rt == 4) return kb <= 6 ? HalfShape{4, 4, kb <= 3 ? 4 : 2, false, kb <= 3 ? 3 : 2} : HalfShape{2, 8, 2, false, 2};
         if (rt == 8 && kb == 1) return {8, 4, 4, false, 2};
     }
     return {};
 }
-constexpr int max_split_rt(int kb, bool score)
+constexpr int max_half_rt(int kb, bool score)
 {
-    return split_shape(kb, score, 8).ni ? 8 : split_shape(kb, score, 4).ni ? 4 : 2;
+    return half_shape(kb, score, 8).ni ? 8 : half_shape(kb, score, 4).ni ? 4 : 2;
 }
 
 // Precision mode a call actually runs in: the thin path is fp32 VALU code; the fp16 second contraction is
@@ -94,7 +90,7 @@ inline uint32_t anchored_flags(uint32_t flags, bool self)
 
 struct Plan {
     bool thin;
-    bool split3;          // three-part operands (pair_split_kernel, pair_sym_kernel)
+    bool parts;           // the fp32 mode's matrix path: operands in parts, 6 bytes a value (pair_half_kernel; symmetric mode)
     int d, dp;            // true and padded dimension (thin: dp == d)
     int ni;               // MFMA: row tiles per wave; thin: rows per thread
     int rows_per_block;
@@ -108,14 +104,14 @@ struct Plan {
 };
 
 // How a call's prepared rows are held (common.h), and the scale of its coordinates: sqrt(c log2 e),
-// times sqrt 2 in the three-part format, which carries the factor 2 of the cross term in both of its operands.
+// times sqrt 2 in the fp32 mode's formats, which carry the factor 2 of the cross term in both of their operands.
 inline int operand_format(const Plan& p, uint32_t flags)
 {
-    return p.split3 ? kFormatSplit3 : (int)effective_prec(flags, p.thin, p.dp);
+    return p.parts ? (p.sym_on ? kFormatSplit3 : kFormatHalf2) : (int)effective_prec(flags, p.thin, p.dp);
 }
 inline double operand_scale(int format, double h)
 {
-    return sqrt(1.4426950408889634074 / (format == kFormatSplit3 ? h * h : 2.0 * h * h));
+    return sqrt(1.4426950408889634074 / (format == kFormatSplit3 || format == kFormatHalf2 ? h * h : 2.0 * h * h));
 }
 
 // Overrides of the plan's own choices, set through sdkde_set_tuning (tests and sweeps); 0: none.
@@ -132,9 +128,8 @@ constexpr int64_t kTargetBlocks = 2048;
 constexpr int kComputeUnits = 256;
 
 // Relative cost per unit of work of running the matrix-path kernels with `ni` row tiles per wave instead of the
-// best count (operand reuse against register pressure), measured on MI355X: the fp32 mode at n = m = 65536 with an earlier
-// order of the Gram products (by the present figures at split_shape the better count is another one for the score at
-// dp = 48 and eval at dp = 96 and 112, by 2, 4 and 12 %), the fp16 input modes at n = 131072 resp. n = 262144, m = 65536.
+// best count (operand reuse against register pressure), measured on MI355X: the fp32 mode by the figures at half_shape, the
+// fp16 input modes at n = 131072 resp. n = 262144, m = 65536.
 double row_tiles_penalty(bool score, int kb, int ni, uint32_t prec)
 {
     if (prec != SDKDE_PREC_FP32) {
@@ -150,11 +145,10 @@ double row_tiles_penalty(bool score, int kb, int ni, uint32_t prec)
     }
     if (score) {
         if (kb == 1) return ni == 8 ? 1.0 : ni == 4 ? 1.01 : 1.05;
-        if (kb == 3) return ni == 2 ? 1.0 : 1.06;
-        return ni == 4 ? 1.0 : kb == 6 ? 1.3 : 1.04;
+        return ni == 4 ? 1.0 : kb == 6 ? 1.3 : kb == 3 ? 1.06 : 1.04;
     }
-    if (kb == 1) return ni == 4 ? 1.0 : ni == 8 ? 1.02 : 1.085;
-    return kb >= 6 ? 1.0 : ni == 4 ? 1.0 : 1.05;
+    if (kb == 1) return ni == 8 ? 1.0 : ni == 4 ? 1.03 : 1.1;
+    return ni == 4 || kb == 8 ? 1.0 : kb >= 6 ? 1.07 : 1.05;
 }
 
 // Estimated time of the pair kernel plus its share of the epilogue for `ni` row tiles per wave and `nsplit`
@@ -174,16 +168,17 @@ double plan_cost(bool score, int kb, uint32_t prec, int64_t m, int64_t m_pad, in
     tps += tps & 1;
     const double slot_bytes = (double)m_pad * (score ? 16 * kb + 1 : 1) * 8.0;
     if (prec == SDKDE_PREC_FP32) {
-        // pair_split_kernel, fitted to sweeps at n = 600 .. 100000: four (eval: one) tiles' time to start a workgroup; waves of
+        // pair_half_kernel, with the constants that sweeps at n = 600 .. 100000 gave for three-part operands (its tiles are a
+        // third shorter; plans, and with them the sizes that workspaces are asked for, stay what they were): four (eval: one) tiles' time to start a workgroup; waves of
         // several workgroups are needed on a SIMD to overlap its matrix and vector work (score at n = 4096, d = 16: one
         // workgroup per compute unit 23.6 us, two 21.3; eval at 32768 x 4096: two 43.3 us, four 38.9); long workgroups
         // leave eval a longer tail (65536 x 8192: four per unit 118 us, eight 114); a slot moves at 6 TB/s.
         double work = (double)rounds * ni * (tps + (score ? 4.0 : 1.0)) * row_tiles_penalty(score, kb, ni, prec);
-        const int64_t waves = rounds * split_shape(kb, score, ni).waves / 4;
+        const int64_t waves = rounds * half_shape(kb, score, ni).waves / 4;
         if (waves == 1) work *= 1.3;
         else if (score && kb == 1 && waves == 2) work *= 1.02;
         else if (!score && kb <= 2 && waves <= 3) work *= waves == 2 ? 1.1 : 1.04;
-        const double tile_clk = score ? 115.0 + 130.0 * kb : 45.0 + 62.0 * kb;      // measured, see split_shape
+        const double tile_clk = score ? 115.0 + 130.0 * kb : 45.0 + 62.0 * kb;
         return work + (score ? 0.11 : 0.25) * ni * tps + nsplit * slot_bytes / 2500.0 / tile_clk;
     }
     const double work = (double)rounds * ni * (tps + 1.0) * row_tiles_penalty(score, kb, ni, prec);
@@ -220,7 +215,7 @@ double plan_cost_thin(bool score, int d, int64_t m, int64_t m_pad, int ntiles, i
 
 int most_row_tiles(int kb, bool score, uint32_t prec)
 {
-    return prec == SDKDE_PREC_FP32 ? max_split_rt(kb, score) : max_row_tiles(kb, score ? kScoreSelf : kEval, (int)prec);
+    return prec == SDKDE_PREC_FP32 ? max_half_rt(kb, score) : max_row_tiles(kb, score ? kScoreSelf : kEval, (int)prec);
 }
 
 Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
@@ -236,11 +231,11 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
     p.n_pad = round_up(n, kRowPad);
     p.m_pad = round_up(m > 0 ? m : 1, kRowPad);
     p.ntiles = (int)((n + 2 * kTile - 1) / (2 * kTile)) * 2;   // even: the pair kernel alternates two operand sets
-    // at least 16 tiles per split; the three-part kernels take 4 (score at n = 600, d = 8: 8 splits 14.2 us, 2 splits 17.8;
+    // at least 16 tiles per split; the fp32 mode's kernels take 4 (score at n = 600, d = 8: 8 splits 14.2 us, 2 splits 17.8;
     // eval at 4096 x 512, d = 64: 64 splits 15.9 us, 16 splits 20.7)
     const uint32_t prec = effective_prec(flags, false, p.dp);
-    p.split3 = !p.thin && prec == SDKDE_PREC_FP32;
-    const int least_tiles = p.split3 ? 4 : 16;
+    p.parts = !p.thin && prec == SDKDE_PREC_FP32;
+    const int least_tiles = p.parts ? 4 : 16;
     const int max_split = p.ntiles >= 2 * least_tiles ? p.ntiles / least_tiles : 1;
 
     // Candidate row-tile counts, largest (most operand reuse) first.
@@ -275,14 +270,14 @@ Plan make_plan(int64_t n, int64_t m, int d, bool score, uint32_t flags)
         if (p.row_blocks < 1) p.row_blocks = 1;
     };
 
-    if (max_split >= 8 || p.split3) {
+    if (max_split >= 8 || p.parts) {
         // Enough samples for one group of splits per XCD: the (row tiles or rows per thread, splits) pair of least
-        // estimated time; ties go to more rows per workgroup, then fewer splits.  Up to n = 16384 the three-part
+        // estimated time; ties go to more rows per workgroup, then fewer splits.  Up to n = 16384 the fp32 mode's
         // kernels may take fewer splits too: whole rounds of workgroups then count for more than each XCD streaming an
         // eighth of the samples.  Score with 7 / 8 / 16 splits at n = 9000: d = 16 50 / 56 / 52 us, d = 64 116 / 148 / 126,
         // d = 128 254 / 325 / 281; with 4 / 8 / 16 at n = 16000: d = 64 310 / 297 / 311, d = 128 682 / 704 / 758.
         const int most = max_split >= 8 ? (max_split / 8 * 8 < 1024 ? max_split / 8 * 8 : 1024) : max_split;
-        const int first = forced_split > 0 ? forced_split : p.split3 && p.ntiles <= 1024 ? 1 : 8;
+        const int first = forced_split > 0 ? forced_split : p.parts && p.ntiles <= 1024 ? 1 : 8;
         const int last = forced_split > 0 ? forced_split : most;
         double best = 0.0;
         int best_ni = 0, best_split = 0;
@@ -366,11 +361,10 @@ void apply_symmetric(Plan& p, int64_t n, uint32_t flags, bool self)
     // Below 512 work items (two rounds of one per CU) the ordinary kernels are well ahead and the flag is ignored
     // (SDKDE_TUNE_SYM_MIN_ITEMS: for tests of the mode at small sizes).  The line is where the mode began to pay with fp32
     // MFMAs, and callers that set the flag get the mode, its workspace and its summation order from there on; with
-    // three-part operands it pays at dp = 16 from about 131072 samples only.  Score, symmetric / ordinary: d = 16 n = 32768
-    // 455 / 425 us, 65536 1.67 / 1.61 ms, 100000 3.79 / 3.74, 131072 6.02 / 6.38, 262144 23.6 / 25.0, 1048576 373 / 398;
-    // d = 8 n = 32768 455 / 414 us, 131072 6.01 / 6.17 ms; d = 32 n = 16384 225 / 176 us, 100000 6.58 / 5.83 ms, 524288
-    // 162 / 153.  (The vector work the mode halves and the matrix work it cuts by a quarter have become cheaper than its
-    // transposes, folds and phase barriers.)
+    // the ordinary kernels on two fp16 parts it no longer pays: its own are on three bf16 parts, and the vector work it
+    // halves and the matrix work it cuts by a quarter have become cheaper than its transposes, folds and phase barriers.
+    // Score, symmetric / ordinary: d = 16 n = 32768 482 / 387 us, 131072 5.99 / 4.76 ms, 262144 23.4 / 18.5; d = 8 n = 131072
+    // 5.99 / 4.38 ms; d = 32 n = 16384 229 / 130 us, 100000 6.27 / 3.87 ms.
     int min_items = tuning(SDKDE_TUNE_SYM_MIN_ITEMS, 512);
     if (min_items < 1) min_items = 1;
     if ((int64_t)ngroups * (ngroups + 1) / 2 < min_items) return;
@@ -387,6 +381,7 @@ struct Workspace {
     uint64_t* stamp;                       // record of the last sample preparation (prep.h)
     float* xs;  float* xt;  float* xn;     // samples: scaled rows, blocked transpose, -|x|^2
     float* ps;  float* pn;                 // evaluation points (alias xs/xn when they are the samples)
+    float* residual;                       // of points held in two parts, behind their rows (half2.h)
     float* shift;                          // per-point exponent shift of the max-shifted mode (separate points only)
     float* part_t;  float* part_d;
     size_t bytes;
@@ -406,7 +401,7 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
     w.centre = (float*)take(sizeof(float) * SDKDE_MAX_D);
     w.stamp = (uint64_t*)take(sizeof(uint64_t) * kStampWords);
     const int format = operand_format(p, flags);
-    auto rows_floats = [&](int64_t rows) { return (size_t)(format == kFormatSplit3 ? split3_floats(rows, p.dp) : rows * p.dp); };
+    auto rows_floats = [&](int64_t rows) { return (size_t)(p.parts ? split3_floats(rows, p.dp) : rows * p.dp); };
     w.xs = (float*)take(sizeof(float) * rows_floats(p.n_pad));
     // blocked transpose for the second contraction: as the rows, or hi/lo fp16 pairs stored twice (2x the bytes)
     const size_t xt_scale = format == SDKDE_PREC_FP16X2_ALL ? 2 : 1;
@@ -414,6 +409,7 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
     w.xn = (float*)take(sizeof(float) * p.n_pad);
     if (separate_points) {
         w.ps = (float*)take(sizeof(float) * rows_floats(p.m_pad));
+        if (format == kFormatHalf2) w.residual = half2_residual(w.ps, p.m_pad, p.dp);
         w.pn = (float*)take(sizeof(float) * p.m_pad);
         w.shift = (float*)take(sizeof(float) * p.m_pad);
     } else {
@@ -433,7 +429,7 @@ bool bad_bandwidth(double h) { return !(h > 0.0) || !isfinite(h); }
 
 // One group of splits per XCD, or a single split for tiny sample sets and on the matrix path: there a buffer may have been
 // made for a plan with fewer splits (the fp32 mode takes five at 13000 samples of d = 16) and is used in another mode, and
-// the three-part copies are half as large again, so that calls may have to give up more slots for them.
+// the fp32 mode's prepared rows are half as large again, so that calls may have to give up more slots for them.
 inline int least_splits(const Plan& p) { return p.ntiles >= 128 && p.thin ? 8 : 1; }
 
 // For a workspace smaller than the plan's own decomposition needs (a buffer sized for another m, say): halves the
@@ -458,16 +454,16 @@ bool fit_workspace(Plan& p, bool score, bool separate_points, void* base, size_t
     return w->bytes <= bytes;
 }
 
-// As above for separate points on the three-part operands, which take 6 bytes a value of a prepared point.  A buffer that
+// As above for separate points in the fp32 mode, which takes 6 bytes a value of a prepared point.  A buffer that
 // would hold the call with 4 bytes a value (640000 queries at dp = 16, one split: 49 MB, with 6 bytes 69 MB) serves it all
 // the same, the points in equal batches of whole workgroups' rows, one pass after the other; the plan is then one batch's.
 // Smaller buffers are refused.  Returns the points of a batch (m: all of them); 0: does not fit.
 int64_t fit_points(Plan& p, bool score, void* base, size_t bytes, uint32_t flags, int64_t m, Workspace* w)
 {
     if (fit_workspace(p, score, true, base, bytes, flags, w)) return m;
-    if (!p.split3) return 0;
+    if (!p.parts) return 0;
     Plan four_bytes = p;
-    four_bytes.split3 = false;
+    four_bytes.parts = false;
     if (layout(four_bytes, score, true, base, flags).bytes > bytes) return 0;
     const int64_t all = p.row_blocks;
     auto fits = [&](int64_t blocks) {
@@ -544,21 +540,17 @@ int launch_thin(const Plan& p, const Workspace& w, const float* shift, hipStream
     return launched();
 }
 
-// The fp32 mode at d >= 4 (score kinds d >= 7).
-template <int KIND, int KB, int RT>
-int launch_split_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+// The fp32 mode at d >= 4 (score kinds d >= 7).  FAR: the max-shifted sums, whose points may lie beyond the fp16 range.
+template <int KIND, bool FAR, int KB, int TAIL, int RT>
+int launch_half_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
-    constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints || KIND == kScoreBand;
-    constexpr SplitShape sh = split_shape(KB, score, RT);
+    constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints;
+    constexpr HalfShape sh = half_shape(KB, score, RT, KIND == kScoreSelf, FAR);
     if constexpr (sh.ni == 0) {
         return SDKDE_EUNSUPPORTED;
     } else {
         static_assert(sh.ni * sh.waves == 4 * RT, "64 rt rows per workgroup");
-        // One MFMA a sample tile where the general form takes three and one fp32 MFMA took 32 clocks: shifted eval of
-        // 262144 x 65536 at d = 4 3.94 ms, with three 4.74, with the fp32 one 4.44; 65536 x 8192 161, 187 and 180 us.
-        if constexpr (KIND == kRowMax && KB == 1)
-            if (p.d <= 4) return launch_split_shape<kRowMaxFour, KB, RT>(p, w, shift, st);
-        hipLaunchKernelGGL((pair_split_kernel<KB, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND>),
+        hipLaunchKernelGGL((pair_half_kernel<KB, TAIL, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND, FAR>),
                            dim3((unsigned)(p.row_blocks * p.nsplit)), dim3(sh.waves * kWave), 0, st, w.ps, w.pn, w.xs, w.xt,
                            w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,
                            1.0f + 0.5f * (float)p.d, shift);
@@ -566,29 +558,30 @@ int launch_split_shape(const Plan& p, const Workspace& w, const float* shift, hi
     }
 }
 
-template <int KIND, int KB>
-int launch_split_kb(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+template <int KIND, bool FAR, int KB, int TAIL>
+int launch_half_tail(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
     switch (p.ni) {
-        case 8: return launch_split_shape<KIND, KB, 8>(p, w, shift, st);
-        case 4: return launch_split_shape<KIND, KB, 4>(p, w, shift, st);
-        case 2: return launch_split_shape<KIND, KB, 2>(p, w, shift, st);
+        case 8: return launch_half_shape<KIND, FAR, KB, TAIL, 8>(p, w, shift, st);
+        case 4: return launch_half_shape<KIND, FAR, KB, TAIL, 4>(p, w, shift, st);
+        case 2: return launch_half_shape<KIND, FAR, KB, TAIL, 2>(p, w, shift, st);
         default: return SDKDE_EUNSUPPORTED;
     }
 }
 
-template <int KIND>
-int launch_split(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+template <int KIND, bool FAR>
+int launch_half(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
+    const bool eight = half_tail(p.d) == kTailEight;
     switch (p.dp / 16) {
-        case 1: return launch_split_kb<KIND, 1>(p, w, shift, st);
-        case 2: return launch_split_kb<KIND, 2>(p, w, shift, st);
-        case 3: return launch_split_kb<KIND, 3>(p, w, shift, st);
-        case 4: return launch_split_kb<KIND, 4>(p, w, shift, st);
-        case 5: return launch_split_kb<KIND, 5>(p, w, shift, st);
-        case 6: return launch_split_kb<KIND, 6>(p, w, shift, st);
-        case 7: return launch_split_kb<KIND, 7>(p, w, shift, st);
-        case 8: return launch_split_kb<KIND, 8>(p, w, shift, st);
+        case 1: return eight ? launch_half_tail<KIND, FAR, 1, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 1, kTailSixteen>(p, w, shift, st);
+        case 2: return launch_half_tail<KIND, FAR, 2, kTailNone>(p, w, shift, st);
+        case 3: return eight ? launch_half_tail<KIND, FAR, 3, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 3, kTailSixteen>(p, w, shift, st);
+        case 4: return launch_half_tail<KIND, FAR, 4, kTailNone>(p, w, shift, st);
+        case 5: return eight ? launch_half_tail<KIND, FAR, 5, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 5, kTailSixteen>(p, w, shift, st);
+        case 6: return launch_half_tail<KIND, FAR, 6, kTailNone>(p, w, shift, st);
+        case 7: return eight ? launch_half_tail<KIND, FAR, 7, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 7, kTailSixteen>(p, w, shift, st);
+        case 8: return launch_half_tail<KIND, FAR, 8, kTailNone>(p, w, shift, st);
         default: return SDKDE_EUNSUPPORTED;
     }
 }
@@ -646,7 +639,11 @@ int launch_pair_prec(const Plan& p, const Workspace& w, uint32_t flags, const fl
     // the thin-d path has no matrix inputs: it runs the same fp32 VALU code for every mode
     if (p.thin) return launch_thin<KIND>(p, w, shift, st);
     const uint32_t prec = effective_prec(flags, p.thin, p.dp);
-    if (prec == SDKDE_PREC_FP32) return launch_split<KIND>(p, w, shift, st);
+    if (prec == SDKDE_PREC_FP32) {
+        if constexpr (KIND == kScoreSelf) return launch_half<KIND, false>(p, w, shift, st);
+        else if constexpr (KIND == kRowMax) return launch_half<KIND, true>(p, w, shift, st);
+        else return shift ? launch_half<KIND, true>(p, w, shift, st) : launch_half<KIND, false>(p, w, shift, st);
+    }
     if constexpr (KIND == kScoreSelf || KIND == kScorePoints) {
         if (prec == SDKDE_PREC_FP16X2_ALL) return launch_mfma<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
         if (prec == SDKDE_PREC_FP16X2_PHI16) return launch_mfma<KIND, SDKDE_PREC_FP16X2_PHI16>(p, w, shift, st);
@@ -697,7 +694,9 @@ int launch_sym_kernel(const Plan& p, const Workspace& w, hipStream_t st)
     Workspace wb = w;                               // its slots follow pair_sym_kernel's
     wb.part_t = w.part_t + (size_t)(p.sym_ngroups + 1) * p.m_pad * p.dp;
     wb.part_d = w.part_d + (size_t)(p.sym_ngroups + 1) * p.m_pad;
-    return launch_split_shape<kScoreBand, KB, 4>(band, wb, nullptr, st);
+    hipLaunchKernelGGL((pair_split_kernel<KB, 4, kWavesPerBlock, 4, true, 2>), dim3((unsigned)band.row_blocks), dim3(kBlock), 0, st,
+                       wb.xs, wb.xt, wb.xn, wb.part_t, wb.part_d, band.ntiles, band.tiles_per_split);
+    return launched();
 }
 
 int launch_symmetric(const Plan& p, const Workspace& w, hipStream_t st)
@@ -729,7 +728,7 @@ int launch_max_shift(const Plan& p, const Workspace& w, uint32_t flags, hipStrea
     int rc = launch_pair_prec<kRowMax>(p, w, flags, nullptr, st);
     if (rc != SDKDE_OK) return rc;
     SDKDE_LAUNCH_EPILOGUE(shift_kernel, p.nsplit, p.m_pad, st, w.part_d, p.nsplit, p.m_pad, w.shift,
-                          p.thin ? nullptr : w.pn);
+                          p.thin ? nullptr : w.pn, w.residual);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
@@ -751,9 +750,9 @@ Stamp make_stamp(const Workspace& w, bool check, bool score, const float* sample
 }
 
 int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, const float* centre_src, int64_t centre_n,
-                float a, const Workspace& w, uint32_t flags, const Stamp& stamp, hipStream_t st)
+                double a, const Workspace& w, uint32_t flags, const Stamp& stamp, hipStream_t st)
 {
-    const PrepCommon common{centre_src, centre_n, w.centre};
+    const PrepCommon common = centre_of(centre_src, centre_n, p.d, w.centre);
     const int64_t per_block = p.thin ? kBlock : kPrepRows;
     if (first.rows_pad % per_block || (second.src && second.rows_pad % per_block)) return SDKDE_EINVAL;
     const int64_t blocks0 = first.rows_pad / per_block;
@@ -761,7 +760,7 @@ int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, cons
     if (blocks0 + blocks1 > 0x7fffffffLL) return SDKDE_EUNSUPPORTED;
     const dim3 grid((unsigned)(blocks0 + blocks1)), block(kBlock);
     if (p.thin)
-        hipLaunchKernelGGL(prep_thin_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, common, a, stamp);
+        hipLaunchKernelGGL(prep_thin_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, common, (float)a, stamp);
     else
         hipLaunchKernelGGL(prep_mfma_kernel, grid, block, prep_lds_bytes(p.dp, operand_format(p, flags)), st, first, second, (int)blocks0, p.d, p.dp, common, a,
                            operand_format(p, flags), stamp);
@@ -829,8 +828,8 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     if (we.xs != ws.xs || wr_begin < dead_begin || wr_end > dead_end) return false;
     if ((const char*)we.ps < (const char*)(we.xn + pe.n_pad)) return false;
     const double a = operand_scale(format, h);
-    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true};
-    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false};
+    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false};
+    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false};
     out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a);
     return true;
 }
@@ -849,11 +848,11 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true};
-    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, false};
+    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted};
     const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
-    rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, (float)a, w, flags, stamp, st)
-                       : launch_prep(p, sample_job, point_job, samples, n, (float)a, w, flags, stamp, st);
+    rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
+                       : launch_prep(p, sample_job, point_job, samples, n, a, w, flags, stamp, st);
     if (rc != SDKDE_OK) return rc;
 
     if ((rc = profile_mark(0, 0, st)) != SDKDE_OK) return rc;
@@ -883,7 +882,7 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
                                prep_lds_bytes(p.dp, format), st, w.part_t,
                                w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, format, inv_ah2, score_out, samples, half_h2,
                                samples_sd_out, quad_io, fused->sd_job, fused->q_job, blocks_sd,
-                               PrepCommon{nullptr, 0, w.centre}, (float)a, fused->stamp);
+                               w.centre, a, fused->stamp);
             return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
         }
         hipLaunchKernelGGL(score_epilogue_quad_kernel, dim3((unsigned)((quads + per_wg - 1) / per_wg)), dim3(kBlock), 0, st,
@@ -942,14 +941,14 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
     const int format = operand_format(p, flags);
     const double a = operand_scale(format, h);
     const bool shifted = (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true};
-    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true, false};
+    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted};
     // all_prepared (sdkde_fit_eval): the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
     if (!all_prepared) {
         const Stamp stamp = make_stamp(w, samples_ready, false, samples, n, d, format, (float)a);
         // reuse_centre: w.centre still holds the centre of an earlier pass over (nearly) the same points
-        rc = samples_ready ? launch_prep(p, query_job, PrepJob{}, nullptr, 0, (float)a, w, flags, stamp, st)
-                           : launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, (float)a, w, flags, stamp, st);
+        rc = samples_ready ? launch_prep(p, query_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
+                           : launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, a, w, flags, stamp, st);
         if (rc != SDKDE_OK) return rc;
     }
 
@@ -962,7 +961,7 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
     if ((rc = profile_mark(1, 1, st)) != SDKDE_OK) return rc;
 
     SDKDE_LAUNCH_EPILOGUE(eval_epilogue_kernel, p.nsplit, m, st, w.part_d, p.nsplit, m, p.m_pad, lognorm, laplace ? 1 : 0,
-                          shift, least_trusted_sum(n), density_out, log_density_out);
+                          shift, w.residual, least_trusted_sum(n), density_out, log_density_out);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
@@ -1077,7 +1076,7 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     int rc = check_common(samples, n, m, d, h, flags);
     if (rc != SDKDE_OK) return rc;
     // The pass takes the decomposition the ordinary call would take, so that both give the same bits, where the built-in
-    // buffer holds a workspace of sdkde_workspace_bytes.  A pass that needs more is served on the three-part operands
+    // buffer holds a workspace of sdkde_workspace_bytes.  A pass that needs more is served on the fp32 mode's operands
     // while both of its steps fit with fewer splits or the queries in batches, and refused before anything is launched
     // otherwise.
     Plan score_plan = make_plan(n, n, d, true, flags), eval_plan = make_plan(n, m, d, false, flags);
@@ -1085,7 +1084,7 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     Workspace unused;
     size_t need = 0;
     if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
-    if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES && !score_plan.split3 && !eval_plan.split3) return SDKDE_ETOOLARGE;
+    if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES && !score_plan.parts && !eval_plan.parts) return SDKDE_ETOOLARGE;
     if (!fit_workspace(score_plan, true, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused) ||
         (m > 0 && !fit_points(eval_plan, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, m, &unused)))
         return SDKDE_ETOOLARGE;

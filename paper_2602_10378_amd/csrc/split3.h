@@ -1,11 +1,11 @@
-// Three-part bf16 operands of the fp32 path: layout of the prepared arrays and the splits.
+// Three-part bf16 operands of the fp32 mode's symmetric path: layout of the prepared arrays and the splits.
 #pragma once
 #include "common.h"
 
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// The fp32 path multiplies on the bf16 matrix units without giving up fp32 operands: every fp32 value v is held as
+// The symmetric path multiplies on the bf16 matrix units without giving up fp32 operands: every fp32 value v is held as
 // three bf16 parts h + m + l = v (8 significant bits each; the 24 bits of v exactly, at any magnitude whose last bit
 // is a normal bf16 number), and a product a b is summed over six of its nine part products,
 //     ah bh + ah bm + am bh + am bm + ah bl + al bh,
@@ -29,6 +29,7 @@ namespace {
 // ------------------------------------------------------------------------------------------
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kChunkRows = 32;
@@ -51,29 +52,14 @@ __device__ __forceinline__ int64_t split3_offset(int64_t row, int c, int dp, int
 
 __device__ __forceinline__ float bf16_value(uint16_t bits) { return __builtin_bit_cast(float, (uint32_t)bits << 16); }
 
-// The fp32 value the three parts stand for (their sum is exact).
-__device__ __forceinline__ float split3_value(const void* ps, int64_t row, int c, int dp)
+// Four fp32 values from their three parts (the sums are exact).
+__device__ __forceinline__ f32x4 split3_sum(const u32x2 (&part)[3])
 {
-    int stride;
-    const char* at = reinterpret_cast<const char*>(ps) + split3_offset(row, c, dp, &stride);
-    const uint16_t h = *reinterpret_cast<const uint16_t*>(at), m = *reinterpret_cast<const uint16_t*>(at + stride),
-                   l = *reinterpret_cast<const uint16_t*>(at + 2 * stride);
-    return bf16_value(h) + (bf16_value(m) + bf16_value(l));
-}
-
-// Columns c .. c+3 (c a multiple of four) of a row.
-__device__ __forceinline__ f32x4 split3_quad(const void* ps, int64_t row, int c, int dp)
-{
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    int stride;
-    const char* at = reinterpret_cast<const char*>(ps) + split3_offset(row, c, dp, &stride);
     f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int q = 2; q >= 0; --q) {
-        const u32x2 part = *reinterpret_cast<const u32x2*>(at + q * stride);
-        v += f32x4{bf16_value(part.x & 0xffffu), __builtin_bit_cast(float, part.x & 0xffff0000u),
-                   bf16_value(part.y & 0xffffu), __builtin_bit_cast(float, part.y & 0xffff0000u)};
-    }
+    for (int q = 2; q >= 0; --q)
+        v += f32x4{bf16_value(part[q].x & 0xffffu), __builtin_bit_cast(float, part[q].x & 0xffff0000u),
+                   bf16_value(part[q].y & 0xffffu), __builtin_bit_cast(float, part[q].y & 0xffff0000u)};
     return v;
 }
 

@@ -44,7 +44,7 @@ def bound_seconds(n: int, m: int, d: int) -> float:
     total = 0.0
     for stage, rows in (("score", n), ("eval", m)):
         plan = B.sdkde_describe_plan(n, rows, d, 0 if stage == "score" else 2)
-        r = cm.roofline(stage, d, float(rows) * n, 1.0, "bf16x3", bool(plan["thin"]))
+        r = cm.roofline(stage, d, float(rows) * n, 1.0, "half2", bool(plan["thin"]))
         total += max(r["seconds_at_peak"].values())
     return total
 
