@@ -154,3 +154,29 @@ def test_points_that_are_not_finite(d):
         assert np.isnan(got[[7, 22]]).all()
         rest = np.setdiff1d(np.arange(m), [7, 22])
         assert np.all(np.abs(got[rest] - want[rest]) <= 1e-4)
+
+
+@pytest.mark.parametrize("d", [17, 32, 44, 48, 90, 128])
+def test_shift_from_leading_products(d):
+    """The shift of max-shifted sums comes from leading products up to a squared norm of 4096 and from all of them beyond: points
+    on both sides of that line, some of them far from every sample, one wave's rows mixed and not."""
+    import paper_2602_10378_amd as P
+    P.load()
+    rng = np.random.default_rng(d)
+    n, m, h = 1500, 700, 0.5
+    x = rng.standard_normal((n, d)) * 2.0
+    x[: n // 3] += 30.0 / np.sqrt(d)                              # clusters: samples with large norms, too
+    q = rng.standard_normal((m, d))
+    radius = np.repeat([1.0, 15.0, 26.0, 27.0, 40.0, 200.0], m // 6 + 1)[:m]     # 64 in units of h / sqrt(log2 e): 26.6
+    radius[m // 2:] = rng.permutation(radius[m // 2:])
+    q *= (radius / np.linalg.norm(q, axis=1))[:, None]
+    x, q = x.astype(np.float32), q.astype(np.float32)
+    print(f"leading products d={d}", flush=True)
+    xd, qd = _gpu(x, q)
+    flags = P.SDKDE_FLAG_MAX_SHIFT
+    ref, e = oracle.eval_log_density(x, q, h), gram_exponent_error(x, q, h)
+    logd = P.sdkde_eval(xd, qd, h, want="log", flags=flags)[1].cpu().numpy()
+    assert np.all(np.abs(logd - ref) <= e + 2.0**-18 + 2.0**-23 * np.abs(ref))
+    bound = _score_bound(x, q, h)
+    err = np.linalg.norm(P.sdkde_score(xd, h, points=qd, flags=flags).cpu().numpy() - oracle.score(x, h, points=q), axis=1)
+    assert np.all(err <= bound), (err / bound).max()
