@@ -26,6 +26,8 @@ namespace {
 //     Behind it, at 1024 + 16 r, what fills the columns that the block's second operand (its only one, if it has at most
 //     eight columns) leaves: kTermFactor, 2^7 of what rounding the norm left, and the second parts of four columns (the
 //     products l l of which then are in the sum, too): columns 8 .. 11 of the block, or 0 .. 3 of eight.
+//   a last 32-column block of at most 24 columns (kTailSpare): kTermFactor and the norm's residual in the first parts of columns
+//     24 .. 27, zeros behind and in the second parts.
 // Prepared transpose ("xt"), chunks of KB * 3072 bytes: 16-column block mb, part q (h, l, 2^-11 h) at mb * 3072 + q * 1024; lane
 //   16 g + r holds column 16 mb + r of rows 4g .. 4g+3 of the first tile and 4g .. 4g+3 of the second, which is the order the
 //   Gram accumulators of the two tiles leave Phi in.
@@ -42,9 +44,20 @@ constexpr float kHalfMax = 65504.0f;             // largest finite fp16 value
 constexpr float kFarPoint = 2047.0f;
 constexpr float kWeightScale = 2048.0f;          // see pair_half.h
 constexpr int half_tile_bytes(int kb) { return kb * 1024 + (kb % 2) * 256; }
-// How the columns beyond whole 32-column blocks are held: none, 9 .. 16 in a 16-column block (two MFMAs), 1 .. 8 (one).
-enum HalfTail { kTailNone = 0, kTailSixteen = 1, kTailEight = 2 };
-__host__ __device__ constexpr int half_tail(int d) { return (d + 15) / 16 % 2 == 0 ? kTailNone : (d - 1) % 16 < 8 ? kTailEight : kTailSixteen; }
+// How the columns beyond whole 32-column blocks are held: none, 9 .. 16 in a 16-column block (two MFMAs), 1 .. 8 (one); 17 .. 24
+// in a 32-column block whose last lane group is free for the row's term (with fewer than eight free columns the term would share
+// its lane group with coordinates, whose products an MFMA then truncates at 2^-24 of the term).
+enum HalfTail { kTailNone = 0, kTailSixteen = 1, kTailEight = 2, kTailSpare = 3 };
+// Added in free columns instead of by four vector instructions a tile the term costs nothing but its split at the start of a row.
+// Adding / in the columns of 17 to 24 of 32: eval of 10000 points against 50000 samples d = 24 110 / 100 us, d = 56 169 / 164, of
+// 8000 points d = 120 258 / 250; max-shifted d = 24 178 / 154; score n = 20000 d = 56 318 / 315, n = 15000 d = 120 458 / 448.  The
+// score at the samples themselves at d <= 24 adds: n = 3000 20.6 / 21.2 (the split of the term), n = 20000 within 2 %.
+constexpr int half_tail(int d, bool self_score)
+{
+    const int last = (d - 1) % 32 + 1;
+    if (self_score && d <= 24 && last > 16) return kTailNone;
+    return last <= 8 ? kTailEight : last <= 16 ? kTailSixteen : last <= 24 ? kTailSpare : kTailNone;
+}
 
 // A value in two parts, the first in the low half of the word.
 __device__ __forceinline__ uint32_t half2_split(float v, float low)       // v + low

@@ -22,7 +22,7 @@ namespace {
 template <int KB, int TAIL, int NI, bool SCORE>
 struct HalfRows {
     static constexpr int PAIRS = KB / 2;            // 32-column blocks
-    static constexpr bool ODD = TAIL != kTailNone;
+    static constexpr bool ODD = TAIL == kTailSixteen || TAIL == kTailEight, SPARE = TAIL == kTailSpare;
     static constexpr int TERM = TAIL == kTailSixteen ? 1 : 0;           // operand and lane group that hold the term
     static constexpr int TERM_GROUP = TAIL == kTailSixteen ? 2 : 3;
     f16x8 b[NI][PAIRS > 0 ? PAIRS : 1][2];          // h, l
@@ -54,31 +54,39 @@ struct HalfRows {
                 // d = 16: error 4.9e-7 with them, 3.2e-7 without)
                 e = SCORE ? f16x8{0, 0, 0, (_Float16)kResidualFactor, e[0], e[1], e[2], e[3]} : f16x8{0, 0, 0, 0, 0, 0, 0, 0};
             }
+            if (SPARE && g == TERM_GROUP) b[t][SPARE ? PAIRS - 1 : 0][0] = f16x8{0, 0, 0, SCORE ? (_Float16)kResidualFactor : (_Float16)0, 0, 0, 0, 0};
             term[t] = pn[row0 + t * kTile + r];
         }
     }
     // What rounding the row's norm left, from its prepared row.
     __device__ __forceinline__ float residual(const float* __restrict__ ps, int64_t row) const
     {
-        if (!ODD) return 0.0f;
+        if (TAIL == kTailNone) return 0.0f;
         const char* tile = reinterpret_cast<const char*>(ps) + row / kTile * (int64_t)half_tile_bytes(KB);
-        return (float)reinterpret_cast<const _Float16*>(tile + PAIRS * 2048 + 1024 + row % kTile * 16)[3] * kResidualFactor;
+        const char* at = SPARE ? tile + (PAIRS - 1) * 2048 + TERM_GROUP * 256 : tile + PAIRS * 2048 + 1024;
+        return (float)reinterpret_cast<const _Float16*>(at + row % kTile * 16)[3] * kResidualFactor;
     }
     // Products as the eval kinds and the row maxima have them.
     __device__ __forceinline__ void bare(int g)
     {
 #pragma unroll
         for (int t = 0; t < NI; ++t)
-            if (ODD && g == TERM_GROUP) o[ODD ? t : 0][TERM] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            if (g == TERM_GROUP) {
+                if (ODD) o[ODD ? t : 0][TERM] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                if (SPARE) b[t][SPARE ? PAIRS - 1 : 0][0] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            }
     }
     // The row's term in the spare columns of the last operand.
     __device__ __forceinline__ void place_term(int t, float v, float residual, int g)
     {
-        if (!ODD) return;
+        if (TAIL == kTailNone) return;
         _Float16 part[3];
         split_term(v, residual, part);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) o[t][TERM][q] = g == TERM_GROUP ? part[q] : o[t][TERM][q];
+        for (int q = 0; q < 3; ++q) {
+            f16x8& e = ODD ? o[ODD ? t : 0][TERM] : b[t][SPARE ? PAIRS - 1 : 0][0];
+            e[q] = g == TERM_GROUP ? part[q] : e[q];
+        }
     }
 };
 
@@ -117,12 +125,12 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     int ntiles, int tiles_per_split, int nsplit, int64_t m_pad, float laplace_c0, const float* __restrict__ shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
-    static_assert((KB % 2 != 0) == (TAIL != kTailNone), "an odd block count has a tail");
+    static_assert((KB % 2 != 0) == (TAIL == kTailSixteen || TAIL == kTailEight), "an odd block count has a tail");
     constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints;
     constexpr bool SELF = KIND == kScoreSelf;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
     constexpr bool ROWMAX = KIND == kRowMax;
-    constexpr bool ODD = TAIL != kTailNone;
+    constexpr bool ODD = HalfRows<KB, TAIL, NI, SCORE>::ODD, TERMED = TAIL != kTailNone;
     constexpr int DP = KB * 16;
     constexpr int KT = SCORE ? KB : 1;
     constexpr int PAIRS = KB / 2;
@@ -218,9 +226,9 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
         constexpr bool LEAD = decltype(lead)::value;        // ROWMAX: leading products of whole blocks only
 #pragma unroll
         for (int t = 0; t < NB; ++t) {
-            const float add = ODD ? 0.0f : rows.term[t0 + t];
-            c[t][0] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : ODD ? nj0 : nj0 + add;
-            c[t][1] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : ODD ? nj1 : nj1 + add;
+            const float add = TERMED ? 0.0f : rows.term[t0 + t];
+            c[t][0] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj0 : nj0 + add;
+            c[t][1] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj1 : nj1 + add;
         }
         if (AHEAD) read_gram(xc, 0, ga[0]);
 #pragma unroll

@@ -107,6 +107,7 @@ struct PrepJob {
     float pad_value;      // thin path only: coordinate value of padding rows
     bool samples;         // the rows are summed over (not only evaluated at)
     bool shifted;         // points of max-shifted sums
+    int tail;             // kFormatHalf2: half_tail of the kernel they are for
 };
 
 // Record of what a prep launch left in the workspace (sample arrays and column sums), kept in the workspace itself:
@@ -241,7 +242,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         }
         __syncthreads();
     }
-    const int kb = dp / 16;
+    const int kb = dp / 16, tail = job.tail;
     char* const rows_out = reinterpret_cast<char*>(job.dst) + r0 / kTile * half_tile_bytes(kb);
     char* const t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
     if (threadIdx.x >= kBlock - kPrepRows) {        // the last wave: at dp = 16 it has no other items
@@ -276,15 +277,18 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
             half2_residual(job.dst, job.rows_pad, dp)[row] = left;
             half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         }
-        if (kb % 2 != 0) {              // what goes into the tail's spare columns
-            const int block = dp - 16, lows = half_tail(d) == kTailSixteen ? block + 8 : block;
+        if (tail != kTailNone) {        // what goes into the last block's spare columns
+            const int block = dp - 16, lows = tail == kTailEight ? block : block + 8;
             uint32_t e[4];
             auto half_bits = [](float v) { return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v); };
             e[0] = half_bits(kTermFactor[0]) | half_bits(kTermFactor[1]) << 16;
             e[1] = half_bits(kTermFactor[2]) | half_bits(left * (1.0f / kResidualFactor)) << 16;
             e[2] = w[lows] >> 16 | (w[lows + 1] & 0xffff0000u);
             e[3] = w[lows + 2] >> 16 | (w[lows + 3] & 0xffff0000u);
-            *reinterpret_cast<u32x4*>(rows_out + rr / kTile * half_tile_bytes(kb) + kb / 2 * 2048 + 1024 + rr % kTile * 16) = u32x4{e[0], e[1], e[2], e[3]};
+            int stride_of;
+            char* const at = tail == kTailSpare ? rows_out + half2_offset(rr, dp - 8, dp, &stride_of)
+                                                : rows_out + rr / kTile * half_tile_bytes(kb) + kb / 2 * 2048 + 1024 + rr % kTile * 16;
+            *reinterpret_cast<u32x4*>(at) = u32x4{e[0], e[1], tail == kTailSpare ? 0u : e[2], tail == kTailSpare ? 0u : e[3]};
         }
     }
     // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other (at dp = 16
@@ -316,7 +320,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
             const _Float16 s0 = (_Float16)(half_low(word[2 * k]) * (1.0f / kWeightScale)), s1 = (_Float16)(half_low(word[2 * k + 1]) * (1.0f / kWeightScale));
             scaled[k] = (uint32_t)__builtin_bit_cast(uint16_t, s0) | (uint32_t)__builtin_bit_cast(uint16_t, s1) << 16;
         }
-        *reinterpret_cast<u32x4*>(at) = h;
+        if (!(of_row && tail == kTailSpare && at_item / kPrepRows * 8 == dp - 8)) *reinterpret_cast<u32x4*>(at) = h;     // (see above)
         *reinterpret_cast<u32x4*>(at + part_stride) = l;
         if (!of_row) *reinterpret_cast<u32x4*>(at + 2 * part_stride) = scaled;
     }

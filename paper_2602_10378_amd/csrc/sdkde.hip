@@ -573,16 +573,17 @@ int launch_half_tail(const Plan& p, const Workspace& w, const float* shift, hipS
 template <int KIND, bool FAR>
 int launch_half(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
-    const bool eight = half_tail(p.d) == kTailEight;
+    const int tail = half_tail(p.d, KIND == kScoreSelf);
+    const bool eight = tail == kTailEight, spare = tail == kTailSpare;
     switch (p.dp / 16) {
         case 1: return eight ? launch_half_tail<KIND, FAR, 1, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 1, kTailSixteen>(p, w, shift, st);
-        case 2: return launch_half_tail<KIND, FAR, 2, kTailNone>(p, w, shift, st);
+        case 2: return spare ? launch_half_tail<KIND, FAR, 2, KIND == kScoreSelf ? kTailNone : kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 2, kTailNone>(p, w, shift, st);
         case 3: return eight ? launch_half_tail<KIND, FAR, 3, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 3, kTailSixteen>(p, w, shift, st);
-        case 4: return launch_half_tail<KIND, FAR, 4, kTailNone>(p, w, shift, st);
+        case 4: return spare ? launch_half_tail<KIND, FAR, 4, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 4, kTailNone>(p, w, shift, st);
         case 5: return eight ? launch_half_tail<KIND, FAR, 5, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 5, kTailSixteen>(p, w, shift, st);
-        case 6: return launch_half_tail<KIND, FAR, 6, kTailNone>(p, w, shift, st);
+        case 6: return spare ? launch_half_tail<KIND, FAR, 6, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 6, kTailNone>(p, w, shift, st);
         case 7: return eight ? launch_half_tail<KIND, FAR, 7, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 7, kTailSixteen>(p, w, shift, st);
-        case 8: return launch_half_tail<KIND, FAR, 8, kTailNone>(p, w, shift, st);
+        case 8: return spare ? launch_half_tail<KIND, FAR, 8, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 8, kTailNone>(p, w, shift, st);
         default: return SDKDE_EUNSUPPORTED;
     }
 }
@@ -829,8 +830,8 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     if (we.xs != ws.xs || wr_begin < dead_begin || wr_end > dead_end) return false;
     if ((const char*)we.ps < (const char*)(we.xn + pe.n_pad)) return false;
     const double a = operand_scale(format, h);
-    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false};
-    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false};
+    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false, half_tail(d, false)};
+    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false, half_tail(d, false)};
     out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a);
     return true;
 }
@@ -849,8 +850,8 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, false};
-    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, false, half_tail(d, self)};
+    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
     const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
     rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
                        : launch_prep(p, sample_job, point_job, samples, n, a, w, flags, stamp, st);
@@ -942,8 +943,8 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
     const int format = operand_format(p, flags);
     const double a = operand_scale(format, h);
     const bool shifted = (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true, false};
-    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, nullptr, w.xn, kPadCoord, true, false, half_tail(d, false)};
+    const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
     // all_prepared (sdkde_fit_eval): the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
     if (!all_prepared) {
         const Stamp stamp = make_stamp(w, samples_ready, false, samples, n, d, format, (float)a);

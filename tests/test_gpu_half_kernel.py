@@ -16,7 +16,7 @@ def _gpu(*arrays):
     return [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in arrays]
 
 
-@pytest.mark.parametrize("d", [8, 9, 15, 24, 40, 41, 48, 65, 72, 73, 104, 105, 112, 127])
+@pytest.mark.parametrize("d", [8, 9, 15, 17, 24, 25, 40, 41, 48, 56, 65, 72, 73, 85, 104, 105, 112, 120, 127])
 @pytest.mark.parametrize("n", [33, 2100])
 def test_every_kind_of_last_block(n, d):
     """One to eight columns beyond whole 32-column blocks take one matrix instruction, nine to sixteen two, the rows' constant
