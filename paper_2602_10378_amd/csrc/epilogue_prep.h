@@ -13,11 +13,12 @@ namespace {
 // values stay in LDS, from where prep_rows writes the eval pass's prepared copy and norms.  `ps` (the score pass's
 // prepared samples, read for p~) and sd_job.dst may be the same memory: a workgroup reads its own rows before it
 // overwrites them and no other workgroup touches them.
+// x_sd is sd_job.src, which prep_rows reads again for samples beyond the fp16 range.
 // Workgroups [blocks_sd, ...): the queries, as prep_mfma_kernel prepares them (centre read from the workspace).
 __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* ps, int nsplit, int64_t m,
     int64_t m_pad, int d, int dp, int format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
-    float half_h2, float* __restrict__ x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
+    float half_h2, float* x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
     const float* centre, double a, Stamp stamp)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
@@ -53,7 +54,8 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             const int64_t at = i * d + c0;
             if (active) {
                 prepared.load(ps, i, c0, dp, format, 0);        // may run past d in the last quad: padding, not stored
-                if (part == 0) xv = load_quad(x + at, quad_io, d - c0);     // (quad_io: d is a multiple of four and the caller's arrays are 16-byte aligned)
+                // quad_io: d is a multiple of four and the caller's arrays are 16-byte aligned
+                if (part == 0) xv = load_quad(x + at, quad_io, d - c0);
 #pragma unroll 4
                 for (int s = part; s < nsplit; s += PARTS) {
                     tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);

@@ -121,7 +121,8 @@ constexpr bool half_sums_in_lds(int kb) { return kb <= 4; }
 
 template <int KB, int TAIL, int NI, int WAVES, int NB, bool AHEAD, int MINW, int KIND, bool FAR>
 __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
-    const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs, const float* __restrict__ xt, const float* __restrict__ xn, float* __restrict__ part_t, float* __restrict__ part_d,
+    const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs, const float* __restrict__ xt,
+    const float* __restrict__ xn, float* __restrict__ part_t, float* __restrict__ part_d,
     int ntiles, int tiles_per_split, int nsplit, int64_t m_pad, float laplace_c0, const float* __restrict__ shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");

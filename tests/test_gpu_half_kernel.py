@@ -20,7 +20,8 @@ def _gpu(*arrays):
 @pytest.mark.parametrize("n", [33, 2100])
 def test_every_kind_of_last_block(n, d):
     """One to eight columns beyond whole 32-column blocks take one matrix instruction, nine to sixteen two, the rows' constant
-    terms in their spare columns; other dimensions have no such block.  At the samples, at points, densities, shifted sums."""
+    terms in their spare columns; 17 to 24 columns of a 32-column block have spare columns, too; other dimensions have none.  At
+    the samples, at points, densities, shifted sums."""
     import paper_2602_10378_amd as P
     P.load()
     m = 45
