@@ -64,6 +64,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             }
             red_t[part][lane] = tacc;
             red_d[part][lane] = dacc;
+            f32x4 shifted = {0.0f, 0.0f, 0.0f, 0.0f};               // and of padding
             __syncthreads();
             if (active && part == 0 && c0 < d) {
                 f32x4 tsum = red_t[0][lane];
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
                 }
                 f32x4 rest;
                 const f32x4 pc = prepared.value(format, 0, &rest);
-                f32x4 out, shifted;
+                f32x4 out;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     out[v] = fmaf(-rest[v], dsum, fmaf(-pc[v], dsum, tsum[v])) / (dsum + 1.0f) * inv_ah2;   // the samples' own pair is not in the sums
@@ -92,9 +93,10 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
                         x_sd[at + v] = shifted[v];
                     }
                 }
+            }
+            if (part == 0) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (c0 + v < d) raw[(item / quads) * (dp + 1) + c0 + v] = shifted[v];
+                for (int v = 0; v < 4; ++v) raw[(item / quads) * (dp + 1) + c0 + v] = c0 + v < d ? shifted[v] : 0.0f;
             }
             __syncthreads();            // red_t / red_d are reused by the next pass; raw is read below
         }

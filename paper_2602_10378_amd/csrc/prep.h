@@ -196,9 +196,9 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
                 const float x = __builtin_bit_cast(float, at[c]), y = c < d ? smean[c] : 0.0f;
                 const float diff = x - y, part = diff - x, left = (x - (diff - part)) + (-y - part);      // x - y = diff + left
                 float v = a_high * diff, low = fmaf(a_high, diff, -v) + fmaf(a_high, left, a_low * diff);
-                const bool out = fabsf(v) > far_from;
-                beyond |= out;
-                if (out || !live || c >= d) v = low = 0.0f;
+                const bool there = live && c < d, out = there && fabsf(v) > far_from;
+                beyond |= out;                      // of a value that is there: such rows are read again below
+                if (out || !there) v = low = 0.0f;
                 const uint32_t word = half2_split(v, low);
                 at[c] = word;
                 const double held = (double)half_low(word) + (double)half_high(word);
