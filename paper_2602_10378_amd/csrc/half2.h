@@ -88,6 +88,26 @@ __host__ __device__ inline float* half2_residual(float* ps, int64_t rows_pad, in
 }
 __host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int dp) { return half2_residual(ps, rows_pad, dp) + rows_pad; }
 
+// Behind the prepared samples, at the same distance from them: a byte a chunk, what a kernel may have to know of its samples.
+constexpr uint32_t kMarkWide = 1;                   // one with half a squared norm above kCoarseSample
+constexpr float kCoarseNorm = 2048.0f, kCoarseSample = 8192.0f;      // see the row maxima in pair_half.h
+__host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int dp)
+{
+    return reinterpret_cast<uint8_t*>(half2_scale(xs, rows_pad, dp) + rows_pad);
+}
+// The marks of chunks first .. last - 1 (and of up to three on either side) together, in all lanes.
+__device__ __forceinline__ uint32_t marks_of(const uint8_t* marks, int first, int last, int lane)
+{
+    const uint32_t* const words = reinterpret_cast<const uint32_t*>(marks);     // rows are padded to 32 chunks
+    uint32_t all = 0, some = 0;
+    for (int w = first / 4 + lane; w * 4 < last; w += kWave) all |= words[w];
+    all |= all >> 16;
+    all |= all >> 8;
+#pragma unroll
+    for (uint32_t bit = 1; bit <= kMarkWide; bit *= 2) some |= __builtin_amdgcn_ballot_w64((all & bit) != 0) != 0 ? bit : 0;
+    return some;
+}
+
 // Four consecutive halves.
 __device__ __forceinline__ f32x4 half_values(const u32x2& two)
 {

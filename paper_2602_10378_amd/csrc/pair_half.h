@@ -96,7 +96,6 @@ struct HalfRows {
 // holds 11 bits down to 2^-25 of a W of one.
 constexpr float kMostWeight = 65000.0f * kWeightScale;      // of a lane's sum of W, so that no w leaves the fp16 range
 constexpr int kRaisedTo = 18;                       // where a row's largest W is put when it has outgrown that
-constexpr float kCoarseNorm = 2048.0f;              // half a squared norm |p~|^2, see there
 constexpr float kLeastShift = -126.0f;              // a W of one then stands for the smallest normal fp32 number
 
 __device__ __forceinline__ void split_weights(const f32x4& p, const f32x4& q, f16x8& h, f16x8& l)
@@ -149,6 +148,14 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     const int64_t row_block = blockIdx.x / nsplit;
     const int64_t row0 = (row_block * WAVES + wave) * (NI * kTile);
 
+    const int c_begin = split * tiles_per_split / 2;
+    const int c_end = min(ntiles, split * tiles_per_split + tiles_per_split) / 2;
+    uint32_t marks = 0;                                     // of the split's samples (wave-uniform)
+    if constexpr (ROWMAX) {
+        const int64_t n_pad = ((int64_t)ntiles * kTile + kRowPad - 1) / kRowPad * kRowPad;
+        marks = marks_of(half2_marks(const_cast<float*>(xs), n_pad, DP), c_begin, c_end, lane);
+    }
+
     HalfRows<KB, TAIL, NI, SCORE> rows;
     rows.load(ps, pn, row0, r, g);
     // FAR: a row may be held as 2^-k times itself, 2^k behind the prepared rows; far: one of the wave's rows is (wave-uniform)
@@ -160,12 +167,13 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
         if (SCORE && far) rows.bare(g);
     }
     // ROWMAX: any shift near the largest exponent serves, as long as the sums use the same.  Of whole 32-column blocks the
-    // leading products do: they are off by 2^-11 |p~| |x~| at most, 4 with kCoarseNorm and samples no further out than twice the
-    // row, and less than 0.09 sqrt(-exponent) with any others.  Rows with larger norms get all products.
+    // leading products do, for rows with half a squared norm up to kCoarseNorm and samples up to kCoarseSample: the two products
+    // left out are 2^-11 |p~| |x~| each at most, 8 together.  (The bound has to be on both: of a row near the centre and a sample
+    // 10^4 bandwidths from it they come to 100 and more, and with every sample that far the sums were 0 or infinite.)
     // (Max-shifted eval of 10007 points against 50021 samples, d = 24: 206 us with all products for every row, 180 so.)
     bool coarse = false;
     if constexpr (ROWMAX) {
-        coarse = !far;
+        coarse = !far && (marks & kMarkWide) == 0;
 #pragma unroll
         for (int t = 0; t < NI; ++t) coarse &= __builtin_amdgcn_ballot_w64(rows.term[t] < -kCoarseNorm) == 0;
     }
@@ -407,8 +415,6 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     };
 
     const int own0 = (int)(row0 / kChunkRows);              // SELF: the wave's own rows are chunks own0 .. own0 + NI/2 - 1
-    const int c_begin = split * tiles_per_split / 2;
-    const int c_end = min(ntiles, split * tiles_per_split + tiles_per_split) / 2;
     const char* const xs_b = reinterpret_cast<const char*>(xs);
     const char* const xt_b = reinterpret_cast<const char*>(xt);
     bool flushed = false;                                   // !SUMLDS: the partial slot holds second-level sums

@@ -273,7 +273,10 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         const double rest = -0.5 * acc - (double)norm;
         const float left = row < job.rows && fabs(rest) < 500.0 ? (float)rest : 0.0f;       // (a norm below 2^31)
         job.dst_n[row] = norm;
-        if (!job.samples) {
+        if (job.samples) {
+            const bool wide = __builtin_amdgcn_ballot_w64(row < job.rows && norm < -kCoarseSample) != 0;
+            if (rr == 0) half2_marks(job.dst, job.rows_pad, dp)[r0 / kChunkRows] = wide ? kMarkWide : 0;
+        } else {
             half2_residual(job.dst, job.rows_pad, dp)[row] = left;
             half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         }

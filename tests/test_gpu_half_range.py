@@ -46,3 +46,51 @@ def test_an_offset_of_all_data_is_not_a_distance(d, flag):
     ref, e = oracle.eval_log_density(x, q, h), gram_exponent_error(x, q, h)
     assert np.all(np.abs(logd - ref) <= e + 2.0**-18 + 2.0**-23 * np.abs(ref))
     assert np.all(_prepared_scales(workspace, P.sdkde_describe_plan(n, m, d, 2, flags)) == 1.0)
+
+
+def _two_clusters(n, m, d, distance, seed):
+    """Samples in two tight clusters `distance` on either side of the middle along a diagonal, queries up to 50 around the
+    middle, at least 1 off it along the axis so that a cluster is the nearer one by more than what fp32 exponents resolve."""
+    rng = np.random.default_rng(seed)
+    axis = rng.choice([-1.0, 1.0], d) / np.sqrt(d)
+    side = np.where(np.arange(n) % 2, 1.0, -1.0)
+    x = side[:, None] * distance * axis + rng.standard_normal((n, d))
+    q = rng.standard_normal((m, d))
+    q *= rng.uniform(0.0, 50.0, m)[:, None] / np.linalg.norm(q, axis=1, keepdims=True)
+    along = q @ axis
+    q += (np.where(along < 0.0, -1.0, 1.0) * np.maximum(1.0 - np.abs(along), 0.0))[:, None] * axis
+    return x.astype(np.float32), q.astype(np.float32)
+
+
+def _check_shifted_far_clusters(P, x, q, h):
+    import torch
+    xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
+    flags = P.SDKDE_FLAG_MAX_SHIFT
+    ref = oracle.eval_log_density(x, q, h)
+    # roundings at the size of the terms, four more for the lane groups of a matrix instruction; coordinates held to 2^-23 of
+    # themselves move an exponent by up to 2^-23 |x| |x - q| / h^2, twice 2^-23 of it here, and the result is rounded once
+    allowed = gram_exponent_error(x, q, h, low_precision_inputs=True) + 3.0 * 2.0**-23 * np.abs(ref) + 2.0**-18
+    logd = P.sdkde_eval(xd, qd, h, want="log", flags=flags)[1].cpu().numpy()
+    worst = (np.abs(logd - ref) / allowed).max()
+    print(f"log density {worst:.3f} of the bound", flush=True)
+    assert worst <= 1.0
+    if x.shape[1] > 6:
+        # which of a cluster's samples count is not resolved, only that they do: their distances from each other
+        ref_s = oracle.score(x, h, points=q)
+        s = P.sdkde_score(xd, h, points=qd, flags=flags).cpu().numpy()
+        spread = 2.0 * np.linalg.norm(x[::2] - x[::2].mean(axis=0), axis=1).max() / (h * h)
+        worst = (np.linalg.norm(s - ref_s, axis=1) / (spread + 2.0**-21 * np.linalg.norm(ref_s, axis=1))).max()
+        assert worst <= 1.0
+
+
+@pytest.mark.parametrize("d", [7, 17, 32, 48, 128])
+@pytest.mark.parametrize("distance", [200.0, 2000.0, 6000.0, 12000.0])
+def test_shifted_sums_between_far_clusters(d, distance):
+    """Every sample far from queries near the centre: the exponents are of the size of the samples' norms, and a shift from
+    leading products only would miss the largest by more than fp32 exponents hold."""
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, h = 1500, 400, 1.0
+    print(f"far clusters d={d} distance {distance}", flush=True)
+    x, q = _two_clusters(n, m, d, distance, d)
+    _check_shifted_far_clusters(P, x, q, h)
