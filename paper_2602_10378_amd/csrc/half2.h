@@ -13,10 +13,11 @@ namespace {
 // of either sign.  Norms are those of h + l, so what is computed is the exact sum for samples and points moved by their
 // split error, whose effect on an exponent is that error times the distance of the pair and not times the norms.
 //
-// Range: a sample's coordinate beyond kHalfMax goes in as zero and keeps its norm: its exponents lie below
-// -kHalfMax^2 / 2 + ..., so its weight is 0.  A point with one, for the max-shifted sums already one beyond kFarPoint, is held as
-// 2^-k times itself (2^k in the prepared `scale`), see pair_half.h: without the shift its weights are 0.  (fp32 exponents at
-// such distances, R / h > 46000, are off by a hundred and more.)
+// Range: a sample or a point further than kReach from the centre has no weight with any point or sample (its fp32 exponents are
+// off by a hundred and more either way): a sample goes in as zeros and keeps its norm, its exponents are below -kReach^2 / 2 +
+// kReach^2 / 8; a point, for the max-shifted sums already one with a coordinate beyond kFarPoint, is held as 2^-k times itself
+// (2^k >= 4 in the prepared `scale`), see pair_half.h.  Distances are norms, not single coordinates: the row's constant term is half
+// a squared norm and is cut off at kLeastTerm, which has to be beyond every row that is not held so.
 //
 // Prepared rows ("xs" / "ps"), in chunks of kChunkRows = 32 rows, two 16-row tiles of half_tile_bytes each (KB = dp / 16):
 //   32-column block b (columns 32b .. 32b+31): part q (h, l) at b * 2048 + q * 1024; lane l = 16 g + r of the operand holds
@@ -38,6 +39,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kHalfMax = 65504.0f;             // largest finite fp16 value
+constexpr float kReach = 60000.0f;               // kReach^2 / 2 and the largest part of a shift beside it stay below -kLeastTerm
 // From here on the shifted sums round a point's exponents at the size of its norm and only then shift them (the exponents'
 // last place is 2^-3 there): rounded differently for the maximum and for the sums they would miss each other, and the sums
 // were 0 or infinite from about 10^5 bandwidths on.
@@ -115,13 +117,15 @@ __device__ __forceinline__ f32x4 half_values(const u32x2& two)
 }
 
 // The constant term of a row's exponents as three elements of a row operand: their sum with kTermFactor is the fp32 value,
-// cut off where every weight is zero (NaN stays NaN).  Each part's factor keeps it inside the fp16 range whatever v's size.
+// cut off where every weight is zero or no sample is within kReach (NaN stays NaN).  Each part's factor keeps it inside the fp16 range whatever v's size.
 constexpr float kTermFactor[3] = {32768.0f, 16.0f, 0.0078125f};
 constexpr float kLeastTerm = -kHalfMax * 32768.0f;
 constexpr float kResidualFactor = 0.0078125f;       // of the samples' norms, see above
+template <bool SHIFTED>
 __device__ __forceinline__ void split_term(float v, float residual, _Float16 (&part)[3])
 {
     v = v < kLeastTerm ? kLeastTerm : v;
+    if (SHIFTED) v = v > -kLeastTerm ? -kLeastTerm : v;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         if (q == 2) v += residual;

@@ -19,7 +19,7 @@
 namespace {
 
 // Row-tile operands of one wave: the parts of p~ as the lane's 16 bytes of each B operand, and the rows' constant terms.
-template <int KB, int TAIL, int NI, bool SCORE>
+template <int KB, int TAIL, int NI, bool SCORE, bool FAR>
 struct HalfRows {
     static constexpr int PAIRS = KB / 2;            // 32-column blocks
     static constexpr bool ODD = TAIL == kTailSixteen || TAIL == kTailEight, SPARE = TAIL == kTailSpare;
@@ -81,7 +81,7 @@ struct HalfRows {
     {
         if (TAIL == kTailNone) return;
         _Float16 part[3];
-        split_term(v, residual, part);
+        split_term<FAR>(v, residual, part);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             f16x8& e = ODD ? o[ODD ? t : 0][TERM] : b[t][SPARE ? PAIRS - 1 : 0][0];
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     constexpr bool SELF = KIND == kScoreSelf;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
     constexpr bool ROWMAX = KIND == kRowMax;
-    constexpr bool ODD = HalfRows<KB, TAIL, NI, SCORE>::ODD, TERMED = TAIL != kTailNone;
+    constexpr bool ODD = HalfRows<KB, TAIL, NI, SCORE, FAR>::ODD, TERMED = TAIL != kTailNone;
     constexpr int DP = KB * 16;
     constexpr int KT = SCORE ? KB : 1;
     constexpr int PAIRS = KB / 2;
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
         marks = marks_of(half2_marks(const_cast<float*>(xs), n_pad, DP), c_begin, c_end, lane);
     }
 
-    HalfRows<KB, TAIL, NI, SCORE> rows;
+    HalfRows<KB, TAIL, NI, SCORE, FAR> rows;
     rows.load(ps, pn, row0, r, g);
     // FAR: a row may be held as 2^-k times itself, 2^k behind the prepared rows; far: one of the wave's rows is (wave-uniform)
     bool far = false;

@@ -178,7 +178,8 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
 {
     static_assert(kPrepRows == kChunkRows && kBlock == 8 * kPrepRows, "a workgroup writes whole chunks, eight lanes a row");
     const int stride = dp + 1;                  // odd: columns are read without bank conflicts
-    const float far_from = job.samples || !job.shifted ? kHalfMax : kFarPoint;      // largest coordinate held as it is
+    const float far_from = job.samples || !job.shifted ? kHalfMax : kFarPoint;      // largest coordinate held as it is, and
+    constexpr double far_square = (double)kReach * kReach;                          // largest squared norm
     auto coordinate = [&](int c, float in) { return a * ((double)in - (double)smean[c]); };
     const float a_high = (float)a, a_low = (float)(a - (double)a_high);
     __shared__ double squares[kPrepRows];
@@ -204,13 +205,13 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
                 const double held = (double)half_low(word) + (double)half_high(word);
                 square = fma(held, held, square);
             }
-        if (beyond) atomicOr(far_rows, 1u << own);          // rows with a coordinate beyond that, a bit each
         square = sum_of_eight(square);
+        if (beyond || square > far_square) atomicOr(far_rows, 1u << own);          // rows beyond that, a bit each
         if (lane8 == 0) squares[own] = square;
     }
     __syncthreads();
     const uint32_t far = *far_rows;
-    // such rows of points: 2^-k times themselves (the largest coordinate then has the exponent 10, k > 0)
+    // such rows of points: 2^-k times themselves (the largest coordinate then has an exponent of 10 at most, k >= 2); of samples: 0
     auto largest = [&](int rr) __attribute__((always_inline)) {
         double most = 0.0;
 #pragma unroll 1
@@ -222,17 +223,17 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     };
     auto finite = [](double v) { return v <= 1.7e308; };
     // 2^k and 2^-k from the exponent bits (beyond 2^1022: 2^-k is 0)
-    auto far_scale = [](double most) __attribute__((always_inline)) {
-        return __builtin_bit_cast(double, ((__builtin_bit_cast(uint64_t, most) >> 52) - 10) << 52);
+    auto far_exponent = [](double most) __attribute__((always_inline)) {
+        const uint64_t e = __builtin_bit_cast(uint64_t, most) >> 52;
+        return e < 1023 + 12 ? (uint64_t)(1023 + 2) : e - 10;
     };
-    auto far_down = [](double most) __attribute__((always_inline)) {
-        return __builtin_bit_cast(double, (2046 - ((__builtin_bit_cast(uint64_t, most) >> 52) - 10)) << 52);
-    };
-    if (far != 0 && !job.samples) {             // the same for all threads
+    auto far_scale = [&](double most) __attribute__((always_inline)) { return __builtin_bit_cast(double, far_exponent(most) << 52); };
+    auto far_down = [&](double most) __attribute__((always_inline)) { return __builtin_bit_cast(double, (2046 - far_exponent(most)) << 52); };
+    if (far != 0) {                             // the same for all threads
 #pragma unroll 1
         for (int rr = 0; rr < kPrepRows; ++rr) {
             if (!(far >> rr & 1u)) continue;
-            const double most = largest(rr);
+            const double most = job.samples ? (double)__builtin_nanf("") : largest(rr);
             const double down = finite(most) ? far_down(most) : 0.0;
 #pragma unroll 1
             for (int c = threadIdx.x; c < d; c += kBlock) {
@@ -251,16 +252,16 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         const uint32_t* w = words + rr * stride;
         double acc = squares[rr], scale = 1.0;
         if (far >> rr & 1u) {
-            if (job.samples) {          // a coordinate that went in as zero counts in the norm
+            acc = 0.0;
+            if (job.samples) {
 #pragma unroll 1
                 for (int c = 0; c < d; ++c) {
                     const double v = coordinate(c, job.src[row * d + c]);
-                    if (fabs(v) > far_from) acc += v * v;
+                    acc = fma(v, v, acc);
                 }
             } else {
                 const double most = largest(rr);
                 if (finite(most)) scale = far_scale(most);
-                acc = 0.0;
 #pragma unroll 1
                 for (int c = 0; c < dp; ++c) {
                     const double v = ((double)half_low(w[c]) + (double)half_high(w[c])) * scale;

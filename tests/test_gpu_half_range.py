@@ -94,3 +94,25 @@ def test_shifted_sums_between_far_clusters(d, distance):
     print(f"far clusters d={d} distance {distance}", flush=True)
     x, q = _two_clusters(n, m, d, distance, d)
     _check_shifted_far_clusters(P, x, q, h)
+
+
+@pytest.mark.parametrize("d", [4, 7, 16, 17, 24, 32, 37, 56, 128])
+@pytest.mark.parametrize("spread", [12000.0, 25000.0, 45000.0])
+def test_a_bandwidth_far_below_every_distance(d, spread):
+    """Coordinates of up to some 10^4 bandwidths: inside the fp16 range one by one or just beyond, but their norms are beyond
+    what a row's constant term takes in its spare columns.  Every pair is too far apart to count, so densities and scores are 0."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, h = 1100, 200, 1.0
+    rng = np.random.default_rng(d)
+    x, q = (rng.standard_normal((k, d)).astype(np.float32) * np.float32(spread) for k in (n, m))
+    q[::2] *= np.float32(0.01)                                                 # rows on both sides of the line in one tile
+    print(f"narrow bandwidth d={d} spread {spread}", flush=True)
+    xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
+    dens, logd = (a.cpu().numpy() for a in P.sdkde_eval(xd, qd, h, want="both"))
+    assert np.all(dens == 0.0) and np.all(np.isneginf(logd))
+    assert np.all(P.sdkde_eval_laplace(xd, qd, h).cpu().numpy() == 0.0)
+    if d > 6:
+        assert np.all(P.sdkde_score(xd, h).cpu().numpy() == 0.0)
+        assert np.all(P.sdkde_score(xd, h, points=qd).cpu().numpy() == 0.0)
