@@ -15,7 +15,7 @@ namespace {
 //
 // Range: a sample or a point further than kReach from the centre has no weight with any point or sample (its fp32 exponents are
 // off by a hundred and more either way): a sample goes in as zeros and keeps its norm, its exponents are below -kReach^2 / 2 +
-// kReach^2 / 8; a point, for the max-shifted sums already one with a coordinate beyond kFarPoint, is held as 2^-k times itself
+// kReach^2 / 8; a point, for the max-shifted sums already one beyond kFarPoint, is held as 2^-k times itself
 // (2^k >= 4 in the prepared `scale`), see pair_half.h.  Distances are norms, not single coordinates: the row's constant term is half
 // a squared norm and is cut off at kLeastTerm, which has to be beyond every row that is not held so.
 //
@@ -43,7 +43,7 @@ constexpr float kReach = 60000.0f;               // kReach^2 / 2 and the largest
 // From here on the shifted sums round a point's exponents at the size of its norm and only then shift them (the exponents'
 // last place is 2^-3 there): rounded differently for the maximum and for the sums they would miss each other, and the sums
 // were 0 or infinite from about 10^5 bandwidths on.
-constexpr float kFarPoint = 2047.0f;
+constexpr float kFarPoint = 2048.0f;
 constexpr float kWeightScale = 2048.0f;          // see pair_half.h
 constexpr int half_tile_bytes(int kb) { return kb * 1024 + (kb % 2) * 256; }
 // How the columns beyond whole 32-column blocks are held: none, 9 .. 16 in a 16-column block (two MFMAs), 1 .. 8 (one); 17 .. 24

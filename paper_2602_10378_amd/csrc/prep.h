@@ -178,8 +178,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
 {
     static_assert(kPrepRows == kChunkRows && kBlock == 8 * kPrepRows, "a workgroup writes whole chunks, eight lanes a row");
     const int stride = dp + 1;                  // odd: columns are read without bank conflicts
-    const float far_from = job.samples || !job.shifted ? kHalfMax : kFarPoint;      // largest coordinate held as it is, and
-    constexpr double far_square = (double)kReach * kReach;                          // largest squared norm
+    const double reach = job.samples || !job.shifted ? kReach : kFarPoint;          // largest norm held as it is
     auto coordinate = [&](int c, float in) { return a * ((double)in - (double)smean[c]); };
     const float a_high = (float)a, a_low = (float)(a - (double)a_high);
     __shared__ double squares[kPrepRows];
@@ -197,7 +196,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
                 const float x = __builtin_bit_cast(float, at[c]), y = c < d ? smean[c] : 0.0f;
                 const float diff = x - y, part = diff - x, left = (x - (diff - part)) + (-y - part);      // x - y = diff + left
                 float v = a_high * diff, low = fmaf(a_high, diff, -v) + fmaf(a_high, left, a_low * diff);
-                const bool there = live && c < d, out = there && fabsf(v) > far_from;
+                const bool there = live && c < d, out = there && fabsf(v) > kHalfMax;
                 beyond |= out;                      // of a value that is there: such rows are read again below
                 if (out || !there) v = low = 0.0f;
                 const uint32_t word = half2_split(v, low);
@@ -206,7 +205,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
                 square = fma(held, held, square);
             }
         square = sum_of_eight(square);
-        if (beyond || square > far_square) atomicOr(far_rows, 1u << own);          // rows beyond that, a bit each
+        if (beyond || square > reach * reach) atomicOr(far_rows, 1u << own);          // rows beyond that, a bit each
         if (lane8 == 0) squares[own] = square;
     }
     __syncthreads();

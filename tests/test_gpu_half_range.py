@@ -49,20 +49,22 @@ def test_an_offset_of_all_data_is_not_a_distance(d, flag):
 
 
 def _two_clusters(n, m, d, distance, seed):
-    """Samples in two tight clusters `distance` on either side of the middle along a diagonal, queries up to 50 around the
-    middle, at least 1 off it along the axis so that a cluster is the nearer one by more than what fp32 exponents resolve."""
+    """Samples in two tight clusters, 2 `distance` apart along one column; queries up to 50 from the centre that the library takes
+    (the mean of evenly strided samples) and at least 1 from the clusters' middle along it, so that one of them is the nearer one by
+    more than what fp32 exponents resolve; and the clusters' size."""
     rng = np.random.default_rng(seed)
-    axis = rng.choice([-1.0, 1.0], d) / np.sqrt(d)
-    side = np.where(np.arange(n) % 2, 1.0, -1.0)
-    x = side[:, None] * distance * axis + rng.standard_normal((n, d))
-    q = rng.standard_normal((m, d))
-    q *= rng.uniform(0.0, 50.0, m)[:, None] / np.linalg.norm(q, axis=1, keepdims=True)
-    along = q @ axis
-    q += (np.where(along < 0.0, -1.0, 1.0) * np.maximum(1.0 - np.abs(along), 0.0))[:, None] * axis
-    return x.astype(np.float32), q.astype(np.float32)
+    step, c = rng.standard_normal((n, d)), d // 2
+    x = step.copy()
+    x[:, c] += rng.choice([-distance, distance], n)
+    rows = min(max(4096 // d, 32), n)
+    q = x[:rows * (n // rows):n // rows].mean(axis=0) + rng.standard_normal((m, d))
+    q[:, c] += rng.choice([-1.0, 1.0], m) * rng.uniform(0.0, 50.0, m)
+    q[:, c] += np.where(np.abs(q[:, c]) < 1.0, 2.0, 0.0)
+    return x.astype(np.float32), q.astype(np.float32), 2.0 * np.linalg.norm(step, axis=1).max()
 
 
-def _check_shifted_far_clusters(P, x, q, h):
+def _check_shifted_far_points(P, x, q, h, size):
+    """Max-shifted log densities and scores where every sample is far; size: how far the samples that may count are apart."""
     import torch
     xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
     flags = P.SDKDE_FLAG_MAX_SHIFT
@@ -78,7 +80,7 @@ def _check_shifted_far_clusters(P, x, q, h):
         # which of a cluster's samples count is not resolved, only that they do: their distances from each other
         ref_s = oracle.score(x, h, points=q)
         s = P.sdkde_score(xd, h, points=qd, flags=flags).cpu().numpy()
-        spread = 2.0 * np.linalg.norm(x[::2] - x[::2].mean(axis=0), axis=1).max() / (h * h)
+        spread = size / (h * h)
         worst = (np.linalg.norm(s - ref_s, axis=1) / (spread + 2.0**-21 * np.linalg.norm(ref_s, axis=1))).max()
         assert worst <= 1.0
 
@@ -92,8 +94,8 @@ def test_shifted_sums_between_far_clusters(d, distance):
     P.load()
     n, m, h = 1500, 400, 1.0
     print(f"far clusters d={d} distance {distance}", flush=True)
-    x, q = _two_clusters(n, m, d, distance, d)
-    _check_shifted_far_clusters(P, x, q, h)
+    x, q, size = _two_clusters(n, m, d, distance, d)
+    _check_shifted_far_points(P, x, q, h, size)
 
 
 @pytest.mark.parametrize("d", [4, 7, 16, 17, 24, 32, 37, 56, 128])
@@ -116,3 +118,20 @@ def test_a_bandwidth_far_below_every_distance(d, spread):
     if d > 6:
         assert np.all(P.sdkde_score(xd, h).cpu().numpy() == 0.0)
         assert np.all(P.sdkde_score(xd, h, points=qd).cpu().numpy() == 0.0)
+
+
+@pytest.mark.parametrize("d", [7, 37, 64, 128])
+def test_shifted_sums_of_points_far_in_every_coordinate(d):
+    """Points with coordinates of up to 2000 units each: far by their norm, 23000 at d = 128, though by no single coordinate.  Their
+    exponents are rounded at the size of the norm, for the maximum and for the sums alike."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 1500, 300
+    rng = np.random.default_rng(d)
+    h = float(np.sqrt(np.log2(np.e)))                                        # one unit is 1
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    q = (rng.choice([-1.0, 1.0], (m, d)) * rng.uniform(1500.0, 2000.0, (m, d))).astype(np.float32)
+    q[::3] *= np.float32(0.5)
+    print(f"far in every coordinate d={d}", flush=True)
+    _check_shifted_far_points(P, x, q, h, 2.0 * np.linalg.norm(x - x.mean(axis=0), axis=1).max())
