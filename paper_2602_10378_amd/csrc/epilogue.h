@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void debias_kernel(const float* x, const fl
 // shift[i] = max over splits of the row maxima left in part_d by a kRowMax pass; on the MFMA path the
 // shift is also folded into the row constant pn (-|p~|^2 - shift), so the main pass needs no extra work; residual (may be
 // null) takes the rounding of that difference.  Rows held scaled down (their
-// scale follows the residuals) keep their norm, see pair_half.h.
+// scale follows the residuals) and those with a shift below kFarShift keep their norm, see pair_half.h.
 // Grid: one workgroup per kBlock / PARTS rows.
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void shift_kernel(const float* __restrict__ part_d, int nsplit, int64_t m_pad,
@@ -277,8 +277,8 @@ __global__ __launch_bounds__(kBlock) void shift_kernel(const float* __restrict__
     const float scale = *(residual && active ? residual + m_pad + i : maxima), left = *(residual && active ? residual + i : maxima);
     const float mx = reduce_slots<PARTS, true>(maxima, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
-    shift[i] = mx;
-    if (pn && !(residual && scale != 1.0f)) {
+    shift[i] = pn && before == kPadNorm ? 0.0f : mx;        // a padding row's is of no interest, nor has it to look far away
+    if (pn && !(residual && (scale != 1.0f || mx < kFarShift))) {
         const float after = before - mx;
         pn[i] = after;
         if (residual) residual[i] = left + (float)(((double)before - (double)mx) - (double)after);

@@ -13,11 +13,11 @@ namespace {
 // of either sign.  Norms are those of h + l, so what is computed is the exact sum for samples and points moved by their
 // split error, whose effect on an exponent is that error times the distance of the pair and not times the norms.
 //
-// Range: a sample or a point further than kReach from the centre has no weight with any point or sample (its fp32 exponents are
-// off by a hundred and more either way): a sample goes in as zeros and keeps its norm, its exponents are below -kReach^2 / 2 +
-// kReach^2 / 8; a point, for the max-shifted sums already one beyond kFarPoint, is held as 2^-k times itself
-// (2^k >= 4 in the prepared `scale`), see pair_half.h.  Distances are norms, not single coordinates: the row's constant term is half
-// a squared norm and is cut off at kLeastTerm, which has to be beyond every row that is not held so.
+// Range: a sample or a point further than kReach from the centre (for the max-shifted sums a point already further than kFarPoint) is
+// held as 2^-k times itself, 2^k >= 4 in the prepared `scale`, with the norm of what it stands for.  Where kernels do not ask for the
+// scale it has no weight: its exponents are below -kReach^2 / 2 + kReach^2 / 4 (fp32 exponents at such distances are off by a hundred
+// and more anyway).  The max-shifted sums ask for it, see pair_half.h.  Distances are norms, not single coordinates: the row's
+// constant term is half a squared norm and is cut off at kLeastTerm, which has to be beyond every row that is not held so.
 //
 // Prepared rows ("xs" / "ps"), in chunks of kChunkRows = 32 rows, two 16-row tiles of half_tile_bytes each (KB = dp / 16):
 //   32-column block b (columns 32b .. 32b+31): part q (h, l) at b * 2048 + q * 1024; lane l = 16 g + r of the operand holds
@@ -40,10 +40,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kHalfMax = 65504.0f;             // largest finite fp16 value
 constexpr float kReach = 60000.0f;               // kReach^2 / 2 and the largest part of a shift beside it stay below -kLeastTerm
-// From here on the shifted sums round a point's exponents at the size of its norm and only then shift them (the exponents'
-// last place is 2^-3 there): rounded differently for the maximum and for the sums they would miss each other, and the sums
-// were 0 or infinite from about 10^5 bandwidths on.
+// From here on the shifted sums round an exponent at the size of the norms and only then shift it (its last place is 2^-3
+// there): rounded differently for the maximum and for the sums they would miss each other, and the sums were 0 or infinite from
+// about 10^5 bandwidths on, with far samples from 10^4 on.
 constexpr float kFarPoint = 2048.0f;
+// So they do for a point that is not that far but has a shift below this: its nearest sample is 5000 units away, every
+// sample more than kFarPoint from the centre, and the row maxima have been formed the same way.
+constexpr float kFarShift = -12582912.0f;
 constexpr float kWeightScale = 2048.0f;          // see pair_half.h
 constexpr int half_tile_bytes(int kb) { return kb * 1024 + (kb % 2) * 256; }
 // How the columns beyond whole 32-column blocks are held: none, 9 .. 16 in a 16-column block (two MFMAs), 1 .. 8 (one); 17 .. 24
@@ -90,8 +93,11 @@ __host__ __device__ inline float* half2_residual(float* ps, int64_t rows_pad, in
 }
 __host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int dp) { return half2_residual(ps, rows_pad, dp) + rows_pad; }
 
-// Behind the prepared samples, at the same distance from them: a byte a chunk, what a kernel may have to know of its samples.
+// Behind the prepared samples, at the same distance from them: their scales, and a byte a chunk, what a kernel may have to know of
+// its samples.
 constexpr uint32_t kMarkWide = 1;                   // one with half a squared norm above kCoarseSample
+constexpr uint32_t kMarkDistant = 2;                // one further than kFarPoint from the centre
+constexpr uint32_t kMarks = 2;                      // how many there are
 constexpr float kCoarseNorm = 2048.0f, kCoarseSample = 8192.0f;      // see the row maxima in pair_half.h
 __host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int dp)
 {
@@ -106,7 +112,7 @@ __device__ __forceinline__ uint32_t marks_of(const uint8_t* marks, int first, in
     all |= all >> 16;
     all |= all >> 8;
 #pragma unroll
-    for (uint32_t bit = 1; bit <= kMarkWide; bit *= 2) some |= __builtin_amdgcn_ballot_w64((all & bit) != 0) != 0 ? bit : 0;
+    for (uint32_t bit = 1; bit < 1u << kMarks; bit *= 2) some |= __builtin_amdgcn_ballot_w64((all & bit) != 0) != 0 ? bit : 0;
     return some;
 }
 

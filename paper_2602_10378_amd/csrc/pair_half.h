@@ -151,19 +151,22 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     const int c_begin = split * tiles_per_split / 2;
     const int c_end = min(ntiles, split * tiles_per_split + tiles_per_split) / 2;
     uint32_t marks = 0;                                     // of the split's samples (wave-uniform)
-    if constexpr (ROWMAX) {
-        const int64_t n_pad = ((int64_t)ntiles * kTile + kRowPad - 1) / kRowPad * kRowPad;
-        marks = marks_of(half2_marks(const_cast<float*>(xs), n_pad, DP), c_begin, c_end, lane);
-    }
+    const int64_t n_pad = ((int64_t)ntiles * kTile + kRowPad - 1) / kRowPad * kRowPad;
+    if constexpr (ROWMAX) marks = marks_of(half2_marks(const_cast<float*>(xs), n_pad, DP), c_begin, c_end, lane);
 
     HalfRows<KB, TAIL, NI, SCORE, FAR> rows;
     rows.load(ps, pn, row0, r, g);
-    // FAR: a row may be held as 2^-k times itself, 2^k behind the prepared rows; far: one of the wave's rows is (wave-uniform)
+    // FAR: a row may be held as 2^-k times itself, 2^k behind the prepared rows, and so may samples; far: one of the wave's rows
+    // is, or its exponents have to be shifted last (wave-uniform).  (Without such a row samples that are held so have no weight.)
     bool far = false;
     const float* const pscale = FAR ? half2_scale(const_cast<float*>(ps), m_pad, DP) : nullptr;
+    const float* const xscale = FAR ? half2_scale(const_cast<float*>(xs), n_pad, DP) : nullptr;
+    auto of_row = [&](const float* at, int t) { return load_at<float>(reinterpret_cast<const char*>(at + row0 + t * kTile), r * 4u); };
+    auto shifted_last = [&](int t) { return (int)(of_row(pscale, t) != 1.0f) | (ROWMAX ? 0 : (int)(of_row(shift, t) < kFarShift)); };
     if constexpr (FAR) {
+        far = ROWMAX && (marks & kMarkDistant) != 0;
 #pragma unroll
-        for (int t = 0; t < NI; ++t) far |= __builtin_amdgcn_ballot_w64(pscale[row0 + t * kTile + r] != 1.0f) != 0;
+        for (int t = 0; t < NI; ++t) far |= __builtin_amdgcn_ballot_w64(shifted_last(t) != 0) != 0;
         if (SCORE && far) rows.bare(g);
     }
     // ROWMAX: any shift near the largest exponent serves, as long as the sums use the same.  Of whole 32-column blocks the
@@ -230,14 +233,14 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     // SCORE: the power of two by which a row's exponents are lowered (kept as what a w of one is worth)
     auto lowered = [&](int t) { return (float)((int)(__builtin_bit_cast(uint32_t, unit[SCORE ? t : 0]) >> 23) - 127 - 11); };
     // Exponents of NB row tiles from t0 on against a chunk's two sample tiles.  own (SELF): the row tile that is the chunk's
-    // first sample tile, if it is one.  to_t: the first operands of the second contraction are read behind.
-    auto exponents = [&](const char* xc, int t0, const f32x4& nj0, const f32x4& nj1, int own, bool to_t, auto lead, f32x4 (&c)[NB][2]) __attribute__((always_inline)) {
+    // first sample tile, if it is one.  c_at: the chunk.  to_t: the first operands of the second contraction are read behind.
+    auto exponents = [&](const char* xc, int c_at, int t0, const f32x4& nj0, const f32x4& nj1, int own, bool to_t, auto lead, f32x4 (&c)[NB][2]) __attribute__((always_inline)) {
         constexpr bool LEAD = decltype(lead)::value;        // ROWMAX: leading products of whole blocks only
 #pragma unroll
         for (int t = 0; t < NB; ++t) {
             const float add = TERMED ? 0.0f : rows.term[t0 + t];
-            c[t][0] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj0 : nj0 + add;
-            c[t][1] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj1 : nj1 + add;
+            c[t][0] = FAR && !LEAD && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj0 : nj0 + add;
+            c[t][1] = FAR && !LEAD && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj1 : nj1 + add;
         }
         if (AHEAD) read_gram(xc, 0, ga[0]);
 #pragma unroll
@@ -271,21 +274,24 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             }
             pin();
         }
-        if (FAR && far) {
+        if (FAR && !LEAD && __builtin_expect(far, 0)) {
+            // such a row's norm is not shifted (shift_kernel): its exponents are rounded at the size of the norms and come out the
+            // same here as for the row maxima, only then are they shifted
+            // (samples that are held as they are have a scale of 1)
+            f32x4 xs[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) xs[u] = load_at<f32x4>(reinterpret_cast<const char*>(xscale + (int64_t)c_at * kChunkRows + u * kTile), g * 16u);
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
-                // such a row's norm is not shifted (shift_kernel): its exponents are rounded at the size of the norm and come
-                // out the same here as for the row maxima, only then are they shifted
-                const int64_t row = row0 + (t0 + t) * kTile + r;
-                const float unscale = pscale[row];
-                const bool scaled = unscale != 1.0f;
-                const float base = scaled ? pn[row] : rows.term[t0 + t];
-                const float less = scaled ? (ROWMAX ? 0.0f : shift[row]) : 0.0f;
-                const float low = scaled && SCORE ? lowered(t0 + t) : 0.0f;
+                const float unscale = of_row(pscale, t0 + t);
+                const bool last = shifted_last(t0 + t) != 0;
+                const float base = SCORE && last ? of_row(pn, t0 + t) : rows.term[t0 + t];
+                const float less = !ROWMAX && last ? of_row(shift, t0 + t) : 0.0f;
+                const float low = last && SCORE ? lowered(t0 + t) : 0.0f;
 #pragma unroll
                 for (int v = 0; v < 8; ++v) {
                     const float norm = v < 4 ? nj0[v % 4] : nj1[v % 4];
-                    c[t][v / 4][v % 4] = ((fmaf(c[t][v / 4][v % 4], unscale, norm) + base) - less) - low;
+                    c[t][v / 4][v % 4] = ((fmaf(c[t][v / 4][v % 4], unscale * xs[v / 4][v % 4], norm) + base) - less) - low;
                 }
             }
         }
@@ -319,13 +325,13 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     };
 
     // One chunk against all NI row tiles.
-    auto chunk = [&](const char* xc, const f32x4& nj0, const f32x4& nj1, int own, auto lead) __attribute__((always_inline)) {
+    auto chunk = [&](const char* xc, int c_at, const f32x4& nj0, const f32x4& nj1, int own, auto lead) __attribute__((always_inline)) {
 #pragma unroll
         for (int t0 = 0; t0 < NI; t0 += NB) {
             f32x4 c[NB][2], phi[NB][2];
             float dt[NB];
             if constexpr (ROWMAX) {
-                exponents(xc, t0, nj0, nj1, own, false, lead, c);
+                exponents(xc, c_at, t0, nj0, nj1, own, false, lead, c);
 #pragma unroll
                 for (int t = 0; t < NB; ++t) {
                     float& d = dacc[t0 + t];
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 }
                 continue;
             }
-            exponents(xc, t0, nj0, nj1, own, SCORE, std::false_type{}, c);
+            exponents(xc, c_at, t0, nj0, nj1, own, SCORE, lead, c);
             auto weigh = [&](int t) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
@@ -456,7 +462,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
 #pragma unroll
             for (int t0 = 0; t0 < NI; t0 += NB) {
                 f32x4 c[NB][2];
-                exponents(stage_lds[0], t0, nj0, nj1, 2 * (c_begin - own0), false, std::false_type{}, c);
+                exponents(stage_lds[0], c_begin, t0, nj0, nj1, 2 * (c_begin - own0), false, std::false_type{}, c);
 #pragma unroll
                 for (int t = 0; t < NB; ++t)
                     set_scale(t0 + t, fminf(fmaxf(excess(c[t]), kLeastShift), 16384.0f), rows.term[t0 + t], residual[SCORE ? t0 + t : 0]);
@@ -466,8 +472,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             const char* cur = stage_lds[(c - c_begin) & 1];
             fetch(c + 1);                                   // lands in registers while this chunk is worked on
             const f32x4 nn0 = norms(c + 1, 0), nn1 = norms(c + 1, 1);
-            if (ROWMAX && PAIRS > 0 && coarse) chunk(cur, nj0, nj1, 0, std::integral_constant<bool, ROWMAX>{});
-            else chunk(cur, nj0, nj1, 2 * (c - own0), std::false_type{});
+            if (ROWMAX && PAIRS > 0 && coarse) chunk(cur, c, nj0, nj1, 0, std::integral_constant<bool, ROWMAX>{});
+            else chunk(cur, c, nj0, nj1, 2 * (c - own0), std::false_type{});
             if (!ROWMAX && ((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
 #pragma unroll
                 for (int t = 0; t < NI; ++t) {

@@ -210,7 +210,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     }
     __syncthreads();
     const uint32_t far = *far_rows;
-    // such rows of points: 2^-k times themselves (the largest coordinate then has an exponent of 10 at most, k >= 2); of samples: 0
+    // such rows: 2^-k times themselves (the largest coordinate then has an exponent of 10 at most, k >= 2)
     auto largest = [&](int rr) __attribute__((always_inline)) {
         double most = 0.0;
 #pragma unroll 1
@@ -220,7 +220,8 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         }
         return most;
     };
-    auto finite = [](double v) { return v <= 1.7e308; };
+    // infinite and NaN coordinates; of a sample also what has an infinite norm
+    auto finite = [&](double most) { return most <= (job.samples ? 1.0e18 : 1.7e308); };
     // 2^k and 2^-k from the exponent bits (beyond 2^1022: 2^-k is 0)
     auto far_exponent = [](double most) __attribute__((always_inline)) {
         const uint64_t e = __builtin_bit_cast(uint64_t, most) >> 52;
@@ -232,7 +233,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
 #pragma unroll 1
         for (int rr = 0; rr < kPrepRows; ++rr) {
             if (!(far >> rr & 1u)) continue;
-            const double most = job.samples ? (double)__builtin_nanf("") : largest(rr);
+            const double most = largest(rr);
             const double down = finite(most) ? far_down(most) : 0.0;
 #pragma unroll 1
             for (int c = threadIdx.x; c < d; c += kBlock) {
@@ -251,34 +252,28 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         const uint32_t* w = words + rr * stride;
         double acc = squares[rr], scale = 1.0;
         if (far >> rr & 1u) {
+            const double most = largest(rr);
+            if (finite(most)) scale = far_scale(most);
             acc = 0.0;
-            if (job.samples) {
 #pragma unroll 1
-                for (int c = 0; c < d; ++c) {
-                    const double v = coordinate(c, job.src[row * d + c]);
-                    acc = fma(v, v, acc);
-                }
-            } else {
-                const double most = largest(rr);
-                if (finite(most)) scale = far_scale(most);
-#pragma unroll 1
-                for (int c = 0; c < dp; ++c) {
-                    const double v = ((double)half_low(w[c]) + (double)half_high(w[c])) * scale;
-                    acc = fma(v, v, acc);
-                }
-                if (!finite(most)) acc = (double)__builtin_nanf("");            // a point that is not finite: NaN
+            for (int c = 0; c < dp; ++c) {
+                const double v = ((double)half_low(w[c]) + (double)half_high(w[c])) * scale;
+                acc = fma(v, v, acc);
             }
+            // not finite: a point's sums are NaN, a sample weighs nothing (with a coordinate that is NaN: NaN)
+            if (!finite(most)) acc = job.samples ? most * most : (double)__builtin_nanf("");
         }
         const float norm = poisoned ? __builtin_nanf("") : row < job.rows ? -(float)(0.5 * acc) : kPadNorm;
         const double rest = -0.5 * acc - (double)norm;
         const float left = row < job.rows && fabs(rest) < 500.0 ? (float)rest : 0.0f;       // (a norm below 2^31)
         job.dst_n[row] = norm;
+        half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         if (job.samples) {
-            const bool wide = __builtin_amdgcn_ballot_w64(row < job.rows && norm < -kCoarseSample) != 0;
-            if (rr == 0) half2_marks(job.dst, job.rows_pad, dp)[r0 / kChunkRows] = wide ? kMarkWide : 0;
+            auto any = [&](bool v) { return __builtin_amdgcn_ballot_w64(row < job.rows && v) != 0; };
+            const uint32_t marks = (any(norm < -kCoarseSample) ? kMarkWide : 0) | (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0);
+            if (rr == 0) half2_marks(job.dst, job.rows_pad, dp)[r0 / kChunkRows] = (uint8_t)marks;
         } else {
             half2_residual(job.dst, job.rows_pad, dp)[row] = left;
-            half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         }
         if (tail != kTailNone) {        // what goes into the last block's spare columns
             const int block = dp - 16, lows = tail == kTailEight ? block : block + 8;

@@ -45,9 +45,10 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 // Four row tiles a wave take the fewest operand reads that the registers allow up to dp = 32 (eval 96); above, eight waves of
 // two share a workgroup's reads instead.  The score at dp = 48 has four at the samples themselves only, without reading ahead
 // (both together spill), likewise four instead of eight at dp = 16 where rows may be scaled.  The row maxima, built for leading
-// and for all products, need a few registers more: two waves a SIMD at dp = 48, eight waves of two row tiles at dp = 96.
+// and for all products, need a few registers more: two waves a SIMD at dp = 48, eight waves of two row tiles at dp = 96, and at
+// d = 25 .. 32 the Gram accumulators of two row tiles at a time instead of four.
 struct HalfShape { int ni, waves, nb; bool ahead; int minw; };
-constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false, bool rowmax = false)
+constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false, bool rowmax = false, int tail = kTailSixteen)
 {
     if (score) {
         if (rt == 2) return {2, 4, 2, true, kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 ? 2 : 1};
@@ -55,7 +56,7 @@ constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, boo
         if (rt == 8 && kb == 1) return far ? HalfShape{4, 8, 2, true, 2} : HalfShape{8, 4, 2, true, 2};
     } else {
         if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : kb <= 4 ? 3 : 2};
-        if (rt == 4) return kb <= (rowmax ? 5 : 6) ? HalfShape{4, 4, kb <= 3 ? 4 : 2, false, kb <= (rowmax ? 2 : 3) ? 3 : 2} : HalfShape{2, 8, 2, false, 2};
+        if (rt == 4) return kb <= (rowmax ? 5 : 6) ? HalfShape{4, 4, kb <= 3 && !(rowmax && kb == 2 && tail == kTailNone) ? 4 : 2, false, kb <= (rowmax ? 2 : 3) ? 3 : 2} : HalfShape{2, 8, 2, false, 2};
         if (rt == 8 && kb == 1) return {8, 4, 4, false, 2};
     }
     return {};
@@ -546,7 +547,7 @@ template <int KIND, bool FAR, int KB, int TAIL, int RT>
 int launch_half_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
 {
     constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints;
-    constexpr HalfShape sh = half_shape(KB, score, RT, KIND == kScoreSelf, FAR, KIND == kRowMax);
+    constexpr HalfShape sh = half_shape(KB, score, RT, KIND == kScoreSelf, FAR, KIND == kRowMax, TAIL);
     if constexpr (sh.ni == 0) {
         return SDKDE_EUNSUPPORTED;
     } else {

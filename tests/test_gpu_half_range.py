@@ -135,3 +135,36 @@ def test_shifted_sums_of_points_far_in_every_coordinate(d):
     q[::3] *= np.float32(0.5)
     print(f"far in every coordinate d={d}", flush=True)
     _check_shifted_far_points(P, x, q, h, 2.0 * np.linalg.norm(x - x.mean(axis=0), axis=1).max())
+
+
+@pytest.mark.parametrize("d", [4, 7, 17, 32, 48, 128])
+@pytest.mark.parametrize("distance", [30000.0, 1e5, 1e7, 1e9])
+def test_shifted_densities_where_every_sample_is_beyond_the_range(d, distance):
+    """Two clusters beyond what the unshifted sums reach, queries between them, and some at the clusters' distance on other
+    sides: their log densities are those of the nearest samples, to what fp32 exponents of that size resolve."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, h = 1500, 300, 1.0
+    print(f"every sample beyond d={d} distance {distance}", flush=True)
+    x, q, _ = _two_clusters(n, m, d, distance, d)
+    q[1::5, 0] += np.float32(distance)
+    xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
+    flags = P.SDKDE_FLAG_MAX_SHIFT
+    ref = oracle.eval_log_density(x, q, h)
+    # as in _check_shifted_far_points; the samples a distance r away are as far from the centre, the queries up to that
+    allowed = gram_exponent_error(x, q, h, low_precision_inputs=True) + 4.0 * 2.0**-23 * np.abs(ref)
+    logd = P.sdkde_eval(xd, qd, h, want="log", flags=flags)[1].cpu().numpy()
+    worst = (np.abs(logd - ref) / allowed).max()
+    print(f"log density {worst:.3f} of the bound", flush=True)
+    assert worst <= 1.0
+    # the others take no notice of one such sample
+    x, q, _ = _two_clusters(n, m, d, 5.0, d)
+    ref, e = oracle.eval_log_density(x, q, h), gram_exponent_error(x, q, h)
+    y = np.concatenate([x, np.zeros((1, d), np.float32)])
+    y[-1, d - 1] = distance
+    for f in (0, flags):
+        logd = P.sdkde_eval(torch.from_numpy(y).cuda(), torch.from_numpy(q).cuda(), h, want="log", flags=f)[1].cpu().numpy()
+        seen = np.isfinite(logd)
+        assert seen.all() or f == 0
+        assert np.all(np.abs(logd - ref - np.log(n / (n + 1)))[seen] <= (e + 2.0**-18 + 2.0**-23 * np.abs(ref))[seen])
