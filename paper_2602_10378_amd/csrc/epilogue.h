@@ -98,6 +98,44 @@ __device__ __forceinline__ f32x4 load_quad(const float* at, int as_quad, int lef
     return v;
 }
 
+// What the sums T of the two-part format are in where a column has a unit of its own (half2.h); the sums D are then below zero, which
+// tells the epilogues without another read.  Of such a column p~ is formed anew from the caller's array, since the prepared one
+// resolves no more than 2^-25; of others the prepared one is better (what its split leaves moved the weights, too, and cancels).
+// (The code for this costs score_epilogue_quad_kernel 1.1 us on small calls, 3.7 / 4.8 us at 2048 x 64, whether as a branch or
+// without one, the units read early, late or not at all.)
+struct ScoreUnits {
+    const float* units;        // behind the prepared samples
+    const float* rows;         // the points, or the samples
+
+    __device__ __forceinline__ static bool there(float& dsum, int format)
+    {
+        const bool below = format == kFormatHalf2 && dsum < 0.0f;
+        dsum = below ? -dsum : dsum;
+        return __builtin_expect(below, 0);
+    }
+    __device__ __forceinline__ void plain(int64_t i, int c, int d, int dp, float& t, float& p, float& rest) const
+    {
+        const float unit = units[c];
+        if (unit == 1.0f) return;
+        const Coordinate own(units[dp + 1], units[dp + 2], rows[i * d + c], units[dp + 4 + c]);
+        t *= inverse_unit(unit);
+        p = own.v;
+        rest = own.low;
+    }
+    // (a loop, so that this rare code is short)
+    __device__ __forceinline__ void plain(int64_t i, int c0, int d, int dp, f32x4& t, f32x4& p, f32x4& rest) const
+    {
+#pragma unroll 1
+        for (int v = 0; v < 4; ++v) {
+            float tv = t.x, pv = p.x, rv = rest.x;
+            if (c0 + v < d) plain(i, c0 + v, d, dp, tv, pv, rv);
+            t = f32x4{t.y, t.z, t.w, tv};
+            p = f32x4{p.y, p.z, p.w, pv};
+            rest = f32x4{rest.y, rest.z, rest.w, rv};
+        }
+    }
+};
+
 // mode 0 (MFMA path, separate points): score = (T/D - p~) * inv_ah2            (T = Phi X regrouping)
 // mode 1 (thin path):                   score = (N/D) * inv_ah2                (direct-form numerator)
 // mode 2 (MFMA path, at the samples):   score = (T' - p~ D') / (D' + 1) * inv_ah2
@@ -109,7 +147,7 @@ template <int PARTS>
 __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
     int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
-    float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, float min_sum)
+    float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, float min_sum, ScoreUnits units)
 {
     constexpr int kEpiOutputs = kBlock / PARTS;
     __shared__ float red[PARTS][kEpiOutputs];
@@ -119,14 +157,16 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const int c = active ? (int)(idx % d) : 0;
     PreparedQuad own = {};
     if (mode != 1) own.load(ps, i, c & ~3, dp, format, mode == 0 ? m_pad : 0);
-    const float tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
-    const float dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
+    float tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
+    float dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
+    const bool in_units = ScoreUnits::there(dsum, format);
     float pc = 0.0f, rest = 0.0f;
     if (mode != 1) {
         f32x4 low;
         pc = own.value(format, mode == 0 ? m_pad : 0, &low)[c & 3];
         rest = low[c & 3];
+        if (in_units) units.plain(i, c, d, dp, tsum, pc, rest);
     }
     float out = 0.0f;
     if (mode == 2) {
@@ -148,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
     int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
     float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, int quad_io,
-    float min_sum)
+    float min_sum, ScoreUnits units)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
     __shared__ f32x4 red_t[PARTS][LANES];
@@ -185,7 +225,8 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
         dsum += red_d[k][lane];
     }
     f32x4 rest;
-    const f32x4 pc = own.value(format, mode == 0 ? m_pad : 0, &rest);
+    f32x4 pc = own.value(format, mode == 0 ? m_pad : 0, &rest);
+    if (ScoreUnits::there(dsum, format)) units.plain(i, c0, d, dp, tsum, pc, rest);
     f32x4 out;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {

@@ -19,7 +19,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* ps, int nsplit, int64_t m,
     int64_t m_pad, int d, int dp, int format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
     float half_h2, float* x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
-    const float* centre, double a, Stamp stamp)
+    const float* centre, double a, Stamp stamp, ScoreUnits units)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
     __shared__ float smean[SDKDE_MAX_D];
@@ -29,8 +29,8 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     __shared__ f32x4 red_t[PARTS][LANES];
     __shared__ float red_d[PARTS][LANES];
     __shared__ int stamp_flag;
-    __shared__ uint32_t far_rows;
-    if (threadIdx.x == 0) far_rows = 0;
+    __shared__ uint32_t far_rows[2];
+    if (threadIdx.x < 2) far_rows[threadIdx.x] = 0;
     const float of_centre = (int)threadIdx.x < d ? centre[threadIdx.x] : 0.0f;      // needed by prep_rows only
     const bool of_queries = (int)blockIdx.x >= blocks_sd;
     const PrepJob job = of_queries ? q_job : sd_job;
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
                     dsum += red_d[k][lane];
                 }
                 f32x4 rest;
-                const f32x4 pc = prepared.value(format, 0, &rest);
+                f32x4 pc = prepared.value(format, 0, &rest);
+                if (ScoreUnits::there(dsum, format)) units.plain(i, c0, d, dp, tsum, pc, rest);
                 f32x4 out;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     if ((int)threadIdx.x < d) smean[threadIdx.x] = of_centre;
     __syncthreads();
     const bool poisoned = stamp_flag != 0;
-    prep_rows(job, r0, d, dp, a, format, poisoned, smean, raw, used, &far_rows);
+    prep_rows(job, r0, d, dp, a, format, poisoned, smean, nullptr, false, raw, used, far_rows);       // (neither job has a dst_t)
 }
 
 }  // namespace

@@ -29,9 +29,14 @@ namespace {
 //     products l l of which then are in the sum, too): columns 8 .. 11 of the block, or 0 .. 3 of eight.
 //   a last 32-column block of at most 24 columns (kTailSpare): kTermFactor and the norm's residual in the first parts of columns
 //     24 .. 27, zeros behind and in the second parts.
-// Prepared transpose ("xt"), chunks of KB * 3072 bytes: 16-column block mb, part q (h, l, 2^-11 h) at mb * 3072 + q * 1024; lane
+// Prepared transpose ("xt"), 2^k times the coordinates, chunks of KB * 3072 bytes: 16-column block mb, part q (h, l, 2^-11 h) at mb * 3072 + q * 1024; lane
 //   16 g + r holds column 16 mb + r of rows 4g .. 4g+3 of the first tile and 4g .. 4g+3 of the second, which is the order the
 //   Gram accumulators of the two tiles leave Phi in.
+//   A column has a k above 0 where the coordinates are small beside 1 (less than 1/4 apart in the mean): two parts resolve 2^-25 of
+//   it and no less, and a score is the small difference of sums of them.  (A column a thousand times narrower than the bandwidth:
+//   its scores were good to 2 10^-5 without, 10^-7 with; one 10^6 times narrower: 2 10^-2.)  How far apart they are is seen on the
+//   rows that the centre comes from, so a value can be beyond the fp16 range in such a unit: its chunk then has its own units, in
+//   which its largest value has the exponent 14.
 // Norms are -|h + l|^2 / 2, rounded once from double; for points `residual` holds what that rounding left.
 // ------------------------------------------------------------------------------------------
 
@@ -97,12 +102,37 @@ __host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int d
 // its samples.
 constexpr uint32_t kMarkWide = 1;                   // one with half a squared norm above kCoarseSample
 constexpr uint32_t kMarkDistant = 2;                // one further than kFarPoint from the centre
-constexpr uint32_t kMarks = 2;                      // how many there are
+constexpr uint32_t kMarkOwnUnits = 4;               // its columns of "xt" are in units of their own
+constexpr uint32_t kMarks = 3;                      // how many there are
 constexpr float kCoarseNorm = 2048.0f, kCoarseSample = 8192.0f;      // see the row maxima in pair_half.h
 __host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int dp)
 {
     return reinterpret_cast<uint8_t*>(half2_scale(xs, rows_pad, dp) + rows_pad);
 }
+// Behind the marks, for scores: the units that the columns of "xt" are in, 2^k of each of the dp columns, a float that is not 0 if any
+// is not 1, the scale a in two floats, one float unused, the centre (dp floats); and for chunks with units of their own 2^e of each
+// column: their values are 2^(k - e) times the coordinates.
+constexpr int kMostUnit = 60;                       // k at most
+__host__ __device__ inline float* half2_units(float* xs, int64_t rows_pad, int dp)
+{
+    return reinterpret_cast<float*>(half2_marks(xs, rows_pad, dp) + rows_pad / 32);
+}
+__host__ __device__ inline float* half2_chunk_units(float* xs, int64_t rows_pad, int dp) { return half2_units(xs, rows_pad, dp) + 2 * dp + 4; }
+// 2^-k of 2^k
+__device__ __forceinline__ float inverse_unit(float unit) { return __builtin_bit_cast(float, 0x7f000000u - __builtin_bit_cast(uint32_t, unit)); }
+
+// A coordinate a (x - mean) as a sum of two floats.
+struct Coordinate {
+    float v, low;
+    __device__ __forceinline__ Coordinate(double a, float x, float mean) : Coordinate((float)a, (float)(a - (double)(float)a), x, mean) {}
+    __device__ __forceinline__ Coordinate(float a_high, float a_low, float x, float mean)
+    {
+        const float diff = x - mean, part = diff - x, left = (x - (diff - part)) + (-mean - part);       // x - mean = diff + left
+        v = a_high * diff;
+        low = fmaf(a_high, diff, -v) + fmaf(a_high, left, a_low * diff);
+    }
+};
+
 // The marks of chunks first .. last - 1 (and of up to three on either side) together, in all lanes.
 __device__ __forceinline__ uint32_t marks_of(const uint8_t* marks, int first, int last, int lane)
 {

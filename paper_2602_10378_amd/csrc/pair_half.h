@@ -150,9 +150,12 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
 
     const int c_begin = split * tiles_per_split / 2;
     const int c_end = min(ntiles, split * tiles_per_split + tiles_per_split) / 2;
-    uint32_t marks = 0;                                     // of the split's samples (wave-uniform)
+    uint32_t marks = 0;                                     // of the split's samples (wave-uniform), where they are asked for
     const int64_t n_pad = ((int64_t)ntiles * kTile + kRowPad - 1) / kRowPad * kRowPad;
-    if constexpr (ROWMAX) marks = marks_of(half2_marks(const_cast<float*>(xs), n_pad, DP), c_begin, c_end, lane);
+    const uint8_t* const marks_at = half2_marks(const_cast<float*>(xs), n_pad, DP);
+    const float* const units = half2_units(const_cast<float*>(xs), n_pad, DP);
+    const float other_units = SCORE ? units[DP] : 0.0f;             // a column of xt is not in plain coordinates
+    if constexpr (ROWMAX) marks = marks_of(marks_at, c_begin, c_end, lane);
 
     HalfRows<KB, TAIL, NI, SCORE, FAR> rows;
     rows.load(ps, pn, row0, r, g);
@@ -468,34 +471,57 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                     set_scale(t0 + t, fminf(fmaxf(excess(c[t]), kLeastShift), 16384.0f), rows.term[t0 + t], residual[SCORE ? t0 + t : 0]);
             }
         }
-        for (int c = c_begin; c < c_end; ++c) {             // the same bounds for all waves of the workgroup
-            const char* cur = stage_lds[(c - c_begin) & 1];
-            fetch(c + 1);                                   // lands in registers while this chunk is worked on
-            const f32x4 nn0 = norms(c + 1, 0), nn1 = norms(c + 1, 1);
-            if (ROWMAX && PAIRS > 0 && coarse) chunk(cur, c, nj0, nj1, 0, std::integral_constant<bool, ROWMAX>{});
-            else chunk(cur, c, nj0, nj1, 2 * (c - own0), std::false_type{});
-            if (!ROWMAX && ((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
+        // SCORE: a chunk with units of its own is summed in them: what has been summed is brought to them and back, on both levels.
+        // Where the split has one every chunk is a turn of the outer loop.  (Asked inside the inner one it cost 3 to 5 % of a score.)
+        auto own_units = [&](int c, bool to) __attribute__((always_inline)) {
+            if (!(marks & marks_at[c] & kMarkOwnUnits)) return;
+#pragma unroll
+            for (int mb = 0; mb < KT; ++mb) {
+                f32x4 by = load_at<f32x4>(reinterpret_cast<const char*>(units + 2 * DP + 4 + (int64_t)c * DP + mb * 16), g * 16u);
+                if (to) by = f32x4{inverse_unit(by.x), inverse_unit(by.y), inverse_unit(by.z), inverse_unit(by.w)};
 #pragma unroll
                 for (int t = 0; t < NI; ++t) {
-                    dsum[t] += dacc[t];
-                    dacc[t] = 0.0f;
-                    if constexpr (SCORE) {
+                    tacc[t][mb] *= by;
+                    if (SUMLDS) sum_lds[wave][t * KT + mb][lane] *= by;
+                    else if (flushed) *slot_at(t, mb) *= by;
+                }
+            }
+        };
+        if (SCORE && (FAR || other_units != 0.0f)) marks = marks_of(marks_at, c_begin, c_end, lane);
+        const bool alone = SCORE && (marks & kMarkOwnUnits) != 0;
+        for (int c = c_begin; c < c_end;) {
+            const int end = alone ? c + 1 : c_end;
+            if (SCORE && alone) own_units(c, true);
+            for (; c < end; ++c) {                          // the same bounds for all waves of the workgroup
+                const char* cur = stage_lds[(c - c_begin) & 1];
+                fetch(c + 1);                               // lands in registers while this chunk is worked on
+                const f32x4 nn0 = norms(c + 1, 0), nn1 = norms(c + 1, 1);
+                if (ROWMAX && PAIRS > 0 && coarse) chunk(cur, c, nj0, nj1, 0, std::integral_constant<bool, ROWMAX>{});
+                else chunk(cur, c, nj0, nj1, 2 * (c - own0), std::false_type{});
+                if (!ROWMAX && ((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
 #pragma unroll
-                        for (int mb = 0; mb < KT; ++mb) {
-                            f32x4* const at = SUMLDS ? &sum_lds[wave][t * KT + mb][lane] : slot_at(t, mb);
-                            *at = SUMLDS || flushed ? *at + tacc[t][mb] : tacc[t][mb];
-                            tacc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int t = 0; t < NI; ++t) {
+                        dsum[t] += dacc[t];
+                        dacc[t] = 0.0f;
+                        if constexpr (SCORE) {
+#pragma unroll
+                            for (int mb = 0; mb < KT; ++mb) {
+                                f32x4* const at = SUMLDS ? &sum_lds[wave][t * KT + mb][lane] : slot_at(t, mb);
+                                *at = SUMLDS || flushed ? *at + tacc[t][mb] : tacc[t][mb];
+                                tacc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                            }
                         }
                     }
+                    flushed = true;
                 }
-                flushed = true;
+                nj0 = nn0;
+                nj1 = nn1;
+                // The other buffer was last read before the previous barrier; this barrier publishes the new chunk and
+                // ends the reads of the current one.
+                deposit(stage_lds[(c + 1 - c_begin) & 1]);
+                __syncthreads();
             }
-            nj0 = nn0;
-            nj1 = nn1;
-            // The other buffer was last read before the previous barrier; this barrier publishes the new chunk and
-            // ends the reads of the current one.
-            deposit(stage_lds[(c + 1 - c_begin) & 1]);
-            __syncthreads();
+            if (SCORE && alone) own_units(end - 1, false);
         }
     }
 #pragma unroll
@@ -515,6 +541,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             const float other = __shfl_xor(dtot, step);
             dtot = ROWMAX ? fmaxf(dtot, other) : dtot + other;
         }
+        if (SCORE && other_units != 0.0f) dtot = -dtot;         // tells the epilogues
         if (g == 0) part_d[(int64_t)split * m_pad + row0 + t * kTile + r] = dtot;
     }
 }

@@ -24,6 +24,16 @@ __device__ __forceinline__ double sum_of_eight(double v)
     return add(v, std::integral_constant<int, 0x141>());    // row_half_mirror
 }
 
+__device__ __forceinline__ float sum_of_eight(float v)
+{
+    auto add = [](float x, auto ctrl) {
+        return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = add(v, std::integral_constant<int, 0xB1>());
+    v = add(v, std::integral_constant<int, 0x4E>());
+    return add(v, std::integral_constant<int, 0x141>());
+}
+
 // The centre all coordinates are taken relative to: the column means of an evenly strided subsample of the
 // samples (about kCentreElems input values, at least 32 rows), summed in double in a fixed order, so every
 // workgroup that computes it gets the same bits.  Any point near the data serves (the exponent
@@ -42,56 +52,106 @@ struct PrepCommon {
     int64_t rows, stride;      // centre_rows of them, this many rows apart (>= 1)
     double weight;             // 1 / rows
     float* centre;             // in the workspace: written by workgroup 0 when computed, read otherwise
+    float* units;              // the same for the units of "xt" (half2.h); null: none wanted
 };
-inline PrepCommon centre_of(const float* src, int64_t n, int d, float* centre)
+inline PrepCommon centre_of(const float* src, int64_t n, int d, float* centre, float* units)
 {
     const int64_t rows = src ? centre_rows(n, d) : 1;
-    return {src, rows, src ? n / rows : 1, 1.0 / (double)rows, centre};
+    return {src, rows, src ? n / rows : 1, 1.0 / (double)rows, centre, units};
 }
 
-// Ends with a barrier; meanwhile() is called before one, once the loads above it have been waited for.
-template <typename F>
-__device__ __forceinline__ void block_centre(const PrepCommon& pc, int d, double* red, float* smean, F meanwhile)
+// The unit of a column whose coordinates are about `spread` apart: 2^k that makes that 32 to 64, if it is below 1/4.
+__device__ __forceinline__ float unit_of(float spread)
+{
+    if (!(spread > 0.0f && spread < 0.25f)) return 1.0f;   // (a constant column, or nothing known: as it is)
+    const int k = 5 + 127 - (int)(__builtin_bit_cast(uint32_t, spread) >> 23);
+    return __builtin_bit_cast(float, (uint32_t)(127 + (k < kMostUnit ? k : kMostUnit)) << 23);
+}
+
+// Ends with a barrier; meanwhile() is called before one, once the loads above it have been waited for.  UNITS: also the columns'
+// units into sunit, from the mean difference of rows that follow each other in a thread (its first: from row 0), which needs
+// no mean; *other (0, since before a barrier): whether one is not 1.
+template <bool UNITS, typename F>
+__device__ __forceinline__ void block_centre(const PrepCommon& pc, int d, float a, double* red, float* smean, float* sunit, uint32_t* other, F meanwhile)
 {
     const int rows_per_iter = kBlock / d;                 // d <= 128 < kBlock
     const int rr = threadIdx.x / d, c = threadIdx.x % d;
     const int rows = (int)pc.rows;
+    __shared__ float red_apart[UNITS ? kBlock : 1];
     double acc = 0.0;
+    float apart = 0.0f;
     if (rr < rows_per_iter) {
+        float before = UNITS ? pc.centre_src[c] : 0.0f;
 #pragma unroll 16
-        for (int k = rr; k < rows; k += rows_per_iter) acc += (double)pc.centre_src[k * pc.stride * d + c];
+        for (int k = rr; k < rows; k += rows_per_iter) {
+            const float x = pc.centre_src[k * pc.stride * d + c];
+            acc += (double)x;
+            if (UNITS) apart += fabsf(x - before);
+            before = x;
+        }
     }
     red[threadIdx.x] = acc;
+    if (UNITS) red_apart[threadIdx.x] = apart;
     meanwhile();
     __syncthreads();
+    auto finish = [&](int col, double sum, float steps) {
+        smean[col] = (float)(sum * pc.weight);
+        if constexpr (UNITS) {
+            const float unit = pc.units ? unit_of(steps * (float)pc.weight * a) : 1.0f;
+            sunit[col] = unit;
+            if (unit != 1.0f) *other = 1;
+        }
+    };
     // eight threads a column (by one the reads of its partial sums were a chain of 256 / d LDS latencies)
     if (8 * d <= kBlock) {
         const int col = threadIdx.x / 8;
         if (col < d) {
             double t = 0.0;
+            float t2 = 0.0f;
 #pragma unroll 4
-            for (int q = threadIdx.x % 8; q < rows_per_iter; q += 8) t += red[q * d + col];
+            for (int q = threadIdx.x % 8; q < rows_per_iter; q += 8) {
+                t += red[q * d + col];
+                if (UNITS) t2 += red_apart[q * d + col];
+            }
             t = sum_of_eight(t);
-            if (threadIdx.x % 8 == 0) smean[col] = (float)(t * pc.weight);
+            if (UNITS) t2 = sum_of_eight(t2);
+            if (threadIdx.x % 8 == 0) finish(col, t, t2);
         }
     } else if ((int)threadIdx.x < d) {
         double t = 0.0;
+        float t2 = 0.0f;
 #pragma unroll 4
-        for (int q = 0; q < rows_per_iter; ++q) t += red[q * d + threadIdx.x];
-        smean[threadIdx.x] = (float)(t * pc.weight);
+        for (int q = 0; q < rows_per_iter; ++q) {
+            t += red[q * d + threadIdx.x];
+            if (UNITS) t2 += red_apart[q * d + threadIdx.x];
+        }
+        finish((int)threadIdx.x, t, t2);
     }
     __syncthreads();
 }
 
-// Centre into smean (computed or read back).  Ends with a barrier.
-template <typename F>
-__device__ __forceinline__ void prep_common(const PrepCommon& pc, int d, double* red, float* smean, F meanwhile)
+// Centre into smean and (UNITS) the columns' units into sunit (computed, or the centre read back, all units 1).  Ends with a barrier.
+template <bool UNITS, typename F>
+__device__ __forceinline__ void prep_common(const PrepCommon& pc, int d, double a, double* red, float* smean, float* sunit, uint32_t* other, F meanwhile)
 {
     if (pc.centre_src) {
-        block_centre(pc, d, red, smean, meanwhile);
+        block_centre<UNITS>(pc, d, (float)a, red, smean, sunit, other, meanwhile);
         if (blockIdx.x == 0 && (int)threadIdx.x < d) pc.centre[threadIdx.x] = smean[threadIdx.x];
+        if (UNITS && pc.units && blockIdx.x == 0 && threadIdx.x < SDKDE_MAX_D) {
+            const int dp = (d + 15) / 16 * 16, c = threadIdx.x;
+            if (c < dp) {
+                pc.units[c] = c < d ? sunit[c] : 1.0f;
+                pc.units[dp + 4 + c] = c < d ? smean[c] : 0.0f;
+            }
+            if (c == 0) {
+                pc.units[dp] = *other ? 1.0f : 0.0f;
+                pc.units[dp + 1] = (float)a;
+                pc.units[dp + 2] = (float)(a - (double)(float)a);
+            }
+        }
     } else {
         if ((int)threadIdx.x < d) smean[threadIdx.x] = pc.centre[threadIdx.x];
+        if (UNITS && (int)threadIdx.x < d) sunit[threadIdx.x] = 1.0f;
         meanwhile();
         __syncthreads();
     }
@@ -106,7 +166,7 @@ struct PrepJob {
     float* dst_n;
     float pad_value;      // thin path only: coordinate value of padding rows
     bool samples;         // the rows are summed over (not only evaluated at)
-    bool shifted;         // points of max-shifted sums
+    bool shifted;         // points of max-shifted sums, or samples of the scores that are such sums
     int tail;             // kFormatHalf2: half_tail of the kernel they are for
 };
 
@@ -168,19 +228,19 @@ struct StagedRows {
 };
 
 // The body of prep_mfma_kernel for one workgroup and two fp16 parts a value (half2.h): rows r0 .. r0 + kPrepRows of `job`.
-// Their input values stand in words[][] as floats.  far_rows: zero, since before a barrier.  Coordinates are
-// formed as sums of two floats: what the split leaves of them is then all that is lost (one float rounded the difference and the
+// Their input values stand in words[][] as floats.  far_rows[2]: zeros, since before a barrier.  sunit: the columns' units, for a
+// job with a dst_t, other: whether one is not 1.  Coordinates are formed as sums of two floats: what the split leaves of them is then all that is lost (one float rounded the difference and the
 // product first; in double, with its conversions, a small launch took 0.8 us longer).  A launch of a few workgroups is a chain
 // of latencies: kernel arguments, centre, coordinates, stores.  Rows loaded beside the centre's, eight lanes summing each
 // column of the centre, one barrier less and the norms in a wave without other work: 4.9 to 4.7 us at 4096 x 1024, d = 16.
 __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, int d, int dp, double a, bool poisoned,
-                                                const float* smean, uint32_t* words, uint32_t* far_rows)
+                                                const float* smean, const float* sunit, bool other, uint32_t* words, uint32_t* far_rows)
 {
     static_assert(kPrepRows == kChunkRows && kBlock == 8 * kPrepRows, "a workgroup writes whole chunks, eight lanes a row");
     const int stride = dp + 1;                  // odd: columns are read without bank conflicts
     const double reach = job.samples || !job.shifted ? kReach : kFarPoint;          // largest norm held as it is
     auto coordinate = [&](int c, float in) { return a * ((double)in - (double)smean[c]); };
-    const float a_high = (float)a, a_low = (float)(a - (double)a_high);
+    const bool may_exceed = job.dst_t != nullptr && (other || job.shifted);      // the range, in a column's unit
     __shared__ double squares[kPrepRows];
     {
         const int own = threadIdx.x >> 3, lane8 = threadIdx.x & 7;
@@ -188,28 +248,29 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         const bool live = row < job.rows;
         double square = 0.0;
         uint32_t* const at = words + own * stride;
-        bool beyond = false;
+        float most = 0.0f;                      // in the columns' units
 #pragma unroll 1
         for (int c0 = 2 * lane8; c0 < dp; c0 += 16)
 #pragma unroll
             for (int c = c0; c < c0 + 2; ++c) {
-                const float x = __builtin_bit_cast(float, at[c]), y = c < d ? smean[c] : 0.0f;
-                const float diff = x - y, part = diff - x, left = (x - (diff - part)) + (-y - part);      // x - y = diff + left
-                float v = a_high * diff, low = fmaf(a_high, diff, -v) + fmaf(a_high, left, a_low * diff);
-                const bool there = live && c < d, out = there && fabsf(v) > kHalfMax;
-                beyond |= out;                      // of a value that is there: such rows are read again below
-                if (out || !there) v = low = 0.0f;
-                const uint32_t word = half2_split(v, low);
+                Coordinate x(a, __builtin_bit_cast(float, at[c]), c < d ? smean[c] : 0.0f);
+                const bool there = live && c < d, out = there && fabsf(x.v) > kHalfMax;
+                if (may_exceed && there) most = fmaxf(most, fabsf(x.v) * sunit[c]);
+                if (out || !there) x.v = x.low = 0.0f;
+                const uint32_t word = half2_split(x.v, x.low);
                 at[c] = word;
                 const double held = (double)half_low(word) + (double)half_high(word);
-                square = fma(held, held, square);
+                square = out ? (double)__builtin_inff() : fma(held, held, square);
             }
         square = sum_of_eight(square);
-        if (beyond || square > reach * reach) atomicOr(far_rows, 1u << own);          // rows beyond that, a bit each
+        const bool beyond = square > reach * reach;         // of values that are there: such rows are read again below
+        if (beyond) atomicOr(far_rows, 1u << own);          // a bit each
+        if (may_exceed && most > kHalfMax && (!beyond || job.shifted)) atomicOr(far_rows + 1, 1u);
         if (lane8 == 0) squares[own] = square;
     }
     __syncthreads();
-    const uint32_t far = *far_rows;
+    const uint32_t far = far_rows[0];
+    const bool own_units = far_rows[1] != 0;
     // such rows: 2^-k times themselves (the largest coordinate then has an exponent of 10 at most, k >= 2)
     auto largest = [&](int rr) __attribute__((always_inline)) {
         double most = 0.0;
@@ -229,7 +290,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     };
     auto far_scale = [&](double most) __attribute__((always_inline)) { return __builtin_bit_cast(double, far_exponent(most) << 52); };
     auto far_down = [&](double most) __attribute__((always_inline)) { return __builtin_bit_cast(double, (2046 - far_exponent(most)) << 52); };
-    if (far != 0) {                             // the same for all threads
+    if (__builtin_expect(far != 0, 0)) {        // the same for all threads
 #pragma unroll 1
         for (int rr = 0; rr < kPrepRows; ++rr) {
             if (!(far >> rr & 1u)) continue;
@@ -243,6 +304,27 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         }
         __syncthreads();
     }
+    // What goes into the transpose of a row's column c: without the shift a far sample has no weight, an infinite value never.
+    auto for_transpose = [&](int rr, int c) __attribute__((always_inline)) {
+        Coordinate x(a, 0.0f, 0.0f);
+        if (c < d && r0 + rr < job.rows && (!(far >> rr & 1u) || job.shifted)) x = Coordinate(a, job.src[(r0 + rr) * d + c], smean[c]);
+        if (fabsf(x.v) > 1.0e18f) x.v = x.low = 0.0f;
+        return x;
+    };
+    __shared__ float chunk_unit[SDKDE_MAX_D];
+    if (__builtin_expect(own_units, 0)) {       // the same for all threads
+#pragma unroll 1
+        for (int c = threadIdx.x; c < dp; c += kBlock) {
+            float most = 0.0f;
+#pragma unroll 1
+            for (int rr = 0; rr < kPrepRows; ++rr) most = fmaxf(most, fabsf(for_transpose(rr, c).v));
+            const double scaled = (double)most * (c < d ? sunit[c] : 1.0f);
+            const uint32_t e = scaled > kHalfMax ? (uint32_t)(__builtin_bit_cast(uint64_t, scaled) >> 52) - 1023 - 14 : 0;
+            chunk_unit[c] = __builtin_bit_cast(float, (127 + e) << 23);
+            half2_chunk_units(job.dst, job.rows_pad, dp)[r0 / kChunkRows * dp + c] = chunk_unit[c];
+        }
+        __syncthreads();
+    }
     const int kb = dp / 16, tail = job.tail;
     char* const rows_out = reinterpret_cast<char*>(job.dst) + r0 / kTile * half_tile_bytes(kb);
     char* const t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
@@ -251,7 +333,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         const int64_t row = r0 + rr;
         const uint32_t* w = words + rr * stride;
         double acc = squares[rr], scale = 1.0;
-        if (far >> rr & 1u) {
+        if (__builtin_expect(far >> rr & 1u, 0)) {
             const double most = largest(rr);
             if (finite(most)) scale = far_scale(most);
             acc = 0.0;
@@ -270,7 +352,8 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         if (job.samples) {
             auto any = [&](bool v) { return __builtin_amdgcn_ballot_w64(row < job.rows && v) != 0; };
-            const uint32_t marks = (any(norm < -kCoarseSample) ? kMarkWide : 0) | (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0);
+            const uint32_t marks = (any(norm < -kCoarseSample) ? kMarkWide : 0) | (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0) |
+                                   (own_units ? kMarkOwnUnits : 0);
             if (rr == 0) half2_marks(job.dst, job.rows_pad, dp)[r0 / kChunkRows] = (uint8_t)marks;
         } else {
             half2_residual(job.dst, job.rows_pad, dp)[row] = left;
@@ -309,6 +392,16 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
             part_stride = kPartBytes;
 #pragma unroll
             for (int k = 0; k < 8; ++k) word[k] = words[(s0 + (k & 3) + (k >> 2) * kTile) * stride + c];
+            if (__builtin_expect(other || own_units || far != 0, 0)) {                 // not what the rows hold
+                const float by = (c < d ? sunit[c] : 1.0f) * (own_units ? inverse_unit(chunk_unit[c]) : 1.0f);
+#pragma unroll 1
+                for (int k = 0; k < 8; ++k) {
+                    const Coordinate x = for_transpose(s0 + (k & 3) + (k >> 2) * kTile, c);
+                    const uint32_t w = half2_split(x.v * by, x.low * by);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) word[q] = q == k ? w : word[q];
+                }
+            }
         }
         u32x4 h, l, scaled;
 #pragma unroll
@@ -339,10 +432,10 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
 // [hi(4g..4g+3) | lo(4g..4g+3)].
 // The body for one workgroup: rows r0 .. r0 + kPrepRows of `job`, whose input values are already in raw[][].
 __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, double a, int format, bool poisoned,
-                                          const float* smean, float* raw_rows, float* used_rows, uint32_t* far_rows)
+                                          const float* smean, const float* sunit, bool other, float* raw_rows, float* used_rows, uint32_t* far_rows)
 {
     if (format == kFormatHalf2) {
-        prep_rows_half2(job, r0, d, dp, a, poisoned, smean, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
+        prep_rows_half2(job, r0, d, dp, a, poisoned, smean, sunit, other, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
         return;
     }
     // kPrepRows rows of dp + 1 floats each (odd stride: columns are read without bank conflicts)
@@ -455,20 +548,20 @@ __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob
                                                            PrepCommon common, double a, int format, Stamp stamp)
 {
     __shared__ double red[kBlock];
-    __shared__ float smean[SDKDE_MAX_D];
+    __shared__ float smean[SDKDE_MAX_D], sunit[SDKDE_MAX_D];
     extern __shared__ float prep_lds[];     // prep_lds_bytes: a (x - mean), then (fp16 formats) the hi + lo multiplied instead
     __shared__ int stamp_flag;
-    __shared__ uint32_t far_rows;
+    __shared__ uint32_t far_rows[3];        // (and whether a unit is not 1)
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob job = second ? job1 : job0;
     const int64_t r0 = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kPrepRows;
     StagedRows staged;
     staged.load(job, r0, d);
-    if (threadIdx.x == 0) far_rows = 0;
+    if (threadIdx.x < 3) far_rows[threadIdx.x] = 0;
     stamp_check(stamp, &stamp_flag);
-    prep_common(common, d, red, smean, [&] { staged.store(prep_lds, d, dp); });
+    prep_common<true>(common, d, a, red, smean, sunit, far_rows + 2, [&] { staged.store(prep_lds, d, dp); });
     const bool poisoned = stamp_flag != 0;
-    prep_rows(job, r0, d, dp, a, format, poisoned, smean, prep_lds, prep_lds + kPrepRows * (dp + 1), &far_rows);
+    prep_rows(job, r0, d, dp, a, format, poisoned, smean, sunit, far_rows[2] != 0, prep_lds, prep_lds + kPrepRows * (dp + 1), far_rows);
 }
 
 // Thin-d variant: dst[row][d] = a (x - mean), padding rows get pad_value in every coordinate.
@@ -480,7 +573,7 @@ __global__ __launch_bounds__(kBlock) void prep_thin_kernel(PrepJob job0, PrepJob
     __shared__ float smean[SDKDE_MAX_D];
     __shared__ int stamp_flag;
     stamp_check(stamp, &stamp_flag);
-    prep_common(common, d, red, smean, [] {});
+    prep_common<false>(common, d, a, red, smean, nullptr, nullptr, [] {});
     const bool poisoned = stamp_flag != 0;
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob& job = second ? job1 : job0;

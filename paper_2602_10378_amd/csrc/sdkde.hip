@@ -44,14 +44,14 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 // Clocks of a wave's 16 x 16 pairs (as in pair_half.h) with rt = 2 / 4 / 8: score d = 16 187 / 180 / 178; eval d = 16 83 / 77 / 75.
 // Four row tiles a wave take the fewest operand reads that the registers allow up to dp = 32 (eval 96); above, eight waves of
 // two share a workgroup's reads instead.  The score at dp = 48 has four at the samples themselves only, without reading ahead
-// (both together spill), likewise four instead of eight at dp = 16 where rows may be scaled.  The row maxima, built for leading
-// and for all products, need a few registers more: two waves a SIMD at dp = 48, eight waves of two row tiles at dp = 96, and at
+// (both together spill), likewise four instead of eight at dp = 16 where rows may be scaled; there two at d = 81 .. 88 do not read
+// ahead either.  The row maxima, built for leading and for all products, need a few registers more: two waves a SIMD at dp = 48, eight waves of two row tiles at dp = 96, and at
 // d = 25 .. 32 the Gram accumulators of two row tiles at a time instead of four.
 struct HalfShape { int ni, waves, nb; bool ahead; int minw; };
 constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false, bool rowmax = false, int tail = kTailSixteen)
 {
     if (score) {
-        if (rt == 2) return {2, 4, 2, true, kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 ? 2 : 1};
+        if (rt == 2) return {2, 4, 2, !(far && kb == 6 && tail == kTailSpare), kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 ? 2 : 1};
         if (rt == 4) return kb <= 2 ? HalfShape{4, 4, 4, true, 2} : kb == 3 && self ? HalfShape{4, 4, 2, false, 2} : kb <= 6 ? HalfShape{2, 8, 2, true, 2} : HalfShape{};
         if (rt == 8 && kb == 1) return far ? HalfShape{4, 8, 2, true, 2} : HalfShape{8, 4, 2, true, 2};
     } else {
@@ -755,7 +755,8 @@ Stamp make_stamp(const Workspace& w, bool check, bool score, const float* sample
 int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, const float* centre_src, int64_t centre_n,
                 double a, const Workspace& w, uint32_t flags, const Stamp& stamp, hipStream_t st)
 {
-    const PrepCommon common = centre_of(centre_src, centre_n, p.d, w.centre);
+    float* const units = operand_format(p, flags) == kFormatHalf2 && first.dst_t ? half2_units(first.dst, first.rows_pad, p.dp) : nullptr;
+    const PrepCommon common = centre_of(centre_src, centre_n, p.d, w.centre, units);
     const int64_t per_block = p.thin ? kBlock : kPrepRows;
     if (first.rows_pad % per_block || (second.src && second.rows_pad % per_block)) return SDKDE_EINVAL;
     const int64_t blocks0 = first.rows_pad / per_block;
@@ -851,7 +852,7 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
-    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, false, half_tail(d, self)};
+    const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, shifted, half_tail(d, self)};
     const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
     const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
     rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
@@ -871,6 +872,7 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const int nslots = p.sym_on ? p.sym_ngroups + 2 : p.nsplit;
     const int mode = p.thin ? 1 : (self ? 2 : 0);        // see score_epilogue_kernel
     const float inv_ah2 = (float)(1.0 / (a * h * h)), half_h2 = (float)(0.5 * h * h);
+    const ScoreUnits units{format == kFormatHalf2 ? half2_units(w.xs, p.n_pad, p.dp) : nullptr, self ? samples : points};
     if (!p.thin && epilogue_parts(nslots, total) == kEpiPartsFew) {
         const int64_t quads = m * (p.dp / 4);
         constexpr int per_wg = kBlock / kEpiPartsFew;
@@ -885,15 +887,15 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
                                prep_lds_bytes(p.dp, format), st, w.part_t,
                                w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, format, inv_ah2, score_out, samples, half_h2,
                                samples_sd_out, quad_io, fused->sd_job, fused->q_job, blocks_sd,
-                               w.centre, a, fused->stamp);
+                               w.centre, a, fused->stamp, units);
             return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
         }
         hipLaunchKernelGGL(score_epilogue_quad_kernel, dim3((unsigned)((quads + per_wg - 1) / per_wg)), dim3(kBlock), 0, st,
                            w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
-                           samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n));
+                           samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units);
     } else {
         SDKDE_LAUNCH_EPILOGUE(score_epilogue_kernel, nslots, total, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d,
-                              p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n));
+                              p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n), units);
     }
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }

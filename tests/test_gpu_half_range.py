@@ -168,3 +168,77 @@ def test_shifted_densities_where_every_sample_is_beyond_the_range(d, distance):
         seen = np.isfinite(logd)
         assert seen.all() or f == 0
         assert np.all(np.abs(logd - ref - np.log(n / (n + 1)))[seen] <= (e + 2.0**-18 + 2.0**-23 * np.abs(ref))[seen])
+
+
+def _column_bound(x, p, h):
+    """Per point and column: an error e in every exponent moves a weight by e of itself (twice: numerator and denominator), the
+    parts of a weight hold it to 2^-22 and sums round some more, 2^-20 of each term's pull in the column; and coordinates are held to
+    2^-23 of themselves and of the column's spread, so the two sums that cancel to 2^-21 of the mean coordinate."""
+    x, p = x.astype(np.float64), p.astype(np.float64)
+    c = x.mean(axis=0)
+    x, p = x - c, p - c
+    r2 = np.maximum((p * p).sum(1)[:, None] + (x * x).sum(1)[None] - 2.0 * p @ x.T, 0.0)
+    u = r2 / (2.0 * h * h)
+    w = np.exp(-(u - u.min(axis=1, keepdims=True)))
+    w /= w.sum(axis=1, keepdims=True)
+    pull = np.stack([(w * np.abs(x[:, k] - p[:, k, None])).sum(1) for k in range(x.shape[1])], axis=1)
+    e = 2.0 * gram_exponent_error(x, p, h)[:, None] + 2.0**-20
+    return (e * pull + 2.0**-21 * (np.abs(p) + w @ np.abs(x) + x.std(axis=0))) / (h * h)
+
+
+def _check_columns(P, x, q, h):
+    import torch
+    xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
+    score, sd = torch.empty_like(xd), torch.empty_like(xd)
+    P.sdkde_fit_eval(xd, qd, h, score_out=score, samples_sd_out=sd, log_density_out=torch.empty(len(q), device="cuda"))
+    worst = []
+    for got, at in ((P.sdkde_score(xd, h), x), (score, x), (P.sdkde_score(xd, h, points=qd), q),
+                    (P.sdkde_score(xd, h, points=qd, flags=P.SDKDE_FLAG_MAX_SHIFT), q)):
+        ref = oracle.score(x, h) if at is x else oracle.score(x, h, points=q)
+        worst.append((np.abs(got.cpu().numpy() - ref) / _column_bound(x, at, h)).max())
+    print("scores by column:", " ".join(f"{v:.3f}" for v in worst), "of the bound", flush=True)
+    assert max(worst) <= 1.0
+
+
+@pytest.mark.parametrize("d,n", [(7, 700), (7, 2100), (16, 700), (16, 2100), (17, 1100), (32, 700), (37, 2100), (64, 1100), (128, 500)])
+def test_scores_of_columns_far_narrower_than_the_bandwidth(d, n):
+    """Columns from as wide as the others to 10^-9 of that, and all of them 1000 times narrower than the bandwidth: two fp16
+    parts resolve 2^-25 of a bandwidth, of which such a column's score is far more than the rounding."""
+    import paper_2602_10378_amd as P
+    P.load()
+    m = 90
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    narrow = np.float32(10.0) ** -(np.arange(d) % 10).astype(np.float32)
+    print(f"narrow columns n={n} d={d}", flush=True)
+    _check_columns(P, x * narrow, q * narrow, float(h))
+    _check_columns(P, x, q, 1000.0 * float(h))
+
+
+@pytest.mark.parametrize("d", [7, 16, 17, 37, 64])
+def test_a_value_far_outside_its_narrow_column(d):
+    """A column 10^6 times narrower than the others, but for a few rows (none of those the centre is formed of) with values of
+    the others' size: beyond the fp16 range in the column's unit."""
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 1300, 90
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    c = d // 2
+    x[:, c] *= np.float32(1e-6)
+    q[:, c] *= np.float32(1e-6)
+    x[[1003, 1009, 1201], c] += np.array([1.0, -0.5, 2.0], dtype=np.float32) * np.float32(h)
+    print(f"values outside a narrow column d={d}", flush=True)
+    _check_columns(P, x, q, float(h))
+
+
+@pytest.mark.parametrize("d", [7, 17, 32, 128])
+@pytest.mark.parametrize("distance", [1e5, 1e7, 1e9])
+def test_shifted_scores_where_every_sample_is_beyond_the_range(d, distance):
+    """The score between two clusters beyond the fp16 range: the nearer one's samples, less the query."""
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, h = 1500, 300, 1.0
+    print(f"scores, every sample beyond d={d} distance {distance}", flush=True)
+    x, q, size = _two_clusters(n, m, d, distance, d)
+    q[1::2, d // 2] += np.float32(0.5 * distance)           # not only around the middle, where the nearer one is not resolved
+    q[::2, d // 2] -= np.float32(0.5 * distance)
+    _check_shifted_far_points(P, x, q, h, size + 2.0**-22 * distance)
