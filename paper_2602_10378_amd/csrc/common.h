@@ -31,8 +31,7 @@ enum PairKind {
     kScorePoints = 1,   // D and T at separate points
     kEval = 2,          // D only (Gaussian KDE)
     kEvalLaplace = 3,   // sum of phi * (1 + d/2 - r^2/2h^2) (Laplace-corrected KDE; signed)
-    kRowMax = 4,        // max_j of the exponent (first pass of the max-shifted mode); kept in the D slot
-    kScoreBand = 5      // as kScoreSelf, but only the samples of the rows' own block (symmetric mode)
+    kRowMax = 4         // max_j of the exponent (first pass of the max-shifted mode); kept in the D slot
 };
 // How the prepared rows of the matrix path are held: SDKDE_PREC_FP16X2 .. SDKDE_PREC_FP16X2_PHI16 as the layouts of those
 // modes' kernels; in the fp32 mode two fp16 parts (half2.h), or three bf16 parts for the symmetric score (split3.h).

@@ -27,9 +27,8 @@ namespace {
 // Row-tile operands of one wave: -|p~|^2/2 and the parts of p~ as the lane's 16 bytes of each B operand.
 template <int KB, int NI>
 struct SplitRows {
-    static constexpr int PAIRS = KB / 2;        // 32-column blocks
-    static constexpr bool ODD = KB % 2 != 0;    // and a 16-column one
-    bf16x8 b[NI][PAIRS > 0 ? PAIRS : 1][3];     // h, m, l
+    static constexpr bool ODD = KB % 2 != 0;    // one 16-column block, else one of 32 columns
+    bf16x8 b[ODD ? 1 : NI][3];                  // h, m, l
     bf16x8 o[ODD ? NI : 1][2];                  // K = 32 as two parts of 16 columns: [h | m] and [l | h]
     float ni[NI];
 
@@ -38,15 +37,13 @@ struct SplitRows {
 #pragma unroll
         for (int t = 0; t < NI; ++t) {
             const char* tile = reinterpret_cast<const char*>(ps) + (row0 / kTile + t) * (int64_t)(KB * 1536);
-#pragma unroll
-            for (int p = 0; p < PAIRS; ++p)
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    b[t][p][q] = *reinterpret_cast<const bf16x8*>(tile + p * 3072 + q * kPartBytes + (16 * g + r) * 16);
             if (ODD) {
-                const char* base = tile + PAIRS * 3072 + (16 * (g & 1) + r) * 16;
-                o[t][0] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 0 : 512));
-                o[t][1] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 1024 : 0));
+                const char* base = tile + (16 * (g & 1) + r) * 16;
+                o[ODD ? t : 0][0] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 0 : 512));
+                o[ODD ? t : 0][1] = *reinterpret_cast<const bf16x8*>(base + (g < 2 ? 1024 : 0));
+            } else {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) b[ODD ? 0 : t][q] = *reinterpret_cast<const bf16x8*>(tile + q * kPartBytes + (16 * g + r) * 16);
             }
             ni[t] = pn[row0 + t * kTile + r];
         }
@@ -61,9 +58,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
     float* __restrict__ part_d, int ntiles, int block_tiles)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
-    static_assert(KB <= 2, "sums of a wave in LDS, operands of two groups in registers");
+    static_assert(KB <= 2, "sums of a wave in LDS, one group of operands");
     constexpr int DP = KB * 16;
-    constexpr int PAIRS = KB / 2;
     constexpr bool ODD = KB % 2 != 0;
     constexpr int XCH = 3 * KB;                                  // 1 KiB pieces of a chunk of xs (and of xt)
     constexpr int CH = 2 * XCH;
@@ -96,21 +92,16 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
 
     // One chunk against all NI row tiles.  own: the row tile that is the chunk's first sample tile, if it is one.
     auto chunk = [&](const char* xc, const char* tc, const f32x4& nj0, const f32x4& nj1, int own) {
-        constexpr int GROUPS = PAIRS + (ODD ? 1 : 0);
-        constexpr int STEPS = 2 * GROUPS - 1;      // leading products of all groups but the last, the last, the others' rest
         // Operands of one group of MFMAs; scheduling barriers keep an early read early.
-        bf16x8 ga[2][2][3], ta[2][3];
+        bf16x8 ga[2][3], ta[2][3];
         auto pin = [] { if (AHEAD) __builtin_amdgcn_sched_barrier(0); };
-        auto read_gram = [&](int s, bf16x8 (&a)[2][3]) {
-            if (GROUPS == 2 && s == GROUPS) return;             // still there from the first step
-            const int p = s < GROUPS ? s : s - GROUPS;
-            const int parts = GROUPS > 2 && s < GROUPS - 1 ? 1 : 3;
+        auto read_gram = [&](bf16x8 (&a)[2][3]) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const char* base = xc + u * (KB * 1536) + p * 3072;
-                if (p < PAIRS) {
+                const char* base = xc + u * (KB * 1536);
+                if (!ODD) {
 #pragma unroll
-                    for (int q = 0; q < parts; ++q) a[u][q] = *reinterpret_cast<const bf16x8*>(base + q * kPartBytes + lane * 16);
+                    for (int q = 0; q < 3; ++q) a[u][q] = *reinterpret_cast<const bf16x8*>(base + q * kPartBytes + lane * 16);
                 } else {                            // [h | h], [m | m], [h | l]
                     const char* half = base + (16 * (g & 1) + r) * 16;
                     a[u][0] = *reinterpret_cast<const bf16x8*>(half);
@@ -131,40 +122,29 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_split_kernel(
                 c[t][0] = nj0 + rows.ni[t0 + t];
                 c[t][1] = nj1 + rows.ni[t0 + t];
             }
-            if (AHEAD) read_gram(0, ga[0]);
+            read_gram(ga);
+            if (AHEAD) read_t(0, ta[0]);
+            pin();
+            // the largest products first: they bring the accumulator from the size of the norms down to that of the distance,
+            // where the small ones round finer
+            if (!ODD) {
+                constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) {
-                if (!AHEAD) read_gram(s, ga[s & 1]);
-                else if (s + 1 < STEPS) read_gram(s + 1, ga[(s + 1) & 1]);
-                else read_t(0, ta[0]);
-                pin();
-                const bf16x8 (&a)[2][3] = ga[s & 1];
-                // the largest products of all groups first: they bring the accumulator from the size of the norms down
-                // to that of the distance, where the small ones round finer (error of the score against 64 bits, fp32
-                // MFMAs / this order: d = 64 1.3e-6 / 1.1e-6, d = 90 2.7e-6 / 1.9e-6, d = 128 3.4e-6 / 2.5e-6)
-                const int p = s < GROUPS ? s : s - GROUPS;
-                const int k0 = s < GROUPS ? 0 : 1, k1 = s < GROUPS - 1 ? 1 : 6;
-                if (p < PAIRS) {
-                    constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+                for (int k = 0; k < 6; ++k)
 #pragma unroll
-                    for (int k = k0; k < k1; ++k)
+                    for (int t = 0; t < NB; ++t)
 #pragma unroll
-                        for (int t = 0; t < NB; ++t)
+                        for (int u = 0; u < 2; ++u) c[t][u] = mfma_bf16(ga[u][PA[k]], rows.b[ODD ? 0 : t0 + t][PB[k]], c[t][u]);
+            } else {
+                // [h | h] [h | m], [m | m] [h | m], [h | l] [l | h]
 #pragma unroll
-                            for (int u = 0; u < 2; ++u)
-                                c[t][u] = mfma_bf16(a[u][PA[k]], rows.b[t0 + t][p < PAIRS ? p : 0][PB[k]], c[t][u]);
-                } else {
-                    // [h | h] [h | m], [m | m] [h | m], [h | l] [l | h]
+                for (int k = 0; k < 3; ++k)
 #pragma unroll
-                    for (int k = 0; k < 3; ++k)
+                    for (int t = 0; t < NB; ++t)
 #pragma unroll
-                        for (int t = 0; t < NB; ++t)
-#pragma unroll
-                            for (int u = 0; u < 2; ++u)
-                                c[t][u] = mfma_bf16(a[u][k], rows.o[ODD ? t0 + t : 0][k == 2 ? 1 : 0], c[t][u]);
-                }
-                pin();
+                        for (int u = 0; u < 2; ++u) c[t][u] = mfma_bf16(ga[u][k], rows.o[ODD ? t0 + t : 0][k == 2 ? 1 : 0], c[t][u]);
             }
+            pin();
             if ((unsigned)own < (unsigned)NI) {         // wave-uniform: the pairs of a point with itself
 #pragma unroll
                 for (int t = 0; t < NB; ++t)

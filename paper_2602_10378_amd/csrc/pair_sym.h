@@ -17,7 +17,7 @@ namespace {
 // pair_split_kernel's time at dp = 16).
 //
 // The samples are cut into blocks of `rb` rows; only pairs (i in an earlier block, j in a later block) are handled here,
-// pairs inside one block go through pair_split_kernel restricted to that block (kScoreBand).
+// pairs inside one block go through pair_split_kernel restricted to that block.
 // A workgroup (8 waves) takes one item = (chunk of rows c: `per_group` blocks, group gam >= c: `per_group` blocks) and,
 // for every block b of the group:
 //   - keeps the accumulators [T_J | D_J] of the block's rb rows in LDS ([KB][rb][16] + [rb] floats),
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kSymBlock, 2) void pair_sym_kernel(
 #pragma unroll
                                 for (int u = 0; u < 2; ++u) {
                                     if (gr < PAIRS)
-                                        cc[t][u] = mfma_bf16(ga[gr][u][PA[k]], rows.b[2 * p + t][gr < PAIRS ? gr : 0][PB[k]], cc[t][u]);
+                                        cc[t][u] = mfma_bf16(ga[gr][u][PA[k]], rows.b[ODD ? 0 : 2 * p + t][PB[k]], cc[t][u]);
                                     else
                                         cc[t][u] = mfma_bf16(ga[gr][u][k < 3 ? k : 0], rows.o[ODD ? 2 * p + t : 0][k == 2 ? 1 : 0], cc[t][u]);
                                 }

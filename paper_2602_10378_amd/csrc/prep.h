@@ -465,10 +465,9 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
         char* t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
         // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other
         // (at dp = 16 one wave each), the norms below are left to the last wave.
-        // A sample's coordinate too large for bf16 goes in as zero: its norm is -inf, so every weight of the sample is
-        // exactly 0 (or NaN, if another coordinate is NaN).  Its parts (inf, NaN, NaN) would make the exponents NaN
-        // instead.  A point keeps them: nothing can be said of its own row.
-        auto usable = [&](float v) { return job.samples && fabsf(v) > kBf16Max ? 0.0f : v; };
+        // A coordinate too large for bf16 goes in as zero: its norm is -inf, so every weight of the sample is exactly 0 (or NaN,
+        // if another coordinate is NaN).  Its parts (inf, NaN, NaN) would make the exponents NaN instead.
+        auto usable = [](float v) { return fabsf(v) > kBf16Max ? 0.0f : v; };
         const int row_items = kPrepRows * dp / 8, t_items = t_out ? kb * kWave : 0;
         for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += kBlock) {
             char* at;

@@ -689,7 +689,7 @@ int launch_sym_kernel(const Plan& p, const Workspace& w, hipStream_t st)
 
     Plan band = p;
     band.nsplit = 1;
-    band.tiles_per_split = p.sym_rb / kTile;        // kScoreBand: the length of a block in tiles
+    band.tiles_per_split = p.sym_rb / kTile;        // the length of a block in tiles
     band.ni = 4;
     band.rows_per_block = kWavesPerBlock * kTile * band.ni;
     band.row_blocks = ((int64_t)p.ntiles * kTile + band.rows_per_block - 1) / band.rows_per_block;
