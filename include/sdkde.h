@@ -13,8 +13,8 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Work is only
  *    enqueued; no call synchronises with the host, and no call allocates device memory.
  *  - h is passed as double so that the derived constants are formed in double and rounded
- *    once; the pairwise arithmetic itself is fp32 (every operand held to its 24 bits, fp32 accumulation) unless
- *    `flags` selects another input mode.
+ *    once; the pairwise arithmetic itself is fp32 (operands to the size of an fp32 rounding, see SDKDE_PREC_FP32,
+ *    fp32 accumulation) unless `flags` selects another input mode.
  *  - Accuracy domain of the matrix path (d >= 7, and the eval calls at d >= 4): squared distances are formed as
  *    |p|^2 + |x|^2 - 2 p.x on coordinates taken relative to a centre of the samples (the mean of an evenly
  *    strided subsample of them).  With E = (|p - centre|^2 + max_j |x_j - centre|^2) / 2h^2 the size of the terms
@@ -27,15 +27,17 @@
  *    sum_j phi_j x_j, two sums of size |p - centre| sum_j phi_j carried in fp32.  On either path, whatever the
  *    size of the result, about 1e-6 (1 + R/h) / h of the score is lost, which shows only where the true score is
  *    that small against 1/h (a sample whose only neighbours are its exact duplicates, a bandwidth so narrow that
- *    every neighbour's weight vanishes).  (Far outside that domain, R/h above ~1e18, the scaled
- *    coordinates overflow fp32 on either path and the outputs are NaN.  A sample with an infinite
+ *    every neighbour's weight vanishes).  (On the fp32 matrix path a sample or a point further than 50000 h
+ *    from the centre has no weight with any other, duplicates of it included: its exponents could be off by a
+ *    hundred.  SDKDE_FLAG_MAX_SHIFT takes such samples and points for what they are.  Far outside that domain, R/h above
+ *    ~1e18, the scaled coordinates overflow fp32 on either path and the outputs are NaN.  A sample with an infinite
  *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path; its term
  *    of the Laplace estimate is NaN.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
  *    is kept, and weights below the smallest normal fp32 number (2^-126) are flushed to zero: a point whose
  *    weights phi_j sum to less than 1000 n 2^-126 (so that the flushed ones could be more than one part in a
  *    thousand of the sum; the point is then farther than about 11.5 - 13 h from every sample, depending on n)
  *    gets the all-underflow results documented with each call instead of a number that may be wrong.
- *  - Results are deterministic: no atomics are used, so repeated calls with the same
+ *  - Results are deterministic: nothing is summed by atomics, so repeated calls with the same
  *    arguments (and a workspace of at least sdkde_workspace_bytes, or of the same size) give
  *    bit-identical outputs.
  *  - Stream capture: the calls only launch kernels (no allocation, no memset, no host
@@ -74,10 +76,13 @@ enum {
     SDKDE_MAX_D = 128,
     /* flags: precision mode of the distance cross term (the Gram-matrix tile of the Method section) */
     SDKDE_PREC_FP32 = 0,    /* fp32 inputs, fp32 accumulate: the reference path.  On the matrix path an operand is the
-                               sum of two fp16 parts (to 2^-23 of it, the size of the fp32 rounding that forming the
-                               coordinates in two floats saves; weights, scaled per point by a power of two, to 2^-22 of
-                               themselves or 2^-42 of the point's largest if that is more) and a product is summed
-                               over the three largest of its four part products: the rest is at most 2^-22 of it.  In the symmetric mode an operand is the sum of three bf16 parts,
+                               sum of two fp16 parts: coordinates, in units of h / 1.2, to 2^-23 of themselves (the size of
+                               the fp32 rounding that forming them in two floats saves) or to 2^-25 of a unit if that is
+                               more; those that the score sums, in a column less than a quarter of a unit wide, in a power
+                               of two of its own, to 2^-25 of the column's width at least; weights, scaled per point by a power
+                               of two, to 2^-22 of themselves or 2^-42 of the point's largest if that is more.  A product
+                               is summed over the three largest of its four part products: the rest is at most 2^-22 of it.
+                               In the symmetric mode an operand is the sum of three bf16 parts,
                                exactly (weights down to about 2^-110 of a weight of one), and a product is summed over
                                the six largest of its nine: the rest is at most 2^-24 of it in the cross term, 1.5 2^-23
                                in Phi X. */
@@ -110,8 +115,8 @@ enum {
     /* flags bit 4: two-pass, max-shifted sums for sdkde_eval, sdkde_eval_laplace and sdkde_score at
        separate points: a first pass finds max_j of the exponent for every point, the second sums
        phi_j / max phi, and the logarithm (or the signed density) gets the shift back.  Results then stay
-       finite however far a point is from the samples (the log density never becomes -inf, the score at
-       a far point is that of its nearest samples), at about 1.75x the time of the call. */
+       finite however far a point is from the samples, and they from the centre (the log density never becomes -inf, the
+       score at a far point is that of its nearest samples), at 1.5 to 1.75 times the time of the call. */
     SDKDE_FLAG_MAX_SHIFT = 16,
     /* flags bit 5: symmetric score.  phi_ij = phi_ji, so for the score at the samples themselves each
        unordered pair needs one Gram-matrix entry and one exp, used for both T_i and T_j (an algorithmic saving

@@ -1,7 +1,7 @@
-"""The fp32 mode's pair kernel (three bf16 parts per operand) in every workgroup shape it is built in, at its edges: one
+"""The fp32 mode's pair kernel (two fp16 parts per operand) in every workgroup shape it is built in, at its edges: one
 and several 16-column blocks, even and odd block counts, a nearly empty and a full last block, a ragged last chunk of
 samples, fewer chunks than splits, own chunks split over workgroups, splits long enough to fold their running sums, and
-weights whose lower parts leave the bf16 range.  Held to what fp32 arithmetic costs, not only to the general tolerance."""
+weights at the bottom of the range.  Held to what fp32 arithmetic costs, not only to the general tolerance."""
 import numpy as np
 import pytest
 
