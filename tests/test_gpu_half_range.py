@@ -242,3 +242,47 @@ def test_shifted_scores_where_every_sample_is_beyond_the_range(d, distance):
     q[1::2, d // 2] += np.float32(0.5 * distance)           # not only around the middle, where the nearer one is not resolved
     q[::2, d // 2] -= np.float32(0.5 * distance)
     _check_shifted_far_points(P, x, q, h, size + 2.0**-22 * distance)
+
+
+@pytest.mark.parametrize("d", [4, 16, 37])
+def test_prepared_samples_with_far_ones_serve_shifted_and_plain_calls(d):
+    """Samples stand prepared by one call and serve others with and without the max shift, some of them beyond the fp16 range."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 1500, 90
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    h = float(h)
+    x[[1003, 1203]] += np.float32(1e5 * h)
+    q[::4] += np.float32(0.999e5 * h)
+    xd, qd = (torch.from_numpy(a).cuda() for a in (x, q))
+    ws = P.make_workspace(n, m, d)
+    print(f"prepared samples with far ones d={d}", flush=True)
+    want = {f: P.sdkde_eval(xd, qd, h, want="log", flags=f)[1] for f in (0, P.SDKDE_FLAG_MAX_SHIFT)}
+    ref = oracle.eval_log_density(x, q, h)
+    allowed = gram_exponent_error(x, q, h, low_precision_inputs=True) + 4.0 * 2.0**-23 * np.abs(ref) + 2.0**-18
+    assert np.all(np.abs(want[P.SDKDE_FLAG_MAX_SHIFT].cpu().numpy() - ref)[::4] <= allowed[::4])
+    for first in want:
+        P.sdkde_eval(xd, qd, h, want="log", flags=first, workspace=ws)
+        for f in want:
+            got = P.sdkde_eval(xd, qd, h, want="log", flags=f | P.SDKDE_FLAG_SAMPLES_PREPARED, workspace=ws)[1]
+            assert torch.equal(got, want[f])
+
+
+def test_points_in_batches_over_narrow_columns(tuning):
+    """Batches after the first find the columns' units where the first one's samples left them: the same bits as in one pass."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m, d = 700, 40000, 16
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, 1)
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=3)
+    narrow = np.float32(10.0) ** -(np.arange(d) % 6).astype(np.float32)
+    xd, qd = (torch.from_numpy(a * narrow).cuda() for a in (x, q))
+    plan = P.sdkde_describe_plan(n, m, d, 1)
+    assert plan["splits"] == 1
+    tight = torch.empty(plan["workspace_bytes"] - 2 * plan["dp"] * (2 * plan["n_pad"] + plan["m_pad"]), dtype=torch.uint8, device="cuda")
+    print("batches over narrow columns", flush=True)
+    for flags in (0, P.SDKDE_FLAG_MAX_SHIFT):
+        want = P.sdkde_score(xd, float(h), points=qd, flags=flags)
+        assert torch.equal(P.sdkde_score(xd, float(h), points=qd, flags=flags, workspace=tight), want)
