@@ -253,8 +253,24 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     }
 }
 
-// log p = log D + lognorm, lognorm = -log n - d log h - (d/2) log 2 pi (formed on the host in double).
-// signed != 0 (Laplace-corrected sum, which may be negative): density = sum * exp(lognorm) only.
+// log p = log D + lognorm, lognorm = -log n - d log h - (d/2) log 2 pi (formed on the host in double); shift_ln: what the weights
+// were divided by, as a logarithm.  is_signed (Laplace-corrected sum, which may be negative): density = sum * exp(lognorm) only.
+__device__ __forceinline__ void eval_outputs(int64_t i, float dsum, double lognorm, double shift_ln, bool is_signed, float min_sum,
+                                             float* __restrict__ density, float* __restrict__ log_density)
+{
+    // too close to the flush threshold of the weights: the all-underflow case (the signed sum of the Laplace-corrected
+    // estimate may be small because its terms cancel, and is left as it is)
+    if (!is_signed && dsum < min_sum) dsum = 0.0f;
+    if (is_signed) {
+        if (density) density[i] = (float)((double)dsum * exp(lognorm + shift_ln));
+        return;
+    }
+    const double lp = log((double)dsum) + lognorm + shift_ln;      // -inf when dsum == 0
+    if (log_density) log_density[i] = (float)lp;
+    // beside the logarithm instead of after it where neither end of the double range is near (the float is 0 or inf there)
+    if (density) density[i] = (float)(fabs(lognorm + shift_ln) < 600.0 ? (double)dsum * exp(lognorm + shift_ln) : exp(lp));
+}
+
 // shift (may be null): per-query base-2 exponent shift of the max-shifted mode.  residual (may be null): half2.h.  min_sum: least_trusted_sum(n).
 // Grid: one workgroup per kBlock / PARTS queries.
 template <int PARTS>
@@ -276,17 +292,7 @@ __global__ __launch_bounds__(kBlock) void eval_epilogue_kernel(const float* __re
     float dsum = reduce_slots<PARTS, false>(sums, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
     const double shift_ln = ((shift ? (double)of_shift : 0.0) + (residual ? (double)of_residual : 0.0)) * 0.69314718055994530942;
-    // too close to the flush threshold of the weights: the all-underflow case (the signed sum of the Laplace-corrected
-    // estimate may be small because its terms cancel, and is left as it is)
-    if (!is_signed && dsum < min_sum) dsum = 0.0f;
-    if (is_signed) {
-        if (density) density[i] = (float)((double)dsum * exp(lognorm + shift_ln));
-        return;
-    }
-    const double lp = log((double)dsum) + lognorm + shift_ln;      // -inf when dsum == 0
-    if (log_density) log_density[i] = (float)lp;
-    // beside the logarithm instead of after it where neither end of the double range is near (the float is 0 or inf there)
-    if (density) density[i] = (float)(fabs(lognorm + shift_ln) < 600.0 ? (double)dsum * exp(lognorm + shift_ln) : exp(lp));
+    eval_outputs(i, dsum, lognorm, shift_ln, is_signed != 0, min_sum, density, log_density);
 }
 
 // out may alias x or s (each thread reads its one element before it writes it): no __restrict__ here.

@@ -98,11 +98,11 @@ __host__ __device__ inline float* half2_residual(float* ps, int64_t rows_pad, in
 }
 __host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int dp) { return half2_residual(ps, rows_pad, dp) + rows_pad; }
 
-// Behind the prepared samples, at the same distance from them: their scales, and a byte a chunk, what a kernel may have to know of
-// its samples.
+// Behind the prepared samples, at the same distance from them: their scales, and a byte a 16-row tile, what a kernel may have to
+// know of its samples.
 constexpr uint32_t kMarkWide = 1;                   // one with half a squared norm above kCoarseSample
 constexpr uint32_t kMarkDistant = 2;                // one further than kFarPoint from the centre
-constexpr uint32_t kMarkOwnUnits = 4;               // its columns of "xt" are in units of their own
+constexpr uint32_t kMarkOwnUnits = 4;               // its chunk's columns of "xt" are in units of their own (on both tiles of it)
 constexpr uint32_t kMarks = 3;                      // how many there are
 constexpr float kCoarseNorm = 2048.0f, kCoarseSample = 8192.0f;      // see the row maxima in pair_half.h
 __host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int dp)
@@ -115,7 +115,7 @@ __host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int
 constexpr int kMostUnit = 60;                       // k at most
 __host__ __device__ inline float* half2_units(float* xs, int64_t rows_pad, int dp)
 {
-    return reinterpret_cast<float*>(half2_marks(xs, rows_pad, dp) + rows_pad / 32);
+    return reinterpret_cast<float*>(half2_marks(xs, rows_pad, dp) + rows_pad / kTile);
 }
 __host__ __device__ inline float* half2_chunk_units(float* xs, int64_t rows_pad, int dp) { return half2_units(xs, rows_pad, dp) + 2 * dp + 4; }
 // 2^-k of 2^k
@@ -133,12 +133,12 @@ struct Coordinate {
     }
 };
 
-// The marks of chunks first .. last - 1 (and of up to three on either side) together, in all lanes.
+// The marks of chunks first .. last - 1 (and of one on either side) together, in all lanes.
 __device__ __forceinline__ uint32_t marks_of(const uint8_t* marks, int first, int last, int lane)
 {
-    const uint32_t* const words = reinterpret_cast<const uint32_t*>(marks);     // rows are padded to 32 chunks
+    const uint32_t* const words = reinterpret_cast<const uint32_t*>(marks);     // rows are padded to 64 tiles
     uint32_t all = 0, some = 0;
-    for (int w = first / 4 + lane; w * 4 < last; w += kWave) all |= words[w];
+    for (int w = first / 2 + lane; w * 2 < last; w += kWave) all |= words[w];
     all |= all >> 16;
     all |= all >> 8;
 #pragma unroll

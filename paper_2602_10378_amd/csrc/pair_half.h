@@ -474,7 +474,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
         // SCORE: a chunk with units of its own is summed in them: what has been summed is brought to them and back, on both levels.
         // Where the split has one every chunk is a turn of the outer loop.  (Asked inside the inner one it cost 3 to 5 % of a score.)
         auto own_units = [&](int c, bool to) __attribute__((always_inline)) {
-            if (!(marks & marks_at[c] & kMarkOwnUnits)) return;
+            if (!(marks & marks_at[2 * c] & kMarkOwnUnits)) return;
 #pragma unroll
             for (int mb = 0; mb < KT; ++mb) {
                 f32x4 by = load_at<f32x4>(reinterpret_cast<const char*>(units + 2 * DP + 4 + (int64_t)c * DP + mb * 16), g * 16u);

@@ -227,22 +227,24 @@ struct StagedRows {
     }
 };
 
-// The body of prep_mfma_kernel for one workgroup and two fp16 parts a value (half2.h): rows r0 .. r0 + kPrepRows of `job`.
+// The body of prep_mfma_kernel for one workgroup and two fp16 parts a value (half2.h): rows r0 .. r0 + ROWS of `job`, by BLOCK threads.
 // Their input values stand in words[][] as floats.  far_rows[2]: zeros, since before a barrier.  sunit: the columns' units, for a
 // job with a dst_t, other: whether one is not 1.  Coordinates are formed as sums of two floats: what the split leaves of them is then all that is lost (one float rounded the difference and the
 // product first; in double, with its conversions, a small launch took 0.8 us longer).  A launch of a few workgroups is a chain
 // of latencies: kernel arguments, centre, coordinates, stores.  Rows loaded beside the centre's, eight lanes summing each
 // column of the centre, one barrier less and the norms in a wave without other work: 4.9 to 4.7 us at 4096 x 1024, d = 16.
+template <int ROWS, int BLOCK>
 __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, int d, int dp, double a, bool poisoned,
                                                 const float* smean, const float* sunit, bool other, uint32_t* words, uint32_t* far_rows)
 {
-    static_assert(kPrepRows == kChunkRows && kBlock == 8 * kPrepRows, "a workgroup writes whole chunks, eight lanes a row");
+    static_assert(ROWS == kPrepRows || ROWS == kTile, "a workgroup writes whole chunks, or tiles (of a job without a dst_t)");
+    static_assert(BLOCK % kWave == 0 && BLOCK >= 8 * ROWS, "eight lanes a row");
     const int stride = dp + 1;                  // odd: columns are read without bank conflicts
     const double reach = job.samples || !job.shifted ? kReach : kFarPoint;          // largest norm held as it is
     auto coordinate = [&](int c, float in) { return a * ((double)in - (double)smean[c]); };
     const bool may_exceed = job.dst_t != nullptr && (other || job.shifted);      // the range, in a column's unit
-    __shared__ double squares[kPrepRows];
-    {
+    __shared__ double squares[ROWS];
+    if (BLOCK == 8 * ROWS || threadIdx.x < 8 * ROWS) {
         const int own = threadIdx.x >> 3, lane8 = threadIdx.x & 7;
         const int64_t row = r0 + own;
         const bool live = row < job.rows;
@@ -292,12 +294,12 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     auto far_down = [&](double most) __attribute__((always_inline)) { return __builtin_bit_cast(double, (2046 - far_exponent(most)) << 52); };
     if (__builtin_expect(far != 0, 0)) {        // the same for all threads
 #pragma unroll 1
-        for (int rr = 0; rr < kPrepRows; ++rr) {
+        for (int rr = 0; rr < ROWS; ++rr) {
             if (!(far >> rr & 1u)) continue;
             const double most = largest(rr);
             const double down = finite(most) ? far_down(most) : 0.0;
 #pragma unroll 1
-            for (int c = threadIdx.x; c < d; c += kBlock) {
+            for (int c = threadIdx.x; c < d; c += BLOCK) {
                 const double v = coordinate(c, job.src[(r0 + rr) * d + c]) * down;
                 words[rr * stride + c] = finite(most) ? half2_split((float)v, (float)(v - (double)(float)v)) : 0u;
             }
@@ -314,10 +316,10 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     __shared__ float chunk_unit[SDKDE_MAX_D];
     if (__builtin_expect(own_units, 0)) {       // the same for all threads
 #pragma unroll 1
-        for (int c = threadIdx.x; c < dp; c += kBlock) {
+        for (int c = threadIdx.x; c < dp; c += BLOCK) {
             float most = 0.0f;
 #pragma unroll 1
-            for (int rr = 0; rr < kPrepRows; ++rr) most = fmaxf(most, fabsf(for_transpose(rr, c).v));
+            for (int rr = 0; rr < ROWS; ++rr) most = fmaxf(most, fabsf(for_transpose(rr, c).v));
             const double scaled = (double)most * (c < d ? sunit[c] : 1.0f);
             const uint32_t e = scaled > kHalfMax ? (uint32_t)(__builtin_bit_cast(uint64_t, scaled) >> 52) - 1023 - 14 : 0;
             chunk_unit[c] = __builtin_bit_cast(float, (127 + e) << 23);
@@ -328,8 +330,8 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     const int kb = dp / 16, tail = job.tail;
     char* const rows_out = reinterpret_cast<char*>(job.dst) + r0 / kTile * half_tile_bytes(kb);
     char* const t_out = job.dst_t ? reinterpret_cast<char*>(job.dst_t) + r0 * 6 * dp : nullptr;
-    if (threadIdx.x >= kBlock - kPrepRows) {        // the last wave: at dp = 16 it has no other items
-        const int rr = threadIdx.x - (kBlock - kPrepRows);
+    if (threadIdx.x >= BLOCK - ROWS) {        // the last wave: at dp = 16 it has no other items
+        const int rr = threadIdx.x - (BLOCK - ROWS);
         const int64_t row = r0 + rr;
         const uint32_t* w = words + rr * stride;
         double acc = squares[rr], scale = 1.0;
@@ -351,10 +353,11 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         job.dst_n[row] = norm;
         half2_scale(job.dst, job.rows_pad, dp)[row] = (float)scale;
         if (job.samples) {
-            auto any = [&](bool v) { return __builtin_amdgcn_ballot_w64(row < job.rows && v) != 0; };
+            const int in_wave = (BLOCK - ROWS + rr) % kWave;            // (a tile's rows are 16 lanes in a row)
+            auto any = [&](bool v) { return (__builtin_amdgcn_ballot_w64(row < job.rows && v) >> (in_wave & 48) & 0xffffu) != 0; };
             const uint32_t marks = (any(norm < -kCoarseSample) ? kMarkWide : 0) | (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0) |
                                    (own_units ? kMarkOwnUnits : 0);
-            if (rr == 0) half2_marks(job.dst, job.rows_pad, dp)[r0 / kChunkRows] = (uint8_t)marks;
+            if (rr % kTile == 0) half2_marks(job.dst, job.rows_pad, dp)[row / kTile] = (uint8_t)marks;
         } else {
             half2_residual(job.dst, job.rows_pad, dp)[row] = left;
         }
@@ -374,14 +377,14 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
     }
     // eight values at a time: of one row (rows_out), then of one column (t_out).  Whole waves take one or the other (at dp = 16
     // one wave each).
-    const int row_items = kPrepRows * dp / 8, t_items = t_out ? kb * kWave : 0;
-    for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += kBlock) {
+    const int row_items = ROWS * dp / 8, t_items = t_out ? kb * kWave : 0;
+    for (int at_item = threadIdx.x; at_item < row_items + t_items; at_item += BLOCK) {
         uint32_t word[8];
         char* at;
         int part_stride;
         const bool of_row = at_item < row_items;
         if (of_row) {
-            const int rr = at_item % kPrepRows, c0 = at_item / kPrepRows * 8;
+            const int rr = at_item % ROWS, c0 = at_item / ROWS * 8;
             at = rows_out + half2_offset(rr, c0, dp, &part_stride);
 #pragma unroll
             for (int k = 0; k < 8; ++k) word[k] = words[rr * stride + c0 + k];
@@ -411,7 +414,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
             const _Float16 s0 = (_Float16)(half_low(word[2 * k]) * (1.0f / kWeightScale)), s1 = (_Float16)(half_low(word[2 * k + 1]) * (1.0f / kWeightScale));
             scaled[k] = (uint32_t)__builtin_bit_cast(uint16_t, s0) | (uint32_t)__builtin_bit_cast(uint16_t, s1) << 16;
         }
-        if (!(of_row && tail == kTailSpare && at_item / kPrepRows * 8 == dp - 8)) *reinterpret_cast<u32x4*>(at) = h;     // (see above)
+        if (!(of_row && tail == kTailSpare && at_item / ROWS * 8 == dp - 8)) *reinterpret_cast<u32x4*>(at) = h;     // (see above)
         *reinterpret_cast<u32x4*>(at + part_stride) = l;
         if (!of_row) *reinterpret_cast<u32x4*>(at + 2 * part_stride) = scaled;
     }
@@ -435,7 +438,7 @@ __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d,
                                           const float* smean, const float* sunit, bool other, float* raw_rows, float* used_rows, uint32_t* far_rows)
 {
     if (format == kFormatHalf2) {
-        prep_rows_half2(job, r0, d, dp, a, poisoned, smean, sunit, other, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
+        prep_rows_half2<kPrepRows, kBlock>(job, r0, d, dp, a, poisoned, smean, sunit, other, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
         return;
     }
     // kPrepRows rows of dp + 1 floats each (odd stride: columns are read without bank conflicts)

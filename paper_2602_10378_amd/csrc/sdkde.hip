@@ -17,6 +17,7 @@
 #include "prep.h"
 #include "pair_mfma.h"
 #include "pair_half.h"
+#include "pair_whole.h"
 #include "pair_split.h"
 #include "pair_sym.h"
 #include "pair_thin.h"
@@ -589,6 +590,74 @@ int launch_half(const Plan& p, const Workspace& w, const float* shift, hipStream
     }
 }
 
+// Small sample sets: row tiles a workgroup's waves share in pair_whole_kernel, 0: the call takes the kernels with split slots.
+// rows: evaluation points.  The line lies where a workgroup's reads of all samples and the rounds of workgroups cost what the saved
+// launch does.  Split slots / whole rows, us a call: one-call pass with n / 4 queries, d = 16 n = 600 23.8 / 17.7, 2048 22.5 / 22.4,
+// 4096 29.1 / 29.6, d = 24 n = 2048 28.4 / 25.5, d = 64 600 29.0 / 21.6, 2048 36.4 / 34.4, d = 128 600 38.3 / 30.2, 2048 50.2 / 52.7;
+// score at points, n = 1200: d = 16, 4000 points 15.9 / 12.9, 16000 23.6 / 32.0, with two row tiles a wave 17.6, 64000 52.1 / 47.9
+// (eval 29.5 / 35.2); d = 48, 4000 22.2 / 17.7, 16000 36.0 / 45.3; d = 128, 50 points 24.3 / 29.5.
+int whole_row_tiles(const Plan& p, int64_t n, int64_t rows, bool score, bool shifted)
+{
+    if (!p.parts || p.sym_on || shifted) return 0;
+    if (tuning(score ? SDKDE_TUNE_SCORE_ROW_TILES : SDKDE_TUNE_EVAL_ROW_TILES, 0) || tuning(score ? SDKDE_TUNE_SCORE_SPLITS : SDKDE_TUNE_EVAL_SPLITS, 0)) return 0;
+    const int kb = p.dp / 16;
+    if (n > 3072 || n * kb > 6144) return 0;
+    return rows <= kComputeUnits * kTile ? 1 : kb == 1 && rows <= 4 * kComputeUnits * kTile ? 2 : 0;
+}
+
+// Lays a call of such a kernel out: as layout() does, without partial slots.
+Workspace whole_layout(Plan p, bool score, bool separate_points, void* base, uint32_t flags)
+{
+    p.nsplit = 0;
+    return layout(p, score, separate_points, base, flags);
+}
+
+template <int KIND, bool FIT, int KB, int TAIL>
+int launch_whole_tail(const Plan& p, const Workspace& w, int row_tiles, int64_t m, const WholeOut& out, hipStream_t st)
+{
+    const int64_t rows = FIT ? p.n_pad : m, blocks = (rows + row_tiles * kTile - 1) / (row_tiles * kTile);
+    // Host-side shape check: every row and chunk exists in the padded arrays, and no wave has more chunks than one level sums.
+    if (blocks > 0x7fffffffLL || blocks * row_tiles * kTile > p.m_pad || (int64_t)p.ntiles * kTile > p.n_pad || p.ntiles % 2 ||
+        p.ntiles / 2 > whole_waves(KB, row_tiles) * kWholeChunks)
+        return SDKDE_EINVAL;
+    const dim3 grid((unsigned)blocks), block(whole_waves(KB, row_tiles) * kWave);
+#define SDKDE_LAUNCH_WHOLE(NI_)                                                                                              \
+    hipLaunchKernelGGL((pair_whole_kernel<KB, TAIL, NI_, KIND, FIT>), grid, block, 0, st, w.ps, w.pn, w.xs, w.xt, w.xn,       \
+                       p.ntiles / 2, p.n_pad, m, p.m_pad, 1.0f + 0.5f * (float)p.d, out)
+    if (row_tiles == 1) {
+        SDKDE_LAUNCH_WHOLE(1);
+    } else if constexpr (KB == 1) {
+        if (row_tiles != 2) return SDKDE_EUNSUPPORTED;
+        SDKDE_LAUNCH_WHOLE(2);
+    } else {
+        return SDKDE_EUNSUPPORTED;
+    }
+#undef SDKDE_LAUNCH_WHOLE
+    return launched();
+}
+
+template <int KIND, bool FIT = false>
+int launch_whole(const Plan& p, const Workspace& w, int row_tiles, int64_t m, const WholeOut& out, hipStream_t st)
+{
+    const int tail = half_tail(p.d, KIND == kScoreSelf);
+    const bool eight = tail == kTailEight, spare = tail == kTailSpare;
+#define SDKDE_WHOLE_ODD(KB_) (eight ? launch_whole_tail<KIND, FIT, KB_, kTailEight>(p, w, row_tiles, m, out, st) : launch_whole_tail<KIND, FIT, KB_, kTailSixteen>(p, w, row_tiles, m, out, st))
+#define SDKDE_WHOLE_EVEN(KB_) (spare ? launch_whole_tail<KIND, FIT, KB_, kTailSpare>(p, w, row_tiles, m, out, st) : launch_whole_tail<KIND, FIT, KB_, kTailNone>(p, w, row_tiles, m, out, st))
+    switch (p.dp / 16) {
+        case 1: return SDKDE_WHOLE_ODD(1);
+        case 2: return spare ? launch_whole_tail<KIND, FIT, 2, KIND == kScoreSelf ? kTailNone : kTailSpare>(p, w, row_tiles, m, out, st) : launch_whole_tail<KIND, FIT, 2, kTailNone>(p, w, row_tiles, m, out, st);
+        case 3: return SDKDE_WHOLE_ODD(3);
+        case 4: return SDKDE_WHOLE_EVEN(4);
+        case 5: return SDKDE_WHOLE_ODD(5);
+        case 6: return SDKDE_WHOLE_EVEN(6);
+        case 7: return SDKDE_WHOLE_ODD(7);
+        case 8: return SDKDE_WHOLE_EVEN(8);
+        default: return SDKDE_EUNSUPPORTED;
+    }
+#undef SDKDE_WHOLE_EVEN
+#undef SDKDE_WHOLE_ODD
+}
+
 // The fp16 input modes.
 template <int KIND, int PREC>
 int launch_mfma(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
@@ -796,6 +865,9 @@ int profile_mark(int which, int edge, hipStream_t st)
 struct FusedPrep {
     PrepJob sd_job, q_job;
     Stamp stamp;
+    bool whole;             // both passes are pair_whole_kernel's (plan_whole_fit), these their plans and places
+    Plan score_plan, eval_plan;
+    Workspace score_at, eval_at;
 };
 
 // Whether the one-call pass can fold the eval pass's preparation into the score epilogue, and with what.  Both passes
@@ -838,10 +910,51 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     return true;
 }
 
+// Whether the score at the samples is one of pair_whole_kernel's, with the epilogue in it.
+bool whole_score(int64_t n, int32_t d, uint32_t flags)
+{
+    flags = anchored_flags(flags, true);
+    Plan p = make_plan(n, n, d, true, flags);
+    apply_symmetric(p, n, flags, true);
+    return whole_row_tiles(p, n, n, true, false) != 0;
+}
+
+// The same for small sample sets whose two passes are pair_whole_kernel's (whole_row_tiles): three launches, the queries prepared with
+// the samples, the shifted samples by the workgroups that form them.  The eval pass's operands stand where a call of its own has
+// them (a later one may rely on the record, SDKDE_FLAG_SAMPLES_PREPARED), the score pass's behind them.
+bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, int64_t m, int32_t d, double h, void* workspace,
+                    size_t workspace_bytes, uint32_t flags, FusedPrep* out)
+{
+    if (m <= 0 || (flags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
+    const uint32_t sflags = anchored_flags(flags, true);
+    Plan& ps = out->score_plan = make_plan(n, n, d, true, sflags);
+    apply_symmetric(ps, n, sflags, true);
+    if (!whole_row_tiles(ps, n, n, true, false)) return false;
+    Plan& pe = out->eval_plan = make_plan(n, m, d, false, flags);
+    if (!whole_row_tiles(pe, n, m, false, false) || ps.n_pad != pe.n_pad) return false;
+    // accepted or refused as the passes one by one are
+    Workspace unused;
+    Plan score_plan = ps, eval_plan = pe;
+    if (!fit_workspace(score_plan, true, false, workspace, workspace_bytes, sflags, &unused) ||
+        fit_points(eval_plan, false, workspace, workspace_bytes, flags, m, &unused) != m)
+        return false;
+    const Workspace& we = out->eval_at = whole_layout(pe, false, true, workspace, flags);
+    Workspace& ws = out->score_at = whole_layout(ps, true, false, (char*)workspace + we.bytes, sflags);
+    if (we.bytes + ws.bytes > workspace_bytes) return false;
+    ws.centre = we.centre;
+    ws.stamp = we.stamp;
+    out->whole = true;
+    const int format = operand_format(pe, flags);
+    out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false, half_tail(d, false)};
+    out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false, half_tail(d, false)};
+    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)operand_scale(format, h));
+    return true;
+}
+
 // One pass of a score call over the samples at m points (null: at the samples themselves, m = n).  samples_ready: they
 // stand prepared in the workspace, by an earlier pass of the same call.
 int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n, const float* points, int64_t m, bool samples_ready,
-               double h, float* score_out, float* samples_sd_out, uint32_t flags, hipStream_t st, const FusedPrep* fused)
+               double h, float* score_out, float* samples_sd_out, uint32_t flags, hipStream_t st, const FusedPrep* fused, int whole_rows)
 {
     int rc;
     const int d = p.d;
@@ -853,13 +966,42 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     // When the points are the samples (m == n, so m_pad == n_pad), one prepared array serves
     // as both operands.
     const PrepJob sample_job{samples, n, p.n_pad, w.xs, w.xt, w.xn, kPadCoord, true, shifted, half_tail(d, self)};
-    const PrepJob point_job{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
+    // (a one-call pass of small sample sets prepares the eval pass's queries here)
+    const PrepJob point_job = fused && whole_rows ? fused->q_job
+                                                  : PrepJob{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
     const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
     rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
                        : launch_prep(p, sample_job, point_job, samples, n, a, w, flags, stamp, st);
     if (rc != SDKDE_OK) return rc;
 
+    const float inv_ah2 = (float)(1.0 / (a * h * h)), half_h2 = (float)(0.5 * h * h);
+    const ScoreUnits units{format == kFormatHalf2 ? half2_units(w.xs, p.n_pad, p.dp) : nullptr, self ? samples : points};
+    const uintptr_t io = (uintptr_t)score_out | (uintptr_t)samples_sd_out | (samples_sd_out ? (uintptr_t)samples : 0);
+    const int quad_io = (d % 4 == 0 && (io & 15) == 0) ? 1 : 0;
     if ((rc = profile_mark(0, 0, st)) != SDKDE_OK) return rc;
+    if (whole_rows) {
+        WholeOut out{};
+        out.d = d;
+        out.min_sum = least_trusted_sum(n);
+        out.inv_ah2 = inv_ah2;
+        out.half_h2 = half_h2;
+        out.score = score_out;
+        out.x = samples;
+        out.x_sd = samples_sd_out;
+        out.quad_io = quad_io;
+        out.units = units;
+        if (fused) {
+            if (!self || !samples_sd_out) return SDKDE_EINVAL;
+            out.sd_job = fused->sd_job;
+            out.centre = w.centre;
+            out.a = a;
+            out.stamp = fused->stamp;
+        }
+        rc = fused  ? launch_whole<kScoreSelf, true>(p, w, whole_rows, m, out, st)
+             : self ? launch_whole<kScoreSelf>(p, w, whole_rows, m, out, st)
+                    : launch_whole<kScorePoints>(p, w, whole_rows, m, out, st);
+        return rc != SDKDE_OK ? rc : profile_mark(0, 1, st);
+    }
     if (shifted && (rc = launch_max_shift(p, w, flags, st)) != SDKDE_OK) return rc;
     const float* shift = shifted ? w.shift : nullptr;
     rc = p.sym_on ? launch_symmetric(p, w, st)
@@ -871,13 +1013,9 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const int64_t total = m * (int64_t)d;
     const int nslots = p.sym_on ? p.sym_ngroups + 2 : p.nsplit;
     const int mode = p.thin ? 1 : (self ? 2 : 0);        // see score_epilogue_kernel
-    const float inv_ah2 = (float)(1.0 / (a * h * h)), half_h2 = (float)(0.5 * h * h);
-    const ScoreUnits units{format == kFormatHalf2 ? half2_units(w.xs, p.n_pad, p.dp) : nullptr, self ? samples : points};
     if (!p.thin && epilogue_parts(nslots, total) == kEpiPartsFew) {
         const int64_t quads = m * (p.dp / 4);
         constexpr int per_wg = kBlock / kEpiPartsFew;
-        const uintptr_t io = (uintptr_t)score_out | (uintptr_t)samples_sd_out | (samples_sd_out ? (uintptr_t)samples : 0);
-        const int quad_io = (d % 4 == 0 && (io & 15) == 0) ? 1 : 0;
         if (fused) {
             // plan_fused_prep has checked that this plan and layout are the ones it was made for
             if (!self || !samples_sd_out || p.sym_on || mode != 2) return SDKDE_EINVAL;
@@ -916,6 +1054,9 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
     if (flags & SDKDE_FLAG_SAMPLES_PREPARED) return SDKDE_EUNSUPPORTED;      // sdkde_eval / sdkde_eval_laplace only
     flags = anchored_flags(flags, self);
+    if (fused && fused->whole)
+        return score_pass(fused->score_plan, fused->score_at, samples, n, nullptr, m, false, h, score_out, samples_sd_out, flags, (hipStream_t)stream,
+                          fused, whole_row_tiles(fused->score_plan, n, m, true, false));
 
     Plan p = make_plan(n, m, d, true, flags);
     apply_symmetric(p, n, flags, self);
@@ -924,11 +1065,17 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if (self ? !fit_workspace(p, true, false, workspace, workspace_bytes, flags, &w)
              : (batch = fit_points(p, true, workspace, workspace_bytes, flags, m, &w)) == 0)
         return SDKDE_EWORKSPACE;
+    int whole_rows = batch == m ? whole_row_tiles(p, n, m, true, !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0) : 0;
+    if (whole_rows) {
+        const Workspace all = whole_layout(p, true, !self, workspace, flags);
+        if (all.bytes <= workspace_bytes) w = all;
+        else whole_rows = 0;
+    }
     for (int64_t first = 0; first < m; first += batch) {
         const int64_t rows = m - first < batch ? m - first : batch;
         if (first > 0) p.row_blocks = (rows + p.rows_per_block - 1) / p.rows_per_block;      // the last batch is shorter
         rc = score_pass(p, w, samples, n, self ? nullptr : points + first * d, rows, first > 0, h,
-                        score_out ? score_out + first * d : nullptr, samples_sd_out, flags, (hipStream_t)stream, fused);
+                        score_out ? score_out + first * d : nullptr, samples_sd_out, flags, (hipStream_t)stream, fused, whole_rows);
         if (rc != SDKDE_OK) return rc;
     }
     return SDKDE_OK;
@@ -939,7 +1086,7 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
 // mode only, not on m, and a pass whose record of them does not match gets NaN for every output.
 int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n, const float* queries, int64_t m, bool samples_ready,
               double h, float* density_out, float* log_density_out, uint32_t flags, hipStream_t st, bool laplace,
-              bool reuse_centre, bool all_prepared)
+              bool reuse_centre, bool all_prepared, int whole_rows)
 {
     int rc;
     const int d = p.d;
@@ -959,6 +1106,17 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
 
     const double lognorm = -log((double)n) - (double)d * log(h) - 0.5 * (double)d * log(6.283185307179586476925286766559);
     if ((rc = profile_mark(1, 0, st)) != SDKDE_OK) return rc;
+    if (whole_rows) {
+        WholeOut out{};
+        out.d = d;
+        out.min_sum = least_trusted_sum(n);
+        out.lognorm = lognorm;
+        out.residual = w.residual;
+        out.density = density_out;
+        out.log_density = log_density_out;
+        rc = laplace ? launch_whole<kEvalLaplace>(p, w, whole_rows, m, out, st) : launch_whole<kEval>(p, w, whole_rows, m, out, st);
+        return rc != SDKDE_OK ? rc : profile_mark(1, 1, st);
+    }
     if (shifted && (rc = launch_max_shift(p, w, flags, st)) != SDKDE_OK) return rc;
     const float* shift = shifted ? w.shift : nullptr;
     rc = laplace ? launch_pair_prec<kEvalLaplace>(p, w, flags, shift, st) : launch_pair_prec<kEval>(p, w, flags, shift, st);
@@ -973,7 +1131,7 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
 // Shared body of sdkde_eval and sdkde_eval_laplace.
 int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, int32_t d, double h,
               float* density_out, float* log_density_out, void* workspace, size_t workspace_bytes, uint32_t flags,
-              void* stream, bool laplace, bool reuse_centre = false, bool all_prepared = false)
+              void* stream, bool laplace, bool reuse_centre = false, const FusedPrep* fused = nullptr)
 {
     int rc = check_common(samples, n, m, d, h, flags);
     if (rc != SDKDE_OK) return rc;
@@ -981,16 +1139,27 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     if (!queries || (!density_out && !log_density_out)) return SDKDE_EINVAL;
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
 
+    const bool all_prepared = fused != nullptr;
+    if (fused && fused->whole)
+        return eval_pass(fused->eval_plan, fused->eval_at, samples, n, queries, m, false, h, density_out, log_density_out, flags, (hipStream_t)stream,
+                         laplace, reuse_centre, all_prepared, whole_row_tiles(fused->eval_plan, n, m, false, false));
+
     Plan p = make_plan(n, m, d, false, flags);
     Workspace w;
     const int64_t batch = fit_points(p, false, workspace, workspace_bytes, flags, m, &w);
     if (batch == 0) return SDKDE_EWORKSPACE;
+    int whole_rows = batch == m ? whole_row_tiles(p, n, m, false, (flags & SDKDE_FLAG_MAX_SHIFT) != 0) : 0;
+    if (whole_rows) {
+        const Workspace all = whole_layout(p, false, true, workspace, flags);
+        if (all.bytes <= workspace_bytes) w = all;
+        else whole_rows = 0;
+    }
     for (int64_t first = 0; first < m; first += batch) {
         const int64_t rows = m - first < batch ? m - first : batch;
         if (first > 0) p.row_blocks = (rows + p.rows_per_block - 1) / p.rows_per_block;      // the last batch is shorter
         rc = eval_pass(p, w, samples, n, queries + first * d, rows, first > 0 || (flags & SDKDE_FLAG_SAMPLES_PREPARED) != 0, h,
                        density_out ? density_out + first : nullptr, log_density_out ? log_density_out + first : nullptr,
-                       flags, (hipStream_t)stream, laplace, reuse_centre, all_prepared);
+                       flags, (hipStream_t)stream, laplace, reuse_centre, all_prepared, whole_rows);
         if (rc != SDKDE_OK) return rc;
     }
     return SDKDE_OK;
@@ -1063,14 +1232,14 @@ int sdkde_fit_eval(const float* samples, int64_t n, const float* queries, int64_
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
     // The centre of the samples stays in the workspace; the shifted samples are centred on it too (any
     // centre is exact, it only has to be near the data).  Where the layouts allow it the score epilogue also
-    // prepares the eval pass's operands: five launches instead of six.
-    FusedPrep fused;
-    const bool fuse = plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused);
-    rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream,
-                    fuse ? &fused : nullptr);
+    // prepares the eval pass's operands: five launches instead of six, three for small sample sets.
+    FusedPrep fused{};
+    const bool fuse = plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused) ||
+                      (!whole_score(n, d, flags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused));
+    rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr);
     if (rc != SDKDE_OK || m == 0) return rc;
     return eval_impl(samples_sd_out, n, queries, m, d, h, density_out, log_density_out, workspace, workspace_bytes,
-                     flags, stream, false, true, fuse);
+                     flags, stream, false, true, fuse ? &fused : nullptr);
 }
 
 int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries, int64_t m, int32_t d, double h,
@@ -1087,9 +1256,11 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     Plan score_plan = make_plan(n, n, d, true, flags), eval_plan = make_plan(n, m, d, false, flags);
     apply_symmetric(score_plan, n, flags, true);
     Workspace unused;
-    size_t need = 0;
-    if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
-    if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES && !score_plan.parts && !eval_plan.parts) return SDKDE_ETOOLARGE;
+    if (!score_plan.parts && !eval_plan.parts) {
+        size_t need = 0;
+        if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
+        if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES) return SDKDE_ETOOLARGE;
+    }
     if (!fit_workspace(score_plan, true, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused) ||
         (m > 0 && !fit_points(eval_plan, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, m, &unused)))
         return SDKDE_ETOOLARGE;
