@@ -112,11 +112,12 @@ enum {
                                at a point with few neighbours whose pulls partly cancel;
                                fp32 accumulate, exp fp32.  Applies where FP16X2_ALL applies, and runs as FP16X2
                                elsewhere. */
-    /* flags bit 4: two-pass, max-shifted sums for sdkde_eval, sdkde_eval_laplace and sdkde_score at
-       separate points: a first pass finds max_j of the exponent for every point, the second sums
-       phi_j / max phi, and the logarithm (or the signed density) gets the shift back.  Results then stay
+    /* flags bit 4: max-shifted sums for sdkde_eval, sdkde_eval_laplace and sdkde_score at
+       separate points: sums of phi_j / max phi; the logarithm (or the signed density) gets the shift back.  Results then stay
        finite however far a point is from the samples, and they from the centre (the log density never becomes -inf, the
-       score at a far point is that of its nearest samples), at 1.5 to 1.75 times the time of the call. */
+       score at a far point is that of its nearest samples).  The fp32 mode's matrix path (d >= 4, scores d >= 7) finds the shifts
+       as it sums, at 1.04 to 1.2 times the time of the call; elsewhere a first pass finds max_j of the exponent for every point,
+       at 1.5 to 1.75 times. */
     SDKDE_FLAG_MAX_SHIFT = 16,
     /* flags bit 5: symmetric score.  phi_ij = phi_ji, so for the score at the samples themselves each
        unordered pair needs one Gram-matrix entry and one exp, used for both T_i and T_j (an algorithmic saving

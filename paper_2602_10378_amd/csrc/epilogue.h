@@ -50,6 +50,30 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     return r;
 }
 
+// The max-shifted sums of the two-part format come with a shift of their own in every slot (pair_half.h): they are added as what they
+// are of the largest one.  2^(shift - most) of a slot, both integers, 0 for a slot without samples.
+__device__ __forceinline__ float slot_weight(float shift, float most) { return ldexpf(1.0f, (int)fmaxf(shift - most, -1000.0f)); }
+
+template <int PARTS>
+__device__ __forceinline__ float reduce_shifted_slots(const float* __restrict__ first, int64_t stride, const float* __restrict__ shifts, int64_t shift_stride,
+                                                      float most, int nslots, bool active, float (*red)[kBlock / PARTS])
+{
+    constexpr int OUTPUTS = kBlock / PARTS;
+    const int lane = threadIdx.x % OUTPUTS, part = threadIdx.x / OUTPUTS;
+    float acc = 0.0f;
+    if (active) {
+#pragma unroll 4
+        for (int s = part; s < nslots; s += PARTS) acc = fmaf(first[(int64_t)s * stride], slot_weight(shifts[(int64_t)s * shift_stride], most), acc);
+    }
+    red[part][lane] = acc;
+    __syncthreads();
+    float r = red[0][lane];
+#pragma unroll
+    for (int q = 1; q < PARTS; ++q) r += red[q][lane];
+    __syncthreads();            // red is reused by the next reduction
+    return r;
+}
+
 // Columns c0 .. c0+3 of prepared row i, in any of the formats.  The loads are asked for apart from their use, without a
 // branch, so that a kernel can have them in flight beside the split slots it sums (read after the sums they are one more
 // memory latency of a kernel that is little else).  scaled_rows (not 0: their padded count): points, whose rows may be held
@@ -142,12 +166,14 @@ struct ScoreUnits {
 //        where T', D' exclude the pair (i, i), whose weight is exactly 1.
 // inv_ah2 = 1 / (a h^2) undoes the coordinate scaling.  D < min_sum (least_trusted_sum of the sample count) gives 0.
 // score and x_sd are both optional outputs; x_sd = x + half_h2 * score (x: the original points, same indexing).
+// SHIFTED: part_shift holds a shift a slot and row, [nsplit][m_pad].
 // Grid: one workgroup per kBlock / PARTS elements of the [m, d] output.
-template <int PARTS>
+template <int PARTS, bool SHIFTED>
 __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
     int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
-    float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, float min_sum, ScoreUnits units)
+    float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, float min_sum, ScoreUnits units,
+    const float* __restrict__ part_shift)
 {
     constexpr int kEpiOutputs = kBlock / PARTS;
     __shared__ float red[PARTS][kEpiOutputs];
@@ -157,8 +183,15 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
     const int c = active ? (int)(idx % d) : 0;
     PreparedQuad own = {};
     if (mode != 1) own.load(ps, i, c & ~3, dp, format, mode == 0 ? m_pad : 0);
-    float tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
-    float dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
+    float tsum, dsum;
+    if constexpr (SHIFTED) {
+        const float most = reduce_slots<PARTS, true>(part_shift + i, m_pad, nsplit, active, red);
+        tsum = reduce_shifted_slots<PARTS>(part_t + i * dp + c, m_pad * dp, part_shift + i, m_pad, most, nsplit, active, red);
+        dsum = reduce_shifted_slots<PARTS>(part_d + i, m_pad, part_shift + i, m_pad, most, nsplit, active, red);
+    } else {
+        tsum = reduce_slots<PARTS, false>(part_t + i * dp + c, m_pad * dp, nsplit, active, red);
+        dsum = reduce_slots<PARTS, false>(part_d + i, m_pad, nsplit, active, red);
+    }
     if (!active || threadIdx.x >= kEpiOutputs) return;
     const bool in_units = ScoreUnits::there(dsum, format);
     float pc = 0.0f, rest = 0.0f;
@@ -184,11 +217,12 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
 // bytes) by a quarter of the workgroups.  Same summation order, hence the same bits.  quad_io: the outputs (and x)
 // may be accessed 16 bytes at a time.
 // Grid: one workgroup per kBlock / kEpiPartsFew (row, four columns) pairs of the [m, dp] partials.
+template <bool SHIFTED>
 __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
     int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
     float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, int quad_io,
-    float min_sum, ScoreUnits units)
+    float min_sum, ScoreUnits units, const float* __restrict__ part_shift)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
     __shared__ f32x4 red_t[PARTS][LANES];
@@ -205,12 +239,26 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f};
     if (x_sd && part == 0) xv = load_quad(x + at, quad_io, d - c0);
     f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
-    float dacc = 0.0f;
+    float dacc = 0.0f, most = kNegHuge;
+    if constexpr (SHIFTED) {
+        if (active) {
+#pragma unroll 4
+            for (int s = part; s < nsplit; s += PARTS) most = fmaxf(most, part_shift[(int64_t)s * m_pad + i]);
+        }
+        red_d[part][lane] = most;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k) most = fmaxf(most, red_d[k][lane]);
+        __syncthreads();
+    }
     if (active) {
 #pragma unroll 4
         for (int s = part; s < nsplit; s += PARTS) {
-            tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
-            dacc += part_d[(int64_t)s * m_pad + i];
+            const f32x4 t = *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
+            const float dd = part_d[(int64_t)s * m_pad + i];
+            const float by = SHIFTED ? slot_weight(part_shift[(int64_t)s * m_pad + i], most) : 1.0f;
+            tacc += SHIFTED ? t * by : t;
+            dacc += SHIFTED ? dd * by : dd;
         }
     }
     red_t[part][lane] = tacc;
@@ -271,9 +319,10 @@ __device__ __forceinline__ void eval_outputs(int64_t i, float dsum, double logno
     if (density) density[i] = (float)(fabs(lognorm + shift_ln) < 600.0 ? (double)dsum * exp(lognorm + shift_ln) : exp(lp));
 }
 
-// shift (may be null): per-query base-2 exponent shift of the max-shifted mode.  residual (may be null): half2.h.  min_sum: least_trusted_sum(n).
+// shift (may be null): per-query base-2 exponent shift of the max-shifted mode; SHIFTED: one a slot and query, [nsplit][m_pad].
+// residual (may be null): half2.h.  min_sum: least_trusted_sum(n).
 // Grid: one workgroup per kBlock / PARTS queries.
-template <int PARTS>
+template <int PARTS, bool SHIFTED>
 __global__ __launch_bounds__(kBlock) void eval_epilogue_kernel(const float* __restrict__ part_d, int nsplit,
                                                                int64_t m, int64_t m_pad, double lognorm, int is_signed,
                                                                const float* __restrict__ shift,
@@ -285,11 +334,18 @@ __global__ __launch_bounds__(kBlock) void eval_epilogue_kernel(const float* __re
     __shared__ float red[PARTS][kEpiOutputs];
     const int64_t i = (int64_t)blockIdx.x * kEpiOutputs + threadIdx.x % kEpiOutputs;
     const bool active = i < m;
-    // max-shifted mode: the sums were taken of phi / 2^shift; residual: what rounding -|p~|^2 / 2 (less the shift) left
+    // max-shifted mode: the sums were taken of phi / 2^shift; residual: what rounding -|p~|^2 / 2 left
     // (read from somewhere in any case: behind a branch their latency would come on top of that of the sums)
     const float* const sums = part_d + (active ? i : 0);
-    const float of_shift = *(shift && active ? shift + i : sums), of_residual = *(residual && active ? residual + i : sums);
-    float dsum = reduce_slots<PARTS, false>(sums, m_pad, nsplit, active, red);
+    float of_shift = *(shift && active ? shift + i : sums), of_residual = *(residual && active ? residual + i : sums);
+    float dsum;
+    if constexpr (SHIFTED) {
+        const float* const shifts = shift + (active ? i : 0);
+        of_shift = reduce_slots<PARTS, true>(shifts, m_pad, nsplit, active, red);
+        dsum = reduce_shifted_slots<PARTS>(sums, m_pad, shifts, m_pad, of_shift, nsplit, active, red);
+    } else {
+        dsum = reduce_slots<PARTS, false>(sums, m_pad, nsplit, active, red);
+    }
     if (!active || threadIdx.x >= kEpiOutputs) return;
     const double shift_ln = ((shift ? (double)of_shift : 0.0) + (residual ? (double)of_residual : 0.0)) * 0.69314718055994530942;
     eval_outputs(i, dsum, lognorm, shift_ln, is_signed != 0, min_sum, density, log_density);
@@ -304,15 +360,12 @@ __global__ __launch_bounds__(kBlock) void debias_kernel(const float* x, const fl
 }
 
 
-// shift[i] = max over splits of the row maxima left in part_d by a kRowMax pass; on the MFMA path the
-// shift is also folded into the row constant pn (-|p~|^2 - shift), so the main pass needs no extra work; residual (may be
-// null) takes the rounding of that difference.  Rows held scaled down (their
-// scale follows the residuals) and those with a shift below kFarShift keep their norm, see pair_half.h.
+// shift[i] = max over splits of the row maxima left in part_d by a kRowMax pass (thin path, fp16 input modes); on the MFMA path the
+// shift is also folded into the row constant pn (-|p~|^2 - shift), so the main pass needs no extra work.
 // Grid: one workgroup per kBlock / PARTS rows.
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void shift_kernel(const float* __restrict__ part_d, int nsplit, int64_t m_pad,
-                                                       float* __restrict__ shift, float* __restrict__ pn,
-                                                       float* __restrict__ residual)
+                                                       float* __restrict__ shift, float* __restrict__ pn)
 {
     constexpr int kEpiOutputs = kBlock / PARTS;
     __shared__ float red[PARTS][kEpiOutputs];
@@ -321,15 +374,10 @@ __global__ __launch_bounds__(kBlock) void shift_kernel(const float* __restrict__
     // read from somewhere in any case, see eval_epilogue_kernel
     const float* const maxima = part_d + (active ? i : 0);
     const float before = *(pn && active ? pn + i : maxima);
-    const float scale = *(residual && active ? residual + m_pad + i : maxima), left = *(residual && active ? residual + i : maxima);
     const float mx = reduce_slots<PARTS, true>(maxima, m_pad, nsplit, active, red);
     if (!active || threadIdx.x >= kEpiOutputs) return;
-    shift[i] = pn && before == kPadNorm ? 0.0f : mx;        // a padding row's is of no interest, nor has it to look far away
-    if (pn && !(residual && (scale != 1.0f || mx < kFarShift))) {
-        const float after = before - mx;
-        pn[i] = after;
-        if (residual) residual[i] = left + (float)(((double)before - (double)mx) - (double)after);
-    }
+    shift[i] = pn && before == kPadNorm ? 0.0f : mx;        // a padding row's is of no interest
+    if (pn) pn[i] = before - mx;
 }
 
 }  // namespace

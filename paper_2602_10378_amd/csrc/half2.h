@@ -46,11 +46,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr float kHalfMax = 65504.0f;             // largest finite fp16 value
 constexpr float kReach = 60000.0f;               // kReach^2 / 2 and the largest part of a shift beside it stay below -kLeastTerm
 // From here on the shifted sums round an exponent at the size of the norms and only then shift it (its last place is 2^-3
-// there): rounded differently for the maximum and for the sums they would miss each other, and the sums were 0 or infinite from
-// about 10^5 bandwidths on, with far samples from 10^4 on.
+// there): with the shift in the row's term the look for the largest exponent and the weights would miss each other, and the sums be 0
+// or infinite from about 10^5 bandwidths on, with far samples from 10^4 on.
 constexpr float kFarPoint = 2048.0f;
-// So they do for a point that is not that far but has a shift below this: its nearest sample is 5000 units away, every
-// sample more than kFarPoint from the centre, and the row maxima have been formed the same way.
+// So they do for a point that is not that far but finds nothing above this at first: its nearest sample so far is 5000 units away,
+// every one more than kFarPoint from the centre.
 constexpr float kFarShift = -12582912.0f;
 constexpr float kWeightScale = 2048.0f;          // see pair_half.h
 constexpr int half_tile_bytes(int kb) { return kb * 1024 + (kb % 2) * 256; }
@@ -100,11 +100,9 @@ __host__ __device__ inline float* half2_scale(float* ps, int64_t rows_pad, int d
 
 // Behind the prepared samples, at the same distance from them: their scales, and a byte a 16-row tile, what a kernel may have to
 // know of its samples.
-constexpr uint32_t kMarkWide = 1;                   // one with half a squared norm above kCoarseSample
-constexpr uint32_t kMarkDistant = 2;                // one further than kFarPoint from the centre
-constexpr uint32_t kMarkOwnUnits = 4;               // its chunk's columns of "xt" are in units of their own (on both tiles of it)
-constexpr uint32_t kMarks = 3;                      // how many there are
-constexpr float kCoarseNorm = 2048.0f, kCoarseSample = 8192.0f;      // see the row maxima in pair_half.h
+constexpr uint32_t kMarkDistant = 1;                // one further than kFarPoint from the centre
+constexpr uint32_t kMarkOwnUnits = 2;               // its chunk's columns of "xt" are in units of their own (on both tiles of it)
+constexpr uint32_t kMarks = 2;                      // how many there are
 __host__ __device__ inline uint8_t* half2_marks(float* xs, int64_t rows_pad, int dp)
 {
     return reinterpret_cast<uint8_t*>(half2_scale(xs, rows_pad, dp) + rows_pad);

@@ -11,6 +11,13 @@
 // Whole calls: score + eval at 32768 samples, d = 16, 641 / 484 us; 262144 x 65536, d = 64, 79.7 / 53.8 ms; eval of 1024 points
 // against 1048576 samples, d = 16, 217 / 155 us.  Error against 64-bit sums over d = 4 .. 128, geometric mean of now / before:
 // score 0.85 (at most 1.07), at separate points 0.94 (1.08), density 0.86, Laplace-corrected 0.67.
+//
+// Max-shifted sums (FAR) find the shift as they go: a row's is set from its largest exponent in a split's first chunk and raised
+// when a weight outgrows what its sums hold (2^100 for the eval kinds, so hardly ever), and each slot keeps its own for the
+// epilogue to add the slots with.  A first pass over all samples for the row maxima, on the leading products, and a launch that put them
+// into the norms came before; two passes / one: eval 50021 x 10007, d = 24, 155 / 110 us, 20000 x 5003, d = 16 50 / 36, d = 128 136 / 93;
+// Laplace 100000 x 20000, d = 32, 659 / 493; score at points 20000 x 20000, d = 16 229 / 155, d = 64 441 / 343, 20000 x 5003,
+// d = 128 299 / 289 (its rows' scales are raised often).  Errors against 64-bit sums as before (0.97 to 1.02).
 #pragma once
 #include "common.h"
 #include "half2.h"
@@ -66,7 +73,7 @@ struct HalfRows {
         const char* at = SPARE ? tile + (PAIRS - 1) * 2048 + TERM_GROUP * 256 : tile + PAIRS * 2048 + 1024;
         return (float)reinterpret_cast<const _Float16*>(at + row % kTile * 16)[3] * kResidualFactor;
     }
-    // Products as the eval kinds and the row maxima have them.
+    // Products as the eval kinds have them.
     __device__ __forceinline__ void bare(int g)
     {
 #pragma unroll
@@ -97,6 +104,8 @@ struct HalfRows {
 constexpr float kMostWeight = 65000.0f * kWeightScale;      // of a lane's sum of W, so that no w leaves the fp16 range
 constexpr int kRaisedTo = 18;                       // where a row's largest W is put when it has outgrown that
 constexpr float kLeastShift = -126.0f;              // a W of one then stands for the smallest normal fp32 number
+// Shifted sums without Phi X have the fp32 range for their weights: a row's first look puts its largest at one.
+constexpr float kMostShifted = 1.0e30f;             // of a lane's sum over the row tiles at hand
 
 __device__ __forceinline__ void split_weights(const f32x4& p, const f32x4& q, f16x8& h, f16x8& l)
 {
@@ -122,14 +131,14 @@ template <int KB, int TAIL, int NI, int WAVES, int NB, bool AHEAD, int MINW, int
 __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs, const float* __restrict__ xt,
     const float* __restrict__ xn, float* __restrict__ part_t, float* __restrict__ part_d,
-    int ntiles, int tiles_per_split, int nsplit, int64_t m_pad, float laplace_c0, const float* __restrict__ shift)
+    int ntiles, int tiles_per_split, int nsplit, int64_t m_pad, float laplace_c0, float* __restrict__ part_shift)
 {
     static_assert(NI % 2 == 0 && NI % NB == 0, "a wave's own rows are whole chunks");
     static_assert((KB % 2 != 0) == (TAIL == kTailSixteen || TAIL == kTailEight), "an odd block count has a tail");
     constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints;
     constexpr bool SELF = KIND == kScoreSelf;
     constexpr bool LAPLACE = KIND == kEvalLaplace;
-    constexpr bool ROWMAX = KIND == kRowMax;
+    static_assert(KIND != kRowMax, "shifted sums find their shifts as they go");
     constexpr bool ODD = HalfRows<KB, TAIL, NI, SCORE, FAR>::ODD, TERMED = TAIL != kTailNone;
     constexpr int DP = KB * 16;
     constexpr int KT = SCORE ? KB : 1;
@@ -155,33 +164,20 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     const uint8_t* const marks_at = half2_marks(const_cast<float*>(xs), n_pad, DP);
     const float* const units = half2_units(const_cast<float*>(xs), n_pad, DP);
     const float other_units = SCORE ? units[DP] : 0.0f;             // a column of xt is not in plain coordinates
-    if constexpr (ROWMAX) marks = marks_of(marks_at, c_begin, c_end, lane);
 
     HalfRows<KB, TAIL, NI, SCORE, FAR> rows;
     rows.load(ps, pn, row0, r, g);
     // FAR: a row may be held as 2^-k times itself, 2^k behind the prepared rows, and so may samples; far: one of the wave's rows
-    // is, or its exponents have to be shifted last (wave-uniform).  (Without such a row samples that are held so have no weight.)
+    // is, or no sample that its first look has seen is within kFarShift of one, and exponents are shifted last (wave-uniform).
+    // (Without such a row samples that are held so have no weight.)
     bool far = false;
     const float* const pscale = FAR ? half2_scale(const_cast<float*>(ps), m_pad, DP) : nullptr;
     const float* const xscale = FAR ? half2_scale(const_cast<float*>(xs), n_pad, DP) : nullptr;
     auto of_row = [&](const float* at, int t) { return load_at<float>(reinterpret_cast<const char*>(at + row0 + t * kTile), r * 4u); };
-    auto shifted_last = [&](int t) { return (int)(of_row(pscale, t) != 1.0f) | (ROWMAX ? 0 : (int)(of_row(shift, t) < kFarShift)); };
     if constexpr (FAR) {
-        far = ROWMAX && (marks & kMarkDistant) != 0;
 #pragma unroll
-        for (int t = 0; t < NI; ++t) far |= __builtin_amdgcn_ballot_w64(shifted_last(t) != 0) != 0;
+        for (int t = 0; t < NI; ++t) far |= __builtin_amdgcn_ballot_w64(of_row(pscale, t) != 1.0f) != 0;
         if (SCORE && far) rows.bare(g);
-    }
-    // ROWMAX: any shift near the largest exponent serves, as long as the sums use the same.  Of whole 32-column blocks the
-    // leading products do, for rows with half a squared norm up to kCoarseNorm and samples up to kCoarseSample: the two products
-    // left out are 2^-11 |p~| |x~| each at most, 8 together.  (The bound has to be on both: of a row near the centre and a sample
-    // 10^4 bandwidths from it they come to 100 and more, and with every sample that far the sums were 0 or infinite.)
-    // (Max-shifted eval of 10007 points against 50021 samples, d = 24: 206 us with all products for every row, 180 so.)
-    bool coarse = false;
-    if constexpr (ROWMAX) {
-        coarse = !far && (marks & kMarkWide) == 0;
-#pragma unroll
-        for (int t = 0; t < NI; ++t) coarse &= __builtin_amdgcn_ballot_w64(rows.term[t] < -kCoarseNorm) == 0;
     }
 
     // Two-level accumulation: the running sums (tacc, dacc) are folded into a second level every kFlushTiles sample
@@ -190,16 +186,18 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     float dacc[NI], dsum[NI];
     float lc0[LAPLACE ? NI : 1];          // Laplace factor constant per row tile: 1 + d/2 + shift_i ln 2
     float unit[SCORE ? NI : 1];           // what a W of one is worth
+    float less[FAR ? NI : 1];             // FAR: by how much the exponents have been lowered, the rows' shift
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
-        dacc[t] = dsum[t] = ROWMAX ? kNegHuge : 0.0f;
+        dacc[t] = dsum[t] = 0.0f;
 #pragma unroll
         for (int mb = 0; mb < KT; ++mb) {
             tacc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (SUMLDS) sum_lds[wave][t * KT + mb][lane] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        if (LAPLACE) lc0[t] = fmaf(shift ? shift[row0 + t * kTile + r] : 0.0f, kLn2, laplace_c0);
+        if (LAPLACE) lc0[t] = laplace_c0;
         if (SCORE) unit[t] = kWeightScale;
+        if (FAR) less[t] = 0.0f;
     }
     auto slot_at = [&](int t, int mb) {
         return reinterpret_cast<f32x4*>(part_t + ((int64_t)split * m_pad + row0 + t * kTile + r) * DP + g * 4 + mb * 16);
@@ -237,17 +235,16 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     auto lowered = [&](int t) { return (float)((int)(__builtin_bit_cast(uint32_t, unit[SCORE ? t : 0]) >> 23) - 127 - 11); };
     // Exponents of NB row tiles from t0 on against a chunk's two sample tiles.  own (SELF): the row tile that is the chunk's
     // first sample tile, if it is one.  c_at: the chunk.  to_t: the first operands of the second contraction are read behind.
-    auto exponents = [&](const char* xc, int c_at, int t0, const f32x4& nj0, const f32x4& nj1, int own, bool to_t, auto lead, f32x4 (&c)[NB][2]) __attribute__((always_inline)) {
-        constexpr bool LEAD = decltype(lead)::value;        // ROWMAX: leading products of whole blocks only
+    auto exponents = [&](const char* xc, int c_at, int t0, const f32x4& nj0, const f32x4& nj1, int own, bool to_t, f32x4 (&c)[NB][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < NB; ++t) {
             const float add = TERMED ? 0.0f : rows.term[t0 + t];
-            c[t][0] = FAR && !LEAD && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj0 : nj0 + add;
-            c[t][1] = FAR && !LEAD && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj1 : nj1 + add;
+            c[t][0] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj0 : nj0 + add;
+            c[t][1] = FAR && far ? f32x4{0.f, 0.f, 0.f, 0.f} : TERMED ? nj1 : nj1 + add;
         }
         if (AHEAD) read_gram(xc, 0, ga[0]);
 #pragma unroll
-        for (int s = 0; s < (LEAD ? GROUPS : STEPS); ++s) {
+        for (int s = 0; s < STEPS; ++s) {
             if (!AHEAD) read_gram(xc, s, ga[s & 1]);
             else if (s + 1 < STEPS) read_gram(xc, s + 1, ga[(s + 1) & 1]);
             else if (to_t) read_t(xc, 0, ta[0]);
@@ -256,7 +253,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             // the largest products of all groups and the row's term first: they bring the accumulator from the size
             // of the norms down to that of the distance, where the small ones round finer
             const int p = s < GROUPS ? s : s - GROUPS;
-            const int k0 = s < GROUPS ? 0 : 1, k1 = LEAD || s < GROUPS - 1 ? 1 : 3;
+            const int k0 = s < GROUPS ? 0 : 1, k1 = s < GROUPS - 1 ? 1 : 3;
             if (p < PAIRS) {
                 constexpr int PA[3] = {0, 1, 0}, PB[3] = {0, 0, 1};
 #pragma unroll
@@ -277,24 +274,20 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             }
             pin();
         }
-        if (FAR && !LEAD && __builtin_expect(far, 0)) {
-            // such a row's norm is not shifted (shift_kernel): its exponents are rounded at the size of the norms and come out the
-            // same here as for the row maxima, only then are they shifted
+        if (FAR && __builtin_expect(far, 0)) {
+            // such rows' exponents are rounded at the size of the norms, the same way whatever the shift, and only then shifted:
+            // with the shift in the row's term a look for the largest and the weights would miss each other
             // (samples that are held as they are have a scale of 1)
             f32x4 xs[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) xs[u] = load_at<f32x4>(reinterpret_cast<const char*>(xscale + (int64_t)c_at * kChunkRows + u * kTile), g * 16u);
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
-                const float unscale = of_row(pscale, t0 + t);
-                const bool last = shifted_last(t0 + t) != 0;
-                const float base = SCORE && last ? of_row(pn, t0 + t) : rows.term[t0 + t];
-                const float less = !ROWMAX && last ? of_row(shift, t0 + t) : 0.0f;
-                const float low = last && SCORE ? lowered(t0 + t) : 0.0f;
+                const float unscale = of_row(pscale, t0 + t), base = of_row(pn, t0 + t);
 #pragma unroll
                 for (int v = 0; v < 8; ++v) {
                     const float norm = v < 4 ? nj0[v % 4] : nj1[v % 4];
-                    c[t][v / 4][v % 4] = ((fmaf(c[t][v / 4][v % 4], unscale * xs[v / 4][v % 4], norm) + base) - less) - low;
+                    c[t][v / 4][v % 4] = (fmaf(c[t][v / 4][v % 4], unscale * xs[v / 4][v % 4], norm) + base) - less[FAR ? t0 + t : 0];
                 }
             }
         }
@@ -309,41 +302,53 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                     }
         }
     };
-    // SCORE: by how much a row's exponents (largest of the lane's eight: its share of the row) have to be lowered
-    auto excess = [&](const f32x4 (&c)[2]) {
+    // a row's largest exponent of a chunk (largest of the lane's eight: its share of the row)
+    auto largest = [&](const f32x4 (&c)[2]) {
         float most = c[0][0];
 #pragma unroll
         for (int v = 1; v < 8; ++v) most = fmaxf(most, c[v / 4][v % 4]);
         most = fmaxf(most, __shfl_xor(most, 16));
-        most = fmaxf(most, __shfl_xor(most, 32));
-        return floorf(most) - (float)kRaisedTo;
+        return fmaxf(most, __shfl_xor(most, 32));
     };
+    // SCORE: by how much a row's exponents have to be lowered
+    auto excess = [&](const f32x4 (&c)[2]) { return floorf(largest(c)) - (float)kRaisedTo; };
     // SCORE: sets row tile t's scale: exponents are 2^-low of what they stand for.  The term anew from the norm: sums of it with
     // several shifts, one after the other, would round every time (2^-18 with a norm of 30 and the shift of 126 that suits any
     // point: score errors of up to 2.4 times the present ones).
     auto set_scale = [&](int t, float low, float norm, float residual) {
         rows.term[t] = norm - low;
         unit[SCORE ? t : 0] = ldexpf(kWeightScale, (int)low);
-        if (!(FAR && far)) rows.place_term(t, rows.term[t], residual, g);
+        rows.place_term(t, rows.term[t], residual, g);
     };
+    // FAR: the same with a shift of any size, which the sums are kept relative to and which goes with them to the slots.  What
+    // rounding norm - low leaves goes into the term's third part; without a term in columns (shift_rest) the sums make up for it.
+    auto shift_rest = [&](float norm, float low) {
+        const float term = norm - low, back = term - norm, rest = (norm - (term - back)) + (-low - back);
+        return fabsf(rest) < 500.0f ? rest : 0.0f;          // (more: there is no sample yet that the shift could be of)
+    };
+    auto set_shift = [&](int t, float low) {
+        const int64_t row = row0 + t * kTile + r;
+        const float norm = pn[row];
+        less[FAR ? t : 0] = low;
+        rows.term[t] = norm - low;
+        if (LAPLACE) lc0[LAPLACE ? t : 0] = fmaf(low, kLn2, laplace_c0);
+        if (TERMED) rows.place_term(t, far ? 0.0f : rows.term[t], far ? 0.0f : shift_rest(norm, low) + (SCORE ? rows.residual(ps, row) : 0.0f), g);
+    };
+    // (above 2^24, where floats are further apart than kRaisedTo, a difference could come out that much too low)
+    auto shift_for = [&](float most) {
+        const float put = SCORE ? (float)kRaisedTo : 0.0f, low = floorf(most) - put;
+        return most - low <= put + 1.0f ? low : floorf(most);
+    };
+    auto rest_of = [&](int t) { return TERMED || far ? 0.0f : shift_rest(of_row(pn, t), less[FAR ? t : 0]); };
 
+    bool flushed = false;                                   // !SUMLDS: the partial slot holds second-level sums
     // One chunk against all NI row tiles.
-    auto chunk = [&](const char* xc, int c_at, const f32x4& nj0, const f32x4& nj1, int own, auto lead) __attribute__((always_inline)) {
+    auto chunk = [&](const char* xc, int c_at, const f32x4& nj0, const f32x4& nj1, int own) __attribute__((always_inline)) {
 #pragma unroll
         for (int t0 = 0; t0 < NI; t0 += NB) {
             f32x4 c[NB][2], phi[NB][2];
             float dt[NB];
-            if constexpr (ROWMAX) {
-                exponents(xc, c_at, t0, nj0, nj1, own, false, lead, c);
-#pragma unroll
-                for (int t = 0; t < NB; ++t) {
-                    float& d = dacc[t0 + t];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) d = fmaxf(d, fmaxf(fmaxf(c[t][u].x, c[t][u].y), fmaxf(c[t][u].z, c[t][u].w)));
-                }
-                continue;
-            }
-            exponents(xc, c_at, t0, nj0, nj1, own, SCORE, lead, c);
+            exponents(xc, c_at, t0, nj0, nj1, own, SCORE, c);
             auto weigh = [&](int t) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
@@ -352,9 +357,11 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 if (LAPLACE) {
                     // c is the base-2 exponent -r^2/(2h^2) log2(e) (less the row's shift), so the Laplace factor
                     // 1 + d/2 - r^2/(2h^2) is lc0 + c ln 2 (Laplace-corrected KDE section)
+                    float& sum = FAR ? dt[t] : dacc[t0 + t];
+                    if (FAR) dt[t] = 0.0f;
 #pragma unroll
                     for (int v = 0; v < 8; ++v)
-                        dacc[t0 + t] = fmaf(phi[t][v / 4][v % 4], fmaf(c[t][v / 4][v % 4], kLn2, lc0[LAPLACE ? t0 + t : 0]), dacc[t0 + t]);
+                        sum = fmaf(phi[t][v / 4][v % 4], fmaf(c[t][v / 4][v % 4], kLn2, lc0[LAPLACE ? t0 + t : 0]), sum);
                 } else {
                     dt[t] = ((phi[t][0].x + phi[t][0].y) + (phi[t][0].z + phi[t][0].w)) +
                             ((phi[t][1].x + phi[t][1].y) + (phi[t][1].z + phi[t][1].w));
@@ -364,11 +371,12 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 weigh(t);
-                if (SCORE) all = t == 0 ? dt[t] : all + dt[t];
+                // (a signed sum near zero does no harm: what has to be seen is what leaves the range, and NaN compares as that)
+                if (SCORE || FAR) all = t == 0 ? (LAPLACE ? fabsf(dt[t]) : dt[t]) : all + (LAPLACE ? fabsf(dt[t]) : dt[t]);
             }
             // a weight may have outgrown its row's scale: that row's exponents are lowered, its largest W is 2^kRaisedTo
             // again (wave-uniform; in place, so that nothing is copied where it does not happen)
-            if (SCORE && __builtin_expect(__builtin_amdgcn_ballot_w64(all > kMostWeight) != 0, 0)) {
+            if (SCORE && !FAR && __builtin_expect(__builtin_amdgcn_ballot_w64(all > kMostWeight) != 0, 0)) {
 #pragma unroll
                 for (int t = 0; t < NB; ++t) {
                     const float up = fminf(fmaxf(excess(c[t]), 0.0f), 16384.0f);
@@ -379,11 +387,52 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                     weigh(t);
                 }
             }
+            // FAR: or the shift may; what has been summed, on both levels, is brought to the new one.  A shift too large, or a
+            // weight too far out, for the difference to be exact: the row is looked at anew.
+            if (FAR && __builtin_expect(__builtin_amdgcn_ballot_w64(!(all <= (SCORE ? kMostWeight : kMostShifted))) != 0, 0)) {
+                float before[NB], by[NB], up[NB];
+                bool exact = true;
+#pragma unroll
+                for (int t = 0; t < NB; ++t) {
+                    before[t] = less[FAR ? t0 + t : 0];
+                    by[t] = rest_of(t0 + t);
+                    up[t] = fmaxf(floorf(largest(c[t])) - (SCORE ? (float)kRaisedTo : 0.0f), 0.0f);
+                    exact &= up[t] < 16384.0f && fabsf(before[t]) < 4194304.0f;
+                }
+                exact = __builtin_amdgcn_ballot_w64(!exact) == 0;
+                if (!exact) {
+#pragma unroll
+                    for (int t = 0; t < NB; ++t) set_shift(t0 + t, 0.0f);
+                    exponents(xc, c_at, t0, nj0, nj1, own, false, c);
+                }
+#pragma unroll
+                for (int t = 0; t < NB; ++t) {
+                    set_shift(t0 + t, exact ? before[t] + up[t] : fmaxf(before[t], shift_for(largest(c[t]))));
+                    const float now = less[FAR ? t0 + t : 0];
+                    by[t] = __builtin_amdgcn_exp2f((before[t] - now) + (by[t] - rest_of(t0 + t)));
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) c[t][u] -= exact ? up[t] : 0.0f;
+                    dacc[t0 + t] *= by[t];
+                    dsum[t0 + t] *= by[t];
+                    if constexpr (SCORE) {
+#pragma unroll
+                        for (int mb = 0; mb < KT; ++mb) {
+                            tacc[t0 + t][mb] *= by[t];
+                            if (SUMLDS) sum_lds[wave][(t0 + t) * KT + mb][lane] *= by[t];
+                            else if (flushed) *slot_at(t0 + t, mb) *= by[t];
+                        }
+                    }
+                }
+                if (!exact) exponents(xc, c_at, t0, nj0, nj1, own, false, c);
+                if (SCORE && AHEAD) read_t(xc, 0, ta[0]);       // (their registers are not kept for this rare path)
+#pragma unroll
+                for (int t = 0; t < NB; ++t) weigh(t);
+            }
             if constexpr (SCORE) {
                 f16x8 w[NB][2];
 #pragma unroll
                 for (int t = 0; t < NB; ++t) {
-                    dacc[t0 + t] = fmaf(dt[t], unit[t0 + t] * (1.0f / kWeightScale), dacc[t0 + t]);
+                    dacc[t0 + t] = fmaf(dt[t], (FAR ? 1.0f : unit[t0 + t]) * (1.0f / kWeightScale), dacc[t0 + t]);
                     // keeps the sum here: the compiler would otherwise sink it behind the MFMAs and hold the Phi tiles live
                     asm volatile("" : "+v"(dacc[t0 + t]));
                     split_weights(phi[t][0], phi[t][1], w[t][0], w[t][1]);
@@ -394,7 +443,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                     for (int t = 0; t < NB; ++t)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            tacc[t0 + t][mb][v] = fmaf(sum[mb & 1][t][v], unit[t0 + t], tacc[t0 + t][mb][v]);
+                            tacc[t0 + t][mb][v] = FAR ? sum[mb & 1][t][v] + tacc[t0 + t][mb][v] : fmaf(sum[mb & 1][t][v], unit[t0 + t], tacc[t0 + t][mb][v]);
                 };
 #pragma unroll
                 for (int mb = 0; mb < KB; ++mb) {
@@ -416,7 +465,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                     if (mb > 0) add(mb - 1);
                 }
                 add(KB - 1);
-            } else if constexpr (!LAPLACE && !ROWMAX) {
+            } else if constexpr (!LAPLACE || FAR) {
 #pragma unroll
                 for (int t = 0; t < NB; ++t) dacc[t0 + t] += dt[t];
             }
@@ -426,7 +475,6 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     const int own0 = (int)(row0 / kChunkRows);              // SELF: the wave's own rows are chunks own0 .. own0 + NI/2 - 1
     const char* const xs_b = reinterpret_cast<const char*>(xs);
     const char* const xt_b = reinterpret_cast<const char*>(xt);
-    bool flushed = false;                                   // !SUMLDS: the partial slot holds second-level sums
     if (c_begin < c_end) {
         const int c_last = c_end - 1;                       // the prefetch past the end re-reads the last chunk (in bounds)
         // The pieces a wave moves: one scalar base and stride each (no branches in the loop).  A piece past the end is the
@@ -452,23 +500,50 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
         };
         f32x4 nj0 = norms(c_begin, 0), nj1 = norms(c_begin, 1);
         fetch(c_begin);                                     // (all first loads are under way before the first is waited for)
-        float residual[SCORE ? NI : 1];
+        float residual[SCORE && !FAR ? NI : 1];
 #pragma unroll
         for (int t = 0; t < NI; ++t) {
-            if (SCORE) residual[SCORE ? t : 0] = rows.residual(ps, row0 + t * kTile + r);
+            if (SCORE && !FAR) residual[SCORE && !FAR ? t : 0] = rows.residual(ps, row0 + t * kTile + r);
             rows.place_term(t, FAR && far ? 0.0f : rows.term[t], 0.0f, g);
         }
+        if (FAR) marks = marks_of(marks_at, c_begin, c_end, lane);
         deposit(stage_lds[0]);
         __syncthreads();
-        if constexpr (SCORE) {
+        if constexpr (SCORE && !FAR) {
             // every row's scale, from its largest weight among the first chunk's samples (without a near one: the smallest)
 #pragma unroll
             for (int t0 = 0; t0 < NI; t0 += NB) {
                 f32x4 c[NB][2];
-                exponents(stage_lds[0], c_begin, t0, nj0, nj1, 2 * (c_begin - own0), false, std::false_type{}, c);
+                exponents(stage_lds[0], c_begin, t0, nj0, nj1, 2 * (c_begin - own0), false, c);
 #pragma unroll
                 for (int t = 0; t < NB; ++t)
-                    set_scale(t0 + t, fminf(fmaxf(excess(c[t]), kLeastShift), 16384.0f), rows.term[t0 + t], residual[SCORE ? t0 + t : 0]);
+                    set_scale(t0 + t, fminf(fmaxf(excess(c[t]), kLeastShift), 16384.0f), rows.term[t0 + t], residual[SCORE && !FAR ? t0 + t : 0]);
+            }
+        }
+        if constexpr (FAR) {
+            // every row's shift, from its largest exponent among the first chunk's samples; where that is below kFarShift, once more
+            // with the exponents of far rows
+            auto look = [&] {
+                bool below = false;
+#pragma unroll
+                for (int t0 = 0; t0 < NI; t0 += NB) {
+                    f32x4 c[NB][2];
+                    exponents(stage_lds[0], c_begin, t0, nj0, nj1, 0, false, c);
+#pragma unroll
+                    for (int t = 0; t < NB; ++t) {
+                        const float most = largest(c[t]);
+                        below |= __builtin_amdgcn_ballot_w64(most < kFarShift) != 0;
+                        set_shift(t0 + t, fmaxf(shift_for(most), kNegHuge));
+                    }
+                }
+                return below;
+            };
+            if (look() && !far && (marks & kMarkDistant) != 0) {
+                far = true;
+                if (SCORE) rows.bare(g);
+#pragma unroll
+                for (int t = 0; t < NI; ++t) set_shift(t, 0.0f);
+                look();
             }
         }
         // SCORE: a chunk with units of its own is summed in them: what has been summed is brought to them and back, on both levels.
@@ -487,7 +562,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 }
             }
         };
-        if (SCORE && (FAR || other_units != 0.0f)) marks = marks_of(marks_at, c_begin, c_end, lane);
+        if (SCORE && !FAR && other_units != 0.0f) marks = marks_of(marks_at, c_begin, c_end, lane);
         const bool alone = SCORE && (marks & kMarkOwnUnits) != 0;
         for (int c = c_begin; c < c_end;) {
             const int end = alone ? c + 1 : c_end;
@@ -496,9 +571,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 const char* cur = stage_lds[(c - c_begin) & 1];
                 fetch(c + 1);                               // lands in registers while this chunk is worked on
                 const f32x4 nn0 = norms(c + 1, 0), nn1 = norms(c + 1, 1);
-                if (ROWMAX && PAIRS > 0 && coarse) chunk(cur, c, nj0, nj1, 0, std::integral_constant<bool, ROWMAX>{});
-                else chunk(cur, c, nj0, nj1, 2 * (c - own0), std::false_type{});
-                if (!ROWMAX && ((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
+                chunk(cur, c, nj0, nj1, 2 * (c - own0));
+                if (((c + 1 - c_begin) & (kFlushTiles / 2 - 1)) == 0) {
 #pragma unroll
                     for (int t = 0; t < NI; ++t) {
                         dsum[t] += dacc[t];
@@ -526,23 +600,27 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
     }
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
+        const float by = FAR ? __builtin_amdgcn_exp2f(rest_of(t)) : 1.0f;
         if constexpr (SCORE) {
 #pragma unroll
             for (int mb = 0; mb < KT; ++mb) {
                 if (SUMLDS) tacc[t][mb] += sum_lds[wave][t * KT + mb][lane];
                 else if (flushed) tacc[t][mb] += *slot_at(t, mb);
+                if (FAR) tacc[t][mb] *= by;
                 *slot_at(t, mb) = tacc[t][mb];
             }
         }
-        // D needs the sum (or maximum) over the four lane groups g
-        float dtot = ROWMAX ? fmaxf(dsum[t], dacc[t]) : dsum[t] + dacc[t];
+        // D needs the sum over the four lane groups g
+        float dtot = dsum[t] + dacc[t];
+        if (FAR) dtot *= by;
 #pragma unroll
-        for (int step = 16; step <= 32; step *= 2) {
-            const float other = __shfl_xor(dtot, step);
-            dtot = ROWMAX ? fmaxf(dtot, other) : dtot + other;
-        }
+        for (int step = 16; step <= 32; step *= 2) dtot += __shfl_xor(dtot, step);
         if (SCORE && other_units != 0.0f) dtot = -dtot;         // tells the epilogues
-        if (g == 0) part_d[(int64_t)split * m_pad + row0 + t * kTile + r] = dtot;
+        if (g == 0) {
+            const int64_t at = (int64_t)split * m_pad + row0 + t * kTile + r;
+            part_d[at] = dtot;
+            if (FAR) part_shift[at] = c_begin < c_end ? less[FAR ? t : 0] : kNegHuge;
+        }
     }
 }
 

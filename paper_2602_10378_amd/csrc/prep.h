@@ -355,7 +355,7 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
         if (job.samples) {
             const int in_wave = (BLOCK - ROWS + rr) % kWave;            // (a tile's rows are 16 lanes in a row)
             auto any = [&](bool v) { return (__builtin_amdgcn_ballot_w64(row < job.rows && v) >> (in_wave & 48) & 0xffffu) != 0; };
-            const uint32_t marks = (any(norm < -kCoarseSample) ? kMarkWide : 0) | (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0) |
+            const uint32_t marks = (any(norm < -0.5f * kFarPoint * kFarPoint) ? kMarkDistant : 0) |
                                    (own_units ? kMarkOwnUnits : 0);
             if (rr % kTile == 0) half2_marks(job.dst, job.rows_pad, dp)[row / kTile] = (uint8_t)marks;
         } else {

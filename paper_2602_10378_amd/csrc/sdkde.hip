@@ -45,19 +45,19 @@ constexpr int max_row_tiles(int kb, int kind, int prec)
 // Clocks of a wave's 16 x 16 pairs (as in pair_half.h) with rt = 2 / 4 / 8: score d = 16 187 / 180 / 178; eval d = 16 83 / 77 / 75.
 // Four row tiles a wave take the fewest operand reads that the registers allow up to dp = 32 (eval 96); above, eight waves of
 // two share a workgroup's reads instead.  The score at dp = 48 has four at the samples themselves only, without reading ahead
-// (both together spill), likewise four instead of eight at dp = 16 where rows may be scaled; there two at d = 81 .. 88 do not read
-// ahead either.  The row maxima, built for leading and for all products, need a few registers more: two waves a SIMD at dp = 48, eight waves of two row tiles at dp = 96, and at
-// d = 25 .. 32 the Gram accumulators of two row tiles at a time instead of four.
+// (both together spill), likewise four instead of eight at dp = 16 where sums are shifted.  Shifted sums need a few registers more:
+// eval the Gram accumulators of two row tiles at a time instead of four at dp = 16 and two waves a SIMD at dp = 48, the score at
+// d = 81 .. 88 one wave a SIMD in the smallest shape.
 struct HalfShape { int ni, waves, nb; bool ahead; int minw; };
-constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false, bool rowmax = false, int tail = kTailSixteen)
+constexpr HalfShape half_shape(int kb, bool score, int rt, bool self = true, bool far = false, int tail = kTailSixteen)
 {
     if (score) {
-        if (rt == 2) return {2, 4, 2, !(far && kb == 6 && tail == kTailSpare), kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 ? 2 : 1};
+        if (rt == 2) return {2, 4, 2, true, kb == 1 && !far ? 4 : kb <= 2 ? 3 : kb <= 6 && !(far && kb == 6 && tail == kTailSpare) ? 2 : 1};
         if (rt == 4) return kb <= 2 ? HalfShape{4, 4, 4, true, 2} : kb == 3 && self ? HalfShape{4, 4, 2, false, 2} : kb <= 6 ? HalfShape{2, 8, 2, true, 2} : HalfShape{};
         if (rt == 8 && kb == 1) return far ? HalfShape{4, 8, 2, true, 2} : HalfShape{8, 4, 2, true, 2};
     } else {
         if (rt == 2) return {2, 4, 2, false, kb <= 2 ? 4 : kb <= 4 ? 3 : 2};
-        if (rt == 4) return kb <= (rowmax ? 5 : 6) ? HalfShape{4, 4, kb <= 3 && !(rowmax && kb == 2 && tail == kTailNone) ? 4 : 2, false, kb <= (rowmax ? 2 : 3) ? 3 : 2} : HalfShape{2, 8, 2, false, 2};
+        if (rt == 4) return kb <= 6 ? HalfShape{4, 4, kb <= 3 && !(far && kb == 1) ? 4 : 2, false, kb <= (far ? 2 : 3) ? 3 : 2} : HalfShape{2, 8, 2, false, 2};
         if (rt == 8 && kb == 1) return {8, 4, 4, false, 2};
     }
     return {};
@@ -387,6 +387,7 @@ struct Workspace {
     float* residual;                       // of points held in two parts, behind their rows (half2.h)
     float* shift;                          // per-point exponent shift of the max-shifted mode (separate points only)
     float* part_t;  float* part_d;
+    float* part_shift;                     // a shift a slot and point (max-shifted sums of the two-part format; a single slot's: `shift`)
     size_t bytes;
 };
 
@@ -424,6 +425,8 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
     if (p.sym_on) slots = (size_t)p.sym_ngroups + 2;     // pair_sym_kernel's, then the in-block pass
     w.part_t = score ? (float*)take(sizeof(float) * slots * p.m_pad * p.dp) : nullptr;
     w.part_d = (float*)take(sizeof(float) * slots * p.m_pad);
+    if (separate_points && format == kFormatHalf2 && (flags & SDKDE_FLAG_MAX_SHIFT))
+        w.part_shift = slots > 1 ? (float*)take(sizeof(float) * slots * p.m_pad) : w.shift;
     w.bytes = off;
     return w;
 }
@@ -545,10 +548,10 @@ int launch_thin(const Plan& p, const Workspace& w, const float* shift, hipStream
 
 // The fp32 mode at d >= 4 (score kinds d >= 7).  FAR: the max-shifted sums, whose points may lie beyond the fp16 range.
 template <int KIND, bool FAR, int KB, int TAIL, int RT>
-int launch_half_shape(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+int launch_half_shape(const Plan& p, const Workspace& w, hipStream_t st)
 {
     constexpr bool score = KIND == kScoreSelf || KIND == kScorePoints;
-    constexpr HalfShape sh = half_shape(KB, score, RT, KIND == kScoreSelf, FAR, KIND == kRowMax, TAIL);
+    constexpr HalfShape sh = half_shape(KB, score, RT, KIND == kScoreSelf, FAR, TAIL);
     if constexpr (sh.ni == 0) {
         return SDKDE_EUNSUPPORTED;
     } else {
@@ -556,36 +559,36 @@ int launch_half_shape(const Plan& p, const Workspace& w, const float* shift, hip
         hipLaunchKernelGGL((pair_half_kernel<KB, TAIL, sh.ni, sh.waves, sh.nb, sh.ahead, sh.minw, KIND, FAR>),
                            dim3((unsigned)(p.row_blocks * p.nsplit)), dim3(sh.waves * kWave), 0, st, w.ps, w.pn, w.xs, w.xt,
                            w.xn, w.part_t, w.part_d, p.ntiles, p.tiles_per_split, p.nsplit, p.m_pad,
-                           1.0f + 0.5f * (float)p.d, shift);
+                           1.0f + 0.5f * (float)p.d, w.part_shift);
         return launched();
     }
 }
 
 template <int KIND, bool FAR, int KB, int TAIL>
-int launch_half_tail(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+int launch_half_tail(const Plan& p, const Workspace& w, hipStream_t st)
 {
     switch (p.ni) {
-        case 8: return launch_half_shape<KIND, FAR, KB, TAIL, 8>(p, w, shift, st);
-        case 4: return launch_half_shape<KIND, FAR, KB, TAIL, 4>(p, w, shift, st);
-        case 2: return launch_half_shape<KIND, FAR, KB, TAIL, 2>(p, w, shift, st);
+        case 8: return launch_half_shape<KIND, FAR, KB, TAIL, 8>(p, w, st);
+        case 4: return launch_half_shape<KIND, FAR, KB, TAIL, 4>(p, w, st);
+        case 2: return launch_half_shape<KIND, FAR, KB, TAIL, 2>(p, w, st);
         default: return SDKDE_EUNSUPPORTED;
     }
 }
 
 template <int KIND, bool FAR>
-int launch_half(const Plan& p, const Workspace& w, const float* shift, hipStream_t st)
+int launch_half(const Plan& p, const Workspace& w, hipStream_t st)
 {
     const int tail = half_tail(p.d, KIND == kScoreSelf);
     const bool eight = tail == kTailEight, spare = tail == kTailSpare;
     switch (p.dp / 16) {
-        case 1: return eight ? launch_half_tail<KIND, FAR, 1, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 1, kTailSixteen>(p, w, shift, st);
-        case 2: return spare ? launch_half_tail<KIND, FAR, 2, KIND == kScoreSelf ? kTailNone : kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 2, kTailNone>(p, w, shift, st);
-        case 3: return eight ? launch_half_tail<KIND, FAR, 3, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 3, kTailSixteen>(p, w, shift, st);
-        case 4: return spare ? launch_half_tail<KIND, FAR, 4, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 4, kTailNone>(p, w, shift, st);
-        case 5: return eight ? launch_half_tail<KIND, FAR, 5, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 5, kTailSixteen>(p, w, shift, st);
-        case 6: return spare ? launch_half_tail<KIND, FAR, 6, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 6, kTailNone>(p, w, shift, st);
-        case 7: return eight ? launch_half_tail<KIND, FAR, 7, kTailEight>(p, w, shift, st) : launch_half_tail<KIND, FAR, 7, kTailSixteen>(p, w, shift, st);
-        case 8: return spare ? launch_half_tail<KIND, FAR, 8, kTailSpare>(p, w, shift, st) : launch_half_tail<KIND, FAR, 8, kTailNone>(p, w, shift, st);
+        case 1: return eight ? launch_half_tail<KIND, FAR, 1, kTailEight>(p, w, st) : launch_half_tail<KIND, FAR, 1, kTailSixteen>(p, w, st);
+        case 2: return spare ? launch_half_tail<KIND, FAR, 2, KIND == kScoreSelf ? kTailNone : kTailSpare>(p, w, st) : launch_half_tail<KIND, FAR, 2, kTailNone>(p, w, st);
+        case 3: return eight ? launch_half_tail<KIND, FAR, 3, kTailEight>(p, w, st) : launch_half_tail<KIND, FAR, 3, kTailSixteen>(p, w, st);
+        case 4: return spare ? launch_half_tail<KIND, FAR, 4, kTailSpare>(p, w, st) : launch_half_tail<KIND, FAR, 4, kTailNone>(p, w, st);
+        case 5: return eight ? launch_half_tail<KIND, FAR, 5, kTailEight>(p, w, st) : launch_half_tail<KIND, FAR, 5, kTailSixteen>(p, w, st);
+        case 6: return spare ? launch_half_tail<KIND, FAR, 6, kTailSpare>(p, w, st) : launch_half_tail<KIND, FAR, 6, kTailNone>(p, w, st);
+        case 7: return eight ? launch_half_tail<KIND, FAR, 7, kTailEight>(p, w, st) : launch_half_tail<KIND, FAR, 7, kTailSixteen>(p, w, st);
+        case 8: return spare ? launch_half_tail<KIND, FAR, 8, kTailSpare>(p, w, st) : launch_half_tail<KIND, FAR, 8, kTailNone>(p, w, st);
         default: return SDKDE_EUNSUPPORTED;
     }
 }
@@ -712,9 +715,9 @@ int launch_pair_prec(const Plan& p, const Workspace& w, uint32_t flags, const fl
     if (p.thin) return launch_thin<KIND>(p, w, shift, st);
     const uint32_t prec = effective_prec(flags, p.thin, p.dp);
     if (prec == SDKDE_PREC_FP32) {
-        if constexpr (KIND == kScoreSelf) return launch_half<KIND, false>(p, w, shift, st);
-        else if constexpr (KIND == kRowMax) return launch_half<KIND, true>(p, w, shift, st);
-        else return shift ? launch_half<KIND, true>(p, w, shift, st) : launch_half<KIND, false>(p, w, shift, st);
+        if constexpr (KIND == kScoreSelf) return launch_half<KIND, false>(p, w, st);
+        else if constexpr (KIND == kRowMax) return SDKDE_EUNSUPPORTED;      // (these kernels find the shifts as they go)
+        else return shift ? launch_half<KIND, true>(p, w, st) : launch_half<KIND, false>(p, w, st);
     }
     if constexpr (KIND == kScoreSelf || KIND == kScorePoints) {
         if (prec == SDKDE_PREC_FP16X2_ALL) return launch_mfma<KIND, SDKDE_PREC_FP16X2_ALL>(p, w, shift, st);
@@ -781,26 +784,37 @@ int launch_symmetric(const Plan& p, const Workspace& w, hipStream_t st)
 }
 
 // Launches an epilogue kernel (template parameter: threads per output) over `outputs` outputs of `nslots` slots.
-#define SDKDE_LAUNCH_EPILOGUE(KERNEL, nslots, outputs, st, ...)                                                    \
+#define SDKDE_LAUNCH_EPILOGUE_AS(nslots, outputs, st, MANY, FEW, ...)                                             \
     do {                                                                                                           \
         if (epilogue_parts(nslots, outputs) == kEpiPartsMany) {                                                    \
             constexpr int per_wg = kBlock / kEpiPartsMany;                                                         \
-            hipLaunchKernelGGL(KERNEL<kEpiPartsMany>, dim3((unsigned)(((outputs) + per_wg - 1) / per_wg)),         \
+            hipLaunchKernelGGL((MANY), dim3((unsigned)(((outputs) + per_wg - 1) / per_wg)),                        \
                                dim3(kBlock), 0, st, __VA_ARGS__);                                                  \
         } else {                                                                                                   \
             constexpr int per_wg = kBlock / kEpiPartsFew;                                                          \
-            hipLaunchKernelGGL(KERNEL<kEpiPartsFew>, dim3((unsigned)(((outputs) + per_wg - 1) / per_wg)),          \
+            hipLaunchKernelGGL((FEW), dim3((unsigned)(((outputs) + per_wg - 1) / per_wg)),                         \
                                dim3(kBlock), 0, st, __VA_ARGS__);                                                  \
         }                                                                                                          \
     } while (0)
+#define SDKDE_COMMA ,
+#define SDKDE_LAUNCH_EPILOGUE(KERNEL, nslots, outputs, st, ...) \
+    SDKDE_LAUNCH_EPILOGUE_AS(nslots, outputs, st, KERNEL<kEpiPartsMany>, KERNEL<kEpiPartsFew>, __VA_ARGS__)
+// As above for a kernel with a second parameter: whether slots have shifts of their own.
+#define SDKDE_LAUNCH_SHIFTED_EPILOGUE(KERNEL, shifted, nslots, outputs, st, ...)                                                              \
+    do {                                                                                                                                      \
+        if (shifted) SDKDE_LAUNCH_EPILOGUE_AS(nslots, outputs, st, KERNEL<kEpiPartsMany SDKDE_COMMA true>, KERNEL<kEpiPartsFew SDKDE_COMMA true>, __VA_ARGS__);   \
+        else SDKDE_LAUNCH_EPILOGUE_AS(nslots, outputs, st, KERNEL<kEpiPartsMany SDKDE_COMMA false>, KERNEL<kEpiPartsFew SDKDE_COMMA false>, __VA_ARGS__);         \
+    } while (0)
 
-// First pass of the max-shifted mode for separate points: row maxima of the exponent, then shift_kernel.
+// First pass of the max-shifted mode for separate points: row maxima of the exponent, then shift_kernel.  (The fp32 mode's matrix
+// path has none.)
 int launch_max_shift(const Plan& p, const Workspace& w, uint32_t flags, hipStream_t st)
 {
+    if (p.parts) return SDKDE_OK;
     int rc = launch_pair_prec<kRowMax>(p, w, flags, nullptr, st);
     if (rc != SDKDE_OK) return rc;
     SDKDE_LAUNCH_EPILOGUE(shift_kernel, p.nsplit, p.m_pad, st, w.part_d, p.nsplit, p.m_pad, w.shift,
-                          p.thin ? nullptr : w.pn, w.residual);
+                          p.thin ? nullptr : w.pn);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
@@ -1028,12 +1042,18 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
                                w.centre, a, fused->stamp, units);
             return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
         }
-        hipLaunchKernelGGL(score_epilogue_quad_kernel, dim3((unsigned)((quads + per_wg - 1) / per_wg)), dim3(kBlock), 0, st,
-                           w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
-                           samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units);
+        const dim3 grid((unsigned)((quads + per_wg - 1) / per_wg));
+        if (w.part_shift)
+            hipLaunchKernelGGL(score_epilogue_quad_kernel<true>, grid, dim3(kBlock), 0, st,
+                               w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
+                               samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units, w.part_shift);
+        else
+            hipLaunchKernelGGL(score_epilogue_quad_kernel<false>, grid, dim3(kBlock), 0, st,
+                               w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
+                               samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units, nullptr);
     } else {
-        SDKDE_LAUNCH_EPILOGUE(score_epilogue_kernel, nslots, total, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d,
-                              p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n), units);
+        SDKDE_LAUNCH_SHIFTED_EPILOGUE(score_epilogue_kernel, w.part_shift, nslots, total, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d,
+                                      p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n), units, w.part_shift);
     }
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
@@ -1123,8 +1143,8 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
     if (rc != SDKDE_OK) return rc;
     if ((rc = profile_mark(1, 1, st)) != SDKDE_OK) return rc;
 
-    SDKDE_LAUNCH_EPILOGUE(eval_epilogue_kernel, p.nsplit, m, st, w.part_d, p.nsplit, m, p.m_pad, lognorm, laplace ? 1 : 0,
-                          shift, w.residual, least_trusted_sum(n), density_out, log_density_out);
+    SDKDE_LAUNCH_SHIFTED_EPILOGUE(eval_epilogue_kernel, w.part_shift, p.nsplit, m, st, w.part_d, p.nsplit, m, p.m_pad, lognorm, laplace ? 1 : 0,
+                                  w.part_shift ? w.part_shift : shift, w.residual, least_trusted_sum(n), density_out, log_density_out);
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
