@@ -26,7 +26,7 @@ PAPER_SECONDS = {("C5", 1048576, 131072): 2.3,        # abstract / conclusion
                  ("C2", 32768, 4096): 2.11e-3}        # runtime table of the Results section (--config C2 --m 4096)
 MODE_FLAGS = {"fp32": 0, "fp16x2": 1, "fp16x2_all": 2, "fp16x2_phi16": 3, "symmetric": 32}
 MODE_NOTES = {
-    "fp16x2": "cross-term inputs split into fp16 hi+lo on the fp16 matrix units, fp32 accumulate; Phi X fp32",
+    "fp16x2": "inputs split into fp16 hi+lo on the fp16 matrix units, fp32 accumulate: served by the fp32 mode's kernels",
     "fp16x2_all": "both contractions on the fp16 matrix units (inputs and Phi split into fp16 hi+lo), fp32 accumulate, "
                   "exp and row sums fp32",
     "fp16x2_phi16": "cross-term inputs as fp16 hi+lo, Phi X on the fp16 matrix units with every weight rounded to one fp16 value "
@@ -166,13 +166,14 @@ class Workload:
         flags = MODE_FLAGS[mode]
         plan_s, plan_e = P.sdkde_describe_plan(n, n, d, 0, flags), P.sdkde_describe_plan(n, m, d, 2, flags)
         # the fp32 mode's matrix path multiplies two fp16 parts per operand, its symmetric mode three bf16 parts
-        eff = {"fp32": "half2", "symmetric": "symmetric_bf16x3"}.get(mode, mode)
+        # (which serve the fp16x2 mode, too, and whatever runs as it)
+        eff = {"fp32": "half2", "fp16x2": "half2", "symmetric": "symmetric_bf16x3"}.get(mode, mode)
         if mode == "symmetric" and not plan_s["symmetric"]:
             eff = "half2"
         if mode == "fp16x2_all" and plan_s["xt_scale"] != 2:
-            eff = "fp16x2"
+            eff = "half2"
         if mode == "fp16x2_phi16" and plan_s["dp"] != 16:
-            eff = "fp16x2"
+            eff = "half2"
         out = {}
         for key, stage, ms, plan, pairs in (("roofline", "score", score_ms, plan_s, float(n) * n),
                                             ("roofline_eval_kernel", "eval", eval_ms, plan_e, float(m) * n)):

@@ -90,7 +90,10 @@ enum {
                                multiplied on the fp16 matrix units with fp32 accumulate; Phi X, exp and all
                                sums stay fp32.  A lower-precision-input mode: its error is reported
                                separately.  Ignored on the thin path (fp32 VALU: d <= 3, the score calls
-                               d <= 6). */
+                               d <= 6).  Where the workspace holds the fp32 mode's operands (one that is as large as
+                               sdkde_workspace_bytes says does) calls in this mode, and those that run as it, are
+                               served by the fp32 mode's kernels, which are faster and no less accurate; so are, with
+                               up to 3072 samples, calls in the two modes below. */
     SDKDE_PREC_FP16X2_ALL = 2, /* as FP16X2, and Phi X on the fp16 matrix units too: Phi is split in registers
                                into fp16 hi + lo (scaled by 2^14 to stay normal), X into hi + lo in the
                                prepared copy; fp32 accumulate, exp and the row sums D stay fp32.  The split

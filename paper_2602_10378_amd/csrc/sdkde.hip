@@ -431,6 +431,33 @@ Workspace layout(const Plan& p, bool score, bool separate_points, void* base, ui
     return w;
 }
 
+// Most samples of a call whose rows are summed whole, and most of them times 16-column blocks (whole_row_tiles).
+constexpr int64_t kWholeSamples = 3072, kWholeBlocks = 6144;
+
+// Calls that would run on the FP16X2 kernels, whose Phi X is on the fp32 matrix units, are served by the fp32 mode's on two fp16
+// parts, where the buffer holds their operands (6 bytes a value instead of 4) with the fewest splits, whatever the number of points,
+// so that calls on one buffer agree on it.  So are calls in the other fp16 modes on few samples, for which the fp32 mode
+// has fewer launches.  These are the flags they then run with, their own mode kept in bits above the caller's (it is part of the record of
+// prepared samples).  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128
+// 1364 / 851; eval d = 16 29.1 / 28.0, 64 90 / 48; 600 x 100, d = 16 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against
+// 64-bit sums 0.36 to 1.0 of theirs.
+constexpr int kAskedModeShift = 16;
+uint32_t two_part_flags(uint32_t flags, int64_t n, int d, bool score, bool self, size_t workspace_bytes)
+{
+    const int dp = (int)round_up(d, 16);
+    if ((flags & 15u) == SDKDE_PREC_FP32 || d <= (score ? kThinMaxDScore : kThinMaxDEval) || (n > kWholeSamples && effective_prec(flags, false, dp) != SDKDE_PREC_FP16X2))
+        return flags;
+    const uint32_t as_fp32 = (flags & ~(15u | SDKDE_FLAG_SYMMETRIC)) | (flags & 15u) << kAskedModeShift;
+    Plan least{};
+    least.parts = true;
+    least.d = d;
+    least.dp = dp;
+    least.n_pad = round_up(n, kRowPad);
+    least.m_pad = self ? least.n_pad : kRowPad;
+    least.nsplit = 1;
+    return layout(least, score, !self, nullptr, as_fp32).bytes <= workspace_bytes ? as_fp32 : flags;
+}
+
 bool bad_bandwidth(double h) { return !(h > 0.0) || !isfinite(h); }
 
 // One group of splits per XCD, or a single split for tiny sample sets and on the matrix path: there a buffer may have been
@@ -604,7 +631,7 @@ int whole_row_tiles(const Plan& p, int64_t n, int64_t rows, bool score, bool shi
     if (!p.parts || p.sym_on || shifted) return 0;
     if (tuning(score ? SDKDE_TUNE_SCORE_ROW_TILES : SDKDE_TUNE_EVAL_ROW_TILES, 0) || tuning(score ? SDKDE_TUNE_SCORE_SPLITS : SDKDE_TUNE_EVAL_SPLITS, 0)) return 0;
     const int kb = p.dp / 16;
-    if (n > 3072 || n * kb > 6144) return 0;
+    if (n > kWholeSamples || n * kb > kWholeBlocks) return 0;
     return rows <= kComputeUnits * kTile ? 1 : kb == 1 && rows <= 4 * kComputeUnits * kTile ? 2 : 0;
 }
 
@@ -823,14 +850,14 @@ int launch_max_shift(const Plan& p, const Workspace& w, uint32_t flags, hipStrea
 // earlier launch on this workspace left it.
 // What identifies prepared samples: the kind of call that prepared them (the score and eval layouts differ), the
 // caller's array, its shape, the operand format and the coordinate scale as it reached the kernels.
-Stamp make_stamp(const Workspace& w, bool check, bool score, const float* samples, int64_t n, int d, int format, float a)
+Stamp make_stamp(const Workspace& w, bool check, bool score, const float* samples, int64_t n, int d, int format, float a, uint32_t flags)
 {
     Stamp s{};
     s.where = w.stamp;
     s.check = check ? 1 : 0;
     uint32_t abits;
     memcpy(&abits, &a, sizeof abits);
-    const uint64_t v[kStampWords] = {score ? 1u : 2u, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, (uint64_t)format, abits};
+    const uint64_t v[kStampWords] = {(score ? 1u : 2u) | flags >> kAskedModeShift << 8, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, (uint64_t)format, abits};
     for (int k = 0; k < kStampWords; ++k) s.value[k] = v[k];
     return s;
 }
@@ -889,25 +916,25 @@ struct FusedPrep {
 // four-part one, and everything the fused launch writes for the eval pass must lie where the score pass no longer
 // reads: the prepared shifted samples over the prepared samples (a workgroup reads its rows before it overwrites
 // them), their norms and the prepared queries inside the blocked transpose, which only the pair kernel reads.
+// sflags, eflags: the two passes' own (anchored_flags, two_part_flags).
 bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, int64_t m, int32_t d, double h, void* workspace,
-                     size_t workspace_bytes, uint32_t flags, FusedPrep* out)
+                     size_t workspace_bytes, uint32_t sflags, uint32_t eflags, FusedPrep* out)
 {
-    if (m <= 0 || (flags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SYMMETRIC | SDKDE_FLAG_SAMPLES_PREPARED))) return false;
+    if (m <= 0 || (eflags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || (sflags & SDKDE_FLAG_SYMMETRIC)) return false;
     if (tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
-    const uint32_t sflags = anchored_flags(flags, true);
     Plan ps = make_plan(n, n, d, true, sflags);
     apply_symmetric(ps, n, sflags, true);
-    const Plan pe = make_plan(n, m, d, false, flags);
+    const Plan pe = make_plan(n, m, d, false, eflags);
     if (ps.thin || pe.thin || ps.sym_on || ps.n_pad != pe.n_pad || ps.dp != pe.dp) return false;
     // One workgroup of the folded launch reduces 32 rows x dp/4 items in dp/8 passes, where the plain epilogue spreads
     // them over dp/8 workgroups: measured per pass of the whole call (folded / separate, same box), d = 16: n = 2048
     // 28.4 / 29.9 us, 4096 33.7 / 35.7, 8192 66.2 / 67.5, 32768 x 4096 662.3 / 665.0; d = 32: 4096 50.0 / 49.1;
     // d = 64: 4096 81.8 / 77.0; d = 128: 145.0 / 131.2.  It pays at dp = 16 only.
     if (ps.dp != 16) return false;
-    const int format = operand_format(pe, flags);
+    const int format = operand_format(pe, eflags);
     if (operand_format(ps, sflags) != format) return false;
     const Workspace ws = layout(ps, true, false, workspace, sflags);
-    const Workspace we = layout(pe, false, true, workspace, flags);
+    const Workspace we = layout(pe, false, true, workspace, eflags);
     if (ws.bytes > workspace_bytes || we.bytes > workspace_bytes) return false;
     if (epilogue_parts(ps.nsplit, n * (int64_t)d) != kEpiPartsFew) return false;
     if (ps.n_pad % kPrepRows || pe.m_pad % kPrepRows || (ps.n_pad + pe.m_pad) / kPrepRows > 0x7fffffffLL) return false;
@@ -920,14 +947,13 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     const double a = operand_scale(format, h);
     out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false, half_tail(d, false)};
     out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false, half_tail(d, false)};
-    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a);
+    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)a, eflags);
     return true;
 }
 
 // Whether the score at the samples is one of pair_whole_kernel's, with the epilogue in it.
 bool whole_score(int64_t n, int32_t d, uint32_t flags)
 {
-    flags = anchored_flags(flags, true);
     Plan p = make_plan(n, n, d, true, flags);
     apply_symmetric(p, n, flags, true);
     return whole_row_tiles(p, n, n, true, false) != 0;
@@ -937,31 +963,30 @@ bool whole_score(int64_t n, int32_t d, uint32_t flags)
 // the samples, the shifted samples by the workgroups that form them.  The eval pass's operands stand where a call of its own has
 // them (a later one may rely on the record, SDKDE_FLAG_SAMPLES_PREPARED), the score pass's behind them.
 bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, int64_t m, int32_t d, double h, void* workspace,
-                    size_t workspace_bytes, uint32_t flags, FusedPrep* out)
+                    size_t workspace_bytes, uint32_t sflags, uint32_t eflags, FusedPrep* out)
 {
-    if (m <= 0 || (flags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
-    const uint32_t sflags = anchored_flags(flags, true);
+    if (m <= 0 || (eflags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
     Plan& ps = out->score_plan = make_plan(n, n, d, true, sflags);
     apply_symmetric(ps, n, sflags, true);
     if (!whole_row_tiles(ps, n, n, true, false)) return false;
-    Plan& pe = out->eval_plan = make_plan(n, m, d, false, flags);
+    Plan& pe = out->eval_plan = make_plan(n, m, d, false, eflags);
     if (!whole_row_tiles(pe, n, m, false, false) || ps.n_pad != pe.n_pad) return false;
     // accepted or refused as the passes one by one are
     Workspace unused;
     Plan score_plan = ps, eval_plan = pe;
     if (!fit_workspace(score_plan, true, false, workspace, workspace_bytes, sflags, &unused) ||
-        fit_points(eval_plan, false, workspace, workspace_bytes, flags, m, &unused) != m)
+        fit_points(eval_plan, false, workspace, workspace_bytes, eflags, m, &unused) != m)
         return false;
-    const Workspace& we = out->eval_at = whole_layout(pe, false, true, workspace, flags);
+    const Workspace& we = out->eval_at = whole_layout(pe, false, true, workspace, eflags);
     Workspace& ws = out->score_at = whole_layout(ps, true, false, (char*)workspace + we.bytes, sflags);
     if (we.bytes + ws.bytes > workspace_bytes) return false;
     ws.centre = we.centre;
     ws.stamp = we.stamp;
     out->whole = true;
-    const int format = operand_format(pe, flags);
+    const int format = operand_format(pe, eflags);
     out->sd_job = PrepJob{samples_sd, n, pe.n_pad, we.xs, nullptr, we.xn, kPadCoord, true, false, half_tail(d, false)};
     out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false, half_tail(d, false)};
-    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)operand_scale(format, h));
+    out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)operand_scale(format, h), eflags);
     return true;
 }
 
@@ -983,7 +1008,7 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     // (a one-call pass of small sample sets prepares the eval pass's queries here)
     const PrepJob point_job = fused && whole_rows ? fused->q_job
                                                   : PrepJob{points, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
-    const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a);
+    const Stamp stamp = make_stamp(w, samples_ready, true, samples, n, d, format, (float)a, flags);
     rc = samples_ready ? launch_prep(p, point_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
                        : launch_prep(p, sample_job, point_job, samples, n, a, w, flags, stamp, st);
     if (rc != SDKDE_OK) return rc;
@@ -1073,7 +1098,7 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if (samples_sd_out && !self) return SDKDE_EINVAL;
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
     if (flags & SDKDE_FLAG_SAMPLES_PREPARED) return SDKDE_EUNSUPPORTED;      // sdkde_eval / sdkde_eval_laplace only
-    flags = anchored_flags(flags, self);
+    flags = two_part_flags(anchored_flags(flags, self), n, d, true, self, workspace_bytes);
     if (fused && fused->whole)
         return score_pass(fused->score_plan, fused->score_at, samples, n, nullptr, m, false, h, score_out, samples_sd_out, flags, (hipStream_t)stream,
                           fused, whole_row_tiles(fused->score_plan, n, m, true, false));
@@ -1117,7 +1142,7 @@ int eval_pass(const Plan& p, const Workspace& w, const float* samples, int64_t n
     const PrepJob query_job{queries, m, p.m_pad, w.ps, nullptr, w.pn, 0.0f, false, shifted, half_tail(d, false)};
     // all_prepared (sdkde_fit_eval): the score epilogue has prepared samples and queries for this plan (plan_fused_prep)
     if (!all_prepared) {
-        const Stamp stamp = make_stamp(w, samples_ready, false, samples, n, d, format, (float)a);
+        const Stamp stamp = make_stamp(w, samples_ready, false, samples, n, d, format, (float)a, flags);
         // reuse_centre: w.centre still holds the centre of an earlier pass over (nearly) the same points
         rc = samples_ready ? launch_prep(p, query_job, PrepJob{}, nullptr, 0, a, w, flags, stamp, st)
                            : launch_prep(p, sample_job, query_job, reuse_centre ? nullptr : samples, n, a, w, flags, stamp, st);
@@ -1159,6 +1184,7 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     if (!queries || (!density_out && !log_density_out)) return SDKDE_EINVAL;
     if (!workspace || ((uintptr_t)workspace & 255)) return SDKDE_EWORKSPACE;
 
+    flags = two_part_flags(flags, n, d, false, false, workspace_bytes);
     const bool all_prepared = fused != nullptr;
     if (fused && fused->whole)
         return eval_pass(fused->eval_plan, fused->eval_at, samples, n, queries, m, false, h, density_out, log_density_out, flags, (hipStream_t)stream,
@@ -1254,8 +1280,10 @@ int sdkde_fit_eval(const float* samples, int64_t n, const float* queries, int64_
     // centre is exact, it only has to be near the data).  Where the layouts allow it the score epilogue also
     // prepares the eval pass's operands: five launches instead of six, three for small sample sets.
     FusedPrep fused{};
-    const bool fuse = plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused) ||
-                      (!whole_score(n, d, flags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused));
+    const uint32_t sflags = two_part_flags(anchored_flags(flags, true), n, d, true, true, workspace_bytes);
+    const uint32_t eflags = two_part_flags(flags, n, d, false, false, workspace_bytes);
+    const bool fuse = plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused) ||
+                      (!whole_score(n, d, sflags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused));
     rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr);
     if (rc != SDKDE_OK || m == 0) return rc;
     return eval_impl(samples_sd_out, n, queries, m, d, h, density_out, log_density_out, workspace, workspace_bytes,
@@ -1349,7 +1377,7 @@ int sdkde_describe_plan(int64_t n, int64_t m, int32_t d, int32_t call, uint32_t 
         size_t need = 0;
         FusedPrep unused;
         if (call == 2 && sdkde_workspace_bytes(n, m, d, flags, &need) == SDKDE_OK)
-            out[25] = plan_fused_prep(nullptr, n, nullptr, m, d, 1.0, base, need, flags, &unused) ? 1 : 0;
+            out[25] = plan_fused_prep(nullptr, n, nullptr, m, d, 1.0, base, need, anchored_flags(flags, true), flags, &unused) ? 1 : 0;
     }
     return SDKDE_OK;
 }

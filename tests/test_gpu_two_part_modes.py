@@ -1,0 +1,67 @@
+"""The fp16x2 mode and the calls that run as it are served by the fp32 mode's kernels where the buffer holds their operands, whatever the
+number of points, and by their own where it does not."""
+import numpy as np
+import pytest
+
+import sdkde_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _calls(P, xd, qd, h, flags, ws):
+    import torch
+    s = torch.empty_like(xd)
+    x_sd, _, logd = P.sdkde_fit_eval(xd, qd, h, score_out=s, want="log", workspace=ws, flags=flags)
+    return [s, x_sd, logd, P.sdkde_score(xd, h, workspace=ws, flags=flags), P.sdkde_score(xd, h, points=qd, workspace=ws, flags=flags),
+            P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=flags)[1], P.sdkde_eval_laplace(xd, qd, h, workspace=ws, flags=flags)]
+
+
+@pytest.mark.parametrize("n,m,d,flags", [(5000, 700, 16, 1), (3072, 100, 16, 2), (1500, 4100, 9, 3), (4000, 900, 33, 2), (3500, 65, 128, 3),
+                                         (5000, 700, 24, 17), (600, 50, 7, 18), (200, 30, 16, 33)])
+def test_calls_on_the_fp32_kernels_have_their_bits(n, m, d, flags):
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h) * (1.5 if d > 64 else 1.0)
+    print(f"calls on the fp32 kernels n={n} m={m} d={d} flags={flags}", flush=True)
+    own = torch.empty(P.sdkde_workspace_bytes(n, m, d, flags), dtype=torch.uint8, device="cuda")
+    for ws in (P.make_workspace(n, m, d), own):
+        for got, want in zip(_calls(P, xd, qd, h, flags, ws), _calls(P, xd, qd, h, flags & 16, ws)):
+            # (a buffer of the mode's own size may hold fewer slots than the fp32 mode's plan has)
+            assert torch.equal(got, want) or (ws is own and float((got - want).norm() / want.norm()) < 1e-5)
+    # prepared samples are those of the mode that was asked for
+    ws = P.make_workspace(n, m, d)
+    want = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=flags)[1]
+    few = qd[:5].contiguous()
+    prepared = P.SDKDE_FLAG_SAMPLES_PREPARED
+    assert torch.equal(P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=flags | prepared)[1], want)
+    assert not bool(torch.isnan(P.sdkde_eval(xd, few, h, want="log", workspace=ws, flags=flags | prepared)[1]).any())
+    assert bool(torch.isnan(P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=(flags & 16) | prepared)[1]).all())
+
+
+@pytest.mark.parametrize("n,m,d", [(4000, 200, 24), (700, 900, 16), (5000, 64, 100)])
+def test_buffers_without_room_for_the_fp32_operands(tuning, n, m, d):
+    """What the mode's own kernels need with one split, and no more: served by them, score and density close to the fp32 mode's."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=n)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h) * (1.5 if d > 64 else 1.0)
+    print(f"buffers without room n={n} m={m} d={d}", flush=True)
+    want_s, want_e = P.sdkde_score(xd, h), P.sdkde_eval(xd, qd, h, want="log")[1]
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, 1)
+    tuning(P.SDKDE_TUNE_EVAL_SPLITS, 1)
+    for call, run, want in ((0, lambda ws: P.sdkde_score(xd, h, workspace=ws, flags=1), want_s),
+                            (2, lambda ws: P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=1)[1], want_e)):
+        plan = P.sdkde_describe_plan(n, n if call == 0 else m, d, call, 1)
+        assert plan["splits"] == 1
+        got = run(torch.empty(plan["workspace_bytes"], dtype=torch.uint8, device="cuda"))
+        # two roundings of 2^-22 a product against two of 2^-23 a coordinate: some 1e-6 of a score, of an exponent 2^-22 of the norms
+        assert float((got - want).norm() / want.norm()) < 1e-5
+        with pytest.raises(P.SdkdeError):
+            run(torch.empty(plan["workspace_bytes"] - 256, dtype=torch.uint8, device="cuda"))
+    ws = torch.empty(P.sdkde_describe_plan(n, m, d, 2, 1)["workspace_bytes"], dtype=torch.uint8, device="cuda")
+    first = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=1)[1]
+    few = P.sdkde_eval(xd, qd[:3].contiguous(), h, want="log", workspace=ws, flags=1 | P.SDKDE_FLAG_SAMPLES_PREPARED)[1]
+    assert float((few - first[:3]).abs().max()) < 1e-4
