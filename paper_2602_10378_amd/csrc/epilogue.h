@@ -216,19 +216,20 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_kernel(
 // coordinates of one row, so the partial T is read with 16-byte loads (1 KiB per wave and slot instead of 256
 // bytes) by a quarter of the workgroups.  Same summation order, hence the same bits.  quad_io: the outputs (and x)
 // may be accessed 16 bytes at a time.
-// Grid: one workgroup per kBlock / kEpiPartsFew (row, four columns) pairs of the [m, dp] partials.
-template <bool SHIFTED>
+// Grid: one workgroup per kBlock / kEpiPartsFew (row, four columns) pairs of the [m, d] outputs.
+template <bool SHIFTED, bool HALF2>
 __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* __restrict__ ps,
-    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int format, float inv_ah2,
+    int nsplit, int64_t m, int64_t m_pad, int d, int dp, int mode, int any_format, float inv_ah2,
     float* __restrict__ score, const float* __restrict__ x, float half_h2, float* __restrict__ x_sd, int quad_io,
     float min_sum, ScoreUnits units, const float* __restrict__ part_shift)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
+    const int format = HALF2 ? kFormatHalf2 : any_format;       // (built apart: the formats' code together takes registers and time)
     __shared__ f32x4 red_t[PARTS][LANES];
     __shared__ float red_d[PARTS][LANES];
     const int lane = threadIdx.x % LANES, part = threadIdx.x / LANES;
-    const int quads = dp / 4;
+    const int quads = (d + 3) / 4;
     const int64_t q = (int64_t)blockIdx.x * LANES + lane;
     const bool active = q < m * quads;
     const int64_t i = active ? q / quads : 0;
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     red_t[part][lane] = tacc;
     red_d[part][lane] = dacc;
     __syncthreads();
-    if (!active || part != 0 || c0 >= d) return;
+    if (!active || part != 0) return;
     f32x4 tsum = red_t[0][lane];
     float dsum = red_d[0][lane];
 #pragma unroll

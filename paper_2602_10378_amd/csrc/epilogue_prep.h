@@ -15,13 +15,15 @@ namespace {
 // overwrites them and no other workgroup touches them.
 // x_sd is sd_job.src, which prep_rows reads again for samples beyond the fp16 range.
 // Workgroups [blocks_sd, ...): the queries, as prep_mfma_kernel prepares them (centre read from the workspace).
+template <bool HALF2>
 __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const float* __restrict__ part_t, const float* __restrict__ part_d, const float* ps, int nsplit, int64_t m,
-    int64_t m_pad, int d, int dp, int format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
+    int64_t m_pad, int d, int dp, int any_format, float inv_ah2, float* __restrict__ score, const float* __restrict__ x,
     float half_h2, float* x_sd, int quad_io, PrepJob sd_job, PrepJob q_job, int blocks_sd,
     const float* centre, double a, Stamp stamp, ScoreUnits units)
 {
     constexpr int PARTS = kEpiPartsFew, LANES = kBlock / PARTS;
+    const int format = HALF2 ? kFormatHalf2 : any_format;       // (built apart, as prep_mfma_kernel)
     __shared__ float smean[SDKDE_MAX_D];
     extern __shared__ float prep_lds[];                     // prep_lds_bytes
     float* const raw = prep_lds;
@@ -35,7 +37,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     const bool of_queries = (int)blockIdx.x >= blocks_sd;
     const PrepJob job = of_queries ? q_job : sd_job;
     const int64_t r0 = (int64_t)(blockIdx.x - (of_queries ? blocks_sd : 0)) * kPrepRows;
-    StagedRows staged;
+    StagedRows<32> staged;                                  // (of dp = 16)
     if (of_queries) staged.load(job, r0, d);
     stamp_check(stamp, &stamp_flag);
     if (of_queries) {
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             const int item = first + lane;
             const int64_t i = r0 + item / quads;
             const int c0 = (item % quads) * 4;
-            const bool active = i < m;
+            const bool active = i < m && c0 < d;
             f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f}, xv = tacc;
             float dacc = 0.0f;
             PreparedQuad prepared = {};
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             red_d[part][lane] = dacc;
             f32x4 shifted = {0.0f, 0.0f, 0.0f, 0.0f};               // and of padding
             __syncthreads();
-            if (active && part == 0 && c0 < d) {
+            if (active && part == 0) {
                 f32x4 tsum = red_t[0][lane];
                 float dsum = red_d[0][lane];
 #pragma unroll
@@ -105,7 +107,9 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
     if ((int)threadIdx.x < d) smean[threadIdx.x] = of_centre;
     __syncthreads();
     const bool poisoned = stamp_flag != 0;
-    prep_rows(job, r0, d, dp, a, format, poisoned, smean, nullptr, false, raw, used, far_rows);       // (neither job has a dst_t)
+    // (neither job has a dst_t)
+    if constexpr (HALF2) prep_rows_half2<kPrepRows, kBlock>(job, r0, d, dp, a, poisoned, smean, nullptr, false, reinterpret_cast<uint32_t*>(raw), far_rows);
+    else prep_rows(job, r0, d, dp, a, format, poisoned, smean, raw, used);
 }
 
 }  // namespace

@@ -432,7 +432,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 f16x8 w[NB][2];
 #pragma unroll
                 for (int t = 0; t < NB; ++t) {
-                    dacc[t0 + t] = fmaf(dt[t], (FAR ? 1.0f : unit[t0 + t]) * (1.0f / kWeightScale), dacc[t0 + t]);
+                    dacc[t0 + t] = FAR ? dacc[t0 + t] + dt[t] : fmaf(dt[t], unit[t0 + t], dacc[t0 + t]);      // kWeightScale times D
                     // keeps the sum here: the compiler would otherwise sink it behind the MFMAs and hold the Phi tiles live
                     asm volatile("" : "+v"(dacc[t0 + t]));
                     split_weights(phi[t][0], phi[t][1], w[t][0], w[t][1]);
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             }
         }
         // D needs the sum over the four lane groups g
-        float dtot = dsum[t] + dacc[t];
+        float dtot = (dsum[t] + dacc[t]) * (SCORE ? 1.0f / kWeightScale : 1.0f);
         if (FAR) dtot *= by;
 #pragma unroll
         for (int step = 16; step <= 32; step *= 2) dtot += __shfl_xor(dtot, step);

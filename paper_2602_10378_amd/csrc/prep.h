@@ -82,9 +82,12 @@ __device__ __forceinline__ void block_centre(const PrepCommon& pc, int d, float 
     float apart = 0.0f;
     if (rr < rows_per_iter) {
         float before = UNITS ? pc.centre_src[c] : 0.0f;
+        const float* at = pc.centre_src + rr * pc.stride * d + c;
+        const int64_t step = rows_per_iter * pc.stride * d;
 #pragma unroll 16
         for (int k = rr; k < rows; k += rows_per_iter) {
-            const float x = pc.centre_src[k * pc.stride * d + c];
+            const float x = *at;
+            at += step;
             acc += (double)x;
             if (UNITS) apart += fabsf(x - before);
             before = x;
@@ -200,15 +203,17 @@ constexpr int kPrepRows = 32;      // rows per workgroup of prep_mfma_kernel (tw
 // The input values of rows r0 .. r0 + kPrepRows of a job, on their way to words[][] (rows of dp + 1 floats): columns
 // 16 k + 2 (threadIdx.x % 8) and the next of row threadIdx.x / 8 by each thread.  Loaded before the centre is known, so that the
 // two latencies of a small call's first launch are one.
+// COLUMNS: most there are.
+template <int COLUMNS>
 struct StagedRows {
-    float own[2 * SDKDE_MAX_D / 16];
+    float own[2 * COLUMNS / 16];
 
     __device__ __forceinline__ void load(const PrepJob& job, int64_t r0, int d)
     {
         const int64_t row = r0 + (threadIdx.x >> 3);
         const float* const in = job.src + row * d;
 #pragma unroll
-        for (int k = 0; k < SDKDE_MAX_D / 16; ++k) {
+        for (int k = 0; k < COLUMNS / 16; ++k) {
             if (16 * k >= d) break;
             const int c = 16 * k + 2 * (threadIdx.x & 7);
             own[2 * k] = row < job.rows && c < d ? in[c] : 0.0f;
@@ -219,7 +224,7 @@ struct StagedRows {
     {
         float* const at = words + (threadIdx.x >> 3) * (dp + 1) + 2 * (threadIdx.x & 7);
 #pragma unroll
-        for (int k = 0; k < SDKDE_MAX_D / 16; ++k) {
+        for (int k = 0; k < COLUMNS / 16; ++k) {
             if (16 * k >= d) break;
             at[16 * k] = own[2 * k];
             at[16 * k + 1] = own[2 * k + 1];
@@ -433,14 +438,11 @@ __device__ __forceinline__ void prep_rows_half2(const PrepJob& job, int64_t r0, 
 // followed by eight halves [lo(4g..4g+3) | the same again] (twice the bytes of the fp32 layout).
 // FP16X2_PHI16: dst_t holds, for tile, column c and lane group g, eight halves
 // [hi(4g..4g+3) | lo(4g..4g+3)].
-// The body for one workgroup: rows r0 .. r0 + kPrepRows of `job`, whose input values are already in raw[][].
+// The body for one workgroup and a format other than half2.h's: rows r0 .. r0 + kPrepRows of `job`, whose input values are already in
+// raw[][].
 __device__ __forceinline__ void prep_rows(const PrepJob& job, int64_t r0, int d, int dp, double a, int format, bool poisoned,
-                                          const float* smean, const float* sunit, bool other, float* raw_rows, float* used_rows, uint32_t* far_rows)
+                                          const float* smean, float* raw_rows, float* used_rows)
 {
-    if (format == kFormatHalf2) {
-        prep_rows_half2<kPrepRows, kBlock>(job, r0, d, dp, a, poisoned, smean, sunit, other, reinterpret_cast<uint32_t*>(raw_rows), far_rows);
-        return;
-    }
     // kPrepRows rows of dp + 1 floats each (odd stride: columns are read without bank conflicts)
     const int stride_f = dp + 1;
     auto raw = [&](int rr) { return raw_rows + rr * stride_f; };
@@ -545,7 +547,9 @@ inline size_t prep_lds_bytes(int dp, int format)
     return sizeof(float) * kPrepRows * (dp + 1) * (format == kFormatSplit3 || format == kFormatHalf2 ? 1 : 2);
 }
 
-// Grid: job0's blocks first (blocks0 of them), then job1's.
+// Grid: job0's blocks first (blocks0 of them), then job1's.  HALF2: the layout is half2.h's (built apart: the formats' code together takes
+// registers).
+template <bool HALF2, int COLUMNS>
 __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob job1, int blocks0, int d, int dp,
                                                            PrepCommon common, double a, int format, Stamp stamp)
 {
@@ -557,13 +561,14 @@ __global__ __launch_bounds__(kBlock) void prep_mfma_kernel(PrepJob job0, PrepJob
     const bool second = (int)blockIdx.x >= blocks0;
     const PrepJob job = second ? job1 : job0;
     const int64_t r0 = (int64_t)(blockIdx.x - (second ? blocks0 : 0)) * kPrepRows;
-    StagedRows staged;
+    StagedRows<COLUMNS> staged;
     staged.load(job, r0, d);
     if (threadIdx.x < 3) far_rows[threadIdx.x] = 0;
     stamp_check(stamp, &stamp_flag);
     prep_common<true>(common, d, a, red, smean, sunit, far_rows + 2, [&] { staged.store(prep_lds, d, dp); });
     const bool poisoned = stamp_flag != 0;
-    prep_rows(job, r0, d, dp, a, format, poisoned, smean, sunit, far_rows[2] != 0, prep_lds, prep_lds + kPrepRows * (dp + 1), far_rows);
+    if constexpr (HALF2) prep_rows_half2<kPrepRows, kBlock>(job, r0, d, dp, a, poisoned, smean, sunit, far_rows[2] != 0, reinterpret_cast<uint32_t*>(prep_lds), far_rows);
+    else prep_rows(job, r0, d, dp, a, format, poisoned, smean, prep_lds, prep_lds + kPrepRows * (dp + 1));
 }
 
 // Thin-d variant: dst[row][d] = a (x - mean), padding rows get pad_value in every coordinate.

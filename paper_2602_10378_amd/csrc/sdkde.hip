@@ -876,8 +876,11 @@ int launch_prep(const Plan& p, const PrepJob& first, const PrepJob& second, cons
     if (p.thin)
         hipLaunchKernelGGL(prep_thin_kernel, grid, block, 0, st, first, second, (int)blocks0, p.d, common, (float)a, stamp);
     else
-        hipLaunchKernelGGL(prep_mfma_kernel, grid, block, prep_lds_bytes(p.dp, operand_format(p, flags)), st, first, second, (int)blocks0, p.d, p.dp, common, a,
-                           operand_format(p, flags), stamp);
+    {
+        const int format = operand_format(p, flags);
+        const auto kernel = format != kFormatHalf2 ? prep_mfma_kernel<false, SDKDE_MAX_D> : p.dp <= 32 ? prep_mfma_kernel<true, 32> : prep_mfma_kernel<true, SDKDE_MAX_D>;
+        hipLaunchKernelGGL(kernel, grid, block, prep_lds_bytes(p.dp, format), st, first, second, (int)blocks0, p.d, p.dp, common, a, format, stamp);
+    }
     return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
 }
 
@@ -930,7 +933,7 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     // them over dp/8 workgroups: measured per pass of the whole call (folded / separate, same box), d = 16: n = 2048
     // 28.4 / 29.9 us, 4096 33.7 / 35.7, 8192 66.2 / 67.5, 32768 x 4096 662.3 / 665.0; d = 32: 4096 50.0 / 49.1;
     // d = 64: 4096 81.8 / 77.0; d = 128: 145.0 / 131.2.  It pays at dp = 16 only.
-    if (ps.dp != 16) return false;
+    if (ps.dp != 16) return false;              // (what the folded launch is built for, too)
     const int format = operand_format(pe, eflags);
     if (operand_format(ps, sflags) != format) return false;
     const Workspace ws = layout(ps, true, false, workspace, sflags);
@@ -1053,14 +1056,15 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
     const int nslots = p.sym_on ? p.sym_ngroups + 2 : p.nsplit;
     const int mode = p.thin ? 1 : (self ? 2 : 0);        // see score_epilogue_kernel
     if (!p.thin && epilogue_parts(nslots, total) == kEpiPartsFew) {
-        const int64_t quads = m * (p.dp / 4);
+        const int64_t quads = m * ((d + 3) / 4);
         constexpr int per_wg = kBlock / kEpiPartsFew;
         if (fused) {
             // plan_fused_prep has checked that this plan and layout are the ones it was made for
             if (!self || !samples_sd_out || p.sym_on || mode != 2) return SDKDE_EINVAL;
             const int blocks_sd = (int)(fused->sd_job.rows_pad / kPrepRows);
             const int blocks_q = (int)(fused->q_job.rows_pad / kPrepRows);
-            hipLaunchKernelGGL(score_epilogue_prep_kernel, dim3((unsigned)(blocks_sd + blocks_q)), dim3(kBlock),
+            const auto kernel = format == kFormatHalf2 ? score_epilogue_prep_kernel<true> : score_epilogue_prep_kernel<false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks_sd + blocks_q)), dim3(kBlock),
                                prep_lds_bytes(p.dp, format), st, w.part_t,
                                w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, format, inv_ah2, score_out, samples, half_h2,
                                samples_sd_out, quad_io, fused->sd_job, fused->q_job, blocks_sd,
@@ -1068,14 +1072,13 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
             return hipGetLastError() == hipSuccess ? SDKDE_OK : SDKDE_EDEVICE;
         }
         const dim3 grid((unsigned)((quads + per_wg - 1) / per_wg));
-        if (w.part_shift)
-            hipLaunchKernelGGL(score_epilogue_quad_kernel<true>, grid, dim3(kBlock), 0, st,
-                               w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
-                               samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units, w.part_shift);
-        else
-            hipLaunchKernelGGL(score_epilogue_quad_kernel<false>, grid, dim3(kBlock), 0, st,
-                               w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, mode, format, inv_ah2, score_out,
-                               samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units, nullptr);
+#define SDKDE_LAUNCH_QUAD(SHIFTED, HALF2)                                                                          \
+    hipLaunchKernelGGL((score_epilogue_quad_kernel<SHIFTED, HALF2>), grid, dim3(kBlock), 0, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d, p.dp, \
+                       mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, quad_io, least_trusted_sum(n), units, w.part_shift)
+        if (w.part_shift) SDKDE_LAUNCH_QUAD(true, true);
+        else if (format == kFormatHalf2) SDKDE_LAUNCH_QUAD(false, true);
+        else SDKDE_LAUNCH_QUAD(false, false);
+#undef SDKDE_LAUNCH_QUAD
     } else {
         SDKDE_LAUNCH_SHIFTED_EPILOGUE(score_epilogue_kernel, w.part_shift, nslots, total, st, w.part_t, w.part_d, w.ps, nslots, m, p.m_pad, d,
                                       p.dp, mode, format, inv_ah2, score_out, samples, half_h2, samples_sd_out, least_trusted_sum(n), units, w.part_shift);
