@@ -195,7 +195,10 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             tacc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (SUMLDS) sum_lds[wave][t * KT + mb][lane] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        if (LAPLACE) lc0[t] = laplace_c0;
+        if (LAPLACE) {
+            lc0[t] = laplace_c0;
+            asm("" : "+v"(lc0[t]));        // in a register a row tile: as one scalar for all the compiler schedules the loop 2 % worse
+        }
         if (SCORE) unit[t] = kWeightScale;
         if (FAR) less[t] = 0.0f;
     }
@@ -357,17 +360,19 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
                 if (LAPLACE) {
                     // c is the base-2 exponent -r^2/(2h^2) log2(e) (less the row's shift), so the Laplace factor
                     // 1 + d/2 - r^2/(2h^2) is lc0 + c ln 2 (Laplace-corrected KDE section)
-                    float& sum = FAR ? dt[t] : dacc[t0 + t];
                     if (FAR) dt[t] = 0.0f;
 #pragma unroll
-                    for (int v = 0; v < 8; ++v)
-                        sum = fmaf(phi[t][v / 4][v % 4], fmaf(c[t][v / 4][v % 4], kLn2, lc0[LAPLACE ? t0 + t : 0]), sum);
+                    for (int v = 0; v < 8; ++v) {
+                        const float factor = fmaf(c[t][v / 4][v % 4], kLn2, lc0[LAPLACE ? t0 + t : 0]);
+                        if constexpr (FAR) dt[t] = fmaf(phi[t][v / 4][v % 4], factor, dt[t]);
+                        else dacc[t0 + t] = fmaf(phi[t][v / 4][v % 4], factor, dacc[t0 + t]);
+                    }
                 } else {
                     dt[t] = ((phi[t][0].x + phi[t][0].y) + (phi[t][0].z + phi[t][0].w)) +
                             ((phi[t][1].x + phi[t][1].y) + (phi[t][1].z + phi[t][1].w));
                 }
             };
-            float all = 0.0f;
+            [[maybe_unused]] float all = 0.0f;
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 weigh(t);
