@@ -635,6 +635,35 @@ int whole_row_tiles(const Plan& p, int64_t n, int64_t rows, bool score, bool shi
     return rows <= kComputeUnits * kTile ? 1 : kb == 1 && rows <= 4 * kComputeUnits * kTile ? 2 : 0;
 }
 
+// Whether a score call of the thin path is thin_whole_kernel's.  Split slots / this at the ends of the range: 4000 samples, d = 1 20.4 / 9.5
+// us, d = 6 46.3 / 21.2; at 8000 points d = 1 22.8 / 9.5, d = 6 73.8 / 32.1; at 50 points d = 1 24.3 / 9.2, d = 6 75.3 / 20.1.  The time grows with
+// the pairs from there on, at sixteen threads a row with reads of their own, and the split slots' from about 8000 samples.
+bool thin_whole(const Plan& p, int64_t n, int64_t rows, bool shifted)
+{
+    if (!p.thin || shifted || tuning(SDKDE_TUNE_SCORE_ROW_TILES, 0) || tuning(SDKDE_TUNE_SCORE_SPLITS, 0)) return false;
+    return n <= 4096 && rows <= 8192;
+}
+
+int launch_thin_whole(const float* samples, int64_t n, const float* points, int64_t m, int d, double h, double a, float* score_out,
+                      float* samples_sd_out, const Stamp& stamp, hipStream_t st)
+{
+    const dim3 grid((unsigned)((m + kThinWholeRows - 1) / kThinWholeRows)), block(kBlock);
+#define SDKDE_LAUNCH_THIN_WHOLE(D_)                                                                                              \
+    hipLaunchKernelGGL(thin_whole_kernel<D_>, grid, block, 0, st, samples, (int)n, points, m, (float)a, (float)(1.0 / (a * h * h)), \
+                       least_trusted_sum(n), score_out, (float)(0.5 * h * h), samples_sd_out, stamp)
+    switch (d) {
+        case 1: SDKDE_LAUNCH_THIN_WHOLE(1); break;
+        case 2: SDKDE_LAUNCH_THIN_WHOLE(2); break;
+        case 3: SDKDE_LAUNCH_THIN_WHOLE(3); break;
+        case 4: SDKDE_LAUNCH_THIN_WHOLE(4); break;
+        case 5: SDKDE_LAUNCH_THIN_WHOLE(5); break;
+        case 6: SDKDE_LAUNCH_THIN_WHOLE(6); break;
+        default: return SDKDE_EUNSUPPORTED;
+    }
+#undef SDKDE_LAUNCH_THIN_WHOLE
+    return launched();
+}
+
 // Lays a call of such a kernel out: as layout() does, without partial slots.
 Workspace whole_layout(Plan p, bool score, bool separate_points, void* base, uint32_t flags)
 {
@@ -1090,7 +1119,7 @@ int score_pass(const Plan& p, const Workspace& w, const float* samples, int64_t 
 // the samples themselves): also writes samples + (h^2/2) score from the same epilogue.
 int score_impl(const float* samples, int64_t n, const float* points, int64_t m, int32_t d, double h,
                float* score_out, float* samples_sd_out, void* workspace, size_t workspace_bytes, uint32_t flags,
-               void* stream, const FusedPrep* fused = nullptr)
+               void* stream, const FusedPrep* fused = nullptr, bool* centre_left = nullptr)
 {
     int rc = check_common(samples, n, m, d, h, flags);
     if (rc != SDKDE_OK) return rc;
@@ -1113,7 +1142,22 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if (self ? !fit_workspace(p, true, false, workspace, workspace_bytes, flags, &w)
              : (batch = fit_points(p, true, workspace, workspace_bytes, flags, m, &w)) == 0)
         return SDKDE_EWORKSPACE;
-    int whole_rows = batch == m ? whole_row_tiles(p, n, m, true, !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0) : 0;
+    const bool shifted = !self && (flags & SDKDE_FLAG_MAX_SHIFT) != 0;
+    if (batch == m && thin_whole(p, n, m, shifted)) {
+        // (a workgroup writes while others read the caller's arrays: outputs over them go the other way)
+        const size_t in = sizeof(float) * d * n, at_points = sizeof(float) * d * m;
+        auto apart = [](const void* x, size_t nx, const void* y, size_t ny) { return !x || !y || (const char*)x + nx <= (const char*)y || (const char*)y + ny <= (const char*)x; };
+        if (apart(score_out, at_points, samples, in) && apart(samples_sd_out, at_points, samples, in) && apart(score_out, at_points, points, at_points) &&
+            apart(score_out, at_points, samples_sd_out, at_points)) {
+            const double a = operand_scale(operand_format(p, flags), h);
+            const Stamp stamp = make_stamp(w, false, true, samples, n, d, operand_format(p, flags), (float)a, flags);
+            if ((rc = profile_mark(0, 0, (hipStream_t)stream)) != SDKDE_OK) return rc;
+            rc = launch_thin_whole(samples, n, self ? samples : points, m, d, h, a, score_out, samples_sd_out, stamp, (hipStream_t)stream);
+            if (centre_left) *centre_left = false;
+            return rc != SDKDE_OK ? rc : profile_mark(0, 1, (hipStream_t)stream);
+        }
+    }
+    int whole_rows = batch == m ? whole_row_tiles(p, n, m, true, shifted) : 0;
     if (whole_rows) {
         const Workspace all = whole_layout(p, true, !self, workspace, flags);
         if (all.bytes <= workspace_bytes) w = all;
@@ -1287,10 +1331,11 @@ int sdkde_fit_eval(const float* samples, int64_t n, const float* queries, int64_
     const uint32_t eflags = two_part_flags(flags, n, d, false, false, workspace_bytes);
     const bool fuse = plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused) ||
                       (!whole_score(n, d, sflags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused));
-    rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr);
+    bool centre_left = true;
+    rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr, &centre_left);
     if (rc != SDKDE_OK || m == 0) return rc;
     return eval_impl(samples_sd_out, n, queries, m, d, h, density_out, log_density_out, workspace, workspace_bytes,
-                     flags, stream, false, true, fuse ? &fused : nullptr);
+                     flags, stream, false, centre_left, fuse ? &fused : nullptr);
 }
 
 int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries, int64_t m, int32_t d, double h,
