@@ -251,7 +251,8 @@ int sdkde_eval_laplace(const float *samples, int64_t n, const float *queries, in
 
 /*
  * Introspection of the host-side plan (grid decomposition and workspace layout) that a call with these
- * sizes would use; touches no device.  call: 0 = sdkde_score at the samples, 1 = sdkde_score at m
+ * sizes would use (in the fp16 modes: on the mode's own kernels; scores and densities of few samples that a kernel
+ * sums whole need no partial slots, and are laid out without them); touches no device.  call: 0 = sdkde_score at the samples, 1 = sdkde_score at m
  * separate points, 2 = sdkde_eval / sdkde_eval_laplace at m queries.  out (host, at least 20 entries):
  *   [0] thin path (0/1)      [1] padded dimension   [2] row tiles per quarter of a workgroup (thin: rows per thread)
  *   [3] rows per workgroup   [4] row blocks         [5] splits of the sample axis
