@@ -210,7 +210,8 @@ int sdkde_eval(const float *samples_sd, int64_t n, const float *queries, int64_t
  *   samples [n, d] in      queries [m, d] in
  *   score_out [n, d] out, may be NULL      samples_sd_out [n, d] out, required
  *   density_out / log_density_out [m] out, either may be NULL, not both (unless m = 0)
- * Results equal those of the three separate calls up to the rounding of the centring.
+ * Results equal those of the three separate calls up to the rounding of the centring.  So they do where the queries are in the
+ * array that the shifted samples or the scores go to: the density is then that at what has been written there.
  */
 int sdkde_fit_eval(const float *samples, int64_t n, const float *queries, int64_t m, int32_t d,
                    double h, float *score_out, float *samples_sd_out, float *density_out,

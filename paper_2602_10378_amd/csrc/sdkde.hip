@@ -458,6 +458,12 @@ uint32_t two_part_flags(uint32_t flags, int64_t n, int d, bool score, bool self,
     return layout(least, score, !self, nullptr, as_fp32).bytes <= workspace_bytes ? as_fp32 : flags;
 }
 
+// Whether two of the caller's arrays share no byte (null: an array that is not there).
+bool apart(const void* x, size_t nx, const void* y, size_t ny)
+{
+    return !x || !y || (const char*)x + nx <= (const char*)y || (const char*)y + ny <= (const char*)x;
+}
+
 bool bad_bandwidth(double h) { return !(h > 0.0) || !isfinite(h); }
 
 // One group of splits per XCD, or a single split for tiny sample sets and on the matrix path: there a buffer may have been
@@ -1146,7 +1152,6 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     if (batch == m && thin_whole(p, n, m, shifted)) {
         // (a workgroup writes while others read the caller's arrays: outputs over them go the other way)
         const size_t in = sizeof(float) * d * n, at_points = sizeof(float) * d * m;
-        auto apart = [](const void* x, size_t nx, const void* y, size_t ny) { return !x || !y || (const char*)x + nx <= (const char*)y || (const char*)y + ny <= (const char*)x; };
         if (apart(score_out, at_points, samples, in) && apart(samples_sd_out, at_points, samples, in) && apart(score_out, at_points, points, at_points) &&
             apart(score_out, at_points, samples_sd_out, at_points)) {
             const double a = operand_scale(operand_format(p, flags), h);
@@ -1326,11 +1331,14 @@ int sdkde_fit_eval(const float* samples, int64_t n, const float* queries, int64_
     // The centre of the samples stays in the workspace; the shifted samples are centred on it too (any
     // centre is exact, it only has to be near the data).  Where the layouts allow it the score epilogue also
     // prepares the eval pass's operands: five launches instead of six, three for small sample sets.
+    // Neither where the queries are in an array that the score pass writes: those forms read them before it has.
     FusedPrep fused{};
+    const size_t in = sizeof(float) * d * n, at_queries = sizeof(float) * d * m;
+    const bool stable = apart(queries, at_queries, samples_sd_out, in) && apart(queries, at_queries, score_out, in);
     const uint32_t sflags = two_part_flags(anchored_flags(flags, true), n, d, true, true, workspace_bytes);
     const uint32_t eflags = two_part_flags(flags, n, d, false, false, workspace_bytes);
-    const bool fuse = plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused) ||
-                      (!whole_score(n, d, sflags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused));
+    const bool fuse = stable && (plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused) ||
+                                 (!whole_score(n, d, sflags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused)));
     bool centre_left = true;
     rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr, &centre_left);
     if (rc != SDKDE_OK || m == 0) return rc;

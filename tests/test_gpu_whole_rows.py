@@ -147,3 +147,24 @@ def test_whole_rows_leave_prepared_samples_and_fit_smaller_buffers(n, m, d):
     static = [torch.empty_like(t) for t in (xd, xd, logd)]
     P.sdkde_fit_eval_static(xd, qd, h, static[0], score_out=static[1], log_density_out=static[2])
     assert torch.equal(static[0], x_sd) and torch.equal(static[1], s) and torch.equal(static[2], logd)
+
+
+@pytest.mark.parametrize("n,d", [(600, 8), (700, 64), (1000, 24), (5000, 16), (4000, 24)])
+@pytest.mark.parametrize("which", ["shifted", "in place", "score"])
+def test_queries_that_the_same_call_writes_are_read_after_it_has(n, d, which):
+    """Queries in the array that the shifted samples or the scores go to: as in the three separate calls, the density is that at what
+    has been written there, also where the pass would prepare the queries before (small sets) or while (d <= 16) the score is formed."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, _, h = sdkde_inputs.gaussian_mixture(n, 1, d, components=3, seed=n)
+    (xd,), h = _gpu(x), float(h)
+    print(f"queries the call writes n={n} d={d} {which}", flush=True)
+    s, x_sd = torch.empty_like(xd), torch.empty_like(xd)
+    P.sdkde_fit_eval(xd, xd, h, score_out=s, samples_sd_out=x_sd, want="log")
+    want = P.sdkde_fit_eval(xd, (s if which == "score" else x_sd).clone(), h, want="log")[2]
+    out = xd.clone() if which == "in place" else torch.zeros_like(xd)
+    score = torch.zeros_like(xd)
+    got = P.sdkde_fit_eval(out if which == "in place" else xd, score if which == "score" else out, h, score_out=score, samples_sd_out=out, want="log")[2]
+    assert torch.equal(score, s) and torch.equal(out, x_sd)
+    assert torch.equal(got, want)
