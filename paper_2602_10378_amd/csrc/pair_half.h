@@ -537,7 +537,8 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
 #pragma unroll
                     for (int t = 0; t < NB; ++t) {
                         const float most = largest(c[t]);
-                        below |= __builtin_amdgcn_ballot_w64(most < kFarShift) != 0;
+                        // (a padding row is far from everything, and nothing for its neighbours in the wave to follow; its term is still its norm here)
+                        below |= __builtin_amdgcn_ballot_w64(most < kFarShift && rows.term[t0 + t] != kPadNorm) != 0;
                         set_shift(t0 + t, fmaxf(shift_for(most), kNegHuge));
                     }
                 }

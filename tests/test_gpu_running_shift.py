@@ -95,3 +95,26 @@ def test_a_query_without_a_value_leaves_its_neighbours_alone(d):
     _check(P, x, bad, 1.0, rows=good)
     flags = P.SDKDE_FLAG_MAX_SHIFT
     assert bool(P.sdkde_eval(*_gpu(x, bad), 1.0, want="log", flags=flags)[1][[5, 77]].isnan().all())
+
+
+@pytest.mark.parametrize("d", [8, 16, 24, 32, 64, 128])
+def test_queries_beside_padding_rows_are_as_they_are_beside_others(tuning, d):
+    """One distant sample, and queries near the others, whose weights do not differ enough for a shift to be raised (which all rows of
+    a wave would be): those that share a wave with padding rows have the bits they have beside other queries."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    rng = np.random.default_rng(d)
+    x, q = rng.standard_normal((1000, d)).astype(np.float32), rng.standard_normal((256, d)).astype(np.float32)
+    h = float(np.sqrt(d))
+    x[601, 0] = 5000.0 * h
+    (xd, qd), flags = _gpu(x, q), P.SDKDE_FLAG_MAX_SHIFT
+    for knob in (P.SDKDE_TUNE_SCORE_ROW_TILES, P.SDKDE_TUNE_EVAL_ROW_TILES):
+        tuning(knob, 2)
+    for knob in (P.SDKDE_TUNE_SCORE_SPLITS, P.SDKDE_TUNE_EVAL_SPLITS):
+        tuning(knob, 1)
+    print(f"beside padding rows d={d}", flush=True)
+    calls = (lambda p: P.sdkde_eval(xd, p, h, want="log", flags=flags)[1], lambda p: P.sdkde_eval_laplace(xd, p, h, flags=flags),
+             lambda p: P.sdkde_score(xd, h, points=p, flags=flags))
+    for call in calls:
+        assert torch.equal(call(qd[:200].contiguous()), call(qd)[:200])
