@@ -437,17 +437,17 @@ constexpr int64_t kWholeSamples = 3072, kWholeBlocks = 6144;
 // Calls that would run on the FP16X2 kernels, whose Phi X is on the fp32 matrix units, are served by the fp32 mode's on two fp16
 // parts, where the buffer holds their operands (6 bytes a value instead of 4) with the fewest splits, whatever the number of points,
 // so that calls on one buffer agree on it.  So are calls in the other fp16 modes on few samples, for which the fp32 mode
-// has fewer launches.  These are the flags they then run with, their own mode kept in bits above the caller's (it is part of the record of
-// prepared samples).  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128
+// has fewer launches.  These are the flags they then run with, the mode they would have run in kept in bits above the caller's (it is part
+// of the record of prepared samples).  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128
 // 1364 / 851; eval d = 16 29.1 / 28.0, 64 90 / 48; 600 x 100, d = 16 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against
 // 64-bit sums 0.36 to 1.0 of theirs.
-constexpr int kAskedModeShift = 16;
+constexpr int kOwnModeShift = 16;
 uint32_t two_part_flags(uint32_t flags, int64_t n, int d, bool score, bool self, size_t workspace_bytes)
 {
     const int dp = (int)round_up(d, 16);
     if ((flags & 15u) == SDKDE_PREC_FP32 || d <= (score ? kThinMaxDScore : kThinMaxDEval) || (n > kWholeSamples && effective_prec(flags, false, dp) != SDKDE_PREC_FP16X2))
         return flags;
-    const uint32_t as_fp32 = (flags & ~(15u | SDKDE_FLAG_SYMMETRIC)) | (flags & 15u) << kAskedModeShift;
+    const uint32_t as_fp32 = (flags & ~(15u | SDKDE_FLAG_SYMMETRIC)) | effective_prec(flags, false, dp) << kOwnModeShift;
     Plan least{};
     least.parts = true;
     least.d = d;
@@ -892,7 +892,7 @@ Stamp make_stamp(const Workspace& w, bool check, bool score, const float* sample
     s.check = check ? 1 : 0;
     uint32_t abits;
     memcpy(&abits, &a, sizeof abits);
-    const uint64_t v[kStampWords] = {(score ? 1u : 2u) | flags >> kAskedModeShift << 8, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, (uint64_t)format, abits};
+    const uint64_t v[kStampWords] = {(score ? 1u : 2u) | flags >> kOwnModeShift << 8, (uint64_t)(uintptr_t)samples, (uint64_t)n, (uint64_t)d, (uint64_t)format, abits};
     for (int k = 0; k < kStampWords; ++k) s.value[k] = v[k];
     return s;
 }

@@ -65,3 +65,18 @@ def test_buffers_without_room_for_the_fp32_operands(tuning, n, m, d):
     first = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=1)[1]
     few = P.sdkde_eval(xd, qd[:3].contiguous(), h, want="log", workspace=ws, flags=1 | P.SDKDE_FLAG_SAMPLES_PREPARED)[1]
     assert float((few - first[:3]).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("first,then,d", [(1, 2, 24), (3, 1, 64), (2, 3, 128), (2, 2, 16)])
+def test_samples_prepared_in_a_mode_serve_those_that_run_as_it(first, then, d):
+    """From 17 columns on all three fp16 modes are the first: samples that one has prepared are those of the others."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    n, m = 4000, 90
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h) * (1.5 if d > 64 else 1.0)
+    print(f"prepared in mode {first}, used in {then}, d={d}", flush=True)
+    ws = P.make_workspace(n, m, d)
+    want = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=first)[1]
+    assert torch.equal(P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=then | P.SDKDE_FLAG_SAMPLES_PREPARED)[1], want)
