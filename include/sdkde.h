@@ -87,13 +87,16 @@ enum {
                                the six largest of its nine: the rest is at most 2^-24 of it in the cross term, 1.5 2^-23
                                in Phi X. */
     SDKDE_PREC_FP16X2 = 1,  /* each input split into two fp16 halves (hi + lo, ~22 mantissa bits) and
-                               multiplied on the fp16 matrix units with fp32 accumulate; Phi X, exp and all
-                               sums stay fp32.  A lower-precision-input mode: its error is reported
+                               multiplied on the fp16 matrix units with fp32 accumulate; exp and all
+                               sums fp32.  A lower-precision-input mode: its error is reported
                                separately.  Ignored on the thin path (fp32 VALU: d <= 3, the score calls
                                d <= 6).  Where the workspace holds the fp32 mode's operands (one that is as large as
                                sdkde_workspace_bytes says does) calls in this mode, and those that run as it, are
-                               served by the fp32 mode's kernels, which are faster and no less accurate; so are, with
-                               up to 3072 samples, calls in the two modes below. */
+                               served by the fp32 mode's kernels, which are faster and no less accurate (error against
+                               64-bit sums at most that of the mode's own kernels at d = 4 .. 128), Phi X included: weights and
+                               samples in two fp16 parts each, as described above.  So are, with up to 3072 samples, calls in
+                               the two modes below.  The mode's own kernels, for smaller buffers, multiply the cross term in all
+                               four part products and form Phi X on the fp32 matrix units. */
     SDKDE_PREC_FP16X2_ALL = 2, /* as FP16X2, and Phi X on the fp16 matrix units too: Phi is split in registers
                                into fp16 hi + lo (scaled by 2^14 to stay normal), X into hi + lo in the
                                prepared copy; fp32 accumulate, exp and the row sums D stay fp32.  The split
@@ -148,8 +151,8 @@ enum {
 /*
  * Bytes of workspace sufficient for each of: sdkde_score at the n samples themselves,
  * sdkde_score at m separate points, and sdkde_eval at m queries, all with n samples of
- * dimension d, called with these flags.  One block of this size serves the whole score ->
- * debias -> eval pipeline.  The size depends on n, m, d and flags together (the grid
+ * dimension d, called with these flags (in the fp16 modes: with their own kernels and with those that serve them).  One block of this
+ * size serves the whole score -> debias -> eval pipeline.  The size depends on n, m, d and flags together (the grid
  * decomposition, and with it the number of partial-sum slots, is chosen per shape and
  * precision mode).  A call given less than its own size (a buffer made for another m, say)
  * falls back to fewer splits of the samples - the same results to rounding, in a different but
@@ -227,7 +230,7 @@ int sdkde_fit_eval(const float *samples, int64_t n, const float *queries, int64_
  * sdkde_fit_eval, and the results are bit-identical to those of sdkde_fit_eval with a workspace of
  * sdkde_workspace_bytes(n, m, d, flags) where that figure is at most SDKDE_STATIC_SCRATCH_BYTES.  A larger pass is
  * served (fp32 matrix path) while both of its steps fit with fewer splits, or the queries in batches (see
- * sdkde_workspace_bytes), and refused with SDKDE_ETOOLARGE, nothing launched, otherwise (the buffer serves e.g. n = m = 32768 at d = 16, n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
+ * sdkde_workspace_bytes; in the fp16 modes while it fits on their own kernels without), and refused with SDKDE_ETOOLARGE, nothing launched, otherwise (the buffer serves e.g. n = m = 32768 at d = 16, n = 65536, m = 8192 at d = 16, n = m = 16384 at d = 64).  The buffer keeps the last call's contents; nothing
  * in it has to start at zero, every call rewrites what it reads.  All calls on one GPU share the one buffer:
  * two calls that overlap in time on the same GPU (different streams or host threads) race; order them on
  * one stream.  The first call on a device looks up the buffer's device address (no stream work); make it

@@ -436,22 +436,29 @@ constexpr int64_t kWholeSamples = 3072, kWholeBlocks = 6144;
 
 // Calls that would run on the FP16X2 kernels, whose Phi X is on the fp32 matrix units, are served by the fp32 mode's on two fp16
 // parts, where the buffer holds their operands (6 bytes a value instead of 4) with the fewest splits, whatever the number of points,
-// so that calls on one buffer agree on it.  So are calls in the other fp16 modes on few samples, for which the fp32 mode
-// has fewer launches.  These are the flags they then run with, the mode they would have run in kept in bits above the caller's (it is part
-// of the record of prepared samples).  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128
-// 1364 / 851; eval d = 16 29.1 / 28.0, 64 90 / 48; 600 x 100, d = 16 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against
-// 64-bit sums 0.36 to 1.0 of theirs.
+// so that calls on one buffer agree on it; one of the size that sdkde_workspace_bytes gives holds them with all splits.  So are calls in the
+// other fp16 modes on few samples, for which the fp32 mode has fewer launches.  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8
+// 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128 1364 / 851; eval d = 16 29.1 / 28.0, 64 90 / 48; 600 x 100, d = 16
+// 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against 64-bit sums, 600 .. 9000 samples, d = 4 .. 128: at most 1.0 of
+// theirs, in the mean 0.69 on scores, 0.47 on densities.
+// two_part_form: the flags such a call then runs with, the mode it would have run in kept in bits above the caller's (it is part of the
+// record of prepared samples); those of other calls unchanged.  flags: of the kind of call (anchored_flags).
 constexpr int kOwnModeShift = 16;
-uint32_t two_part_flags(uint32_t flags, int64_t n, int d, bool score, bool self, size_t workspace_bytes)
+uint32_t two_part_form(uint32_t flags, int64_t n, int d, bool score)
 {
     const int dp = (int)round_up(d, 16);
     if ((flags & 15u) == SDKDE_PREC_FP32 || d <= (score ? kThinMaxDScore : kThinMaxDEval) || (n > kWholeSamples && effective_prec(flags, false, dp) != SDKDE_PREC_FP16X2))
         return flags;
-    const uint32_t as_fp32 = (flags & ~(15u | SDKDE_FLAG_SYMMETRIC)) | effective_prec(flags, false, dp) << kOwnModeShift;
+    return (flags & ~(15u | SDKDE_FLAG_SYMMETRIC)) | effective_prec(flags, false, dp) << kOwnModeShift;
+}
+uint32_t two_part_flags(uint32_t flags, int64_t n, int d, bool score, bool self, size_t workspace_bytes)
+{
+    const uint32_t as_fp32 = two_part_form(flags, n, d, score);
+    if (as_fp32 == flags) return flags;
     Plan least{};
     least.parts = true;
     least.d = d;
-    least.dp = dp;
+    least.dp = (int)round_up(d, 16);
     least.n_pad = round_up(n, kRowPad);
     least.m_pad = self ? least.n_pad : kRowPad;
     least.nsplit = 1;
@@ -520,6 +527,30 @@ int64_t fit_points(Plan& p, bool score, void* base, size_t bytes, uint32_t flags
     const int64_t batches = (all + most - 1) / most;
     fits((all + batches - 1) / batches);
     return p.m_pad;
+}
+
+// Bytes that hold the largest of: score at the samples themselves, score at m separate points, eval at m queries, each with its own
+// decomposition on the kernels of its mode; two_part: in the fp16 modes also on those that serve the call in their place.
+size_t calls_bytes(int64_t n, int64_t m, int d, uint32_t flags, bool two_part)
+{
+    size_t need = 0;
+    auto cover = [&](uint32_t of_call, bool score, bool self) {
+        Plan p = make_plan(n, self ? n : m, d, score, of_call);
+        if (self) apply_symmetric(p, n, of_call, true);
+        const size_t b = layout(p, score, !self, nullptr, of_call).bytes;
+        need = b > need ? b : need;
+    };
+    auto of_kind = [&](bool score, bool self) {
+        const uint32_t own = score ? anchored_flags(flags, self) : flags, instead = two_part_form(own, n, d, score);
+        cover(own, score, self);
+        if (two_part && instead != own) cover(instead, score, self);
+    };
+    of_kind(true, true);
+    if (m > 0) {
+        of_kind(true, false);
+        of_kind(false, false);
+    }
+    return need;
 }
 
 // Optional instrumentation: event pairs around the main pair kernel of each call.
@@ -1297,18 +1328,7 @@ int sdkde_workspace_bytes(int64_t n, int64_t m, int32_t d, uint32_t flags, size_
     if (!bytes) return SDKDE_EINVAL;
     int rc = check_common(bytes, n, m, d, 1.0, flags);
     if (rc != SDKDE_OK) return rc;
-    // Largest of: score at the samples themselves, score at m separate points, eval at m queries.
-    Plan self_plan = make_plan(n, n, d, true, flags);
-    apply_symmetric(self_plan, n, flags, true);
-    size_t need = layout(self_plan, true, false, nullptr, flags).bytes;
-    if (m > 0) {
-        const uint32_t at_points = anchored_flags(flags, false);      // the mode a score at separate points runs in
-        size_t b = layout(make_plan(n, m, d, true, at_points), true, true, nullptr, at_points).bytes;
-        need = b > need ? b : need;
-        b = layout(make_plan(n, m, d, false, flags), false, true, nullptr, flags).bytes;
-        need = b > need ? b : need;
-    }
-    *bytes = need;
+    *bytes = calls_bytes(n, m, d, flags, true);
     return SDKDE_OK;
 }
 
@@ -1360,11 +1380,7 @@ int sdkde_fit_eval_static(const float* samples, int64_t n, const float* queries,
     Plan score_plan = make_plan(n, n, d, true, flags), eval_plan = make_plan(n, m, d, false, flags);
     apply_symmetric(score_plan, n, flags, true);
     Workspace unused;
-    if (!score_plan.parts && !eval_plan.parts) {
-        size_t need = 0;
-        if ((rc = sdkde_workspace_bytes(n, m, d, flags, &need)) != SDKDE_OK) return rc;
-        if (need > (size_t)SDKDE_STATIC_SCRATCH_BYTES) return SDKDE_ETOOLARGE;
-    }
+    if (!score_plan.parts && !eval_plan.parts && calls_bytes(n, m, d, flags, false) > (size_t)SDKDE_STATIC_SCRATCH_BYTES) return SDKDE_ETOOLARGE;
     if (!fit_workspace(score_plan, true, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, &unused) ||
         (m > 0 && !fit_points(eval_plan, false, nullptr, SDKDE_STATIC_SCRATCH_BYTES, flags, m, &unused)))
         return SDKDE_ETOOLARGE;

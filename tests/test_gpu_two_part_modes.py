@@ -17,7 +17,8 @@ def _calls(P, xd, qd, h, flags, ws):
 
 
 @pytest.mark.parametrize("n,m,d,flags", [(5000, 700, 16, 1), (3072, 100, 16, 2), (1500, 4100, 9, 3), (4000, 900, 33, 2), (3500, 65, 128, 3),
-                                         (5000, 700, 24, 17), (600, 50, 7, 18), (200, 30, 16, 33)])
+                                         (5000, 700, 24, 17), (600, 50, 7, 18), (200, 30, 16, 33), (9000, 300, 24, 1), (100, 900, 128, 1),
+                                         (600, 20, 48, 3), (14000, 100, 16, 1), (3100, 64, 96, 2)])
 def test_calls_on_the_fp32_kernels_have_their_bits(n, m, d, flags):
     import torch
     import paper_2602_10378_amd as P
@@ -28,8 +29,7 @@ def test_calls_on_the_fp32_kernels_have_their_bits(n, m, d, flags):
     own = torch.empty(P.sdkde_workspace_bytes(n, m, d, flags), dtype=torch.uint8, device="cuda")
     for ws in (P.make_workspace(n, m, d), own):
         for got, want in zip(_calls(P, xd, qd, h, flags, ws), _calls(P, xd, qd, h, flags & 16, ws)):
-            # (a buffer of the mode's own size may hold fewer slots than the fp32 mode's plan has)
-            assert torch.equal(got, want) or (ws is own and float((got - want).norm() / want.norm()) < 1e-5)
+            assert torch.equal(got, want)
     # prepared samples are those of the mode that was asked for
     ws = P.make_workspace(n, m, d)
     want = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=flags)[1]
@@ -65,6 +65,23 @@ def test_buffers_without_room_for_the_fp32_operands(tuning, n, m, d):
     first = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=1)[1]
     few = P.sdkde_eval(xd, qd[:3].contiguous(), h, want="log", workspace=ws, flags=1 | P.SDKDE_FLAG_SAMPLES_PREPARED)[1]
     assert float((few - first[:3]).abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("n,m,d,flags", [(4000, 500, 16, 1), (9000, 700, 24, 1), (20000, 100, 16, 1), (6000, 800, 64, 2), (300, 40, 33, 3)])
+def test_static_scratch_has_the_bits_of_a_buffer_of_the_size_that_is_asked_for(n, m, d, flags):
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h)
+    print(f"static scratch in fp16 modes n={n} m={m} d={d} flags={flags}", flush=True)
+    need = P.sdkde_workspace_bytes(n, m, d, flags)
+    assert need <= P.SDKDE_STATIC_SCRATCH_BYTES
+    s, x_sd, logd = torch.empty_like(xd), torch.empty_like(xd), torch.empty(m, device="cuda")
+    P.sdkde_fit_eval_static(xd, qd, h, x_sd, score_out=s, log_density_out=logd, flags=flags)
+    own_s = torch.empty_like(xd)
+    own_x, _, own_logd = P.sdkde_fit_eval(xd, qd, h, score_out=own_s, want="log", workspace=torch.empty(need, dtype=torch.uint8, device="cuda"), flags=flags)
+    assert torch.equal(s, own_s) and torch.equal(x_sd, own_x) and torch.equal(logd, own_logd)
 
 
 @pytest.mark.parametrize("first,then,d", [(1, 2, 24), (3, 1, 64), (2, 3, 128), (2, 2, 16)])

@@ -137,6 +137,39 @@ def test_one_workspace_serves_every_precision_mode(n, m, d, other):
                     assert P.sdkde_describe_plan(n, m, d, call, flags)["workspace_bytes"] <= size
 
 
+@settings(max_examples=300, deadline=None)
+@given(n=st.one_of(st.integers(1, 3200), st.integers(1, 1_000_000)), m=st.one_of(st.integers(0, 3000), st.integers(0, 500_000)), d=st.integers(4, 128),
+       prec=st.sampled_from([P.SDKDE_PREC_FP16X2, P.SDKDE_PREC_FP16X2_ALL, P.SDKDE_PREC_FP16X2_PHI16]), shift=st.sampled_from([0, P.SDKDE_FLAG_MAX_SHIFT]),
+       symmetric=st.sampled_from([0, P.SDKDE_FLAG_SYMMETRIC]))
+def test_workspace_of_an_fp16_mode_holds_the_plans_of_the_kernels_that_serve_it(n, m, d, prec, shift, symmetric):
+    """Calls that run as FP16X2, and those of up to 3072 samples in any fp16 mode, take the fp32 mode's kernels: a buffer of the size that
+    is asked for holds that mode's own decomposition of each kind of call."""
+    size = P.sdkde_workspace_bytes(n, m, d, prec | shift | symmetric)
+    for call in range(3 if m else 1):
+        if d <= (3 if call == 2 else 6):
+            continue
+        runs_as_x2 = prec == P.SDKDE_PREC_FP16X2 or d > 16 or (call == 1 and not shift)
+        if n <= 3072 or runs_as_x2:
+            assert P.sdkde_describe_plan(n, m, d, call, shift)["workspace_bytes"] <= size
+
+
+def test_static_scratch_refuses_by_the_size_on_a_mode_s_own_kernels():
+    """The scratch buffer takes a pass in an fp16 mode by what its own kernels need: one that the kernels serving it need more for
+    than it has is still accepted.  (Host only: what is accepted goes on to look for a device.)"""
+    import ctypes
+    lib, fake = P.load(), 1 << 20
+    d, m, at = 48, 4000, {}
+    for n in range(30000, 120000, 2048):
+        own = max(P.sdkde_describe_plan(n, m, d, call, P.SDKDE_PREC_FP16X2)["workspace_bytes"] for call in range(3))
+        at.setdefault((own <= P.SDKDE_STATIC_SCRATCH_BYTES, P.sdkde_workspace_bytes(n, m, d, P.SDKDE_PREC_FP16X2) <= P.SDKDE_STATIC_SCRATCH_BYTES), n)
+    assert (True, False) in at and (False, False) in at
+    status = lambda n: lib.sdkde_fit_eval_static(fake, n, fake, m, d, ctypes.c_double(1.0), None, fake, fake, None, P.SDKDE_PREC_FP16X2, None)
+    assert status(at[(False, False)]) == P.SDKDE_ETOOLARGE
+    import torch
+    if not torch.cuda.is_available():
+        assert status(at[(True, False)]) != P.SDKDE_ETOOLARGE
+
+
 def test_describe_plan_rejects_bad_arguments():
     for args in ((0, 1, 16, 0, 0), (10, 10, 16, 3, 0), (10, 10, 200, 0, 0), (10, 10, 16, 0, 100)):
         with pytest.raises(P.SdkdeError):
