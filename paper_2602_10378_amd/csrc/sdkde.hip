@@ -975,7 +975,8 @@ int profile_mark(int which, int edge, hipStream_t st)
 struct FusedPrep {
     PrepJob sd_job, q_job;
     Stamp stamp;
-    bool whole;             // both passes are pair_whole_kernel's (plan_whole_fit), these their plans and places
+    bool whole_score;       // the score pass is pair_whole_kernel's
+    bool whole;             // both passes are (plan_whole_fit), these their plans and places
     Plan score_plan, eval_plan;
     Workspace score_at, eval_at;
 };
@@ -1020,15 +1021,7 @@ bool plan_fused_prep(const float* samples_sd, int64_t n, const float* queries, i
     return true;
 }
 
-// Whether the score at the samples is one of pair_whole_kernel's, with the epilogue in it.
-bool whole_score(int64_t n, int32_t d, uint32_t flags)
-{
-    Plan p = make_plan(n, n, d, true, flags);
-    apply_symmetric(p, n, flags, true);
-    return whole_row_tiles(p, n, n, true, false) != 0;
-}
-
-// The same for small sample sets whose two passes are pair_whole_kernel's (whole_row_tiles): three launches, the queries prepared with
+// Whether the one-call pass is that of small sample sets whose two passes are pair_whole_kernel's (whole_row_tiles): three launches, the queries prepared with
 // the samples, the shifted samples by the workgroups that form them.  The eval pass's operands stand where a call of its own has
 // them (a later one may rely on the record, SDKDE_FLAG_SAMPLES_PREPARED), the score pass's behind them.
 bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, int64_t m, int32_t d, double h, void* workspace,
@@ -1037,7 +1030,8 @@ bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, in
     if (m <= 0 || (eflags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
     Plan& ps = out->score_plan = make_plan(n, n, d, true, sflags);
     apply_symmetric(ps, n, sflags, true);
-    if (!whole_row_tiles(ps, n, n, true, false)) return false;
+    out->whole_score = whole_row_tiles(ps, n, n, true, false) != 0;
+    if (!out->whole_score) return false;
     Plan& pe = out->eval_plan = make_plan(n, m, d, false, eflags);
     if (!whole_row_tiles(pe, n, m, false, false) || ps.n_pad != pe.n_pad) return false;
     // accepted or refused as the passes one by one are
@@ -1057,6 +1051,20 @@ bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, in
     out->q_job = PrepJob{queries, m, pe.m_pad, we.ps, nullptr, we.pn, 0.0f, false, false, half_tail(d, false)};
     out->stamp = make_stamp(we, false, false, samples_sd, n, d, format, (float)operand_scale(format, h), eflags);
     return true;
+}
+
+// What the one-call pass folds together, if anything.  (Plans cost 0.4 us each at n = 4096, 3 us at 2^20, in front of the first launch: the
+// number of samples alone rules the small form out.)
+bool plan_fit(const float* samples_sd, int64_t n, const float* queries, int64_t m, int32_t d, double h, void* workspace, size_t workspace_bytes,
+              uint32_t flags, FusedPrep* out)
+{
+    const uint32_t sflags = two_part_flags(anchored_flags(flags, true), n, d, true, true, workspace_bytes);
+    const uint32_t eflags = two_part_flags(flags, n, d, false, false, workspace_bytes);
+    if (n <= kWholeSamples) {
+        if (plan_whole_fit(samples_sd, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, out)) return true;
+        if (out->whole_score) return false;         // (its kernel has its epilogue in it)
+    }
+    return plan_fused_prep(samples_sd, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, out);
 }
 
 // One pass of a score call over the samples at m points (null: at the samples themselves, m = n).  samples_ready: they
@@ -1355,10 +1363,7 @@ int sdkde_fit_eval(const float* samples, int64_t n, const float* queries, int64_
     FusedPrep fused{};
     const size_t in = sizeof(float) * d * n, at_queries = sizeof(float) * d * m;
     const bool stable = apart(queries, at_queries, samples_sd_out, in) && apart(queries, at_queries, score_out, in);
-    const uint32_t sflags = two_part_flags(anchored_flags(flags, true), n, d, true, true, workspace_bytes);
-    const uint32_t eflags = two_part_flags(flags, n, d, false, false, workspace_bytes);
-    const bool fuse = stable && (plan_whole_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused) ||
-                                 (!whole_score(n, d, sflags) && plan_fused_prep(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, sflags, eflags, &fused)));
+    const bool fuse = stable && plan_fit(samples_sd_out, n, queries, m, d, h, workspace, workspace_bytes, flags, &fused);
     bool centre_left = true;
     rc = score_impl(samples, n, nullptr, n, d, h, score_out, samples_sd_out, workspace, workspace_bytes, flags, stream, fuse ? &fused : nullptr, &centre_left);
     if (rc != SDKDE_OK || m == 0) return rc;

@@ -170,6 +170,27 @@ def test_static_scratch_refuses_by_the_size_on_a_mode_s_own_kernels():
         assert status(at[(True, False)]) != P.SDKDE_ETOOLARGE
 
 
+def test_a_one_call_pass_plans_no_more_than_its_forms_need():
+    """A pass too large for the small form, refused for its buffer before anything is launched, costs the host the two plans of the folded
+    form and the score's own, not five: 2.5 times what a refused score takes, beside 3.8 (with the calls' own overhead)."""
+    import ctypes
+    import time
+    lib, fake, n, m, d = P.load(), 1 << 20, 1 << 20, 1 << 17, 16
+    h = ctypes.c_double(1.0)
+    calls = (lambda: lib.sdkde_score(fake, n, None, n, d, h, fake, fake, 256, 0, None),
+             lambda: lib.sdkde_fit_eval(fake, n, fake << 10, m, d, h, None, fake << 20, fake, None, fake, 256, 0, None))
+    best = [float("inf")] * 2
+    for call in calls:
+        assert call() == 3              # SDKDE_EWORKSPACE
+    for _ in range(30):
+        for k, call in enumerate(calls):
+            t0 = time.perf_counter()
+            for _ in range(200):
+                call()
+            best[k] = min(best[k], time.perf_counter() - t0)
+    assert best[1] < 3.2 * best[0], best
+
+
 def test_describe_plan_rejects_bad_arguments():
     for args in ((0, 1, 16, 0, 0), (10, 10, 16, 3, 0), (10, 10, 200, 0, 0), (10, 10, 16, 0, 100)):
         with pytest.raises(P.SdkdeError):
