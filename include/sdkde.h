@@ -31,8 +31,8 @@
  *    from the centre has no weight with any other, duplicates of it included: its exponents could be off by a
  *    hundred.  SDKDE_FLAG_MAX_SHIFT takes such samples and points for what they are.  Far outside that domain, R/h above
  *    ~1e18, the scaled coordinates overflow fp32 on either path and the outputs are NaN.  A sample with an infinite
- *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path; its term
- *    of the Laplace estimate is NaN.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
+ *    coordinate that is none of the centre's rows weighs nothing on the fp32 matrix path, and any such sample in the thin
+ *    path's scores on up to 4096 samples, which need no centre; its term of the Laplace estimate is NaN.)  Unless SDKDE_FLAG_MAX_SHIFT is set no running maximum
  *    is kept, and weights below the smallest normal fp32 number (2^-126) are flushed to zero: a point whose
  *    weights phi_j sum to less than 1000 n 2^-126 (so that the flushed ones could be more than one part in a
  *    thousand of the sum; the point is then farther than about 11.5 - 13 h from every sample, depending on n)

@@ -177,6 +177,27 @@ __global__ __launch_bounds__(kBlock) void thin_whole_kernel(
     int j = part;
     for (; j + (AHEAD - 1) * PARTS < n; j += AHEAD * PARTS) pairs(j, std::true_type{});
     if (j < n) pairs(j, std::false_type{});
+    // A sample with an infinite coordinate weighs nothing, but 0 times its difference is NaN: the numerator again without such terms
+    // (in the loop above the choice is an instruction a coordinate, for samples that hardly any call has).
+    bool infinite = false;
+#pragma unroll
+    for (int k = 0; k < D; ++k) infinite |= num[k] != num[k];
+    if (__builtin_expect(infinite && den == den, 0)) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) num[k] = 0.0f;
+#pragma unroll 1
+        for (j = part; j < n; j += PARTS) {
+            float t[D], r2 = 0.0f;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                t[k] = a * (samples[(int64_t)j * D + k] - p[k]);
+                r2 = fmaf(t[k], t[k], r2);
+            }
+            const float phi = __builtin_amdgcn_exp2f(-r2);
+#pragma unroll
+            for (int k = 0; k < D; ++k) num[k] = fmaf(phi, phi == 0.0f ? 0.0f : t[k], num[k]);
+        }
+    }
     sums[D][part][r] = den;
 #pragma unroll
     for (int k = 0; k < D; ++k) sums[k][part][r] = num[k];

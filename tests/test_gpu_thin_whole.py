@@ -71,3 +71,26 @@ def test_thin_whole_over_its_inputs_and_prepared_samples(tuning, d):
     assert bool(torch.isnan(P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=prepared)[1]).all())
     x_sd, _, logd = P.sdkde_fit_eval(xd, qd, h, want="log", workspace=ws)
     assert torch.equal(P.sdkde_eval(x_sd, qd, h, want="log", workspace=ws, flags=prepared)[1], logd)
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 6])
+@pytest.mark.parametrize("n,m", [(17, 5), (600, 50), (4096, 100)])
+def test_an_infinite_sample_weighs_nothing_on_the_thin_path(n, m, d):
+    """Score at the other samples and at points: that of the set without the sample (all its weights are zero)."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=n + d)
+    h = 2.0 * float(h)
+    rest = np.arange(n) != n // 2
+    for value, k in ((np.inf, d - 1), (-np.inf, 0)):
+        x[n // 2, k] = value
+        xd, qd, restd = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), torch.from_numpy(x[rest]).cuda()
+        print(f"thin whole, infinite sample n={n} m={m} d={d} {value}", flush=True)
+        s, x_sd = torch.empty_like(xd), torch.empty_like(xd)
+        P.sdkde_fit_eval(xd, qd, h, score_out=s, samples_sd_out=x_sd, want="log")
+        keep = torch.from_numpy(rest).cuda()
+        for got, want, at in ((s[keep], P.sdkde_score(restd, h), x[rest]), (P.sdkde_score(xd, h, points=qd), P.sdkde_score(restd, h, points=qd), q)):
+            err = (got - want).norm(dim=1).cpu().numpy()        # (the terms come in another order)
+            assert np.all(err <= 2.0 * score_resolution(x[rest], at, h))
+        assert bool(torch.isfinite(x_sd[keep]).all())
