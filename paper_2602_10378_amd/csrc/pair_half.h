@@ -101,7 +101,7 @@ struct HalfRows {
 // the division by 2^kWeightScale, comes out in a range of its own: with W = 2^11 w, h = fp16(w), l = fp16(W - 2^11 h), and l
 // meets the transposed samples' third part, 2^-11 h.  Where the first part alone would be below the fp16 range the second still
 // holds 11 bits down to 2^-25 of a W of one.
-constexpr float kMostWeight = 65000.0f * kWeightScale;      // of a lane's sum of W, so that no w leaves the fp16 range
+constexpr float kMostWeight = 65000.0f * kWeightScale;      // of a lane's sum of W of a row, so that no w leaves the fp16 range
 constexpr int kRaisedTo = 18;                       // where a row's largest W is put when it has outgrown that
 constexpr float kLeastShift = -126.0f;              // a W of one then stands for the smallest normal fp32 number
 // Shifted sums without Phi X have the fp32 range for their weights: a row's first look puts its largest at one.
@@ -376,8 +376,10 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
 #pragma unroll
             for (int t = 0; t < NB; ++t) {
                 weigh(t);
-                // (a signed sum near zero does no harm: what has to be seen is what leaves the range, and NaN compares as that)
-                if (SCORE || FAR) all = t == 0 ? (LAPLACE ? fabsf(dt[t]) : dt[t]) : all + (LAPLACE ? fabsf(dt[t]) : dt[t]);
+                // SCORE: the largest of the rows that a lane holds: fmaxf passes a NaN over, beside which a sum would see no other row.
+                // (Without Phi X what leaves the range, and NaN, has to be seen; a signed sum near zero does no harm.)
+                if (SCORE) all = t == 0 ? dt[t] : fmaxf(all, dt[t]);
+                else if (FAR) all = t == 0 ? (LAPLACE ? fabsf(dt[t]) : dt[t]) : all + (LAPLACE ? fabsf(dt[t]) : dt[t]);
             }
             // a weight may have outgrown its row's scale: that row's exponents are lowered, its largest W is 2^kRaisedTo
             // again (wave-uniform; in place, so that nothing is copied where it does not happen)
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(WAVES * kWave, MINW) void pair_half_kernel(
             }
             // FAR: or the shift may; what has been summed, on both levels, is brought to the new one.  A shift too large, or a
             // weight too far out, for the difference to be exact: the row is looked at anew.
-            if (FAR && __builtin_expect(__builtin_amdgcn_ballot_w64(!(all <= (SCORE ? kMostWeight : kMostShifted))) != 0, 0)) {
+            if (FAR && __builtin_expect(__builtin_amdgcn_ballot_w64(SCORE ? all > kMostWeight : !(all <= kMostShifted)) != 0, 0)) {
                 float before[NB], by[NB], up[NB];
                 bool exact = true;
 #pragma unroll

@@ -222,11 +222,11 @@ __global__ __launch_bounds__(whole_waves(KB, NI) * kWave) void pair_whole_kernel
             lower(kLeastShift);
             exponents();            // beside a term as large as the norms an MFMA truncates the small products (score errors 1.02 to 1.05 times as large)
         }
-        float all = 0.0f;
+        [[maybe_unused]] float all = 0.0f;
 #pragma unroll
         for (int t = 0; t < NI; ++t) {
             weigh(t);
-            all += dt[t];
+            all = t == 0 ? dt[t] : fmaxf(all, dt[t]);          // (not a sum: see pair_half.h)
         }
         if (SCORE && __builtin_expect(__builtin_amdgcn_ballot_w64(all > kMostWeight) != 0, 0)) {
             lower(0.0f);

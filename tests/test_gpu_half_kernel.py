@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import sdkde_inputs
-from parity import assert_laplace_close, gram_exponent_error
+from parity import assert_laplace_close, gram_exponent_error, score_resolution
 from test_gpu_split_kernel import _score_bound
 
 pytestmark = pytest.mark.gpu
@@ -181,3 +181,29 @@ def test_shift_from_leading_products(d):
     bound = _score_bound(x, q, h)
     err = np.linalg.norm(P.sdkde_score(xd, h, points=qd, flags=flags).cpu().numpy() - oracle.score(x, h, points=q), axis=1)
     assert np.all(err <= bound), (err / bound).max()
+
+
+@pytest.mark.parametrize("n,m,d,splits", [(5000, 100, 16, 1), (5000, 100, 40, 1), (5000, 100, 64, 1), (2000, 4200, 16, 0)])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_a_point_that_is_not_a_number_leaves_the_others_their_scales(tuning, n, m, d, splits, value):
+    """Rows r and r + 16 of a wave share a lane, and one test of whether a weight has outgrown its row's scale.  Here row 17's near
+    samples come last, so that its scale has to be raised, and row 1's weights are NaN."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, splits)
+    rng = np.random.default_rng(d)
+    x, q = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((m, d)).astype(np.float32)
+    h = 0.5 * d**0.5
+    away = np.float32(10.0 * h / d**0.5)                      # e^-50 between the two groups
+    x[3 * n // 4:] += away
+    q[17::32] += away
+    xd, qd = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    print(f"scales beside NaN n={n} m={m} d={d} {value}", flush=True)
+    want = P.sdkde_score(xd, h, points=qd)
+    qd[1::32, d // 2] = value
+    got = P.sdkde_score(xd, h, points=qd)
+    keep = np.arange(m) % 32 != 1
+    # (a scale that is raised at another chunk is another rounding of the row's term)
+    err = (got - want).norm(dim=1).cpu().numpy()[keep]
+    assert np.all(err <= score_resolution(x, q[keep], h))
