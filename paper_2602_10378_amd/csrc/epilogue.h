@@ -12,7 +12,7 @@ namespace {
 
 // The partial slots of one output are shared by PARTS threads (slots part, part + PARTS, ...), which keeps many
 // loads in flight instead of one long dependent chain on a few compute units (a call with few points has up to
-// thousands of slots and few outputs), and are combined through LDS in the fixed order part 0, 1, ..., PARTS - 1.
+// thousands of slots and few outputs), and are combined through LDS in a fixed order (sum_parts).
 // The host picks PARTS from the slot and output counts alone (epilogue_parts), so a plan always sums in the same
 // order: the many-thread form only where the outputs are too few to fill the chip otherwise, since its loads are
 // narrow (kBlock / PARTS consecutive floats per slot).  32 / 4 threads: 1024 outputs of 1024 slots 5.3 / 22.6 us, 4000 of
@@ -24,6 +24,33 @@ constexpr int64_t kEpiFewOutputs = 16384;           // most outputs for kEpiPart
 inline int epilogue_parts(int nslots, int64_t outputs)
 {
     return nslots >= kEpiManySlots && outputs <= kEpiFewOutputs ? kEpiPartsMany : kEpiPartsFew;
+}
+
+// Sum of N (a power of two) elements in pairs.  T is two sums most of which cancel against p~ D, and what adding their parts one
+// after the other rounds is most of a score's error: 32 parts of 72 slots 1.7 times the error that they give in pairs (9000 samples x 300
+// points, d = 9 .. 33; the same time), sixteen waves' sums in pair_whole.h 1.3 times (n = 600 .. 2000, d = 8 .. 24).
+template <typename T, int N, typename F>
+__device__ __forceinline__ T tree_sum(F element)
+{
+    T v[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] = element(q);
+#pragma unroll
+    for (int step = N / 2; step > 0; step /= 2)
+#pragma unroll
+        for (int q = 0; q < step; ++q) v[q] += v[q + step];
+    return v[0];
+}
+
+// The sum of an output's parts in LDS: of many in pairs, of a few one after the other.
+template <int PARTS>
+__device__ __forceinline__ float sum_parts(float (*red)[kBlock / PARTS], int lane)
+{
+    if constexpr (PARTS == kEpiPartsMany) return tree_sum<float, PARTS>([&](int q) { return red[q][lane]; });
+    float r = red[0][lane];
+#pragma unroll
+    for (int q = 1; q < PARTS; ++q) r += red[q][lane];
+    return r;
 }
 
 template <int PARTS, bool MAX>
@@ -43,9 +70,14 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     }
     red[part][lane] = acc;
     __syncthreads();
-    float r = red[0][lane];
+    float r;
+    if constexpr (MAX) {
+        r = red[0][lane];
 #pragma unroll
-    for (int q = 1; q < PARTS; ++q) r = MAX ? fmaxf(r, red[q][lane]) : r + red[q][lane];
+        for (int q = 1; q < PARTS; ++q) r = fmaxf(r, red[q][lane]);
+    } else {
+        r = sum_parts<PARTS>(red, lane);
+    }
     __syncthreads();            // red is reused by the next reduction
     return r;
 }
@@ -67,9 +99,7 @@ __device__ __forceinline__ float reduce_shifted_slots(const float* __restrict__ 
     }
     red[part][lane] = acc;
     __syncthreads();
-    float r = red[0][lane];
-#pragma unroll
-    for (int q = 1; q < PARTS; ++q) r += red[q][lane];
+    const float r = sum_parts<PARTS>(red, lane);
     __syncthreads();            // red is reused by the next reduction
     return r;
 }

@@ -44,21 +44,6 @@ constexpr int whole_waves(int kb, int row_tiles) { return kb <= 2 && row_tiles =
 // Most chunks a wave sums in one level (the larger kernels fold their sums as often, kFlushTiles).
 constexpr int kWholeChunks = kFlushTiles / 2;
 
-// Sum of N (a power of two) elements in pairs: one after the other the roundings of sixteen waves' T, most of which cancels against
-// p~ D, made a score's error 1.3 times as large (n = 600 .. 2000, d = 8 .. 24).
-template <typename T, int N, typename F>
-__device__ __forceinline__ T tree_sum(F element)
-{
-    T v[N];
-#pragma unroll
-    for (int q = 0; q < N; ++q) v[q] = element(q);
-#pragma unroll
-    for (int step = N / 2; step > 0; step /= 2)
-#pragma unroll
-        for (int q = 0; q < step; ++q) v[q] += v[q + step];
-    return v[0];
-}
-
 template <int KB, int TAIL, int NI, int KIND, bool FIT>
 __global__ __launch_bounds__(whole_waves(KB, NI) * kWave) void pair_whole_kernel(
     const float* __restrict__ ps, const float* __restrict__ pn, const float* __restrict__ xs, const float* __restrict__ xt,

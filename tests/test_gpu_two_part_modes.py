@@ -97,3 +97,28 @@ def test_samples_prepared_in_a_mode_serve_those_that_run_as_it(first, then, d):
     ws = P.make_workspace(n, m, d)
     want = P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=first)[1]
     assert torch.equal(P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=then | P.SDKDE_FLAG_SAMPLES_PREPARED)[1], want)
+
+
+@pytest.mark.parametrize("flags", [0, 1, 17])
+@pytest.mark.parametrize("n,d", [(9000, 9), (9000, 16), (9000, 33), (30000, 16)])
+def test_scores_from_many_slots_are_as_exact_as_from_few(tuning, n, d, flags):
+    """A call with few points has more slots, each a shorter sum, and 32 threads an output for them: the error is to be no larger than
+    with the 32 slots that the fp16x2 mode's own kernels had there (0.92 to 0.94 of it; 1.60 to 1.74 with the 32 parts added one after the other)."""
+    import torch
+    import oracle
+    import paper_2602_10378_amd as P
+    P.load()
+    m = 300
+    error = {}
+    print(f"many slots n={n} d={d} flags={flags}", flush=True)
+    for seed in range(3):
+        x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=4, seed=seed)
+        xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h)
+        ref = oracle.score(x, h, points=q)
+        for splits in (0, 32):
+            tuning(P.SDKDE_TUNE_SCORE_SPLITS, splits)
+            assert splits or P.sdkde_describe_plan(n, m, d, 1, flags & 16)["splits"] >= 64
+            got = P.sdkde_score(xd, h, points=qd, flags=flags).cpu().numpy()
+            error[splits] = error.get(splits, 0.0) + np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"many slots / 32: {error[0] / error[32]:.3f} of {error[32] / 3:.3g}", flush=True)
+    assert error[0] <= 1.1 * error[32]
