@@ -12,7 +12,7 @@ namespace {
 
 // The partial slots of one output are shared by PARTS threads (slots part, part + PARTS, ...), which keeps many
 // loads in flight instead of one long dependent chain on a few compute units (a call with few points has up to
-// thousands of slots and few outputs), and are combined through LDS in a fixed order (sum_parts).
+// thousands of slots and few outputs), and are combined through LDS in a fixed order (tree_sum).
 // The host picks PARTS from the slot and output counts alone (epilogue_parts), so a plan always sums in the same
 // order: the many-thread form only where the outputs are too few to fill the chip otherwise, since its loads are
 // narrow (kBlock / PARTS consecutive floats per slot).  32 / 4 threads: 1024 outputs of 1024 slots 5.3 / 22.6 us, 4000 of
@@ -26,7 +26,7 @@ inline int epilogue_parts(int nslots, int64_t outputs)
     return nslots >= kEpiManySlots && outputs <= kEpiFewOutputs ? kEpiPartsMany : kEpiPartsFew;
 }
 
-// Sum of N (a power of two) elements in pairs.  T is two sums most of which cancel against p~ D, and what adding their parts one
+// Sum of N (a power of two) elements in pairs.  T is a sum most of which cancels against p~ D, and what adding its parts one
 // after the other rounds is most of a score's error: 32 parts of 72 slots 1.7 times the error that they give in pairs (9000 samples x 300
 // points, d = 9 .. 33; the same time), sixteen waves' sums in pair_whole.h 1.3 times (n = 600 .. 2000, d = 8 .. 24).
 template <typename T, int N, typename F>
@@ -42,16 +42,33 @@ __device__ __forceinline__ T tree_sum(F element)
     return v[0];
 }
 
-// The sum of an output's parts in LDS: of many in pairs, of a few one after the other.
-template <int PARTS>
-__device__ __forceinline__ float sum_parts(float (*red)[kBlock / PARTS], int lane)
+// Slots part, part + PARTS, ... of an output: four at a time in pairs, their loads in flight together (512 slots of 1024 queries 4.8 us,
+// one at a time 11.6).  One after the other, and the parts likewise, a score's error is 1.04 to 1.08 times as large (4096 .. 32768 samples,
+// d = 8 .. 64).  slot(s): a sum of any kind.
+template <int PARTS, typename T, typename F>
+__device__ __forceinline__ T sum_slots(int part, int nslots, T acc, F slot)
 {
-    if constexpr (PARTS == kEpiPartsMany) return tree_sum<float, PARTS>([&](int q) { return red[q][lane]; });
-    float r = red[0][lane];
-#pragma unroll
-    for (int q = 1; q < PARTS; ++q) r += red[q][lane];
-    return r;
+    int s = part;
+    for (; s + 3 * PARTS < nslots; s += 4 * PARTS) {
+        const T v0 = slot(s), v1 = slot(s + PARTS), v2 = slot(s + 2 * PARTS), v3 = slot(s + 3 * PARTS);
+        acc += (v0 + v1) + (v2 + v3);
+    }
+    if (s + PARTS < nslots) {
+        const T v0 = slot(s), v1 = slot(s + PARTS);
+        acc += v0 + v1;
+        s += 2 * PARTS;
+    }
+    if (s < nslots) acc += slot(s);
+    return acc;
 }
+
+// T (four columns) and D of a row.
+struct RowSums {
+    f32x4 t;
+    float d;
+    __device__ __forceinline__ RowSums operator+(const RowSums& o) const { return {t + o.t, d + o.d}; }
+    __device__ __forceinline__ RowSums& operator+=(const RowSums& o) { return *this = *this + o; }
+};
 
 template <int PARTS, bool MAX>
 __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, int64_t stride, int nslots, bool active,
@@ -61,11 +78,11 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
     const int lane = threadIdx.x % OUTPUTS, part = threadIdx.x / OUTPUTS;
     float acc = MAX ? kNegHuge : 0.0f;
     if (active) {
-        // several loads in flight, added in slot order (512 slots of 1024 queries 4.8 us, one at a time 11.6)
+        if constexpr (MAX) {
 #pragma unroll 4
-        for (int s = part; s < nslots; s += PARTS) {
-            const float v = first[(int64_t)s * stride];
-            acc = MAX ? fmaxf(acc, v) : acc + v;
+            for (int s = part; s < nslots; s += PARTS) acc = fmaxf(acc, first[(int64_t)s * stride]);
+        } else {
+            acc = sum_slots<PARTS>(part, nslots, 0.0f, [&](int s) { return first[(int64_t)s * stride]; });
         }
     }
     red[part][lane] = acc;
@@ -76,7 +93,7 @@ __device__ __forceinline__ float reduce_slots(const float* __restrict__ first, i
 #pragma unroll
         for (int q = 1; q < PARTS; ++q) r = fmaxf(r, red[q][lane]);
     } else {
-        r = sum_parts<PARTS>(red, lane);
+        r = tree_sum<float, PARTS>([&](int q) { return red[q][lane]; });
     }
     __syncthreads();            // red is reused by the next reduction
     return r;
@@ -93,13 +110,11 @@ __device__ __forceinline__ float reduce_shifted_slots(const float* __restrict__ 
     constexpr int OUTPUTS = kBlock / PARTS;
     const int lane = threadIdx.x % OUTPUTS, part = threadIdx.x / OUTPUTS;
     float acc = 0.0f;
-    if (active) {
-#pragma unroll 4
-        for (int s = part; s < nslots; s += PARTS) acc = fmaf(first[(int64_t)s * stride], slot_weight(shifts[(int64_t)s * shift_stride], most), acc);
-    }
+    if (active)
+        acc = sum_slots<PARTS>(part, nslots, 0.0f, [&](int s) { return first[(int64_t)s * stride] * slot_weight(shifts[(int64_t)s * shift_stride], most); });
     red[part][lane] = acc;
     __syncthreads();
-    const float r = sum_parts<PARTS>(red, lane);
+    const float r = tree_sum<float, PARTS>([&](int q) { return red[q][lane]; });
     __syncthreads();            // red is reused by the next reduction
     return r;
 }
@@ -269,8 +284,7 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
     own.load(ps, i, c0, dp, format, mode == 0 ? m_pad : 0);       // may run past d in the last quad: padding, not stored
     f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f};
     if (x_sd && part == 0) xv = load_quad(x + at, quad_io, d - c0);
-    f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
-    float dacc = 0.0f, most = kNegHuge;
+    [[maybe_unused]] float most = kNegHuge;
     if constexpr (SHIFTED) {
         if (active) {
 #pragma unroll 4
@@ -282,27 +296,22 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_quad_kernel(
         for (int k = 0; k < PARTS; ++k) most = fmaxf(most, red_d[k][lane]);
         __syncthreads();
     }
+    RowSums acc = {{0.0f, 0.0f, 0.0f, 0.0f}, 0.0f};
     if (active) {
-#pragma unroll 4
-        for (int s = part; s < nsplit; s += PARTS) {
+        acc = sum_slots<PARTS>(part, nsplit, acc, [&](int s) {
             const f32x4 t = *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
             const float dd = part_d[(int64_t)s * m_pad + i];
-            const float by = SHIFTED ? slot_weight(part_shift[(int64_t)s * m_pad + i], most) : 1.0f;
-            tacc += SHIFTED ? t * by : t;
-            dacc += SHIFTED ? dd * by : dd;
-        }
+            if constexpr (!SHIFTED) return RowSums{t, dd};
+            const float by = slot_weight(part_shift[(int64_t)s * m_pad + i], most);
+            return RowSums{t * by, dd * by};
+        });
     }
-    red_t[part][lane] = tacc;
-    red_d[part][lane] = dacc;
+    red_t[part][lane] = acc.t;
+    red_d[part][lane] = acc.d;
     __syncthreads();
     if (!active || part != 0) return;
-    f32x4 tsum = red_t[0][lane];
-    float dsum = red_d[0][lane];
-#pragma unroll
-    for (int k = 1; k < PARTS; ++k) {
-        tsum += red_t[k][lane];
-        dsum += red_d[k][lane];
-    }
+    f32x4 tsum = tree_sum<f32x4, PARTS>([&](int k) { return red_t[k][lane]; });
+    float dsum = tree_sum<float, PARTS>([&](int k) { return red_d[k][lane]; });
     f32x4 rest;
     f32x4 pc = own.value(format, mode == 0 ? m_pad : 0, &rest);
     if (ScoreUnits::there(dsum, format)) units.plain(i, c0, d, dp, tsum, pc, rest);

@@ -50,32 +50,25 @@ __global__ __launch_bounds__(kBlock) void score_epilogue_prep_kernel(
             const int64_t i = r0 + item / quads;
             const int c0 = (item % quads) * 4;
             const bool active = i < m && c0 < d;
-            f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f}, xv = tacc;
-            float dacc = 0.0f;
+            f32x4 xv = {0.0f, 0.0f, 0.0f, 0.0f};
+            RowSums acc = {xv, 0.0f};
             PreparedQuad prepared = {};
             const int64_t at = i * d + c0;
             if (active) {
                 prepared.load(ps, i, c0, dp, format, 0);        // may run past d in the last quad: padding, not stored
                 // quad_io: d is a multiple of four and the caller's arrays are 16-byte aligned
                 if (part == 0) xv = load_quad(x + at, quad_io, d - c0);
-#pragma unroll 4
-                for (int s = part; s < nsplit; s += PARTS) {
-                    tacc += *reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0);
-                    dacc += part_d[(int64_t)s * m_pad + i];
-                }
+                acc = sum_slots<PARTS>(part, nsplit, acc, [&](int s) {
+                    return RowSums{*reinterpret_cast<const f32x4*>(part_t + ((int64_t)s * m_pad + i) * dp + c0), part_d[(int64_t)s * m_pad + i]};
+                });
             }
-            red_t[part][lane] = tacc;
-            red_d[part][lane] = dacc;
+            red_t[part][lane] = acc.t;
+            red_d[part][lane] = acc.d;
             f32x4 shifted = {0.0f, 0.0f, 0.0f, 0.0f};               // and of padding
             __syncthreads();
             if (active && part == 0) {
-                f32x4 tsum = red_t[0][lane];
-                float dsum = red_d[0][lane];
-#pragma unroll
-                for (int k = 1; k < PARTS; ++k) {
-                    tsum += red_t[k][lane];
-                    dsum += red_d[k][lane];
-                }
+                f32x4 tsum = tree_sum<f32x4, PARTS>([&](int k) { return red_t[k][lane]; });
+                float dsum = tree_sum<float, PARTS>([&](int k) { return red_d[k][lane]; });
                 f32x4 rest;
                 f32x4 pc = prepared.value(format, 0, &rest);
                 if (ScoreUnits::there(dsum, format)) units.plain(i, c0, d, dp, tsum, pc, rest);
