@@ -659,22 +659,34 @@ int launch_half(const Plan& p, const Workspace& w, hipStream_t st)
 
 // Small sample sets: row tiles a workgroup's waves share in pair_whole_kernel, 0: the call takes the kernels with split slots.
 // rows: evaluation points.  The line lies where a workgroup's reads of all samples and the rounds of workgroups cost what the saved
-// launch does.  Split slots / whole rows, us a call: one-call pass with n / 4 queries, d = 16 n = 600 23.8 / 17.7, 2048 22.5 / 22.4,
-// 4096 29.1 / 29.6, d = 24 n = 2048 28.4 / 25.5, d = 64 600 29.0 / 21.6, 2048 36.4 / 34.4, d = 128 600 38.3 / 30.2, 2048 50.2 / 52.7;
-// score at points, n = 1200: d = 16, 4000 points 15.9 / 12.9, 16000 23.6 / 32.0, with two row tiles a wave 17.6, 64000 52.1 / 47.9
-// (eval 29.5 / 35.2); d = 48, 4000 22.2 / 17.7, 16000 36.0 / 45.3; d = 128, 50 points 24.3 / 29.5.
-int whole_row_tiles(const Plan& p, int64_t n, int64_t rows, bool score, bool shifted)
+// launch does.  Split slots / whole rows, us a call, one after the other: one-call pass with n / 4 queries, d = 8 n = 3072 26.7 / 21.9, d = 16
+// n = 600 25.1 / 18.0, 2048 23.3 / 22.0, 2560 26.6 / 23.8, 3072 26.9 / 25.5, 4096 29.1 / 29.6, d = 24 n = 3072 32.1 / 29.7, d = 64 512 27.2 / 21.6,
+// 1536 32.3 / 30.0, d = 128 256 34.3 / 25.3, 768 38.8 / 32.9; score at the samples 2048 15.1 / 14.0, 3072 18.2 / 15.8, d = 64 1536 20.2 / 19.7, d = 128
+// 768 23.7 / 21.9; score at 16000 points, d = 16, n = 3072 32.1 / 29.6, 1200 21.8 / 19.2 with two row tiles a wave.
+// Scores at few points have split slots to fill the chip with, where whole rows leave it to a few workgroups, each with all samples:
+// d = 24, n = 1536 at 64 points 15.2 / 15.3, 4096 points 19.1 / 16.3; n = 3072 64 points 17.1 / 19.9, 1024 18.6 / 19.3, 4096 23.6 / 20.0; d = 64, n = 1024
+// 64 points 16.3 / 17.1, 1024 18.2 / 17.3; n = 1536 17.3 / 20.2, 20.0 / 19.9; d = 80, n = 1024 18.0 / 18.9, 20.8 / 19.3; d = 96, n = 1024 19.5 / 21.8, 22.2 / 21.2.
+// Densities: from about 800 samples on (d <= 8: 2300) the kernels take longer and the call, which the launches bound, does not: d = 16,
+// 64 queries, n = 1024 15.5 / 13.1, alone 25.9 / 26.7, from a graph 9.2 / 10.0; 2048 15.4 / 12.7, 26.3 / 28.0, 9.6 / 11.4; 3072 15.6 / 13.3, 26.7 / 29.5,
+// 10.0 / 12.9.  The line is that of the one-call pass, whose densities a call on its prepared samples repeats to the bit.
+int whole_row_tiles(const Plan& p, int64_t n, int64_t rows, bool score, bool self, bool shifted)
 {
     if (!p.parts || p.sym_on || shifted) return 0;
     if (tuning(score ? SDKDE_TUNE_SCORE_ROW_TILES : SDKDE_TUNE_EVAL_ROW_TILES, 0) || tuning(score ? SDKDE_TUNE_SCORE_SPLITS : SDKDE_TUNE_EVAL_SPLITS, 0)) return 0;
     const int kb = p.dp / 16;
-    if (n > kWholeSamples || n * kb > kWholeBlocks) return 0;
+    int64_t most = kWholeBlocks;
+    if (score && !self) {
+        if (rows < 1024) most = kb <= 4 ? 3072 : 5120;
+        else if (rows < 2048 && kb <= 4) most = 5120;
+    }
+    if (n > kWholeSamples || n * kb > most) return 0;
     return rows <= kComputeUnits * kTile ? 1 : kb == 1 && rows <= 4 * kComputeUnits * kTile ? 2 : 0;
 }
 
-// Whether a score call of the thin path is thin_whole_kernel's.  Split slots / this at the ends of the range: 4000 samples, d = 1 20.4 / 9.5
-// us, d = 6 46.3 / 21.2; at 8000 points d = 1 22.8 / 9.5, d = 6 73.8 / 32.1; at 50 points d = 1 24.3 / 9.2, d = 6 75.3 / 20.1.  The time grows with
-// the pairs from there on, at sixteen threads a row with reads of their own, and the split slots' from about 8000 samples.
+// Whether a score call of the thin path is thin_whole_kernel's.  Split slots / this, us a call: 600 samples, d = 1 15.8 / 8.6, 2000, d = 6
+// 41.9 / 12.5; 4096 d = 1 14.1 / 9.9, d = 6 28.0 / 21.8; 3072 at 8192 points d = 2 27.6 / 14.0, d = 6 57.7 / 28.2; 4096 at 8192 points, where
+// the split slots are 16 instead of 8, d = 2 16.7 / 16.6, 4 22.5 / 19.7, 5 24.0 / 23.6 and d = 6 28.8 / 32.7, left for its error, 0.70 of theirs.
+// The time grows with the pairs, at sixteen threads a row with reads of their own.
 bool thin_whole(const Plan& p, int64_t n, int64_t rows, bool shifted)
 {
     if (!p.thin || shifted || tuning(SDKDE_TUNE_SCORE_ROW_TILES, 0) || tuning(SDKDE_TUNE_SCORE_SPLITS, 0)) return false;
@@ -1030,10 +1042,10 @@ bool plan_whole_fit(const float* samples_sd, int64_t n, const float* queries, in
     if (m <= 0 || (eflags & (SDKDE_FLAG_MAX_SHIFT | SDKDE_FLAG_SAMPLES_PREPARED)) || tuning(SDKDE_TUNE_SEPARATE_PREP, 0) == 1) return false;
     Plan& ps = out->score_plan = make_plan(n, n, d, true, sflags);
     apply_symmetric(ps, n, sflags, true);
-    out->whole_score = whole_row_tiles(ps, n, n, true, false) != 0;
+    out->whole_score = whole_row_tiles(ps, n, n, true, true, false) != 0;
     if (!out->whole_score) return false;
     Plan& pe = out->eval_plan = make_plan(n, m, d, false, eflags);
-    if (!whole_row_tiles(pe, n, m, false, false) || ps.n_pad != pe.n_pad) return false;
+    if (!whole_row_tiles(pe, n, m, false, false, false) || ps.n_pad != pe.n_pad) return false;
     // accepted or refused as the passes one by one are
     Workspace unused;
     Plan score_plan = ps, eval_plan = pe;
@@ -1178,7 +1190,7 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
     flags = two_part_flags(anchored_flags(flags, self), n, d, true, self, workspace_bytes);
     if (fused && fused->whole)
         return score_pass(fused->score_plan, fused->score_at, samples, n, nullptr, m, false, h, score_out, samples_sd_out, flags, (hipStream_t)stream,
-                          fused, whole_row_tiles(fused->score_plan, n, m, true, false));
+                          fused, whole_row_tiles(fused->score_plan, n, m, true, true, false));
 
     Plan p = make_plan(n, m, d, true, flags);
     apply_symmetric(p, n, flags, self);
@@ -1201,7 +1213,7 @@ int score_impl(const float* samples, int64_t n, const float* points, int64_t m, 
             return rc != SDKDE_OK ? rc : profile_mark(0, 1, (hipStream_t)stream);
         }
     }
-    int whole_rows = batch == m ? whole_row_tiles(p, n, m, true, shifted) : 0;
+    int whole_rows = batch == m ? whole_row_tiles(p, n, m, true, self, shifted) : 0;
     if (whole_rows) {
         const Workspace all = whole_layout(p, true, !self, workspace, flags);
         if (all.bytes <= workspace_bytes) w = all;
@@ -1279,13 +1291,13 @@ int eval_impl(const float* samples, int64_t n, const float* queries, int64_t m, 
     const bool all_prepared = fused != nullptr;
     if (fused && fused->whole)
         return eval_pass(fused->eval_plan, fused->eval_at, samples, n, queries, m, false, h, density_out, log_density_out, flags, (hipStream_t)stream,
-                         laplace, reuse_centre, all_prepared, whole_row_tiles(fused->eval_plan, n, m, false, false));
+                         laplace, reuse_centre, all_prepared, whole_row_tiles(fused->eval_plan, n, m, false, false, false));
 
     Plan p = make_plan(n, m, d, false, flags);
     Workspace w;
     const int64_t batch = fit_points(p, false, workspace, workspace_bytes, flags, m, &w);
     if (batch == 0) return SDKDE_EWORKSPACE;
-    int whole_rows = batch == m ? whole_row_tiles(p, n, m, false, (flags & SDKDE_FLAG_MAX_SHIFT) != 0) : 0;
+    int whole_rows = batch == m ? whole_row_tiles(p, n, m, false, false, (flags & SDKDE_FLAG_MAX_SHIFT) != 0) : 0;
     if (whole_rows) {
         const Workspace all = whole_layout(p, false, true, workspace, flags);
         if (all.bytes <= workspace_bytes) w = all;

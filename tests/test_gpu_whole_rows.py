@@ -168,3 +168,23 @@ def test_queries_that_the_same_call_writes_are_read_after_it_has(n, d, which):
     got = P.sdkde_fit_eval(out if which == "in place" else xd, score if which == "score" else out, h, score_out=score, samples_sd_out=out, want="log")[2]
     assert torch.equal(score, s) and torch.equal(out, x_sd)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n,m,d,whole", [(1536, 1023, 24, True), (1537, 1023, 24, False), (2560, 1024, 32, True), (2561, 1024, 32, False), (3072, 2047, 24, False),
+                                         (3072, 2048, 24, True), (768, 64, 64, True), (769, 64, 64, False), (1024, 100, 80, True), (1025, 100, 80, False),
+                                         (1025, 1024, 80, True)])
+def test_scores_at_few_points_keep_the_split_slots(tuning, n, m, d, whole):
+    """Both sides of the lines between whole rows and split slots for scores at separate points: close to what the split slots give, which
+    are what runs beyond the line, bit for bit."""
+    import torch
+    import paper_2602_10378_amd as P
+    P.load()
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=n + d)
+    xd, qd = _gpu(x, q)
+    print(f"whole rows or split slots n={n} m={m} d={d}", flush=True)
+    got = P.sdkde_score(xd, float(h), points=qd)
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, P.sdkde_describe_plan(n, m, d, 1)["splits"])
+    split = P.sdkde_score(xd, float(h), points=qd)
+    assert torch.equal(got, split) != whole
+    err = (got - split).norm(dim=1).cpu().numpy()
+    assert np.all(err <= 2.0 * score_resolution(x, q, h))
