@@ -50,7 +50,7 @@ __global__ __launch_bounds__(whole_waves(KB, NI) * kWave) void pair_whole_kernel
     const float* __restrict__ xn, int nchunks, int64_t n_pad, int64_t m, int64_t m_pad, float laplace_c0, WholeOut out)
 {
     static_assert((KB % 2 != 0) == (TAIL == kTailSixteen || TAIL == kTailEight), "an odd block count has a tail");
-    static_assert(!FIT || KIND == kScoreSelf, "shifted samples are those of the score at the samples");
+    static_assert(!FIT || (KIND == kScoreSelf && NI == 1), "shifted samples are those of the score at the samples, a tile a workgroup");
     constexpr int WAVES = whole_waves(KB, NI), THREADS = WAVES * kWave;
     constexpr bool SCORE = KIND == kScoreSelf || KIND == kScorePoints;
     constexpr bool SELF = KIND == kScoreSelf, LAPLACE = KIND == kEvalLaplace;

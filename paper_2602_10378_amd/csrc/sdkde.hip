@@ -734,7 +734,7 @@ int launch_whole_tail(const Plan& p, const Workspace& w, int row_tiles, int64_t 
                        p.ntiles / 2, p.n_pad, m, p.m_pad, 1.0f + 0.5f * (float)p.d, out)
     if (row_tiles == 1) {
         SDKDE_LAUNCH_WHOLE(1);
-    } else if constexpr (KB == 1) {
+    } else if constexpr (KB == 1 && KIND != kScoreSelf) {           // (two: from more rows on than there are samples here)
         if (row_tiles != 2) return SDKDE_EUNSUPPORTED;
         SDKDE_LAUNCH_WHOLE(2);
     } else {
