@@ -270,7 +270,7 @@ int sdkde_eval_laplace(const float *samples, int64_t n, const float *queries, in
  *   block however few real coordinates it holds
  * and, when out_len >= 26: [25] call 2 only: 1 if sdkde_fit_eval at these sizes and flags, with a workspace of
  *   sdkde_workspace_bytes, prepares the eval pass's operands inside its score epilogue (five launches instead
- *   of six), else 0
+ *   of six), else 0: a property of the kernels with split slots, which few samples (up to 3072) do not run on
  */
 int sdkde_describe_plan(int64_t n, int64_t m, int32_t d, int32_t call, uint32_t flags, int64_t *out,
                         int32_t out_len);

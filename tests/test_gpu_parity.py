@@ -355,7 +355,9 @@ def test_fused_call_matches_oracle_and_three_calls(lib, n, m, d, seed):
 
 @pytest.mark.parametrize("n,m,d,flags", [(4096, 1024, 16, 0), (3000, 333, 16, 0), (2048, 512, 9, 0), (1333, 77, 13, 0),
                                           (5000, 1, 7, 0), (3000, 700, 16, 1), (4096, 1024, 16, 2), (4096, 1024, 16, 3),
-                                          (20000, 3000, 12, 0), (70000, 9000, 16, 0)])
+                                          (20000, 3000, 12, 0), (70000, 9000, 16, 0),
+                                          # (with up to 3072 samples whole rows take the folded form's place: the same at its edges above)
+                                          (3100, 333, 16, 0), (3333, 512, 9, 0), (4099, 77, 13, 0), (3073, 700, 16, 1)])
 def test_one_call_pass_with_and_without_the_folded_preparation(lib, tuning, n, m, d, flags):
     """sdkde_fit_eval prepares the eval pass's operands inside its score epilogue where the layouts allow it; with the
     knob that keeps the preparation in a launch of its own every output has the same bits, and the record the

@@ -122,3 +122,56 @@ def test_scores_from_many_slots_are_as_exact_as_from_few(tuning, n, d, flags):
             error[splits] = error.get(splits, 0.0) + np.linalg.norm(got - ref) / np.linalg.norm(ref)
     print(f"many slots / 32: {error[0] / error[32]:.3f} of {error[32] / 3:.3g}", flush=True)
     assert error[0] <= 1.1 * error[32]
+
+
+@pytest.mark.parametrize("shift", [0, 16])
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("d", [4, 9, 16, 24, 32, 64, 128])
+def test_the_modes_own_kernels_match_the_oracle(tuning, d, splits, shift):
+    """Every call of the fp16x2 mode on a buffer that holds its own operands and not the fp32 mode's; at d <= 16 also the two other modes, which
+    keep their own kernels above 3072 samples."""
+    import torch
+    import oracle
+    import paper_2602_10378_amd as P
+    from parity import assert_laplace_close, assert_log_density_close, assert_score_close, score_resolution
+    P.load()
+    n, m = 4000, 200
+    x, q, h = sdkde_inputs.gaussian_mixture(n, m, d, components=3, seed=d)
+    h = np.float64(h) * (1.8 if d > 64 else 1.2)
+    if shift:
+        q[: m // 2] += np.float32(9.0 * h / np.sqrt(d))       # beyond what plain sums hold
+    x, q, h = x * np.float32(0.4 / h), q * np.float32(0.4 / h), np.float64(0.4)         # (h^-d (2 pi)^-d/2 about one: densities in the fp32 range)
+    xd, qd, h = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), float(h)
+    tuning(P.SDKDE_TUNE_SCORE_SPLITS, splits)
+    tuning(P.SDKDE_TUNE_EVAL_SPLITS, splits)
+    at = np.arange(0, n, 17)
+    ref = {"score": oracle.score(x, h)[at], "points": oracle.score(x, h, points=q), "log": oracle.eval_log_density(x, q, h),
+           "laplace": oracle.eval_laplace_density(x, q, h)}
+    size = oracle.eval_laplace_abs_density(x, q, h)
+    for mode in (1, 2, 3) if d <= 16 else (1,):
+        flags = mode | shift
+        print(f"own kernels d={d} splits={splits} flags={flags}", flush=True)
+        calls = {"points": (1, lambda ws, f: P.sdkde_score(xd, h, points=qd, workspace=ws, flags=f)),
+                 "log": (2, lambda ws, f: P.sdkde_eval(xd, qd, h, want="log", workspace=ws, flags=f)[1]),
+                 "laplace": (2, lambda ws, f: P.sdkde_eval_laplace(xd, qd, h, workspace=ws, flags=f))}
+        if not shift:
+            calls["score"] = (0, lambda ws, f: P.sdkde_score(xd, h, workspace=ws, flags=f))
+        for what, (call, run) in calls.items():
+            if d <= (6 if what in ("score", "points") else 3):
+                continue                                        # (no matrix units there)
+            plan = P.sdkde_describe_plan(n, m, d, call, flags)
+            assert plan["splits"] == splits and not plan["thin"]
+            got = run(torch.empty(plan["workspace_bytes"], dtype=torch.uint8, device="cuda"), flags)
+            assert not torch.equal(got, run(P.make_workspace(n, m, d), shift)), what      # (the fp32 mode's kernels have other bits)
+            got = got.cpu().numpy()
+            if what == "laplace":
+                assert_laplace_close(got, ref[what], size, f"{what} d={d}")
+            elif what == "log":
+                assert_log_density_close(got, ref[what], f"{what} d={d}")
+            elif mode == 3:         # weights of one fp16 value: 2^-11 of sum phi |x - p| / (h^2 D) at most, see the header
+                pull = np.array([np.sum(w * np.linalg.norm(x - p, axis=1)) / np.sum(w) for p in (x[at] if what == "score" else q).astype(np.float64)
+                                 for w in [np.exp(-(np.sum((x - p) ** 2, axis=1) - np.min(np.sum((x - p) ** 2, axis=1))) / (2 * h * h))]])
+                err = np.linalg.norm((got[at] if what == "score" else got) - ref[what], axis=1)
+                assert np.all(err <= 2.0**-11 * pull / h**2 + score_resolution(x, x[at] if what == "score" else q, h)), (err * h**2 / pull).max()
+            else:
+                assert_score_close(got[at] if what == "score" else got, ref[what], f"{what} d={d}", score_resolution(x, x[at] if what == "score" else q, h))
