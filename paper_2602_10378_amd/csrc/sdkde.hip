@@ -439,8 +439,8 @@ constexpr int64_t kWholeSamples = 3072, kWholeBlocks = 6144;
 // so that calls on one buffer agree on it; one of the size that sdkde_workspace_bytes gives holds them with all splits.  So are calls in the
 // other fp16 modes on few samples, for which the fp32 mode has fewer launches.  FP16X2 / fp32 mode: one call, 20000 x 5003, d = 8
 // 193 / 153 us, 16 192 / 170, 24 342 / 221, 64 673 / 377, 128 1364 / 851; eval d = 16 29.1 / 28.0, 64 90 / 48; 600 x 100, d = 16
-// 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against 64-bit sums, 600 .. 9000 samples, d = 4 .. 128: at most 1.0 of
-// theirs, in the mean 0.69 on scores, 0.47 on densities.
+// 26.4 / 18.0; score, n = 1048576, d = 16 376 / 289 ms.  Errors against 64-bit sums, 600 .. 30000 samples, d = 4 .. 128: at most 1.0
+// of theirs, in the mean 0.72 on scores, 0.80 on log densities, 0.55 on Laplace-corrected ones.
 // two_part_form: the flags such a call then runs with, the mode it would have run in kept in bits above the caller's (it is part of the
 // record of prepared samples); those of other calls unchanged.  flags: of the kind of call (anchored_flags).
 constexpr int kOwnModeShift = 16;
